@@ -70,14 +70,16 @@ typedef enum {
 
 /* Arithmetic of the per-block triangular solve (everything else is FP64). */
 typedef enum {
-  GLS_FP64 = 0,     /* plain FP64 MFMA                                           */
+  GLS_FP64 = 0,     /* plain FP64 MFMA; a SNP whose values are all whole numbers of
+                       magnitude at most 127 (dosages) takes the product of
+                       GLS_INT8_EMU if n > 256                                   */
   GLS_FP32_IR = 1,  /* FP32 MFMA bulk + FP64 residual refinement sweeps          */
   GLS_FP16_IR = 2,  /* FP16 MFMA (power-of-two column scaling) + FP64 refinement */
   GLS_BF16_IR = 3,  /* BF16 MFMA (power-of-two column scaling) + FP64 refinement */
   GLS_INT8_EMU = 4  /* dosage input only (the _u8 and _u2 entry points): the product
-                       with L^-1 as eight exact int8 slice products on the integer
+                       with L^-1 as seven exact int8 slice products on the integer
                        matrix cores, combined in FP64 (FP64-level accuracy); FP64
-                       input on such a handle runs the plain FP64 product        */
+                       input on such a handle is treated as by GLS_FP64          */
 } gls_precision;
 
 /* gls_opts.flags: keep Phi and the factor terms needed by the adjoint. */
@@ -131,11 +133,11 @@ gls_status gls_block(gls_handle h, int32_t mb, const double* XR, int64_t ld_xr,
 
 /* One SNP block (Sec. 2.2, as gls_block) given as genotype bytes: G is
  * n x mb uint8 (ld_g >= n), entries 0..127 (dosages 0, 1, 2).  GLS_INT8_EMU
- * sums exact int32 products, so it needs n * 127 * max(G) < 2^31: any byte
- * value for n <= 133,000, dosages 0..2 for n up to 8.4 million.  Same outputs and asynchrony as
- * gls_block.  With GLS_FP64 or the mixed forms the bytes are widened to FP64
- * on the device and the results are bitwise those of gls_block on the same
- * values; with GLS_INT8_EMU the product runs on the integer matrix cores
+ * sums exact int32 products, so it needs n * 128 * max(G) < 2^31: any byte
+ * value for n <= 132,000, dosages 0..2 for n up to 8.3 million.  Same outputs and asynchrony as
+ * gls_block.  With GLS_FP64 or the mixed forms the results are bitwise those
+ * of gls_block on the same values (the mixed forms widen the bytes to FP64 on
+ * the device); with GLS_INT8_EMU the product runs on the integer matrix cores
  * (see gls_precision).  Moves 1 byte per sample instead of 8. */
 gls_status gls_block_u8(gls_handle h, int32_t mb, const uint8_t* G, int64_t ld_g,
                         double* b, int64_t ld_b, double* sigma2, double* v,
@@ -160,7 +162,9 @@ typedef struct {
   int64_t h2d_bytes;     /* host-to-device bytes                              */
   int64_t d2h_bytes;     /* device-to-host bytes                              */
   double wall_ms;        /* first copy enqueue to last result landed          */
-  double compute_ms;     /* sum over blocks of the block's device time        */
+  double compute_ms;     /* sum over blocks of the block's device time: from the
+                            start of its solve (of its first part, where a block
+                            is solved in parts as they arrive) to its end       */
   int64_t file_bytes;    /* bytes read from storage (gls_stream_file)         */
   double read_ms;        /* time the reader spent in read calls (gls_stream_file) */
 } gls_stream_stats;
@@ -175,7 +179,9 @@ typedef struct {
  * With block_cols >= 2,048 the stream starts with shorter blocks
  * (block_cols / 8, growing by a quarter per block, multiples of 64), so the
  * first copy, which nothing overlaps, is short; results are bitwise the same
- * for any blocking.
+ * for any blocking.  A handle that solves SNPs of whole numbers on the
+ * integer matrix cores copies each block in up to four parts of 512 columns
+ * or more and solves them as they arrive.
  * copy_stream NULL (recommended): the study runs on the handle's own compute
  * and copy streams, after the work already queued on compute_stream.  HIP
  * multiplexes streams onto a few hardware queues, and on a shared queue the

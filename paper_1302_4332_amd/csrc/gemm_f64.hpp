@@ -44,6 +44,18 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 enum { TRI_NONE = 0, TRI_LOWER = 1, TRI_UPPER = 2 };
 enum { MAP_GRID = 0, MAP_XCD = 1 };
 
+// Per-column flags of a block: column j is flagged if any of its count chunks
+// is (at[c ncols + j] != 0).  at == nullptr: no flags.
+struct ColFlags {
+  const int* at;
+  int count;
+  __device__ __forceinline__ bool flagged(int j, int ncols) const {
+    int f = 0;
+    for (int c = 0; c < count; ++c) f |= at[(int64_t)c * ncols + j];
+    return f != 0;
+  }
+};
+
 struct GemmArgs {
   const double* A; int64_t lda;     // op(A) = A (TRANS_A false) or A^T
   const double* B; int64_t ldb;     // op(B) = B (TRANS_B false) or B^T
@@ -74,6 +86,9 @@ struct GemmArgs {
   // the running value in order, so a sum split over launches at stage
   // boundaries gives bitwise the result of one launch
   int acc_cin;
+  // trmm_f64_dma_kernel only: with flags, tiles without a flagged column do
+  // nothing and only flagged columns of C are stored
+  ColFlags only;
 };
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }

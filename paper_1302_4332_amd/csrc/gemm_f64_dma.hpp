@@ -51,6 +51,16 @@ void trmm_f64_dma_kernel(GemmArgs g) {
   if (!XcdMap::tile(g, blockIdx.x, Mt, Nt, &ti, &tj)) return;
   const int i0 = ti * BM, j0 = tj * BN;
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;   // a tile wholly above the lower part
+  if (g.only.at) {
+    int* any = reinterpret_cast<int*>(smem);
+    if (threadIdx.x == 0) *any = 0;
+    __syncthreads();
+    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && g.only.flagged(j0 + threadIdx.x, g.ncols)) *any = 1;
+    __syncthreads();
+    const bool none = *any == 0;
+    if (none) return;
+    __syncthreads();   // smem is the ring from here on
+  }
   // k range of the tile: a lower-triangular A ends at the tile's last row, an upper-triangular one starts at its
   // first, a lower-triangular B starts at the tile's first column (each holds explicit zeros across its diagonal
   // block)
@@ -186,7 +196,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
 #pragma unroll
     for (int c = 0; c < FC; ++c) {
       const int j = j0 + wn * WTN + c * 4 + (lane & 3);
-      if (j >= g.ncols) continue;
+      if (j >= g.ncols || (g.only.at && !g.only.flagged(j, g.ncols))) continue;
       double val = g.alpha * acc[a][c];
       if (g.beta != 0.0 && !g.acc_cin) val += g.beta * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
       g.C[(int64_t)i + (int64_t)j * g.ldc] = val;

@@ -57,6 +57,10 @@ int64_t padded_n(int64_t n) { return (n + NPAD - 1) / NPAD * NPAD; }
 static_assert(NPAD % NB_LEAF == 0 && NPAD % LP_BM == 0 && NPAD % OZ_BM == 0 && NPAD % DB_BM == 0 && NPAD % 64 == 0,
               "the row padding must be a multiple of every row tile");
 
+// FP64 handles look for SNPs of whole numbers from this padded sample count on (see OZ_MIN_N's use in the plan): the
+// integer product of such SNPs needs L^-1 sliced at setup and a packed copy of each block.
+constexpr int64_t OZ_MIN_N = 512;
+
 // Largest T1 buffer of the recursive factorization: (b - mid) * (mid - a) leaves.
 static int64_t recursion_temp_leaves(int a, int b) {
   if (b - a <= 1) return 0;
@@ -131,10 +135,14 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
                  : (o->precision == GLS_FP16_IR || o->precision == GLS_BF16_IR) ? 2 : 0;
   pl->off_ub0 = take((size_t)n * bc);
   pl->off_ub1 = take((size_t)n * bc);
-  if (o->precision == GLS_INT8_EMU) {
-    pl->off_ubp = take((size_t)N * pl->bcp);
-    pl->off_sl = take((size_t)OZ_SLICES * N * N);
-    pl->off_ex = take(sizeof(int) * N);
+  // Sliced L^-1 and its row exponents (under half of an N x N FP64 matrix).  L itself is read after setup only by
+  // the refinement residual and the adjoint; without those its region is free and holds them.
+  pl->whole = pl->lp_bytes == 0 && (o->precision == GLS_INT8_EMU || N >= OZ_MIN_N);
+  if (pl->whole) {
+    const size_t at = align_up(oz_factor_bytes(N), 256), ex = sizeof(int) * N;
+    if (o->flags & GLS_KEEP_FOR_GRAD) pl->off_sl = take(at + ex);
+    else pl->off_sl = pl->off_L;
+    pl->off_ex = pl->off_sl + at;
   }
   pl->off_x64 = take(sizeof(double) * N * bc);
   if (pl->lp_bytes) {
@@ -400,11 +408,14 @@ static void tri_apply(Ctx* c, const double* V, double* part, double* W, hipStrea
 // its first K rows: K = n, or n rounded up to 16 when X's rows n..K-1 are
 // zero.  rows = N, or n rounded up to the product's 128-row tiles when only
 // the sample rows (and the zero rows up to that tile edge) are read later.
-void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, double* Xt, hipStream_t s) {
+// With flags, only flagged columns are formed.
+static void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, double* Xt, ColFlags only,
+                        hipStream_t s) {
   GemmArgs g = gemm_args(c->Linv, c->N, X, ldx, Xt, c->N, rows, mb, K, 1.0);
   g.a_tri = TRI_LOWER;
   g.a_diag = 0;
   g.map_desc = 1;
+  g.only = only;
   gemm(false, false, true, g, s);
 }
 
@@ -413,7 +424,8 @@ void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, 
 // [X~_L | y~] and of x~^2 over the tile's rows ((t (p + 1) + q) mb + j).
 // Returns false, launching nothing, when the direct-load kernel does not
 // take the shape.
-static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, hipStream_t s) {
+static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, ColFlags only,
+                              hipStream_t s) {
   GemmArgs g = gemm_args(c->Linv, c->N, X, ldx, c->Xt, c->N, rows, mb, K, 1.0);
   g.a_tri = TRI_LOWER;
   g.a_diag = 0;
@@ -422,21 +434,22 @@ static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int 
   g.ld_red_W = c->N;
   g.red_part = c->Xt;
   g.red_q = c->p + 1;
+  g.only = only;
   return gemm_dma(g, s);
 }
 
 template <int P>
-static void launch_snp_partials_p(Ctx* c, int Mt, int mb, double* b, int64_t ldb, double* s2, double* v, int* st,
-                                  hipStream_t s) {
-  hipLaunchKernelGGL(snp_partials_solve_kernel<P>, dim3((mb + 255) / 256), dim3(256), 0, s, c->Xt, Mt, mb, c->small,
-                     (int)c->n, b, ldb, s2, v, st);
+static void launch_snp_partials_p(Ctx* c, int Mt, const double* part8, int Mt8, ColFlags sel, int mb, double* b,
+                                  int64_t ldb, double* s2, double* v, int* st, hipStream_t s) {
+  hipLaunchKernelGGL(snp_partials_solve_kernel<P>, dim3((mb + PS_SNPS - 1) / PS_SNPS), dim3(PS_SNPS * PS_GROUPS), 0, s,
+                     c->Xt, Mt, part8, Mt8, sel, mb, c->small, (int)c->n, b, ldb, s2, v, st);
 }
 
-static void snp_partials_solve(Ctx* c, int Mt, int mb, double* b, int64_t ldb, double* s2, double* v, int* st,
-                               hipStream_t s) {
+static void snp_partials_solve(Ctx* c, int Mt, const double* part8, int Mt8, ColFlags sel, int mb, double* b,
+                               int64_t ldb, double* s2, double* v, int* st, hipStream_t s) {
   switch (c->p) {
 #define GLS_P_CASE(P) \
-  case P: launch_snp_partials_p<P>(c, Mt, mb, b, ldb, s2, v, st, s); break;
+  case P: launch_snp_partials_p<P>(c, Mt, part8, Mt8, sel, mb, b, ldb, s2, v, st, s); break;
     GLS_P_CASE(1) GLS_P_CASE(2) GLS_P_CASE(3) GLS_P_CASE(4) GLS_P_CASE(5) GLS_P_CASE(6) GLS_P_CASE(7)
     GLS_P_CASE(8) GLS_P_CASE(9) GLS_P_CASE(10) GLS_P_CASE(11) GLS_P_CASE(12) GLS_P_CASE(13) GLS_P_CASE(14)
     GLS_P_CASE(15) GLS_P_CASE(16) GLS_P_CASE(17) GLS_P_CASE(18) GLS_P_CASE(19) GLS_P_CASE(20)
@@ -573,13 +586,13 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
   }
   c->ub[0] = reinterpret_cast<uint8_t*>(ws + pl.off_ub0);
   c->ub[1] = reinterpret_cast<uint8_t*>(ws + pl.off_ub1);
-  if (opts->precision == GLS_INT8_EMU) {
-    c->ubp = reinterpret_cast<uint8_t*>(ws + pl.off_ubp);
+  if (pl.whole) {
     c->sl = reinterpret_cast<int8_t*>(ws + pl.off_sl);
     c->ex = reinterpret_cast<int*>(ws + pl.off_ex);
-    hipLaunchKernelGGL(row_exponent_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, c->Linv, (int)N, c->ex);
-    hipLaunchKernelGGL(slice_factor_kernel, dim3((unsigned)(N / 64), (unsigned)(N / 64)), dim3(256), 0, s, c->Linv,
-                       (int)N, (const int*)c->ex, c->sl);
+    const unsigned T = (unsigned)(N / OZ_BM);
+    hipLaunchKernelGGL(row_max_kernel, dim3(T, (unsigned)((N + 255) / 256)), dim3(256), 0, s, c->Linv, (int)N, c->Xt);
+    hipLaunchKernelGGL(slice_factor_kernel, dim3(T, T), dim3(256), 0, s, c->Linv, (int)N, (const double*)c->Xt, c->ex,
+                       c->sl);
   }
   c->x64 = reinterpret_cast<double*>(ws + pl.off_x64);
   if (pl.lp_bytes) {
@@ -1017,12 +1030,20 @@ static void lp_solve(Ctx* c, const double* src, int64_t lds, int mb, double beta
 // every whitened block are zero off the identity padding, so sums may run to it.
 static int k16(const Ctx* c) { return (int)((c->n + DB_BK - 1) / DB_BK * DB_BK); }
 
+// Columns of a block into the zero-padded FP64 buffer x64 (rows n..rows-1 zero): all of them, or only the flagged.
+template <int SRC>
+static void widen_columns(Ctx* c, const void* src, int64_t ld, int mb, int rows, ColFlags flags, hipStream_t s) {
+  hipLaunchKernelGGL(widen_columns_kernel<SRC>, dim3(std::min(mb, 1024), (unsigned)((rows + WIDEN_ROWS - 1) / WIDEN_ROWS)),
+                     dim3(256), 0, s, src, ld, (int)c->n, rows, mb, c->x64, c->N, flags);
+}
+
 // The FP64 block operand of the product with L^-1: X itself when its layout
 // feeds the direct-load kernel (n a multiple of 16, 16-byte aligned, even
-// ld), else a copy in c->x64 (ld N) whose rows n..K-1 are zero.  Blocks
-// already in c->x64 (widened bytes) carry zero rows up to N.  Sets *K, the
-// rows the product sums over.
-static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb, int* K, hipStream_t s) {
+// ld), else a copy in c->x64 (ld N) whose rows n..K-1 are zero (with flags, of
+// the flagged columns).  Blocks already in c->x64 (widened bytes) carry zero
+// rows up to N.  Sets *K, the rows the product sums over.
+static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb, int* K, ColFlags flags,
+                                  hipStream_t s) {
   if (X == c->x64) {
     *K = k16(c);
     return X;
@@ -1030,10 +1051,83 @@ static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb,
   *K = (int)c->n;
   if (dma_b_operand_ok(X, *ldx, c->n)) return X;
   *K = k16(c);
-  hipLaunchKernelGGL(pad_copy_kernel, dim3(grid_for((int64_t)*K * mb)), dim3(256), 0, s, c->x64, c->N, X, *ldx,
-                     (int)c->n, *K, mb);
+  widen_columns<OZ_F64>(c, X, *ldx, mb, *K, flags, s);
   *ldx = c->N;
   return c->x64;
+}
+
+// Products with L^-1 of SNPs that are whole numbers, on the integer matrix
+// cores.  The block's int8 operand lies in units[], after the per-SNP sums of
+// the two products (their 128- and 64-row tiles) in c->Xt:
+// (p + 1) (8 / 128 + 8 / 64) + 1 + 1 / 64 <= 5 of the 8 bytes per row and SNP.
+struct WholeBlock {
+  uint8_t* units = nullptr;
+  int* flags_at = nullptr;
+  double* part8 = nullptr;
+  int nkb = 0, Jb = 0, Mt8 = 0;
+  ColFlags flags{nullptr, 0};
+};
+
+static WholeBlock whole_block(Ctx* c, double* region, bool sums, int mb, int rows) {
+  WholeBlock w;
+  w.nkb = rows / OZ_BK;
+  w.Mt8 = rows / OZ_BM;
+  w.Jb = (mb + 15) / 16;
+  double* at = region;
+  if (sums) {
+    w.part8 = at + (int64_t)((c->n + DB_BM - 1) / DB_BM) * (c->p + 1) * mb;
+    at = w.part8 + (int64_t)w.Mt8 * (c->p + 1) * mb;
+  }
+  w.units = reinterpret_cast<uint8_t*>(align_up((size_t)at, 256));
+  w.flags_at = reinterpret_cast<int*>(w.units + (size_t)w.nkb * w.Jb * OZ_UNIT);
+  return w;
+}
+
+// The block's int8 operand; with check, the columns that do not qualify are
+// flagged (values that are no whole numbers, or so large that a digit's sum
+// could leave int32).
+template <int SRC>
+static void pack_units(Ctx* c, const void* src, int64_t ld, int mb, bool check, WholeBlock* w, hipStream_t s) {
+  // long chunks leave fewer flags to read, short ones more workgroups: 1,024 of them if the block has that many
+  int chunk = 32;
+  while (chunk > 4 && w->Jb * ((w->nkb + chunk - 1) / chunk) < 1024) chunk /= 2;
+  const int chunks = (w->nkb + chunk - 1) / chunk;
+  const int xmax = (int)std::min<int64_t>(127, (((int64_t)1 << 31) - 1) / (128 * c->n));
+  if (check) w->flags = ColFlags{w->flags_at, chunks};
+  hipLaunchKernelGGL(pack_units_kernel<SRC>, dim3(w->Jb, chunks), dim3(256), 0, s, src, ld, (int)c->n, w->nkb, mb,
+                     w->Jb, chunk, xmax, w->units, check ? w->flags_at : nullptr);
+}
+
+static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w, hipStream_t s) {
+  if (((uintptr_t)X & 15) == 0 && (ld & 1) == 0) pack_units<OZ_F64_ALIGNED>(c, X, ld, mb, true, w, s);
+  else pack_units<OZ_F64>(c, X, ld, mb, true, w, s);
+}
+
+// The integer product: per-SNP sums into w.part8, or with Xt the product itself.
+static void whole_product(Ctx* c, const WholeBlock& w, int mb, double* Xt, hipStream_t s) {
+  OzArgs a;
+  std::memset(&a, 0, sizeof a);
+  a.A = c->sl;
+  a.ex = c->ex;
+  a.B = w.units;
+  a.Jb = w.Jb;
+  a.N = (int)c->N;
+  a.Mt = w.Mt8;
+  a.ncols = mb;
+  a.flags = w.flags;
+  if (Xt) {
+    a.C = Xt;
+    a.ldc = c->N;
+  } else {
+    a.W = c->W;
+    a.ldw = c->N;
+    a.red_part = w.part8;
+    a.red_q = c->p + 1;
+  }
+  GemmArgs m{};
+  m.map_gm = OZ_MAP_GM;
+  m.map_gn = OZ_MAP_GN;
+  hipLaunchKernelGGL(ozaki_i8_kernel, dim3(XcdMap::grid(m, w.Mt8, (mb + OZ_BN - 1) / OZ_BN)), dim3(OZ_THREADS), 0, s, a);
 }
 
 static void residual_fp64(Ctx* c, const double* X, int64_t ldx, int mb, hipStream_t s) {
@@ -1063,21 +1157,26 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
       lp_solve(c, c->R, c->N, mb, 1.0, s);
     }
   } else {
-    // Plain FP64: the per-SNP sums are fused into the product's epilogue, so
+    // Plain FP64: the per-SNP sums are fused into the products' epilogues, so
     // X~ is neither stored nor read back; row tiles wholly past the last
-    // sample are not computed (their rows would only add zeros).
+    // sample are not computed (their rows would only add zeros).  SNPs of
+    // whole numbers take the integer product, the others the FP64 one; the
+    // choice is each SNP's own, so its results do not depend on its block.
     const int rows = (int)((c->n + DB_BM - 1) / DB_BM * DB_BM);
-    bool fused;
+    WholeBlock w;
     {
       PhaseTimer t(c, PH_WHITEN, s);
+      if (c->plan.whole) {
+        w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_BM - 1) / OZ_BM * OZ_BM));
+        pack_f64(c, XR, ld_xr, mb, &w, s);
+        whole_product(c, w, mb, nullptr, s);
+      }
       int K = 0;
-      const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, s);
-      fused = whiten_fp64_fused(c, X, ld_xr, mb, K, rows, s);
-      if (!fused) whiten_fp64(c, X, ld_xr, mb, K, rows, c->Xt, s);
+      const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, w.flags, s);
+      whiten_fp64_fused(c, X, ld_xr, mb, K, rows, w.flags, s);
     }
     PhaseTimer t(c, PH_SNP, s);
-    if (fused) snp_partials_solve(c, rows / DB_BM, mb, b, ld_b, s2, v, st, s);
-    else snp_reduce_solve(c, c->Xt, mb, b, ld_b, s2, v, st, s);
+    snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.flags, mb, b, ld_b, s2, v, st, s);
     return GLS_OK;
   }
   {
@@ -1091,75 +1190,52 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
 
 namespace gls {
 
-// XCD grouping of the int8-slice product's tiles: 4 row tiles x 4 column tiles
-// per group (measured best of 1x16 .. 16x1 at n = 10,000, 8,192 SNPs).
-constexpr int OZ_MAP_GM = 4, OZ_MAP_GN = 4;
-
-// The product of L^-1 with the block's dosages in c->ubp (N x mb bytes, rows
-// >= n zero) on the integer matrix cores, into c->Xt.
-static void ozaki_product(Ctx* c, int mb, hipStream_t s) {
-  const int64_t N = c->N;
-  OzArgs a;
-  a.A = c->sl;
-  a.ex = c->ex;
-  a.B = c->ubp;
-  a.C = c->Xt;
-  a.ldc = N;
-  a.N = (int)N;
-  a.ncols = mb;
-  a.map_gm = OZ_MAP_GM;
-  a.map_gn = OZ_MAP_GN;
-  GemmArgs m{};
-  m.map_gm = a.map_gm;
-  m.map_gn = a.map_gn;
-  hipLaunchKernelGGL(ozaki_i8_kernel, dim3(XcdMap::grid(m, (int)(N / OZ_BM), (mb + OZ_BN - 1) / OZ_BN)),
-                     dim3(OZ_THREADS), 0, s, a);
-}
-
 // Dosage bytes (or packed 2-bit dosages) of a block widened into the zero-padded FP64 buffer x64 (ld N).
 void widen_u8(Ctx* c, const uint8_t* G, int64_t ldg, int mb, hipStream_t s) {
-  const int64_t N = c->N;
-  hipLaunchKernelGGL(u8_to_f64_kernel, dim3(grid_for(N * mb)), dim3(256), 0, s, G, ldg, (int)c->n, (int)N, mb, c->x64);
+  widen_columns<OZ_U8>(c, G, ldg, mb, (int)c->N, ColFlags{nullptr, 0}, s);
 }
 void widen_u2(Ctx* c, const uint8_t* G2, int64_t ldg, int mb, hipStream_t s) {
-  const int64_t N = c->N;
-  hipLaunchKernelGGL(unpack_u2_f64_kernel, dim3(grid_for(N / 4 * mb)), dim3(256), 0, s, G2, ldg, (int)c->n, (int)N,
-                     mb, c->x64);
+  widen_columns<OZ_U2>(c, G2, ldg, mb, (int)c->N, ColFlags{nullptr, 0}, s);
+}
+
+// Bytes (or 2-bit codes) on the integer matrix cores without a detour over
+// FP64.  In an FP64 handle, bytes above the int8 range are flagged and take the
+// FP64 product, as the same values given in FP64 do; a GLS_INT8_EMU handle's
+// bytes are the caller's promise, and 2-bit codes always qualify (n <= 2^20).
+template <int SRC>
+static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t ldg, double* b, int64_t ld_b,
+                                      double* s2, double* v, int* st, hipStream_t s) {
+  const int rows = (int)((c->n + DB_BM - 1) / DB_BM * DB_BM);
+  WholeBlock w;
+  {
+    PhaseTimer t(c, PH_WHITEN, s);
+    w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_BM - 1) / OZ_BM * OZ_BM));
+    const bool check = SRC == OZ_U8 && c->opts.precision != GLS_INT8_EMU;
+    pack_units<SRC>(c, G, ldg, mb, check, &w, s);
+    whole_product(c, w, mb, nullptr, s);
+    if (check) {
+      const int K = k16(c);
+      widen_columns<SRC>(c, G, ldg, mb, K, w.flags, s);
+      whiten_fp64_fused(c, c->x64, c->N, mb, K, rows, w.flags, s);
+    }
+  }
+  PhaseTimer t(c, PH_SNP, s);
+  snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.flags, mb, b, ld_b, s2, v, st, s);
+  return GLS_OK;
 }
 
 gls_status block_forward_u8(Ctx* c, int mb, const uint8_t* G, int64_t ldg, double* b, int64_t ld_b, double* s2,
                             double* v, int* st, hipStream_t s) {
-  const int64_t N = c->N;
-  if (c->opts.precision == GLS_INT8_EMU) {
-    {
-      PhaseTimer t(c, PH_WHITEN, s);
-      hipLaunchKernelGGL(pack_u8_kernel, dim3(grid_for(N * mb)), dim3(256), 0, s, G, ldg, (int)c->n, (int)N, mb, c->ubp);
-      ozaki_product(c, mb, s);
-    }
-    PhaseTimer t(c, PH_SNP, s);
-    snp_reduce_solve(c, c->Xt, mb, b, ld_b, s2, v, st, s);
-    return GLS_OK;
-  }
+  if (c->plan.whole) return block_forward_whole<OZ_U8>(c, mb, G, ldg, b, ld_b, s2, v, st, s);
   widen_u8(c, G, ldg, mb, s);
-  return block_forward(c, mb, c->x64, N, b, ld_b, s2, v, st, s);
+  return block_forward(c, mb, c->x64, c->N, b, ld_b, s2, v, st, s);
 }
 
 gls_status block_forward_u2(Ctx* c, int mb, const uint8_t* G2, int64_t ldg, double* b, int64_t ld_b, double* s2,
                             double* v, int* st, hipStream_t s) {
-  const int64_t N = c->N;
-  if (c->opts.precision == GLS_INT8_EMU) {
-    {
-      PhaseTimer t(c, PH_WHITEN, s);
-      hipLaunchKernelGGL(unpack_u2_kernel, dim3(grid_for(N / 4 * mb)), dim3(256), 0, s, G2, ldg, (int)c->n, (int)N,
-                         mb, reinterpret_cast<uint32_t*>(c->ubp));
-      ozaki_product(c, mb, s);
-    }
-    PhaseTimer t(c, PH_SNP, s);
-    snp_reduce_solve(c, c->Xt, mb, b, ld_b, s2, v, st, s);
-    return GLS_OK;
-  }
+  if (c->plan.whole) return block_forward_whole<OZ_U2>(c, mb, G2, ldg, b, ld_b, s2, v, st, s);
   widen_u2(c, G2, ldg, mb, s);
-  return block_forward(c, mb, c->x64, N, b, ld_b, s2, v, st, s);
+  return block_forward(c, mb, c->x64, c->N, b, ld_b, s2, v, st, s);
 }
 
 void reset_adjoint(Ctx* c, hipStream_t s) {
@@ -1208,9 +1284,15 @@ static void recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, 
       lp_solve(c, c->R, c->N, mb, 1.0, s);
     }
   } else {
+    WholeBlock w;
+    if (c->plan.whole) {   // the int8 operand in Xtb, which is written after X~
+      w = whole_block(c, c->Xtb, false, mb, (int)c->N);
+      pack_f64(c, XR, ld_xr, mb, &w, s);
+      whole_product(c, w, mb, c->Xt, s);
+    }
     int K = 0;
-    const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, s);
-    whiten_fp64(c, X, ld_xr, mb, K, (int)c->N, c->Xt, s);
+    const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, w.flags, s);
+    whiten_fp64(c, X, ld_xr, mb, K, (int)c->N, c->Xt, w.flags, s);
   }
 }
 

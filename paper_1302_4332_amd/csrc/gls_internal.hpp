@@ -26,7 +26,10 @@ struct Plan {
   int64_t bcp = 0;           // block columns rounded up to the tile width
   size_t off_Llp = 0, off_Blp = 0, off_R = 0, off_cs = 0, off_red = 0;
   // byte input
-  size_t off_ub0 = 0, off_ub1 = 0, off_ubp = 0, off_x64 = 0, off_sl = 0, off_ex = 0;
+  size_t off_ub0 = 0, off_ub1 = 0, off_x64 = 0;
+  // SNPs of whole numbers: L^-1 sliced for the integer matrix cores
+  bool whole = false;
+  size_t off_sl = 0, off_ex = 0;
   // adjoint (GLS_KEEP_FOR_GRAD)
   size_t off_Phi = 0, off_Lbar = 0, off_T1 = 0, off_T2 = 0, off_Xtb = 0, off_Xb = 0;
   size_t off_Cb = 0, off_eb = 0, off_ct = 0, off_Wb = 0, off_W0b = 0, off_acc = 0;
@@ -68,10 +71,9 @@ struct gls_ctx {
   double* red = nullptr;    // [0]: 2^-e of the factor; [8..]: reduction scratch
   // byte input
   uint8_t* ub[2] = {nullptr, nullptr};  // streaming staging, n x block_cols bytes
-  uint8_t* ubp = nullptr;   // N x bcp packed bytes (GLS_INT8_EMU operand)
   double* x64 = nullptr;    // N x block_cols FP64: bytes widened, or a block copied with zero rows past n
-  int8_t* sl = nullptr;     // OZ_SLICES x N x N int8 slices of L^-1 (GLS_INT8_EMU)
-  int* ex = nullptr;        // N row exponents of L^-1 (GLS_INT8_EMU)
+  int8_t* sl = nullptr;     // int8 slices of L^-1 (plan.whole; in L's region unless the handle keeps L)
+  int* ex = nullptr;        // N row exponents of L^-1
   // adjoint state (GLS_KEEP_FOR_GRAD)
   bool grad = false;
   double* Phi = nullptr;    // N x N, lower triangle of Phi (zero padding)
@@ -129,7 +131,6 @@ void set_last_error_str(const char* what);
 int64_t padded_n(int64_t n);
 bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl);
 
-void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, double* Xt, hipStream_t s);
 void prepare_low_precision(Ctx* c, hipStream_t s);
 void reset_adjoint(Ctx* c, hipStream_t s);
 void snp_reduce_solve(Ctx* c, const double* Xt, int mb, double* b, int64_t ldb, double* s2, double* v, int* st,

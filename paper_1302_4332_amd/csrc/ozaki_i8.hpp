@@ -1,15 +1,27 @@
-// FP64-accurate per-block product on the integer matrix cores, for genotype
-// dosages held as bytes.
+// FP64-accurate per-block product on the integer matrix cores, for SNP values
+// that are whole numbers (genotype dosages), held as FP64, bytes or packed
+// 2-bit codes.
 //
-// Each row i of L^-1 is split exactly into S int8 slices (Ozaki-style):
-//     L^-1[i, k] = 2^e_i * sum_{s<S} a_s[i, k] * 2^(-7 (s+1))  +  r_ik,
-//     |a_s| <= 127,  |r_ik| < 2^(e_i - 7 S),  max_k |L^-1[i, k]| < 2^e_i,
-// obtained by repeatedly scaling by 2^7 and taking the integer part (every
-// step exact in FP64).  Dosages x are small integers, exact in int8, so
-//     (L^-1 X)[i, j] = sum_s 2^(e_i - 7(s+1)) * (a_s X)[i, j]   (+ truncation)
-// where each a_s X is an exact int32 product (|a_s x| sums stay below 2^31
-// for n * 127 * max|x| < 2^31).  With S = 8 the truncation is below 2^-56 of
-// the row's largest entry, under FP64 rounding of the result.
+// Each row i of L^-1 is rounded to a 56-bit fixed-point number and split into
+// seven signed base-256 digits (the slicing of Ozaki, Ogita, Oishi and Rump's
+// error-free matrix product transformation, with balanced digits):
+//     L^-1[i, k] = 2^(e_i - 55) * sum_{s<7} a_s[i, k] * 256^s  +  r_ik,
+//     -128 <= a_s <= 127,  |r_ik| <= 2^(e_i - 56),  max_k |L^-1[i, k]| <= 0.99 * 2^e_i.
+// Whole numbers x with |x| <= 127 are exact in int8, so
+//     (L^-1 X)[i, j] = sum_s 2^(e_i - 55) 256^s (a_s X)[i, j]   (+ r)
+// where each a_s X is an exact int32 sum (n * 128 * max|x| < 2^31).  The
+// rounding r is below 2^-55 of the row's largest entry, under FP64 rounding of
+// the result, and there is one FP64 rounding per digit instead of one per
+// sample.  Balanced digits carry eight bits each, so seven of them hold what
+// eight truncated 7-bit slices did (the same 2^-56 bound) with an eighth less
+// work.
+//
+// Operands are kept in the order the matrix instruction reads them.  A unit is
+// 1 KB: 16 rows (of L^-1) or 16 SNPs times 64 k, byte b of lane l being element
+// (l % 16, 16 (l / 16) + b), which is v_mfma_i32_16x16x64_i8's A (and B) operand
+// layout (checked on gfx950 with known operands).  Every load from global memory
+// to LDS is then a contiguous 1 KB, and every fragment read from LDS one
+// contiguous, conflict-free 1 KB without address arithmetic.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -20,74 +32,82 @@
 
 namespace gls {
 
-constexpr int OZ_SLICES = 8;
+constexpr int OZ_SLICES = 7;
+constexpr int OZ_UNIT = 1024;                        // bytes of a unit
+constexpr int OZ_BM = 64, OZ_BK = 64;                // rows of L^-1 and k per stage
+constexpr int OZ_STRIPS = OZ_BM / 16;
+constexpr int OZ_ATILE = OZ_STRIPS * OZ_SLICES * OZ_UNIT;   // one (row tile, k block) of the sliced factor
+
+// Bytes of the sliced factor: row tile t holds the k blocks 0..t that reach the lower triangle.
+inline size_t oz_factor_bytes(int64_t N) {
+  const int64_t T = N / OZ_BM;
+  return (size_t)(T * (T + 1) / 2) * OZ_ATILE;
+}
 
 typedef int i4_t __attribute__((ext_vector_type(4)));
 
-// Per-row exponent: ex[i] with max_k |Li[i, k]| < 2^ex[i] (0 for a zero row).
-// One thread per row; threads of a wave read consecutive rows (coalesced).
-__global__ void row_exponent_kernel(const double* __restrict__ Li, int N, int* __restrict__ ex) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
+// Largest |Li[i, k]| over k in [256 s, 256 s + 256), k <= i: part[s N + i].
+// Workgroup (row block, s): 64 rows, four waves over k.
+__global__ __launch_bounds__(256) void row_max_kernel(const double* __restrict__ Li, int N, double* __restrict__ part) {
+  __shared__ double red[256];
+  const int i0 = blockIdx.x * 64, k0 = blockIdx.y * 256;
+  if (k0 > i0 + 63) return;
+  const int r = threadIdx.x & 63, g = threadIdx.x >> 6, i = i0 + r;
   double m = 0.0;
-  for (int k = 0; k <= i; ++k) m = fmax(m, fabs(Li[(int64_t)i + (int64_t)k * N]));
-  int e = 0;
-  if (m > 0.0) frexp(m, &e);
-  ex[i] = e;
+  const int kend = min(k0 + 256, i0 + 64);
+#pragma unroll 8
+  for (int k = k0 + g; k < kend; k += 4) m = fmax(m, fabs(Li[(int64_t)i + (int64_t)k * N]));
+  red[threadIdx.x] = m;
+  __syncthreads();
+  if (g == 0)
+    part[(int64_t)blockIdx.y * N + i] = fmax(fmax(red[r], red[64 + r]), fmax(red[128 + r], red[192 + r]));
 }
 
-// Slices: out[s][i * N + k] = a_s[i, k] (row-major, k contiguous) for a 64 x 64
-// tile per workgroup; reads Li column-major through LDS.
+// The digits of a 64 x 64 block of L^-1 (row tile ti, k block kb <= ti), and
+// the rows' exponents: ex[i] with max_k |Li[i, k]| <= 0.99 * 2^ex[i], so that the
+// top digit stays within [-128, 127] after the lower digits' carries.  Thread
+// (row r, k group kq) reads 16 consecutive k of its row (coalesced over rows)
+// and writes its lane's 16 bytes of each digit's unit.
 __global__ __launch_bounds__(256) void slice_factor_kernel(const double* __restrict__ Li, int N,
-                                                           const int* __restrict__ ex, int8_t* __restrict__ out) {
-  __shared__ double tile[64][65];
-  const int i0 = blockIdx.y * 64, k0 = blockIdx.x * 64;
-  for (int idx = threadIdx.x; idx < 64 * 64; idx += 256) {
-    const int ii = idx % 64, kk = idx / 64;
-    tile[ii][kk] = Li[(int64_t)(i0 + ii) + (int64_t)(k0 + kk) * N];
-  }
-  __syncthreads();
-  const int64_t plane = (int64_t)N * N;
-  for (int idx = threadIdx.x; idx < 64 * 64; idx += 256) {
-    const int kk = idx % 64, ii = idx / 64;
-    double v = ldexp(tile[ii][kk], -ex[i0 + ii]);   // |v| < 1, exact
-    const int64_t o = (int64_t)(i0 + ii) * N + (k0 + kk);
+                                                           const double* __restrict__ part, int* __restrict__ ex,
+                                                           int8_t* __restrict__ out) {
+  const int ti = blockIdx.y, kb = blockIdx.x;
+  if (kb > ti) return;
+  const int r = threadIdx.x & 63, kq = threadIdx.x >> 6;
+  const int i = ti * 64 + r;
+  double x[16];
+#pragma unroll
+  for (int b = 0; b < 16; ++b) x[b] = Li[(int64_t)i + (int64_t)(kb * 64 + kq * 16 + b) * N];
+  double m = 0.0;
+  for (int s = 0; s <= (ti * 64 + 63) / 256; ++s) m = fmax(m, part[(int64_t)s * N + i]);
+  int e = 0;
+  if (m > 0.0 && frexp(m, &e) > 0.99) ++e;
+  if (kb == 0 && kq == 0) ex[i] = e;
+  uint32_t w[OZ_SLICES][4];
+#pragma unroll
+  for (int s = 0; s < OZ_SLICES; ++s)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[s][q] = 0u;
+#pragma unroll
+  for (int b = 0; b < 16; ++b) {
+    long long q = __double2ll_rn(ldexp(x[b], 55 - e));
 #pragma unroll
     for (int s = 0; s < OZ_SLICES; ++s) {
-      v *= 128.0;                   // exact
-      const double d = trunc(v);    // |d| <= 127
-      v -= d;                       // exact
-      out[s * plane + o] = (int8_t)d;
+      const int d = (int)(int8_t)(q & 255);
+      q = (q - d) >> 8;
+      w[s][b >> 2] |= (uint32_t)(d & 255) << (8 * (b & 3));
     }
   }
-}
-
-// Bytes of a block into an N-row, zero-padded column-major buffer.
-__global__ void pack_u8_kernel(const uint8_t* __restrict__ G, int64_t ldg, int n, int N, int mb,
-                               uint8_t* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)N * mb;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(idx % N), j = (int)(idx / N);
-    out[idx] = (k < n) ? G[(int64_t)k + (int64_t)j * ldg] : (uint8_t)0;
-  }
-}
-
-// Bytes of a block as FP64 (exact), N-row zero-padded, ld N.
-__global__ void u8_to_f64_kernel(const uint8_t* __restrict__ G, int64_t ldg, int n, int N, int mb,
-                                 double* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)N * mb;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(idx % N), j = (int)(idx / N);
-    out[idx] = (k < n) ? (double)G[(int64_t)k + (int64_t)j * ldg] : 0.0;
-  }
+  int8_t* o = out + ((int64_t)ti * (ti + 1) / 2 + kb) * OZ_ATILE + (r >> 4) * (OZ_SLICES * OZ_UNIT) +
+              16 * (kq * 16 + (r & 15));
+#pragma unroll
+  for (int s = 0; s < OZ_SLICES; ++s)
+    *reinterpret_cast<uint4*>(o + s * OZ_UNIT) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
 // Packed dosages: four 2-bit codes per byte, sample k of a column in bits
 // [2 (k % 4), 2 (k % 4) + 2) of the column's byte k / 4; code value = dosage
-// (0..3).  Bits of the last byte past row n - 1 are ignored.  One thread per
-// four output rows; rows n..N-1 are zero.
+// (0..3).  Bits of the last byte past row n - 1 are ignored.
 __device__ __forceinline__ uint32_t unpack_quad(const uint8_t* __restrict__ G2, int64_t ldg, int n, int q, int j) {
   const int k0 = 4 * q;
   if (k0 >= n) return 0u;
@@ -98,184 +118,279 @@ __device__ __forceinline__ uint32_t unpack_quad(const uint8_t* __restrict__ G2, 
   return w;   // byte t = dosage of row k0 + t
 }
 
-// Packed dosages of a block into an N-row, zero-padded column-major byte buffer.
-__global__ void unpack_u2_kernel(const uint8_t* __restrict__ G2, int64_t ldg, int n, int N, int mb,
-                                 uint32_t* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int Q = N / 4;
-  const int64_t total = (int64_t)Q * mb;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int q = (int)(idx % Q), j = (int)(idx / Q);
-    out[idx] = unpack_quad(G2, ldg, n, q, j);
+// Where a block's int8 operand and its column flags come from.
+enum { OZ_F64 = 0, OZ_F64_ALIGNED = 1, OZ_U8 = 2, OZ_U2 = 3 };
+
+// A block's SNP values as units [k block][SNP group of 16] (Jb groups).  flags
+// (nullptr: none are needed) receives, for every k chunk c and SNP j,
+// flags[c mb + j] = 1 if a value of the chunk is not a whole number of magnitude
+// at most xmax.  A wave whose SNPs are all flagged stops: their results come
+// from the FP64 product.  Workgroup (group, chunk of chunk_kb k blocks), four
+// waves over the chunk's k blocks; a lane holds its 16 bytes' values, so FP64
+// columns are read as whole 128-byte lines.
+template <int SRC>
+__global__ __launch_bounds__(256) void pack_units_kernel(const void* __restrict__ src, int64_t ld, int n, int nkb,
+                                                         int mb, int Jb, int chunk_kb, int xmax,
+                                                         uint8_t* __restrict__ out, int* __restrict__ flags) {
+  __shared__ int seen[4];
+  const int jb = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = jb * 16 + (lane & 15), kq = lane >> 4;
+  const bool col = j < mb;
+  const unsigned cols = (mb - jb * 16 >= 16) ? 0xffffu : (1u << (mb - jb * 16)) - 1u;
+  const int kb1 = min(nkb, (int)(blockIdx.y + 1) * chunk_kb);
+  unsigned bad = 0;   // flagged columns (wave-uniform)
+  for (int kb = blockIdx.y * chunk_kb + wave; kb < kb1; kb += 4) {
+    const int k0 = kb * 64 + kq * 16;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if constexpr (SRC == OZ_F64 || SRC == OZ_F64_ALIGNED) {
+      double x[16];
+#pragma unroll
+      for (int b = 0; b < 16; ++b) x[b] = 0.0;
+      if (col) {
+        const double* p = static_cast<const double*>(src) + (int64_t)j * ld + k0;
+        if (k0 + 16 <= n) {
+          if (SRC == OZ_F64_ALIGNED) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              const double2 v = reinterpret_cast<const double2*>(p)[q];
+              x[2 * q] = v.x;
+              x[2 * q + 1] = v.y;
+            }
+          } else {
+#pragma unroll
+            for (int b = 0; b < 16; ++b) x[b] = p[b];
+          }
+        } else {
+#pragma unroll
+          for (int b = 0; b < 16; ++b)
+            if (k0 + b < n) x[b] = p[b];
+        }
+      }
+      bool ok = true;
+#pragma unroll
+      for (int b = 0; b < 16; ++b) {
+        const int v = (int)x[b];   // saturates; NaN gives 0
+        ok = ok && (double)v == x[b] && v <= xmax && v >= -xmax;
+        w[b >> 2] |= (uint32_t)(v & 255) << (8 * (b & 3));
+      }
+      const unsigned long long m = __ballot(!ok);
+      bad |= (unsigned)((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xffffu);
+      if (bad == cols) break;
+    } else if constexpr (SRC == OZ_U8) {
+      if (col && k0 < n) {
+        const uint8_t* p = static_cast<const uint8_t*>(src) + (int64_t)j * ld + k0;
+        if (k0 + 16 <= n) {
+          __builtin_memcpy(w, p, 16);
+        } else {
+          for (int b = 0; b < n - k0; ++b) w[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
+        }
+      }
+      if (flags) {
+        bool ok = true;
+#pragma unroll
+        for (int b = 0; b < 16; ++b) ok = ok && (int)((w[b >> 2] >> (8 * (b & 3))) & 255u) <= xmax;
+        const unsigned long long m = __ballot(!ok);
+        bad |= (unsigned)((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xffffu);
+        if (bad == cols) break;
+      }
+    } else {
+      if (col) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = unpack_quad(static_cast<const uint8_t*>(src), ld, n, k0 / 4 + q, j);
+      }
+    }
+    *reinterpret_cast<uint4*>(out + ((int64_t)kb * Jb + jb) * OZ_UNIT + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  if (flags) {
+    if (lane == 0) seen[wave] = (int)bad;
+    __syncthreads();
+    if (threadIdx.x < 16 && j < mb)
+      flags[(int64_t)blockIdx.y * mb + j] = ((seen[0] | seen[1] | seen[2] | seen[3]) >> threadIdx.x) & 1;
   }
 }
 
-// Packed dosages of a block as FP64 (exact), N-row zero-padded, ld N.
-__global__ void unpack_u2_f64_kernel(const uint8_t* __restrict__ G2, int64_t ldg, int n, int N, int mb,
-                                     double* __restrict__ out) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int Q = N / 4;
-  const int64_t total = (int64_t)Q * mb;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int q = (int)(idx % Q), j = (int)(idx / Q);
-    const uint32_t w = unpack_quad(G2, ldg, n, q, j);
-    double2* o = reinterpret_cast<double2*>(out + (int64_t)j * N + 4 * q);
-    o[0] = double2{(double)(w & 0xffu), (double)((w >> 8) & 0xffu)};
-    o[1] = double2{(double)((w >> 16) & 0xffu), (double)(w >> 24)};
+// Columns of a block widened (or copied) into the zero-padded FP64 buffer out
+// (ld ldo, rows n..rows-1 zero): every column, or with flags only the flagged
+// ones.  Workgroup (x, y): rows [WIDEN_ROWS y, ...) of columns x, x + gridDim.x, ...
+constexpr int WIDEN_ROWS = 2048;
+
+template <int SRC>
+__global__ __launch_bounds__(256) void widen_columns_kernel(const void* __restrict__ src, int64_t ld, int n, int rows,
+                                                            int mb, double* __restrict__ out, int64_t ldo,
+                                                            ColFlags flags) {
+  for (int j = blockIdx.x; j < mb; j += gridDim.x) {
+    if (flags.at && !flags.flagged(j, mb)) continue;
+    double* o = out + (int64_t)j * ldo;
+    const int k1 = min(rows, (int)(blockIdx.y + 1) * WIDEN_ROWS);
+#pragma unroll 4
+    for (int k = blockIdx.y * WIDEN_ROWS + threadIdx.x; k < k1; k += 256) {
+      double v = 0.0;
+      if (k < n) {
+        if constexpr (SRC == OZ_U8) v = (double)static_cast<const uint8_t*>(src)[(int64_t)k + (int64_t)j * ld];
+        else if constexpr (SRC == OZ_U2)
+          v = (double)((static_cast<const uint8_t*>(src)[(int64_t)j * ld + (k >> 2)] >> (2 * (k & 3))) & 3);
+        else v = static_cast<const double*>(src)[(int64_t)k + (int64_t)j * ld];
+      }
+      o[k] = v;
+    }
   }
 }
 
 struct OzArgs {
-  const int8_t* A;        // OZ_SLICES planes of N x N, row-major
+  const int8_t* A;        // sliced factor: row tile t's k blocks 0..t of OZ_ATILE bytes
   const int* ex;          // row exponents
-  const uint8_t* B;       // N x ncols bytes, column-major, ld N (rows >= n are zero)
-  double* C; int64_t ldc; // N x ncols FP64
-  int N, ncols;
-  int map_gm, map_gn;
+  const uint8_t* B;       // units [k block][Jb]
+  int Jb;                 // SNP groups of 16
+  int N, Mt, ncols;       // Mt row tiles of OZ_BM
+  ColFlags flags;         // flagged columns are left out (at == nullptr: none)
+  // per-SNP sums (red_q > 0): red_part[(t red_q + q) ncols + j] as in GemmArgs, over row tile t of OZ_BM rows
+  const double* W; int64_t ldw;
+  double* red_part;
+  int red_q;
+  double* C; int64_t ldc; // red_q == 0: the product itself, N x ncols FP64
 };
 
-// v_mfma_i32_16x16x64_i8 operand layout (checked on gfx950 with known
-// operands): lane l holds A[l % 16][16 (l / 16) + e] and B[16 (l / 16) + e][l % 16]
-// for bytes e = 0..15 (any k order shared by A and B gives the same sum);
-// accumulator element t is D[4 (l / 16) + t][l % 16].
+// A workgroup of eight waves owns 64 rows x 192 SNPs: wave w takes the 16-row
+// strip w & 3 and the 96-SNP half w >> 2 with all seven digits, 7 x 6
+// accumulators of 16 x 16 (168 registers; two waves per SIMD).  Per 64-deep
+// stage it reads seven + six 1 KB fragments for 42 MFMAs, so the LDS port is
+// busy 0.86 of the MFMA time with the stage's own 40 KB of writes; the 32 x 256
+// tile of sixteen waves with 4 x 4 accumulators that this replaced needed 1.25
+// of it and ran the MFMA pipes 47% of the time.  Stages move straight from
+// global memory into a ring of three LDS buffers, two ahead of the MFMAs.
 //
-// The kernel computes the transpose, D = X^T a_s^T, so that the accumulator's
-// fast index (l % 16) runs down a column of the column-major result and the
-// FP64 stores are 128-byte runs.  A workgroup of sixteen waves owns a 32 x 256
-// output tile: wave w takes the 16-row strip w & 1, the 64-column strip
-// (w >> 1) & 3 and the slice half w >> 3 (slices 0..3 or 4..7), holding 4 x 4
-// accumulators (one per slice and 16-column group).  Splitting the slices over
-// two waves halves the accumulators, so four waves share each SIMD instead of
-// two and one wave's wait at the stage barrier no longer idles the matrix
-// pipe as often (5% faster than eight waves holding all eight slices, with
-// bitwise the same results).  Per 64-deep k step a wave reads four byte
-// fragments and one fragment per slice from LDS and issues 16 MFMAs.  At the
-// end the second half adds its slices 7..4 into an LDS buffer (reusing the
-// ring) and the first half continues with 3..0: the same order as one wave
-// summing all eight.
-//
-// Operands reach LDS by direct global-to-LDS loads (global_load_lds_dwordx4:
-// no staging registers) into a ring of OZ_STAGES buffers, OZ_STAGES - 1 steps
-// ahead of the MFMAs (see lds_dma.hpp).  One load instruction moves 1 KB: sixteen 64-byte rows, lane l
-// writing bytes [16 l, 16 l + 16) of it.  Chunk c of row r is stored in slot
-// c ^ oz_swz(r), so that a fragment read (sixteen rows, one chunk each) puts
-// every eight consecutive lanes on distinct 128-byte bank lines and all sixteen
-// on distinct 256-byte lines.
-constexpr int OZ_BM = 32, OZ_BN = 256, OZ_BK = 64, OZ_THREADS = 1024, OZ_STAGES = 4;
+// A wave's accumulator element t of lane l is row 4 (l / 16) + t, SNP l % 16 of
+// its 16 x 16 block, so a sum over the rows is four values of the lane and two
+// lane exchanges.
+constexpr int OZ_BN = 192, OZ_THREADS = 512, OZ_STAGES = 3;
+constexpr int OZ_MAP_GM = 4, OZ_MAP_GN = 8;
 
-__device__ __forceinline__ int oz_swz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
-
-__global__ __launch_bounds__(OZ_THREADS) void ozaki_i8_kernel(OzArgs g) {
-  constexpr int BM = OZ_BM, BN = OZ_BN, BK = OZ_BK, S = OZ_SLICES, NW = OZ_THREADS / 64, NS = OZ_STAGES;
-  constexpr int SH = S / 2;                      // slices per wave: the two wave halves take slices 0..3 and 4..7
-  constexpr int RB = BK;                         // bytes per LDS row
-  constexpr int ABYTES = S * BM * RB, STAGE = ABYTES + BN * RB;
-  constexpr int QA = S * BM / 16 / NW;           // 1 KB load instructions per wave and stage
-  constexpr int QB = BN / 16 / NW;
-  static_assert(BK == 64 && BM == 32 && NW == 4 * (BN / 64), "two row strips x BN / 64 column strips x two slice halves");
-  static_assert(QA * 16 * NW == S * BM && QB * 16 * NW == BN && NS >= 2 && NS <= 5, "loader split");
-  constexpr int PS = BN + 2;                     // row stride of the partial sums: 16 rows on distinct banks
-  static_assert(NS * STAGE <= 160 * 1024 && BM * PS * 8 <= NS * STAGE, "LDS (the ring holds the partial sums at the end)");
+__global__ __launch_bounds__(OZ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void ozaki_i8_kernel(OzArgs g) {
+  constexpr int S = OZ_SLICES, NW = OZ_THREADS / 64, NS = OZ_STAGES;
+  constexpr int BU = OZ_BN / 16, FC = BU / 2;              // SNP groups per tile and per wave
+  constexpr int AU = OZ_STRIPS * S, STAGE = (AU + BU) * OZ_UNIT, NLD = (AU + BU) / NW;
+  constexpr int QC = 10;                                   // sums per pass of the epilogue's LDS exchange
+  static_assert(NLD * NW == AU + BU && NS * STAGE <= 160 * 1024 && OZ_STRIPS * QC * OZ_BN * 8 <= NS * STAGE, "LDS");
   __shared__ __align__(1024) int8_t smem[NS * STAGE];
+  __shared__ int any;
 
   int ti, tj;
   {
     GemmArgs m{};
-    m.map_gm = g.map_gm;
-    m.map_gn = g.map_gn;
+    m.map_gm = OZ_MAP_GM;
+    m.map_gn = OZ_MAP_GN;
     m.map_desc = 1;
-    const int Mt = g.N / BM, Nt = (g.ncols + BN - 1) / BN;
-    if (!XcdMap::tile(m, blockIdx.x, Mt, Nt, &ti, &tj)) return;
+    if (!XcdMap::tile(m, blockIdx.x, g.Mt, (g.ncols + OZ_BN - 1) / OZ_BN, &ti, &tj)) return;
   }
-  const int i0 = ti * BM, j0 = tj * BN;
-  const int nk = (i0 + BM + BK - 1) / BK;   // lower triangular factor: k < i0 + BM
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wi = wave & 1, wj = (wave >> 1) & 3, wsl = wave >> 3;
-  const int64_t plane = (int64_t)g.N * g.N;
+  const int nk = ti + 1;   // lower triangular factor
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ws = wave & 3, wc = wave >> 2;
+  const int j0 = tj * OZ_BN, jb0 = tj * BU;
 
-  const int lrow = lane >> 2, lchunk = ((lane & 3) ^ oz_swz(lrow)) * 16;
-  const int8_t* pa[QA];
-  const uint8_t* pb[QB];
-#pragma unroll
-  for (int q = 0; q < QA; ++q) {
-    const int r = 16 * (q * NW + wave) + lrow, s = r / BM, ri = r % BM;
-    pa[q] = g.A + s * plane + (int64_t)(i0 + ri) * g.N + lchunk;
-  }
-#pragma unroll
-  for (int q = 0; q < QB; ++q) {
-    const int j = min(j0 + 16 * (q * NW + wave) + lrow, g.ncols - 1);   // columns past the end: any valid
-    pb[q] = g.B + (int64_t)j * g.N + lchunk;                            // column, their results are dropped
-  }
+  const int8_t* Abase = g.A + (int64_t)ti * (ti + 1) / 2 * OZ_ATILE;
   const uint32_t lds0 = lds_address(smem);
-  auto issue = [&](int kstep) {
-    const uint32_t base = lds0 + (uint32_t)((kstep % NS) * STAGE);
-    const int kt = kstep * BK;
+  const uint32_t voff = 16 * lane;
+  auto issue = [&](int kb) {
+    const uint32_t base = lds0 + (uint32_t)((kb % NS) * STAGE);
 #pragma unroll
-    for (int q = 0; q < QA; ++q)
-      lds_load16(pa[q] + kt, __builtin_amdgcn_readfirstlane(base + 1024 * (q * NW + wave)));
-#pragma unroll
-    for (int q = 0; q < QB; ++q)
-      lds_load16(pb[q] + kt, __builtin_amdgcn_readfirstlane(base + ABYTES + 1024 * (q * NW + wave)));
+    for (int q = 0; q < NLD; ++q) {
+      const int u = q * NW + wave;   // wave-uniform: A's units, then B's (groups past the end: the last one's, dropped)
+      const void* p = (u < AU) ? (const void*)(Abase + (int64_t)kb * OZ_ATILE + u * OZ_UNIT)
+                               : (const void*)(g.B + ((int64_t)kb * g.Jb + min(jb0 + u - AU, g.Jb - 1)) * OZ_UNIT);
+      lds_load16_sv(p, voff, base + (uint32_t)(u * OZ_UNIT));
+    }
   };
-
-  i4_t acc[SH][4];
-#pragma unroll
-  for (int s = 0; s < SH; ++s)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[s][c] = i4_t{0, 0, 0, 0};
-
-  const int fr = lane & 15, slot = ((lane >> 4) ^ oz_swz(fr)) * 16;
-  const int oa = (wsl * SH * BM + wi * 16 + fr) * RB + slot;
-  const int ob = ABYTES + (wj * 64 + fr) * RB + slot;
-
   for (int q = 0; q < NS - 1; ++q)
     if (q < nk) issue(q);
-  for (int it = 0; it < nk; ++it) {
-    wait_stages<QA + QB>(min(nk - 1 - it, NS - 2));
+  if (g.flags.at) {   // a tile whose every SNP is flagged has nothing to do
+    if (threadIdx.x == 0) any = 0;
     __syncthreads();
-    if (it + NS - 1 < nk) issue(it + NS - 1);
-    const int8_t* st = smem + (it % NS) * STAGE;
-    i4_t bf[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) bf[c] = *reinterpret_cast<const i4_t*>(st + ob + c * 16 * RB);
-#pragma unroll
-    for (int s = 0; s < SH; ++s) {
-      const i4_t af = *reinterpret_cast<const i4_t*>(st + oa + s * BM * RB);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[s][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[c], af, acc[s][c], 0, 0, 0);
+    if (threadIdx.x < OZ_BN && j0 + (int)threadIdx.x < g.ncols && !g.flags.flagged(j0 + threadIdx.x, g.ncols)) any = 1;
+    __syncthreads();
+    if (!any) {
+      wait_vmcnt<0>();   // no load into this workgroup's LDS may outlive it
+      return;
     }
   }
 
-  // slices 7..4 (second half) first, then 3..0, the same order as one wave holding all eight
-  const int i = i0 + wi * 16 + fr;
-  const int e = g.ex[i];
-  double* part = reinterpret_cast<double*>(smem);   // 32 x 256 partial sums of the second half (row stride PS)
-  wait_vmcnt<0>();
-  __syncthreads();                                  // every wave is done with the ring
-  if (wsl == 1) {
+  i4_t acc[S][FC];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+  for (int s = 0; s < S; ++s)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        double v = 0.0;
+    for (int c = 0; c < FC; ++c) acc[s][c] = i4_t{0, 0, 0, 0};
+
+  const int oa = ws * S * OZ_UNIT + 16 * lane, ob = (AU + wc * FC) * OZ_UNIT + 16 * lane;
+  for (int it = 0; it < nk; ++it) {
+    wait_stages<NLD>(min(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
+    __syncthreads();                              // ... and every wave's; stage (it - 1) % NS is free
+    if (it + NS - 1 < nk) issue(it + NS - 1);
+    const int8_t* st = smem + (it % NS) * STAGE;
+    i4_t bf[FC];
 #pragma unroll
-        for (int s = SH - 1; s >= 0; --s) v += ldexp((double)acc[s][c][t], e - 7 * (SH + s + 1));
-        part[(wi * 16 + fr) * PS + wj * 64 + c * 16 + 4 * (lane >> 4) + t] = v;
-      }
+    for (int c = 0; c < FC; ++c) bf[c] = *reinterpret_cast<const i4_t*>(st + ob + c * OZ_UNIT);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const i4_t af = *reinterpret_cast<const i4_t*>(st + oa + s * OZ_UNIT);
+#pragma unroll
+      for (int c = 0; c < FC; ++c) acc[s][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf[c], acc[s][c], 0, 0, 0);
+    }
   }
-  __syncthreads();
-  if (wsl == 0) {
+
+  // the digits' sums, smallest first: one FP64 rounding each, then an exact scaling
+  const int i = ti * OZ_BM + ws * 16 + 4 * (lane >> 4);   // the lane's first row
+  const int4 e = *reinterpret_cast<const int4*>(g.ex + i);
+  double v[FC][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+  for (int c = 0; c < FC; ++c)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int jl = wj * 64 + c * 16 + 4 * (lane >> 4) + t;
-        const int j = j0 + jl;
-        double v = part[(wi * 16 + fr) * PS + jl];
+    for (int t = 0; t < 4; ++t) {
+      double x = (double)acc[0][c][t];
 #pragma unroll
-        for (int s = SH - 1; s >= 0; --s) v += ldexp((double)acc[s][c][t], e - 7 * (s + 1));
-        if (j < g.ncols) g.C[(int64_t)i + (int64_t)j * g.ldc] = v;
+      for (int s = 1; s < S; ++s) x = fma(x, 1.0 / 256.0, (double)acc[s][c][t]);
+      v[c][t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 55 + 8 * (S - 1));
+    }
+  if (g.red_q == 0) {
+#pragma unroll
+    for (int c = 0; c < FC; ++c) {
+      const int j = j0 + (wc * FC + c) * 16 + (lane & 15);
+      if (j >= g.ncols || (g.flags.at && g.flags.flagged(j, g.ncols))) continue;
+      double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)j * g.ldc);
+      o[0] = double2{v[c][0], v[c][1]};
+      o[1] = double2{v[c][2], v[c][3]};
+    }
+    return;
+  }
+  double* red = reinterpret_cast<double*>(smem);   // [strip][QC][192]
+  for (int q0 = 0; q0 < g.red_q; q0 += QC) {
+    const int qn = min(QC, g.red_q - q0);
+    __syncthreads();   // every wave is done with the ring (or with the previous pass)
+    for (int qq = 0; qq < qn; ++qq) {
+      const int q = q0 + qq;
+      const bool norm = q == g.red_q - 1;
+      double w[4] = {0.0, 0.0, 0.0, 0.0};
+      if (!norm) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) w[t] = g.W[(int64_t)(i + t) + (int64_t)q * g.ldw];
       }
+#pragma unroll
+      for (int c = 0; c < FC; ++c) {
+        double x = 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x += v[c][t] * (norm ? v[c][t] : w[t]);
+        x += __shfl_xor(x, 16, 64);
+        x += __shfl_xor(x, 32, 64);
+        if (lane < 16) red[(ws * QC + qq) * OZ_BN + (wc * FC + c) * 16 + lane] = x;
+      }
+    }
+    __syncthreads();
+    for (int f = threadIdx.x; f < qn * OZ_BN; f += OZ_THREADS) {   // the strips in order
+      const int qq = f / OZ_BN, jl = f % OZ_BN;
+      const double* r = red + qq * OZ_BN + jl;
+      if (j0 + jl < g.ncols)
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
+            ((r[0] + r[QC * OZ_BN]) + r[2 * QC * OZ_BN]) + r[3 * QC * OZ_BN];
     }
   }
 }

@@ -9,6 +9,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "gemm_f64.hpp"
 #include "setup_kernels.hpp"
 
 namespace gls {
@@ -140,26 +141,49 @@ void snp_reduce_solve_kernel(const double* __restrict__ Xt, int64_t ldx, int N, 
   }
 }
 
-// The per-SNP solve from row-tile partial sums (the product's fused epilogue):
+// The per-SNP solve from row-tile partial sums (the products' fused epilogues):
 // part[(t (P + 1) + q) mb + j] for row tiles t < Mt holds SNP j's sums over
-// tile t of x~ times [X~_L | y~] column q (q < P) and of x~^2 (q = P).  One
-// thread per SNP adds the tiles in order, then solves as snp_reduce_solve_kernel.
+// tile t of x~ times [X~_L | y~] column q (q < P) and of x~^2 (q = P).  SNPs
+// flagged in sel (all, if sel.at is nullptr) take the FP64 product's tiles
+// (part, Mt), the others the integer product's (part8, Mt8).
+//
+// Adding the tiles is a chain of dependent additions on scattered reads, so
+// eight threads share an SNP: thread group g adds tiles g, g + 8, ..., and the
+// first group adds the eight sums in order and solves as
+// snp_reduce_solve_kernel does.
+constexpr int PS_SNPS = 32, PS_GROUPS = 8;
+
 template <int P>
-__global__ __launch_bounds__(256) void snp_partials_solve_kernel(const double* __restrict__ part, int Mt, int mb,
-                                                                  const double* __restrict__ small, int n,
-                                                                  double* __restrict__ b, int64_t ldb,
-                                                                  double* __restrict__ sigma2, double* __restrict__ v,
-                                                                  int* __restrict__ status) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= mb) return;
+__global__ __launch_bounds__(PS_SNPS * PS_GROUPS)
+void snp_partials_solve_kernel(const double* __restrict__ part, int Mt, const double* __restrict__ part8, int Mt8,
+                               ColFlags sel, int mb, const double* __restrict__ small, int n, double* __restrict__ b,
+                               int64_t ldb, double* __restrict__ sigma2, double* __restrict__ v,
+                               int* __restrict__ status) {
+  __shared__ double red[PS_GROUPS - 1][P + 1][PS_SNPS];
+  const int s = threadIdx.x % PS_SNPS, g = threadIdx.x / PS_SNPS;
+  const int j = blockIdx.x * PS_SNPS + s;
   double sv[P + 1];
 #pragma unroll
   for (int q = 0; q <= P; ++q) sv[q] = 0.0;
-  for (int t = 0; t < Mt; ++t) {
-    const double* pt = part + (int64_t)t * (P + 1) * mb + j;
+  if (j < mb) {
+    const bool f64 = !part8 || (sel.at && sel.flagged(j, mb));
+    const double* pt = (f64 ? part : part8) + j;
+    const int T = f64 ? Mt : Mt8;
+#pragma unroll 2
+    for (int t = g; t < T; t += PS_GROUPS) {
 #pragma unroll
-    for (int q = 0; q <= P; ++q) sv[q] += pt[(int64_t)q * mb];
+      for (int q = 0; q <= P; ++q) sv[q] += pt[((int64_t)t * (P + 1) + q) * mb];
+    }
   }
+  if (g > 0) {
+#pragma unroll
+    for (int q = 0; q <= P; ++q) red[g - 1][q][s] = sv[q];
+  }
+  __syncthreads();
+  if (g > 0 || j >= mb) return;
+#pragma unroll
+  for (int q = 0; q <= P; ++q)
+    for (int o = 0; o < PS_GROUPS - 1; ++o) sv[q] += red[o][q][s];
   double bo[P];
   double s2, vv;
   int st;

@@ -1,0 +1,126 @@
+"""SNPs of whole numbers on the integer matrix cores, beside SNPs that are not.
+
+A GLS_FP64 handle with n > 256 samples gives every SNP whose values are whole
+numbers of magnitude at most 127 to the int8-slice product and every other one
+to the FP64 product.  Checked at the edges of both products' tiles (64 rows and
+192 SNPs; 128 rows and 64 SNPs), of the 16-SNP groups and of the 256-row
+padding, for aligned and unaligned columns:
+
+- every output against the CPU oracle at the plain-FP64 bar (1e-10);
+- each SNP's outputs bitwise the same alone and in the mixed block;
+- the same values as bytes, bitwise (values above 127 included).
+
+The integer product's own error bound: L^-1 is rounded at 2^-56 of its row's
+largest entry and each digit's sum is exact, so x~ is off by at most
+2^-55 n max|x| rowmax, below the FP64 product's n 2^-53 bound.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gls_oracle as O
+from paper_1302_4332_amd import synth
+from paper_1302_4332_amd.gls import GLSContext, GLSFunction, t2_loss
+from parity_util import as_numpy, compare
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _t(a):
+    return torch.tensor(np.ascontiguousarray(a), device=DEV)
+
+
+def _study(n, p, m):
+    Phi = synth.kinship(n, n + p)
+    XL = synth.covariates(n, p, n, "gauss") if p > 1 else np.empty((n, 0))
+    return Phi, XL, synth.phenotype(n, n), synth.genotypes(n, 0, m, n)
+
+
+def _mix(XR):
+    """Every third SNP leaves the integer product for another reason."""
+    X = XR.copy()
+    n = X.shape[1]
+    for k, j in enumerate(range(0, X.shape[0], 3)):
+        i = (37 * k) % n
+        if k % 5 == 0: X[j, i] += 0.25
+        elif k % 5 == 1: X[j, n - 1] = 128.0
+        elif k % 5 == 2: X[j] *= 1.0 / 3.0
+        elif k % 5 == 3: X[j, 0] = -1e300 if k % 2 else 2.0 ** -1074
+        else: X[j, i] = 2.0 ** 40
+    for j in range(1, X.shape[0], 3):   # whole numbers of either sign, and minus zero, stay
+        X[j] = np.where(X[j] == 0, -0.0, X[j] - 1.0) if j % 2 else X[j] * 63.0
+    return X
+
+
+@pytest.mark.parametrize("n,p,mb", [
+    (257, 4, 1), (320, 1, 15), (448, 3, 17), (511, 20, 191), (512, 4, 192), (513, 2, 193), (641, 8, 400), (1000, 4, 64),
+])
+def test_mixed_block(n, p, mb):
+    Phi, XL, y, XR = _study(n, p, mb)
+    X = _mix(XR)
+    X[np.abs(X) > 1e200] = 129.0   # the oracle's sums of squares stay finite
+    ctx = GLSContext(_t(Phi), 0.4, _t(XL) if p > 1 else None, _t(y), block_cols=mb)
+    whole = as_numpy(ctx.block(_t(X)))
+    err = compare(whole, O.gls_sequence(Phi, 0.4, XL, y, X), 1e-10)
+    off = torch.empty(mb * n + 1, dtype=torch.float64, device=DEV)[1:].view(mb, n)   # 8-byte aligned columns
+    off.copy_(_t(X))
+    un = as_numpy(ctx.block(off))
+    some = sorted({0, 1, 2, mb // 2, mb - 1} & set(range(mb)))
+    Xd = _t(X)
+    for k in ("b", "sigma2", "v", "status"):
+        assert np.array_equal(whole[k].view(np.uint8), un[k].view(np.uint8)), f"{k}: unaligned columns"
+    for j in some:
+        one = as_numpy(ctx.block(Xd[j:j + 1]))
+        for k in ("b", "sigma2", "v", "status"):
+            assert np.array_equal(one[k].view(np.uint8), whole[k][j:j + 1].view(np.uint8)), f"{k} of SNP {j}"
+    ctx.close()
+    print(f"n={n} p={p} mb={mb}: max rel err b {err:.1e}")
+
+
+@pytest.mark.parametrize("n,mb", [(300, 33), (1003, 200)])
+def test_bytes_beside_their_values(n, mb):
+    Phi, XL, y, XR = _study(n, 4, mb)
+    G = XR.astype(np.uint8)
+    G[::2] *= 60
+    G[5::7, 3] = 255
+    ctx = GLSContext(_t(Phi), 0.4, _t(XL), _t(y), block_cols=mb)
+    a, b = as_numpy(ctx.block_u8(_t(G))), as_numpy(ctx.block(_t(G.astype(np.float64))))
+    for k in a:
+        assert np.array_equal(a[k].view(np.uint8), b[k].view(np.uint8)), k
+    compare(a, O.gls_sequence(Phi, 0.4, XL, y, G.astype(np.float64)), 1e-10)
+    ctx.close()
+
+
+def test_values_that_are_no_numbers():
+    """NaN and infinite samples make their own SNP singular (status 1), and no other."""
+    n, mb = 700, 48
+    Phi, XL, y, XR = _study(n, 4, mb)
+    X = XR.copy()
+    X[3, 5], X[20, n - 1], X[40, 0] = np.nan, np.inf, -np.inf
+    ctx = GLSContext(_t(Phi), 0.4, _t(XL), _t(y), block_cols=mb)
+    got, ref = as_numpy(ctx.block(_t(X))), as_numpy(ctx.block(_t(XR)))
+    bad = np.zeros(mb, bool)
+    bad[[3, 20, 40]] = True
+    assert np.array_equal(got["status"], bad.astype(np.int32))
+    for k in ("b", "sigma2", "v"):
+        assert np.array_equal(got[k][~bad].view(np.uint8), ref[k][~bad].view(np.uint8)), k
+        assert np.isnan(got[k][bad]).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,bc", [(300, 50), (700, 96)])
+def test_gradient_of_a_mixed_study(n, bc):
+    """The adjoint recomputes a mixed block by both products: its gradients against the same study with every value
+    moved off the whole numbers by a relative 2^-40 (all on the FP64 product), whose gradients differ by about that."""
+    Phi, XL, y, XR = _study(n, 3, 130)
+    X = XR.copy()
+    X[::4] *= 1.0 / 3.0
+    grads = []
+    for f in (1.0, 1.0 + 2.0 ** -40):
+        yt, Xt = _t(y).requires_grad_(True), _t(X * f).requires_grad_(True)
+        h2 = torch.tensor(0.4, dtype=torch.float64, device=DEV, requires_grad=True)
+        out = GLSFunction.apply(yt, Xt, h2, _t(Phi), _t(XL), bc)
+        grads.append([g.cpu().numpy() for g in torch.autograd.grad(t2_loss(*out), (yt, Xt, h2))])
+    for a, b in zip(*grads):
+        assert np.abs(a - b).max() <= 1e-9 * np.abs(b).max()
