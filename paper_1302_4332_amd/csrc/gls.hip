@@ -589,7 +589,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
   if (pl.whole) {
     c->sl = reinterpret_cast<int8_t*>(ws + pl.off_sl);
     c->ex = reinterpret_cast<int*>(ws + pl.off_ex);
-    const unsigned T = (unsigned)(N / OZ_BM);
+    const unsigned T = (unsigned)(N / OZ_TM);
     hipLaunchKernelGGL(row_max_kernel, dim3(T, (unsigned)((N + 255) / 256)), dim3(256), 0, s, c->Linv, (int)N, c->Xt);
     hipLaunchKernelGGL(slice_factor_kernel, dim3(T, T), dim3(256), 0, s, c->Linv, (int)N, (const double*)c->Xt, c->ex,
                        c->sl);
@@ -1058,8 +1058,8 @@ static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb,
 
 // Products with L^-1 of SNPs that are whole numbers, on the integer matrix
 // cores.  The block's int8 operand lies in units[], after the per-SNP sums of
-// the two products (their 128- and 64-row tiles) in c->Xt:
-// (p + 1) (8 / 128 + 8 / 64) + 1 + 1 / 64 <= 5 of the 8 bytes per row and SNP.
+// the two products (their 128- and 32-row tiles) in c->Xt:
+// (p + 1) (8 / 128 + 8 / 32) + 1 + 1 / 64 < 7.6 of the 8 bytes per row and SNP.
 struct WholeBlock {
   uint8_t* units = nullptr;
   int* flags_at = nullptr;
@@ -1167,7 +1167,7 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
     {
       PhaseTimer t(c, PH_WHITEN, s);
       if (c->plan.whole) {
-        w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_BM - 1) / OZ_BM * OZ_BM));
+        w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
         pack_f64(c, XR, ld_xr, mb, &w, s);
         whole_product(c, w, mb, nullptr, s);
       }
@@ -1209,7 +1209,7 @@ static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t 
   WholeBlock w;
   {
     PhaseTimer t(c, PH_WHITEN, s);
-    w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_BM - 1) / OZ_BM * OZ_BM));
+    w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
     const bool check = SRC == OZ_U8 && c->opts.precision != GLS_INT8_EMU;
     pack_units<SRC>(c, G, ldg, mb, check, &w, s);
     whole_product(c, w, mb, nullptr, s);

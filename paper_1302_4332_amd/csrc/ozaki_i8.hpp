@@ -34,13 +34,14 @@ namespace gls {
 
 constexpr int OZ_SLICES = 7;
 constexpr int OZ_UNIT = 1024;                        // bytes of a unit
-constexpr int OZ_BM = 64, OZ_BK = 64;                // rows of L^-1 and k per stage
+constexpr int OZ_BM = 32, OZ_BK = 64;                // rows of a product tile and k per stage
 constexpr int OZ_STRIPS = OZ_BM / 16;
-constexpr int OZ_ATILE = OZ_STRIPS * OZ_SLICES * OZ_UNIT;   // one (row tile, k block) of the sliced factor
+constexpr int OZ_TM = 64;                            // rows of a tile of the sliced factor
+constexpr int OZ_ATILE = OZ_TM / 16 * OZ_SLICES * OZ_UNIT;   // one (row tile, k block) of the sliced factor
 
 // Bytes of the sliced factor: row tile t holds the k blocks 0..t that reach the lower triangle.
 inline size_t oz_factor_bytes(int64_t N) {
-  const int64_t T = N / OZ_BM;
+  const int64_t T = N / OZ_TM;
   return (size_t)(T * (T + 1) / 2) * OZ_ATILE;
 }
 
@@ -250,28 +251,36 @@ struct OzArgs {
   double* C; int64_t ldc; // red_q == 0: the product itself, N x ncols FP64
 };
 
-// A workgroup of eight waves owns 64 rows x 192 SNPs: wave w takes the 16-row
-// strip w & 3 and the 96-SNP half w >> 2 with all seven digits, 7 x 6
+// A workgroup of four waves owns 32 rows x 192 SNPs: wave w takes the 16-row
+// strip w & 1 and the 96-SNP half w >> 1 with all seven digits, 7 x 6
 // accumulators of 16 x 16 (168 registers; two waves per SIMD).  Per 64-deep
-// stage it reads seven + six 1 KB fragments for 42 MFMAs, so the LDS port is
-// busy 0.86 of the MFMA time with the stage's own 40 KB of writes; the 32 x 256
-// tile of sixteen waves with 4 x 4 accumulators that this replaced needed 1.25
-// of it and ran the MFMA pipes 47% of the time.  Stages move straight from
-// global memory into a ring of three LDS buffers, two ahead of the MFMAs.
+// stage it reads seven + six 1 KB fragments for 42 MFMAs; sixteen waves of
+// 4 x 4 accumulators on a 32 x 256 tile read eight for 16 and kept the LDS port
+// busy for longer than the MFMA pipes.  Stages move straight from global memory
+// into a ring of three LDS buffers, two ahead of the MFMAs.
+//
+// What bounds it: the MFMA pipes are busy 58% of the launch and the clock falls
+// to 2.1 GHz under its power (n = 10,000, 8,192 SNPs: 2.3 ms, 2,500 TOPS; with
+// all-zero SNPs 2.0 ms).  The rest is waits after the stage barrier, which is why
+// two workgroups with barriers of their own share a compute unit: one workgroup
+// of eight waves (64 rows) had its pipes busy 48% and took 2.6 ms.  XCD groups of
+// 4 x 8 tiles; 2 x 16 and 4 x 16 are equal within noise, 8 x 4 and 8 x 8 6%
+// slower.
 //
 // A wave's accumulator element t of lane l is row 4 (l / 16) + t, SNP l % 16 of
 // its 16 x 16 block, so a sum over the rows is four values of the lane and two
 // lane exchanges.
-constexpr int OZ_BN = 192, OZ_THREADS = 512, OZ_STAGES = 3;
+constexpr int OZ_BN = 192, OZ_THREADS = 256, OZ_STAGES = 3;
 constexpr int OZ_MAP_GM = 4, OZ_MAP_GN = 8;
 
 __global__ __launch_bounds__(OZ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ozaki_i8_kernel(OzArgs g) {
   constexpr int S = OZ_SLICES, NW = OZ_THREADS / 64, NS = OZ_STAGES;
   constexpr int BU = OZ_BN / 16, FC = BU / 2;              // SNP groups per tile and per wave
-  constexpr int AU = OZ_STRIPS * S, STAGE = (AU + BU) * OZ_UNIT, NLD = (AU + BU) / NW;
+  constexpr int AU = OZ_STRIPS * S, STAGE = (AU + BU) * OZ_UNIT;
+  constexpr int NLD = (AU + BU + NW - 1) / NW, FULL = AU + BU - (NLD - 1) * NW;   // loads a stage; waves < FULL do NLD, the others one less
   constexpr int QC = 10;                                   // sums per pass of the epilogue's LDS exchange
-  static_assert(NLD * NW == AU + BU && NS * STAGE <= 160 * 1024 && OZ_STRIPS * QC * OZ_BN * 8 <= NS * STAGE, "LDS");
+  static_assert(NS * STAGE <= 80 * 1024 && OZ_STRIPS * QC * OZ_BN * 8 <= NS * STAGE, "LDS");
   __shared__ __align__(1024) int8_t smem[NS * STAGE];
   __shared__ int any;
 
@@ -283,20 +292,21 @@ void ozaki_i8_kernel(OzArgs g) {
     m.map_desc = 1;
     if (!XcdMap::tile(m, blockIdx.x, g.Mt, (g.ncols + OZ_BN - 1) / OZ_BN, &ti, &tj)) return;
   }
-  const int nk = ti + 1;   // lower triangular factor
+  const int nk = ti * OZ_BM / OZ_TM + 1;   // lower triangular factor
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ws = wave & 3, wc = wave >> 2;
+  const int ws = wave & 1, wc = wave >> 1;
   const int j0 = tj * OZ_BN, jb0 = tj * BU;
 
-  const int8_t* Abase = g.A + (int64_t)ti * (ti + 1) / 2 * OZ_ATILE;
+  const int8_t* Abase = g.A + (int64_t)(nk - 1) * nk / 2 * OZ_ATILE + ti % (OZ_TM / OZ_BM) * (AU * OZ_UNIT);
   const uint32_t lds0 = lds_address(smem);
   const uint32_t voff = 16 * lane;
   auto issue = [&](int kb) {
     const uint32_t base = lds0 + (uint32_t)((kb % NS) * STAGE);
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
-      const int u = q * NW + wave;   // wave-uniform: A's units, then B's (groups past the end: the last one's, dropped)
+      const int u = q * NW + wave;
+      if (u >= AU + BU) break;       // wave-uniform: A's units, then B's (groups past the end: the last one's, dropped)
       const void* p = (u < AU) ? (const void*)(Abase + (int64_t)kb * OZ_ATILE + u * OZ_UNIT)
                                : (const void*)(g.B + ((int64_t)kb * g.Jb + min(jb0 + u - AU, g.Jb - 1)) * OZ_UNIT);
       lds_load16_sv(p, voff, base + (uint32_t)(u * OZ_UNIT));
@@ -323,7 +333,8 @@ void ozaki_i8_kernel(OzArgs g) {
 
   const int oa = ws * S * OZ_UNIT + 16 * lane, ob = (AU + wc * FC) * OZ_UNIT + 16 * lane;
   for (int it = 0; it < nk; ++it) {
-    wait_stages<NLD>(min(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
+    if (wave < FULL) wait_stages<NLD>(min(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
+    else wait_stages<NLD - 1>(min(nk - 1 - it, NS - 2));
     __syncthreads();                              // ... and every wave's; stage (it - 1) % NS is free
     if (it + NS - 1 < nk) issue(it + NS - 1);
     const int8_t* st = smem + (it % NS) * STAGE;
@@ -390,7 +401,7 @@ void ozaki_i8_kernel(OzArgs g) {
       const double* r = red + qq * OZ_BN + jl;
       if (j0 + jl < g.ncols)
         g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
-            ((r[0] + r[QC * OZ_BN]) + r[2 * QC * OZ_BN]) + r[3 * QC * OZ_BN];
+            r[0] + r[QC * OZ_BN];
     }
   }
 }

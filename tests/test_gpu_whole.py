@@ -2,7 +2,7 @@
 
 A GLS_FP64 handle with n > 256 samples gives every SNP whose values are whole
 numbers of magnitude at most 127 to the int8-slice product and every other one
-to the FP64 product.  Checked at the edges of both products' tiles (64 rows and
+to the FP64 product.  Checked at the edges of both products' tiles (32 rows and
 192 SNPs; 128 rows and 64 SNPs), of the 16-SNP groups and of the 256-row
 padding, for aligned and unaligned columns:
 
