@@ -186,10 +186,12 @@ typedef struct {
  * and copy streams, after the work already queued on compute_stream.  HIP
  * multiplexes streams onto a few hardware queues, and on a shared queue the
  * copy pipeline's cross-stream waits hold up the other stream: copies and
- * solves would run one after another.  gls_setup therefore checks that a wait
- * on its copy stream does not hold up its compute stream, and re-creates the
- * copy stream (at most four times) until it does not.  A caller-given copy
- * stream gets no such check.
+ * solves would run one after another.  The library therefore checks that a
+ * wait on its copy stream does not hold up its compute stream, and re-creates
+ * the copy stream (at most four times) until it does not.  A handle takes such
+ * a pair at its first streamed study, from the pairs that closed handles left
+ * (at most four a device are kept) or a new one.  A caller-given copy stream
+ * gets no such check.
  * Returns after every result has landed.  col0 > 0 resumes an interrupted
  * run: outputs for columns < col0 are not touched.  col0 == m (an empty
  * stream) returns GLS_OK at once, and the pointers may then be NULL. */

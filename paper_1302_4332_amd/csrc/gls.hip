@@ -122,6 +122,7 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
       pl->side_at[d] = at;
       at += most[d] * NB_LEAF * NB_LEAF;
     }
+    pl->side_products = at > 0;
     pl->off_side = take(sizeof(double) * std::max<int64_t>(at, 1));
   }
   pl->off_buf0 = take(sizeof(double) * n * bc);
@@ -654,6 +655,12 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
 // queue do overlap, so sharing c's queue does not fail the check; a slow host
 // can only make its answer a false "shared".)  The copy stream is re-created
 // until the check passes, at most four times.
+//
+// Creating and checking a pair takes about 0.8 ms, as long as the whole of a
+// study of 512 samples, and a stream keeps its hardware queue for life.  So a
+// handle takes its pair at its first streamed study without a copy stream, and
+// gives it back when it is destroyed; idle pairs (and the setup's side streams)
+// of each device wait in a pool of at most POOL_MAX for the next handle.
 __global__ void idle_kernel(int rounds) {
   for (int r = 0; r < rounds; ++r) __builtin_amdgcn_s_sleep(127);
 }
@@ -672,6 +679,56 @@ static bool wait_is_isolated(hipStream_t comp, hipStream_t copy, hipStream_t c, 
   return ok;
 }
 
+constexpr size_t POOL_MAX = 4;   // idle pairs, and idle side streams, kept per device
+
+struct IdleStreams {
+  struct Pair {
+    int device;
+    hipStream_t st[2];
+  };
+  struct Side {
+    int device;
+    hipStream_t st;
+  };
+  std::mutex mu;
+  std::vector<Pair> pairs;
+  std::vector<Side> sides;
+};
+// never destroyed: a handle may be closed while the process ends
+static IdleStreams& idle_streams() {
+  static IdleStreams* pool = new IdleStreams;
+  return *pool;
+}
+
+static hipError_t take_side_stream(int device, hipStream_t* st) {
+  {
+    IdleStreams& pool = idle_streams();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    for (size_t i = 0; i < pool.sides.size(); ++i) {
+      if (pool.sides[i].device != device) continue;
+      *st = pool.sides[i].st;
+      pool.sides.erase(pool.sides.begin() + i);
+      return hipSuccess;
+    }
+  }
+  return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+}
+
+// The stream has nothing left to run.
+static void give_side_stream(int device, hipStream_t st) {
+  {
+    IdleStreams& pool = idle_streams();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    size_t have = 0;
+    for (const auto& s : pool.sides) have += s.device == device;
+    if (have < POOL_MAX) {
+      pool.sides.push_back({device, st});
+      return;
+    }
+  }
+  (void)hipStreamDestroy(st);
+}
+
 static hipError_t make_stream_pair(hipStream_t st[2], hipStream_t caller, hipEvent_t ev) {
   hipError_t e = hipStreamCreateWithFlags(&st[0], hipStreamNonBlocking);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&st[1], hipStreamNonBlocking);
@@ -688,6 +745,41 @@ static hipError_t make_stream_pair(hipStream_t st[2], hipStream_t caller, hipEve
   }
   for (hipStream_t r : rejected) (void)hipStreamDestroy(r);
   return hipSuccess;
+}
+
+hipError_t take_stream_pair(Ctx* c, hipStream_t caller) {
+  if (c->own_st[0]) return hipSuccess;
+  {
+    IdleStreams& pool = idle_streams();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    for (size_t i = 0; i < pool.pairs.size(); ++i) {
+      if (pool.pairs[i].device != c->device) continue;
+      c->own_st[0] = pool.pairs[i].st[0];
+      c->own_st[1] = pool.pairs[i].st[1];
+      pool.pairs.erase(pool.pairs.begin() + i);
+      return hipSuccess;
+    }
+  }
+  return make_stream_pair(c->own_st, caller, c->ev_join);
+}
+
+static void give_stream_pair(Ctx* c) {
+  hipStream_t* st = c->own_st;
+  bool idle = st[0] && st[1];
+  for (int i = 0; i < 2; ++i)
+    if (st[i] && hipStreamSynchronize(st[i]) != hipSuccess) idle = false;
+  if (idle) {
+    IdleStreams& pool = idle_streams();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    size_t have = 0;
+    for (const auto& q : pool.pairs) have += q.device == c->device;
+    if (have < POOL_MAX) {
+      pool.pairs.push_back({c->device, {st[0], st[1]}});
+      st[0] = st[1] = nullptr;
+    }
+  }
+  for (int i = 0; i < 2; ++i)
+    if (st[i]) (void)hipStreamDestroy(st[i]);
 }
 
 }  // namespace gls
@@ -746,21 +838,21 @@ gls_status gls_setup(gls_handle* out, int64_t n, int32_t p, const double* Phi, i
     gls_destroy(c);
     return hip_fail(e, "gls_setup: event create");
   }
-  hipStream_t side = nullptr;   // the factorization's side products
-  if ((e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking)) != hipSuccess) {
+  if ((e = hipGetDevice(&c->device)) != hipSuccess) {
+    gls_destroy(c);
+    return hip_fail(e, "gls_setup: device");
+  }
+  hipStream_t side = nullptr;   // the factorization's side products, where it has any
+  if (pl.side_products && (e = take_side_stream(c->device, &side)) != hipSuccess) {
     gls_destroy(c);
     return hip_fail(e, "gls_setup: side stream create");
   }
   st = setup_into(c, pl, n, p, Phi, ld_phi, h2, XL, ld_xl, y, static_cast<char*>(workspace), opts, side,
                   static_cast<hipStream_t>(stream), info);
-  (void)hipStreamDestroy(side);   // joined into `stream`, which setup_into synchronized
+  if (side) give_side_stream(c->device, side);   // joined into `stream`, which setup_into synchronized
   if (st != GLS_OK) {
     gls_destroy(c);
     return st;
-  }
-  if ((e = make_stream_pair(c->own_st, static_cast<hipStream_t>(stream), c->ev_join)) != hipSuccess) {
-    gls_destroy(c);
-    return hip_fail(e, "gls_setup: stream create");
   }
   c->ready = true;
   *out = c;
@@ -864,12 +956,7 @@ void gls_destroy(gls_handle h) {
     (void)hipEventDestroy(r.b);
   }
   for (hipEvent_t e : c->prof_free) (void)hipEventDestroy(e);
-  for (int i = 0; i < 2; ++i) {
-    if (c->own_st[i]) {
-      (void)hipStreamSynchronize(c->own_st[i]);
-      (void)hipStreamDestroy(c->own_st[i]);
-    }
-  }
+  give_stream_pair(c);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
   for (int i = 0; i < 2; ++i) {
     if (c->ev_copy[i]) (void)hipEventDestroy(c->ev_copy[i]);

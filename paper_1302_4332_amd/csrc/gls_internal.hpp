@@ -37,6 +37,7 @@ struct Plan {
   // one region per recursion depth (offsets in doubles from off_side)
   size_t off_side = 0;
   int64_t side_at[16] = {0};
+  bool side_products = false;   // some node's product runs there
   int leaves = 0;   // NB_LEAF-row diagonal blocks factored: rows n..N-1 past them are the identity
   size_t total = 0;
 };
@@ -49,6 +50,7 @@ struct gls_ctx {
   int64_t n = 0, N = 0, bc = 0;
   int p = 0;
   double h2 = 0.0;
+  int device = 0;
   bool ready = false;
   // device regions (inside the workspace)
   int* info = nullptr;      // [0] pivot of M, [1] pivot of S_TL
@@ -90,8 +92,8 @@ struct gls_ctx {
   double* acc = nullptr;    // nc accumulated shared adjoints, then partial sums
   hipEvent_t ev_copy[2] = {nullptr, nullptr};
   hipEvent_t ev_comp[2] = {nullptr, nullptr};
-  // the handle's own compute and copy streams for streamed studies, and the
-  // event that orders them after the caller's stream
+  // the handle's own compute and copy streams for streamed studies (from its
+  // first one on), and the event that orders them after the caller's stream
   hipStream_t own_st[2] = {nullptr, nullptr};
   hipEvent_t ev_join = nullptr;
   // phase timing (gls_profile_*)
@@ -129,6 +131,7 @@ gls_status hip_fail(hipError_t e, const char* what);
 gls_status arg_fail(const char* what);
 void set_last_error_str(const char* what);
 int64_t padded_n(int64_t n);
+hipError_t take_stream_pair(Ctx* c, hipStream_t caller);
 bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl);
 
 void prepare_low_precision(Ctx* c, hipStream_t s);

@@ -119,7 +119,7 @@ int64_t part_start(int64_t cols, int parts, int q) {
 }
 
 // The streams a study runs on: the caller's pair, or, without a copy stream,
-// the handle's own pair (checked at setup not to share a hardware queue),
+// the handle's own pair (checked not to share a hardware queue),
 // after the work already queued on the caller's compute stream.
 struct RunStreams {
   hipStream_t sc = nullptr, sx = nullptr;
@@ -132,9 +132,15 @@ hipError_t run_streams(Ctx* c, void* compute_stream, void* copy_stream, RunStrea
     r->sx = copy_stream ? static_cast<hipStream_t>(copy_stream) : caller;
     return hipSuccess;
   }
+  int current = 0;
+  hipError_t e = hipGetDevice(&current);
+  if (e == hipSuccess && current != c->device) e = hipSetDevice(c->device);
+  if (e == hipSuccess) e = take_stream_pair(c, caller);
+  if (current != c->device) (void)hipSetDevice(current);
+  if (e != hipSuccess) return e;
   r->sc = c->own_st[0];
   r->sx = c->own_st[1];
-  hipError_t e = hipEventRecord(c->ev_join, caller);
+  e = hipEventRecord(c->ev_join, caller);
   if (e == hipSuccess) e = hipStreamWaitEvent(r->sc, c->ev_join, 0);
   if (e == hipSuccess) e = hipStreamWaitEvent(r->sx, c->ev_join, 0);
   return e;
@@ -169,10 +175,11 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
   }
   EventPool pool;
   hipError_t e;
-  // per block: compute start/stop; wall start/stop; the arrival of each part of the two buffers
-  if ((e = pool.make(2 * nblk + 2 + 2 * STREAM_PARTS)) != hipSuccess) return hip_fail(e, "gls_stream: event create");
+  // per block: compute start/stop; wall start/stop; the arrival of the two buffers' parts after the first
+  const int more = parts_of(c, XR_host, bc) - 1;
+  if ((e = pool.make(2 * nblk + 2 + 2 * more)) != hipSuccess) return hip_fail(e, "gls_stream: event create");
   hipEvent_t wall0 = pool.ev[2 * nblk], wall1 = pool.ev[2 * nblk + 1];
-  auto arrived = [&](int buf, int q) { return pool.ev[2 * nblk + 2 + buf * STREAM_PARTS + q]; };
+  auto arrived = [&](int buf, int q) { return q == 0 ? c->ev_copy[buf] : pool.ev[2 * nblk + 2 + buf * more + q - 1]; };
 
   auto cols_of = [&](int64_t blk) { return bstart[blk + 1] - bstart[blk]; };
   auto src_of = [&](int64_t blk) { return XR_host + (col0 + bstart[blk]) * ld_xr; };
@@ -200,7 +207,7 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
     const int64_t col = col0 + bstart[blk];
     if (blk + 1 < nblk && sx != sc) {
       // beta may only be overwritten once the solve that last read it is done
-      if (blk >= 1 && (e = hipStreamWaitEvent(sx, c->ev_comp[nxt], 0)) != hipSuccess)
+      if (blk >= 1 && (e = hipStreamWaitEvent(sx, pool.ev[2 * (blk - 1) + 1], 0)) != hipSuccess)
         return hip_fail(e, "gls_stream: wait");
       if ((e = copy_block(blk + 1, nxt)) != hipSuccess) return hip_fail(e, "gls_stream: H2D");
     }
@@ -215,7 +222,6 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
                                  c->os2 + j0, c->ov + j0, c->ost + j0, sc);
       if (r != GLS_OK) return r;
     }
-    if ((e = hipEventRecord(c->ev_comp[cur], sc)) != hipSuccess) return hip_fail(e, "gls_stream: record");
     if ((e = hipEventRecord(pool.ev[2 * blk + 1], sc)) != hipSuccess) return hip_fail(e, "gls_stream: record");
     // results of this block; same stream, so the next block's kernels wait for them
     struct {

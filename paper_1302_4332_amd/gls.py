@@ -342,7 +342,7 @@ class GLSContext:
 
         The study runs after the work queued on compute_stream (default: the
         current stream).  With copy_stream None it runs on the handle's own
-        compute and copy streams, which setup checked do not share a hardware
+        compute and copy streams, which are checked not to share a hardware
         queue; a caller-given copy stream gets no such check.  Returns
         (b, sigma2, v, status) host tensors and the stats struct.
         """
