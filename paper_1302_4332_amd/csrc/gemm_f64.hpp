@@ -247,10 +247,13 @@ struct Stager {
   }
 };
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool TRANS_A, bool TRANS_B, int MAP, bool VEC,
-          bool M4 = true>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
-void gemm_f64_kernel(GemmArgs g) {
+// LDS doubles of a tile's two buffers (A's, then B's).
+template <int BM, int BN, int BK>
+constexpr int gemm_lds() { return 2 * BK * (BM + 16 + BN + 16); }
+
+// Tile (ti, tj) of a product, by one workgroup; lds: gemm_lds() doubles.
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool TRANS_A, bool TRANS_B, bool VEC, bool M4>
+__device__ __forceinline__ void gemm_f64_tile(const GemmArgs& g, int ti, int tj, double* lds) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M;
   constexpr int WTN = BN / WAVES_N;
@@ -262,18 +265,8 @@ void gemm_f64_kernel(GemmArgs g) {
   static_assert(BM % (16 * WAVES_M) == 0 && BN % (16 * WAVES_N) == 0, "tile");
   static_assert(BK % 8 == 0, "k step");
 
-  __shared__ double As[2][BK * SA];
-  __shared__ double Bs[2][BK * SB];
-
-  int ti, tj;
-  if (MAP == MAP_XCD) {
-    const int Mt = g.M / BM;
-    const int Nt = (g.ncols + BN - 1) / BN;
-    if (!XcdMap::tile(g, blockIdx.x, Mt, Nt, &ti, &tj)) return;
-  } else {
-    tj = blockIdx.x;
-    ti = blockIdx.y;
-  }
+  double* As = lds;                 // [2][BK * SA]
+  double* Bs = lds + 2 * BK * SA;   // [2][BK * SB]
   const int i0 = ti * BM;
   const int j0 = tj * BN;
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;
@@ -310,13 +303,13 @@ void gemm_f64_kernel(GemmArgs g) {
   St st;
   if (nk > 0) {
     st.load(g, i0, j0, klo, tid);
-    st.store(As[0], Bs[0], tid);
+    st.store(As, Bs, tid);
     __syncthreads();
     for (int it = 0; it < nk; ++it) {
       const int buf = it & 1;
       if (it + 1 < nk) st.load(g, i0, j0, klo + (it + 1) * BK, tid);
-      const double* as = As[buf];
-      const double* bs = Bs[buf];
+      const double* as = As + buf * (BK * SA);
+      const double* bs = Bs + buf * (BK * SB);
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 4) {
         const int kr = kk + (lane >> 4);
@@ -341,7 +334,7 @@ void gemm_f64_kernel(GemmArgs g) {
               acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
         }
       }
-      if (it + 1 < nk) st.store(As[buf ^ 1], Bs[buf ^ 1], tid);
+      if (it + 1 < nk) st.store(As + (buf ^ 1) * (BK * SA), Bs + (buf ^ 1) * (BK * SB), tid);
       __syncthreads();
     }
   }
@@ -381,6 +374,38 @@ void gemm_f64_kernel(GemmArgs g) {
       }
     }
   }
+}
+
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool TRANS_A, bool TRANS_B, int MAP, bool VEC,
+          bool M4 = true>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
+void gemm_f64_kernel(GemmArgs g) {
+  __shared__ double lds[gemm_lds<BM, BN, BK>()];
+  int ti, tj;
+  if (MAP == MAP_XCD) {
+    const int Mt = g.M / BM;
+    const int Nt = (g.ncols + BN - 1) / BN;
+    if (!XcdMap::tile(g, blockIdx.x, Mt, Nt, &ti, &tj)) return;
+  } else {
+    tj = blockIdx.x;
+    ti = blockIdx.y;
+  }
+  gemm_f64_tile<BM, BN, BK, WAVES_M, WAVES_N, TRANS_A, TRANS_B, VEC, M4>(g, ti, tj, lds);
+}
+
+// Two products of one node of the factorization in one launch (blockIdx.z):
+// the trailing update A B^T and the product A B with the same A.  32 x 32 tiles
+// and long stages: the small nodes' products have too few 64 x 64 tiles to
+// occupy the chip, and a stage waits once for memory whatever its depth.
+constexpr int PAIR_BM = 32, PAIR_BN = 32, PAIR_BK = 64;
+
+__global__ __launch_bounds__(256) void gemm_f64_pair_kernel(GemmArgs g0, GemmArgs g1) {
+  __shared__ double lds[gemm_lds<PAIR_BM, PAIR_BN, PAIR_BK>()];
+  const int ti = blockIdx.y, tj = blockIdx.x;
+  const GemmArgs& g = blockIdx.z == 0 ? g0 : g1;
+  if (ti * PAIR_BM >= g.M || tj * PAIR_BN >= g.ncols) return;
+  if (blockIdx.z == 0) gemm_f64_tile<PAIR_BM, PAIR_BN, PAIR_BK, 2, 2, false, true, true, true>(g0, ti, tj, lds);
+  else gemm_f64_tile<PAIR_BM, PAIR_BN, PAIR_BK, 2, 2, false, false, true, true>(g1, ti, tj, lds);
 }
 
 // Whether the chunked (VEC) loader may be used for these arguments.

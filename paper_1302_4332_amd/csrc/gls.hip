@@ -292,6 +292,18 @@ struct SetupSide {
   }
 };
 
+// S <- alpha Li S (columns of S) or S <- alpha S Li^T (ROWS) in place, for the w x w lower-triangular Li and
+// `strips` columns or rows of S (ld both), w and strips multiples of 128.  w <= 1,024: nodes of less than 1,024 x
+// 1,024 outputs split their leaves evenly.
+template <bool ROWS>
+static void tri_strips(const double* Li, int64_t ld, double* S, int w, int strips, double alpha, hipStream_t s) {
+  const dim3 grid(strips / 16), block(512);
+  if (w <= 128) hipLaunchKernelGGL((tri_strip_kernel<128, ROWS>), grid, block, 0, s, Li, ld, S, w, alpha);
+  else if (w <= 256) hipLaunchKernelGGL((tri_strip_kernel<256, ROWS>), grid, block, 0, s, Li, ld, S, w, alpha);
+  else if (w <= 512) hipLaunchKernelGGL((tri_strip_kernel<512, ROWS>), grid, block, 0, s, Li, ld, S, w, alpha);
+  else hipLaunchKernelGGL((tri_strip_kernel<1024, ROWS>), grid, block, 0, s, Li, ld, S, w, alpha);
+}
+
 static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipStream_t s) {
   const int64_t N = c->N;
   double* L = c->L;
@@ -311,8 +323,24 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
   const double* Li11 = Li + r1 + r1 * N;
   double* Li21 = Li + r2 + r1 * N;
   const double* Li22 = Li + r2 + r2 * N;
+  if (!big_product(w2, w1)) {
+    // Small nodes are bound by latency: three launches, every product in place.  T = L21 L11^-1 waits for its last
+    // product in the block of L^-1 that this will overwrite.
+    tri_strips<true>(Li11, N, A21, w1, w2, 1.0, s);   // L21 = A21 L11^-T
+    GemmArgs u = gemm_args(A21, N, A21, N, A22, N, w2, w2, w1, -1.0);   // A22 -= L21 L21^T (lower tiles)
+    u.beta = 1.0;
+    u.c_lower = 1;
+    u.c_diag = 0;
+    GemmArgs t = gemm_args(A21, N, Li11, N, Li21, N, w2, w1, w1, 1.0);   // T
+    t.b_tri = TRI_LOWER;
+    t.b_diag = 0;
+    hipLaunchKernelGGL(gemm_f64_pair_kernel, dim3(std::max(w1, w2) / PAIR_BN, w2 / PAIR_BM, 2), dim3(256), 0, s, u, t);
+    chol_inv_rec(c, mid, b, depth + 1, side, s);
+    tri_strips<false>(Li22, N, Li21, w2, w1, -1.0, s);   // (L^-1)21 = -L22^-1 T
+    return;
+  }
   double* T = c->Xt;  // w2 x w1, ld w2
-  if (big_product(w2, w1)) {
+  {
     // Both products without transposed operands, so they run on the direct-load kernel:
     //   U = L21^T = L11^-1 A21^T (U, A21^T: w1 x w2, ld w1), L21 = U^T, A22 -= L21 U.
     double* At = c->Xt;
@@ -336,25 +364,8 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
       g.map_desc = 1;
       gemm(false, false, true, g, s);
     }
-  } else {
-    hipLaunchKernelGGL(copy2d_kernel, dim3(grid_for((int64_t)w2 * w1)), dim3(256), 0, s, T, (int64_t)w2, A21, N, w2,
-                       w1);
-    {  // L21 = T * L11^-T   (op(B)[k][j] = Li11[j][k], non-zero for k <= j: upper)
-      GemmArgs g = gemm_args(T, w2, Li11, N, A21, N, w2, w1, w1, 1.0);
-      g.b_tri = TRI_UPPER;
-      g.b_diag = 0;
-      gemm(false, true, false, g, s);
-    }
-    {  // A22 -= L21 L21^T  (lower tiles)
-      GemmArgs g = gemm_args(A21, N, A21, N, A22, N, w2, w2, w1, -1.0);
-      g.beta = 1.0;
-      g.c_lower = 1;
-      g.c_diag = 0;
-      g.map_desc = 1;
-      gemm(false, true, big_product(w2, w2), g, s);
-    }
   }
-  const bool on_side = big_product(w2, w1) && depth < 16 && side->st != nullptr;
+  const bool on_side = depth < 16 && side->st != nullptr;
   if (on_side) {   // T = L21 L11^-1 on the side stream, into this depth's region
     T = side->base + c->plan.side_at[depth];
     side->check(hipEventRecord(side->fork, s));
@@ -372,14 +383,14 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
     GemmArgs g = gemm_args(A21, N, Li11, N, T, w2, w2, w1, w1, 1.0);
     g.b_tri = TRI_LOWER;
     g.b_diag = 0;
-    gemm(false, false, big_product(w2, w1), g, s);
+    gemm(false, false, true, g, s);
   }
   {  // (L^-1)21 = -L22^-1 T   (op(A) = Li22 lower: non-zero for k <= i)
     GemmArgs g = gemm_args(Li22, N, T, w2, Li21, N, w2, w1, w2, -1.0);
     g.a_tri = TRI_LOWER;
     g.a_diag = 0;
     g.map_desc = 1;
-    gemm(false, false, big_product(w2, w1), g, s);
+    gemm(false, false, true, g, s);
   }
 }
 

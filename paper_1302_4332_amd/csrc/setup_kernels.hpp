@@ -170,44 +170,57 @@ __global__ void tri_apply_sum_kernel(const double* __restrict__ part, int N, int
   }
 }
 
-// 1/p to full double precision: hardware reciprocal estimate plus two
-// Newton steps (off the IEEE division's long sequence; used where the last
-// bit is immaterial, the pivots of the right-looking update).
-__device__ __forceinline__ double fast_rcp(double p) {
-  double r = __builtin_amdgcn_rcp(p);
-  double e = __builtin_fma(-p, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-p, r, 1.0);
-  return __builtin_fma(r, e, r);
+// 1 / sqrt(d) to full double precision: the hardware estimate (relative error
+// below 2^-22) and one third-order step, r (1 + e / 2 + 3 e^2 / 8) with
+// e = 1 - d r^2.  (A dependent FP64 fma takes 20 cycles, a multiplication or
+// addition 8: one such step is shorter than two of Newton's.)
+__device__ __forceinline__ double fast_rsqrt(double d) {
+  const double r = __builtin_amdgcn_rsq(d);
+  const double e = __builtin_fma(-(d * r), r, 1.0);
+  return __builtin_fma(r * e, 0.375 * e + 0.5, r);
+}
+
+// The value that lane k of the wave holds, in scalar registers.
+__device__ __forceinline__ double lane_value(double x, int k) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), k), hi = __builtin_amdgcn_readlane(__double2hiint(x), k);
+  return __hiloint2double(hi, lo);
 }
 
 // One diagonal block of the blocked factorization, entirely on chip.
 //
-// The NB_LEAF x NB_LEAF block (128 x 128 doubles, 129 KB with the padded
-// column stride) sits in LDS and is processed as 8 x 8 blocks of 16 x 16:
-//   Cholesky, panel by panel (16 columns at a time):
-//     - one wave factors the 16 x 16 diagonal block (lane i owns row i; the
-//       column of each step is exchanged through LDS within the wave);
-//     - every row below solves against it (one thread per row, forward
-//       substitution with the stored 1 / L[k][k]);
-//     - the trailing lower blocks take the rank-16 update on
-//       v_mfma_f64_16x16x4f64; wave 0 updates the next diagonal block first
-//       and factors it while the other waves finish the update.
-//   Inverse, in place: the 16 x 16 diagonal inverses (one per wave), then
-//   block columns from right to left,
-//     X[i][j] = -(sum_{k=j+1..i} X[i][k] L[k][j]) X[j][j]   (i > j),
-//   again on 16 x 16 matrix-core products.
-// Block columns of the factor and of the inverse are written to A and Ainv
-// (ld, zeros above the diagonal) as soon as they are final.  A non-positive or
-// NaN pivot sets *info = row0 + j + 1 if *info is still 0 (the 1-based global
-// pivot; blocks run in order, so the first failure wins).
+// The lower triangle of the NB_LEAF x NB_LEAF block (128 x 128 doubles) sits in
+// LDS as 8 x 8 blocks of 16 x 16 and is factored panel by panel (16 columns); the
+// inverse is formed row block by row block behind it.
+//   Panel p: up to three waves, each with the 16 rows of the diagonal block in
+//     lanes 0..15 (factored by every wave alike, so none waits for another) and
+//     48 of the rows below in the others, a row's 16 values in registers.  Step j
+//     scales column j by 1 / sqrt(pivot) and subtracts its products with
+//     L[k][j], read from lane k.  Rows 128..143 of each panel are the identity's:
+//     against the block they become L_pp^-T, the inverse of the diagonal block.
+//   Look-ahead: all waves update block column p + 1 with panel p.
+//   Then the panel waves factor panel p + 1 while the others update the block
+//     columns after it and form row block p of the inverse,
+//       X[p][j] = -X[p][p] sum_{k=j..p-1} L[p][k] X[k][j]   (j < p),
+//     on v_mfma_f64_16x16x4f64, whose accumulator layout is its B operand's, so the
+//     sum goes into the last product without leaving the registers.
+// Finished blocks are written to A (with zeros above the diagonal) and Ainv
+// (which holds them already; ld) at once.  A non-positive or NaN pivot sets *info = row0 + j + 1 if
+// *info is still 0 (the 1-based global pivot; blocks run in order, so the first
+// failure wins).
+//
+// The chain of 128 pivots bounds it: 27 us a block (54 us with one wave per
+// diagonal block exchanging columns through LDS, a separate solve of the rows
+// below and the inverse formed afterwards).  A panel takes 2 us, about 250 cycles
+// a pivot for some 50 instructions; the first loads take 3 us.
 
 typedef double l4_t __attribute__((ext_vector_type(4)));
 
 constexpr int LT = 16;                 // inner block size
 constexpr int LNB = NB_LEAF / LT;      // inner blocks per side
-constexpr int LD = NB_LEAF + 1;        // LDS column stride: odd, so 16 lanes reading along a row hit 16 banks
-static_assert(NB_LEAF % LT == 0 && LNB == 8, "the inverse's scratch blocks assume 8 x 8 inner blocks");
+constexpr int LROWS = NB_LEAF + LT;    // the block's rows and the identity's
+constexpr int LD = LROWS + 1;          // LDS column stride: odd, so 16 lanes reading along a row hit 16 banks
+constexpr int LPR = 64 - LT;           // rows below the diagonal block per panel wave
+static_assert(NB_LEAF % LT == 0 && LNB == 8, "eight waves share the look-ahead blocks");
 
 __device__ __forceinline__ double* leaf_blk(double* S, int bi, int bj) { return S + (LT * bj) * LD + LT * bi; }
 
@@ -239,161 +252,221 @@ __device__ __forceinline__ void leaf_st_acc(double* p, l4_t v, int lane) {
   p[q + 12 + c * LD] = v[3];
 }
 
-// One wave factors the 16 x 16 diagonal block of panel p in place.  Lane i
-// (< 16) owns row i; at step j the column goes through LDS (the operations of
-// one wave on LDS complete in order; the empty asm statements with a memory
-// clobber stop the compiler from carrying values across the exchange).
-// Stores 1 / L[k][k] in rd[16 p + k]; returns the first non-positive pivot
-// (1-based within the leaf) or 0.
-__device__ __forceinline__ int leaf_factor16(double* S, int p, double* col, double* rd, int lane) {
-  const int i = lane & 15;
-  double* D = leaf_blk(S, p, p);
-  double w[LT];
+// Panel waves that panel p needs for its rows below the diagonal block.
+__device__ __forceinline__ int leaf_panel_waves(int p) { return (LROWS - LT * (p + 1) + LPR - 1) / LPR; }
+
+// Panel p by wave `wave` of its panel waves.  Returns the first non-positive
+// pivot (1-based within the leaf) or 0.
+__device__ __forceinline__ int leaf_panel(double* S, int p, int wave, int lane) {
+  const int row = LT * p + (lane < LT ? lane : lane + LPR * wave);   // past the last row: a spare one, not stored
+  double* P = S + (LT * p) * LD + min(row, LROWS);
+  double x[LT];
 #pragma unroll
-  for (int k = 0; k < LT; ++k) w[k] = D[i + k * LD];
-  int bad = 0;
+  for (int k = 0; k < LT; ++k) x[k] = P[k * LD];
+  double d = lane_value(x[0], 0), own = 0.0;   // the pivot; lane j's own
 #pragma unroll
   for (int j = 0; j < LT; ++j) {
-    if (lane < LT) col[i] = w[j];
-    asm volatile("" ::: "memory");
-    double c[LT];
+    own = (lane == j) ? d : own;
+    const double r = fast_rsqrt(d);
+    // the next pivot from this column before it is scaled, so that its root does not wait for the column
+    if (j + 1 < LT) {
+      const double a = lane_value(x[j], j + 1) * r;
+      d = __builtin_fma(-a, a, lane_value(x[j + 1], j + 1));
+    }
+    x[j] *= r;
+    // five lane reads, then their five products: a product right behind its read waits for it
 #pragma unroll
-    for (int k = j; k < LT; ++k) c[k] = col[k];
-    asm volatile("" ::: "memory");
-    const double d = c[j];
-    if (bad == 0 && !(d > 0.0)) bad = LT * p + j + 1;
-    const double sd = sqrt(d);
-    const double r = fast_rcp(sd);
-    const double lr = (i < j) ? 0.0 : w[j] * r * r;   // L[i][j] / L[j][j]
-    w[j] = (i < j) ? 0.0 : ((i == j) ? sd : w[j] * r);
+    for (int k0 = j + 1; k0 < LT; k0 += 5) {
+      double l[5];
 #pragma unroll
-    for (int k = j + 1; k < LT; ++k) w[k] -= lr * c[k];
-    if (lane == 0) rd[LT * p + j] = r;
+      for (int u = 0; u < 5; ++u) l[u] = lane_value(x[j], k0 + u < LT ? k0 + u : LT - 1);
+      asm volatile("" ::"s"(l[0]), "s"(l[1]), "s"(l[2]), "s"(l[3]), "s"(l[4]));
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        if (k0 + u >= LT) break;
+        x[k0 + u] = __builtin_fma(-x[j], l[u], x[k0 + u]);
+        asm volatile("" : "+v"(x[k0 + u]));   // formed here: put off to its use, it would hold its l in scalar registers
+      }
+    }
   }
-  if (lane < LT) {
+  const unsigned bads = (unsigned)__ballot(!(own > 0.0)) & 0xffffu;
+  const int bad = bads ? LT * p + __ffs(bads) : 0;
+  if (lane < LT ? wave == 0 : row < LROWS) {   // the diagonal block's upper triangle is not read again
 #pragma unroll
-    for (int k = 0; k < LT; ++k) D[i + k * LD] = w[k];
+    for (int k = 0; k < LT; ++k) P[k * LD] = x[k];
   }
+  if (wave == 0 && lane < LT) P[lane * LD] = sqrt(own);
   return bad;
 }
 
-// Block column q (columns 16 q .. 16 q + 15) of the lower triangle of S to G (ld), zeros above the diagonal.
-__device__ __forceinline__ void leaf_store_col(const double* S, double* G, int64_t ld, int q, int t) {
-  for (int idx = t; idx < NB_LEAF * LT; idx += 512) {
-    const int r = idx % NB_LEAF, c = LT * q + idx / NB_LEAF;
-    G[(int64_t)r + (int64_t)c * ld] = (r >= c) ? S[r + c * LD] : 0.0;
+// What waves other than the panel's do once panel p is final (wave w of n):
+// the trailing update of block columns p + 2.., row block p of the inverse, and
+// the stores of both results.
+__device__ __forceinline__ void leaf_behind(double* S, double* A, double* Ainv, int64_t ld, int p, int w, int n,
+                                            int lane) {
+  const int c16 = lane & 15, q = lane >> 4;
+  const int nb = LNB - 2 - p;   // block columns left to update
+  const int tasks = p + (nb > 0 ? nb * (nb + 1) / 2 : 0);
+  for (int task = w; task < tasks; task += n) {
+    if (task < p) {   // X[p][j], the longest sum first
+      const int j = task;
+      l4_t acc = {0.0, 0.0, 0.0, 0.0};
+      leaf_mma16(acc, leaf_blk(S, p, j), 1, LD, leaf_blk(S, LNB, j), LD, 1, false, lane);
+      for (int k = j + 1; k < p; ++k) leaf_mma16(acc, leaf_blk(S, p, k), 1, LD, leaf_blk(S, j, k), 1, LD, false, lane);
+      l4_t x = {0.0, 0.0, 0.0, 0.0};
+      const double* D = leaf_blk(S, LNB, p) + c16 * LD;   // row c16 of X[p][p]
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(-D[4 * s + q], acc[s], x, 0, 0, 0);
+      leaf_st_acc(leaf_blk(S, j, p), x, lane);   // kept above the diagonal, where the factor has nothing
+      double* o = Ainv + (LT * p + q) + (int64_t)(LT * j + c16) * ld;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o[4 * t] = x[t];
+    } else {          // A[i][c] -= L[i][p] L[c][p]^T
+      int c = 0, rem = task - p;
+      while (rem >= nb - c) {
+        rem -= nb - c;
+        ++c;
+      }
+      const int bc = p + 2 + c, bi = bc + rem;
+      double* C = leaf_blk(S, bi, bc);
+      l4_t acc = leaf_ld_acc(C, lane);
+      leaf_mma16(acc, leaf_blk(S, bi, p), 1, LD, leaf_blk(S, bc, p), LD, 1, true, lane);
+      leaf_st_acc(C, acc, lane);
+    }
+  }
+  // block column p of the factor (zeros above its diagonal), the inverse's diagonal block
+  for (int c = w; c < LT; c += n) {
+    const int col = LT * p + c;
+    for (int r = lane; r < NB_LEAF; r += 64) A[(int64_t)r + (int64_t)col * ld] = (r >= col) ? S[r + col * LD] : 0.0;
+    if (lane >= c && lane < LT) Ainv[(int64_t)(LT * p + lane) + (int64_t)col * ld] = S[NB_LEAF + c + (LT * p + lane) * LD];
   }
 }
 
 __global__ __launch_bounds__(512) void leaf_potrf_trtri_kernel(double* __restrict__ A, double* __restrict__ Ainv,
                                                                int64_t ld, int row0, int* __restrict__ info) {
   __shared__ __align__(16) double S[NB_LEAF * LD];
-  __shared__ double rd[NB_LEAF];   // 1 / L[k][k]
-  __shared__ double colw[LT];      // wave 0's column exchange
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   {  // all loads first, then the LDS stores: one memory latency instead of one per element
     constexpr int PER = NB_LEAF * NB_LEAF / 512;
     static_assert(512 % NB_LEAF == 0, "a thread keeps its row");
     const int r = t % NB_LEAF, c0 = t / NB_LEAF;
     double v[PER];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) v[q] = A[(int64_t)r + (int64_t)(c0 + q * (512 / NB_LEAF)) * ld];
+    for (int q = 0; q < PER; ++q) {
+      const int c = c0 + q * (512 / NB_LEAF);
+      v[q] = (r >= c / LT * LT) ? A[(int64_t)r + (int64_t)c * ld] : 0.0;
+    }
 #pragma unroll
-    for (int q = 0; q < PER; ++q) S[r + (c0 + q * (512 / NB_LEAF)) * LD] = v[q];
+    for (int q = 0; q < PER; ++q) {
+      const int c = c0 + q * (512 / NB_LEAF);
+      if (r >= c / LT * LT) S[r + c * LD] = v[q];
+    }
+    for (int f = t; f < LT * NB_LEAF; f += 512) {
+      const int e = f % LT, c = f / LT;
+      S[NB_LEAF + e + c * LD] = (e == c % LT) ? 1.0 : 0.0;
+    }
   }
   __syncthreads();
   int bad = 0;   // meaningful in wave 0
-  if (wave == 0) bad = leaf_factor16(S, 0, colw, rd, lane);
+  if (wave < leaf_panel_waves(0)) bad = leaf_panel(S, 0, wave, lane);
   __syncthreads();
-  for (int p = 0; p < LNB; ++p) {
-    // rows below the diagonal block, one thread each:
-    //   L[r][16p + k] = (A[r][16p + k] - sum_{m<k} L[r][16p + m] L[16p + k][16p + m]) / L[16p + k][16p + k]
-    {
-      const int r = LT * (p + 1) + t;
-      if (r < NB_LEAF) {
-        const double* D = leaf_blk(S, p, p);
-        double* Pr = S + (LT * p) * LD + r;
-        double x[LT];
-#pragma unroll
-        for (int k = 0; k < LT; ++k) x[k] = Pr[k * LD];
-#pragma unroll
-        for (int k = 0; k < LT; ++k) {
-          x[k] *= rd[LT * p + k];
-#pragma unroll
-          for (int m = k + 1; m < LT; ++m) x[m] -= x[k] * D[m + k * LD];
-        }
-#pragma unroll
-        for (int k = 0; k < LT; ++k) Pr[k * LD] = x[k];
-      }
+  for (int p = 0; p < LNB - 1; ++p) {
+    const int bi = p + 1 + wave;
+    if (bi < LNB) {   // A[i][p + 1] -= L[i][p] L[p + 1][p]^T
+      double* C = leaf_blk(S, bi, p + 1);
+      l4_t acc = leaf_ld_acc(C, lane);
+      leaf_mma16(acc, leaf_blk(S, bi, p), 1, LD, leaf_blk(S, p + 1, p), LD, 1, true, lane);
+      leaf_st_acc(C, acc, lane);
     }
     __syncthreads();
-    leaf_store_col(S, A, ld, p, t);   // block column p of the factor is final
-    if (p == LNB - 1) break;
-    // trailing update A[i][c] -= L[i][p] L[c][p]^T for p < c <= i.  Task 0 is
-    // the next diagonal block: wave 0 updates it and factors it at once; waves
-    // 1..7 share the other tasks.
-    {
-      const int nb = LNB - 1 - p;
-      const int tasks = nb * (nb + 1) / 2;
-      for (int task = wave; task < tasks; task += (wave == 0) ? tasks : LNB - 1) {
-        int c = 0, rem = task;
-        while (rem >= nb - c) {
-          rem -= nb - c;
-          ++c;
-        }
-        const int bc = p + 1 + c, bi = bc + rem;
-        double* C = leaf_blk(S, bi, bc);
-        l4_t acc = leaf_ld_acc(C, lane);
-        leaf_mma16(acc, leaf_blk(S, bi, p), 1, LD, leaf_blk(S, bc, p), LD, 1, true, lane);
-        leaf_st_acc(C, acc, lane);
-      }
-      if (wave == 0) {
-        const int b = leaf_factor16(S, p + 1, colw, rd, lane);
-        if (bad == 0) bad = b;
-      }
+    const int np = leaf_panel_waves(p + 1);
+    if (wave < np) {
+      const int b = leaf_panel(S, p + 1, wave, lane);
+      if (bad == 0) bad = b;
+    } else {
+      leaf_behind(S, A, Ainv, ld, p, wave - np, LNB - np, lane);
     }
     __syncthreads();
   }
+  leaf_behind(S, A, Ainv, ld, LNB - 1, wave, LNB, lane);
   if (wave == 0 && lane == 0 && bad != 0 && *info == 0) *info = row0 + bad;
-  __syncthreads();
-  // the 16 x 16 diagonal inverses, in place: wave w takes block w, lane c < 16 forms column c
-  {
-    const int c = lane & 15;
-    double* D = leaf_blk(S, wave, wave);
-    double x[LT];
+}
+
+// Strips of a product with a triangular inverse, in place: S <- alpha Li S for
+// the w x w lower-triangular Li (column-major, ld) and a w x 16 strip S per
+// workgroup, either columns of a column-major matrix (ROWS false) or rows of one
+// (ROWS true: S^T <- alpha S^T Li^T).  The strip sits in LDS; each of the eight
+// waves forms 16-row blocks of the result, Li's fragments read straight from
+// memory sixteen k steps ahead.  For the small nodes of the factorization, whose
+// products have few tiles and are bound by latency: in place there is no copy of
+// the operand, and a node of 128 columns has w / 16 workgroups that each wait for
+// memory twice, instead of four that walked eight k stages.  A node of 128 rows
+// and columns: 7 us for each strip product and 10 us for the other two in one
+// launch, where a copy and four 64 x 64-tile products took 65 us.  With 256
+// threads a workgroup a study of 10,000 samples took 1 ms longer.
+template <int W, bool ROWS>
+__global__ __launch_bounds__(512) void tri_strip_kernel(const double* __restrict__ Li, int64_t ld, double* Sg, int w,
+                                                        double alpha) {
+  constexpr int NB = 16, PF = 16, LS = NB + 1;
+  __shared__ double Ss[W * LS];   // Ss[k * LS + c]
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int c16 = lane & 15, q = lane >> 4;
+  double* Sb = ROWS ? Sg + blockIdx.x * NB : Sg + (int64_t)blockIdx.x * NB * ld;
+  if (ROWS) {   // 16 consecutive rows of each column
+    double v[W / 32];
 #pragma unroll
-    for (int k = 0; k < LT; ++k) x[k] = (k == c) ? 1.0 : 0.0;
-#pragma unroll
-    for (int k = 0; k < LT; ++k) {
-      x[k] *= rd[LT * wave + k];
-#pragma unroll
-      for (int m = k + 1; m < LT; ++m) x[m] -= D[m + k * LD] * x[k];
+    for (int u = 0; u < W / 32; ++u) {
+      const int k = (t >> 4) + 32 * u;
+      v[u] = (k < w) ? Sb[(t & 15) + (int64_t)k * ld] : 0.0;
     }
-    if (lane < LT) {
 #pragma unroll
-      for (int k = 0; k < LT; ++k) D[k + c * LD] = x[k];
+    for (int u = 0; u < W / 32; ++u) {
+      const int k = (t >> 4) + 32 * u;
+      if (k < w) Ss[k * LS + (t & 15)] = v[u];
+    }
+  } else {      // columns, w long
+    for (int c = wave; c < NB; c += 8) {
+      double v[W / 64];
+#pragma unroll
+      for (int u = 0; u < W / 64; ++u) {
+        const int k = lane + 64 * u;
+        v[u] = (k < w) ? Sb[k + (int64_t)c * ld] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < W / 64; ++u) {
+        const int k = lane + 64 * u;
+        if (k < w) Ss[k * LS + c] = v[u];
+      }
     }
   }
   __syncthreads();
-  leaf_store_col(S, Ainv, ld, LNB - 1, t);
-  // block columns of the inverse, right to left; T goes to a scratch block of
-  // the strictly upper triangle (never read as data)
-  for (int j = LNB - 2; j >= 0; --j) {
-    const int bi = j + 1 + wave;
-    double* T = (wave < LNB - 1) ? leaf_blk(S, wave, LNB - 1) : leaf_blk(S, 0, LNB - 2);
+  const int nb = w / 16;   // a multiple of eight
+  for (int u = 0; u < nb / 8; ++u) {
+    const int b = (u & 1) ? u * 8 + 7 - wave : u * 8 + wave;   // snake: the sums get longer with b
+    const double* Lr = Li + 16 * b + c16;   // A element (r, k) at Lr[k ld]
+    const int steps = 4 * (b + 1);          // k < 16 (b + 1), four a step
     l4_t acc = {0.0, 0.0, 0.0, 0.0};
-    if (bi < LNB) {
-      for (int k = j + 1; k <= bi; ++k) leaf_mma16(acc, leaf_blk(S, bi, k), 1, LD, leaf_blk(S, k, j), 1, LD, false, lane);
-      leaf_st_acc(T, acc, lane);
+    double a[PF], an[PF];
+#pragma unroll
+    for (int f = 0; f < PF; ++f) a[f] = (f < steps) ? Lr[(int64_t)(4 * f + q) * ld] : 0.0;
+    for (int s0 = 0; s0 < steps; s0 += PF) {
+#pragma unroll
+      for (int f = 0; f < PF; ++f) an[f] = (s0 + PF + f < steps) ? Lr[(int64_t)(4 * (s0 + PF + f) + q) * ld] : 0.0;
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+        if (s0 + f < steps)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[f], Ss[(4 * (s0 + f) + q) * LS + c16], acc, 0, 0, 0);
+#pragma unroll
+      for (int f = 0; f < PF; ++f) a[f] = an[f];
     }
-    __syncthreads();
-    if (bi < LNB) {
-      acc = l4_t{0.0, 0.0, 0.0, 0.0};
-      leaf_mma16(acc, T, 1, LD, leaf_blk(S, j, j), 1, LD, true, lane);
-      leaf_st_acc(leaf_blk(S, bi, j), acc, lane);
+    // the strip's values are all in LDS: the result may overwrite them in memory
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = 16 * b + q + 4 * e;
+      Sb[ROWS ? c16 + (int64_t)k * ld : k + (int64_t)c16 * ld] = alpha * acc[e];
     }
-    __syncthreads();
-    leaf_store_col(S, Ainv, ld, j, t);   // block column j of the inverse is final
   }
 }
 
