@@ -361,12 +361,16 @@ __global__ __launch_bounds__(256) void h2_contract_kernel(const double* __restri
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// out[0] = sum of part[0..count) in index order (one thread: fixed order).
-__global__ void sum_ordered_kernel(const double* __restrict__ part, int count, double* __restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// out[0] = sum of part[0..count) by one wave: each lane its share in index
+// order, then a fixed butterfly.  (One thread in index order took 62 us for
+// 1,024 values, a chain of as many dependent loads and additions.)
+__global__ __launch_bounds__(64) void sum_ordered_kernel(const double* __restrict__ part, int count,
+                                                         double* __restrict__ out) {
   double s = 0.0;
-  for (int i = 0; i < count; ++i) s += part[i];
-  out[0] = s;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < count; i += 64) s += part[i];
+  s = wave_sum(s);
+  if (threadIdx.x == 0) out[0] = s;
 }
 
 // Phi copy for the h2 adjoint: P (N x N, ld N) = lower triangle of Phi (n x n), zeros elsewhere.

@@ -89,6 +89,9 @@ struct GemmArgs {
   // trmm_f64_dma_kernel only: with flags, tiles without a flagged column do
   // nothing and only flagged columns of C are stored
   ColFlags only;
+  // trmm_f64_small_kernel only: rows >= kvalid of op(B) are not in memory and
+  // read as zero (0: all K are)
+  int kvalid;
 };
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }

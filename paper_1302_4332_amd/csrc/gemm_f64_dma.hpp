@@ -17,6 +17,60 @@
 
 namespace gls {
 
+// Results of a tile of 128 rows (two strips wm of 64) x BN columns: lane holds
+// C[4 ((lane >> 2) & 3) + (lane >> 4)][lane & 3] of each of its wave's 4 x FC
+// slices of 16 x 4.  red: LDS for 2 red_q BN doubles.
+template <int BN, int FC, int NT>
+__device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const double (&acc)[4][FC], double* red, int ti,
+                                                  int i0, int j0, int wm, int wn) {
+  constexpr int WTN = 4 * FC;
+  const int lane = threadIdx.x & 63;
+  if (g.red_q > 0) {
+    // Per-column sums over this tile's rows instead of C: each lane sums its four rows (a ascending), a
+    // butterfly over the sixteen lanes of a column adds those (every lane ends with the same sum), and the
+    // two row-strip waves are added in the order wm = 0, 1.  The order depends only on the tile, so every
+    // column's sums are independent of the block's width and of the column's place in it.
+    __syncthreads();   // every wave is done with the ring, which now holds the two strips' sums as red[wm][q][BN columns]
+    for (int q = 0; q < g.red_q; ++q) {
+      const bool norm = q == g.red_q - 1;
+      double w[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        w[a] = norm ? 0.0 : g.red_W[(int64_t)(i0 + wm * 64 + a * 16 + 4 * ((lane >> 2) & 3) + (lane >> 4)) +
+                                   (int64_t)q * g.ld_red_W];
+#pragma unroll
+      for (int c = 0; c < FC; ++c) {
+        double t = 0.0;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) t += acc[a][c] * (norm ? acc[a][c] : w[a]);
+#pragma unroll
+        for (int off = 4; off < 64; off <<= 1) t += __shfl_xor(t, off, 64);
+        if (lane < 4) red[(wm * g.red_q + q) * BN + wn * WTN + c * 4 + lane] = t;
+      }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < g.red_q * BN; e += NT) {
+      const int q = e / BN, jl = e % BN;
+      if (j0 + jl < g.ncols)
+        g.red_part[(int64_t)(ti * g.red_q + q) * g.ncols + j0 + jl] = red[q * BN + jl] + red[(g.red_q + q) * BN + jl];
+    }
+    return;
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int i = i0 + wm * 64 + a * 16 + 4 * ((lane >> 2) & 3) + (lane >> 4);
+    if (i >= g.mvalid) continue;
+#pragma unroll
+    for (int c = 0; c < FC; ++c) {
+      const int j = j0 + wn * WTN + c * 4 + (lane & 3);
+      if (j >= g.ncols || (g.only.at && !g.only.flagged(j, g.ncols))) continue;
+      double val = g.alpha * acc[a][c];
+      if (g.beta != 0.0 && !g.acc_cin) val += g.beta * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
+      g.C[(int64_t)i + (int64_t)j * g.ldc] = val;
+    }
+  }
+}
+
 // 128 x 64 tiles, 16 k per stage, eight waves of 64 x 16 (two row strips x four
 // column strips; each wave 4 x 4 v_mfma_f64_4x4x4_4b_f64 accumulators as in
 // gemm_f64_kernel).  Permuting k saves half of the B fragment reads.  A stage
@@ -156,55 +210,126 @@ void trmm_f64_dma_kernel(GemmArgs g) {
     }
   }
 
-  // lane holds C[4 ((lane >> 2) & 3) + (lane >> 4)][lane & 3] of each 16 x 4 slice
-  if (g.red_q > 0) {
-    // Per-column sums over this tile's rows instead of C: each lane sums its four rows (a ascending), a
-    // butterfly over the sixteen lanes of a column adds those (every lane ends with the same sum), and the
-    // two row-strip waves are added in the order wm = 0, 1.  The order depends only on the tile, so every
-    // column's sums are independent of the block's width and of the column's place in it.
-    __syncthreads();   // every wave is done with the ring, which now holds the two strips' sums
-    double* red = reinterpret_cast<double*>(smem);   // [wm][q][64 columns]
-    for (int q = 0; q < g.red_q; ++q) {
-      const bool norm = q == g.red_q - 1;
-      double w[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        w[a] = norm ? 0.0 : g.red_W[(int64_t)(i0 + wm * 64 + a * 16 + 4 * ((lane >> 2) & 3) + (lane >> 4)) +
-                                   (int64_t)q * g.ld_red_W];
-#pragma unroll
-      for (int c = 0; c < FC; ++c) {
-        double t = 0.0;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) t += acc[a][c] * (norm ? acc[a][c] : w[a]);
-#pragma unroll
-        for (int off = 4; off < 64; off <<= 1) t += __shfl_xor(t, off, 64);
-        if (lane < 4) red[(wm * g.red_q + q) * BN + wn * WTN + c * 4 + lane] = t;
-      }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < g.red_q * BN; e += DB_THREADS) {
-      const int q = e / BN, jl = e % BN;
-      if (j0 + jl < g.ncols)
-        g.red_part[(int64_t)(ti * g.red_q + q) * g.ncols + j0 + jl] = red[q * BN + jl] + red[(g.red_q + q) * BN + jl];
-    }
-    return;
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int i = i0 + wm * 64 + a * 16 + 4 * ((lane >> 2) & 3) + (lane >> 4);
-    if (i >= g.mvalid) continue;
-#pragma unroll
-    for (int c = 0; c < FC; ++c) {
-      const int j = j0 + wn * WTN + c * 4 + (lane & 3);
-      if (j >= g.ncols || (g.only.at && !g.only.flagged(j, g.ncols))) continue;
-      double val = g.alpha * acc[a][c];
-      if (g.beta != 0.0 && !g.acc_cin) val += g.beta * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
-      g.C[(int64_t)i + (int64_t)j * g.ldc] = val;
-    }
-  }
+  trmm_f64_epilogue<BN, FC, DB_THREADS>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn);
 }
 
-// Whether trmm_f64_dma_kernel applies to a product without transposes: A
+// The same product, bitwise, for short sums and grids of few tiles: 128 x BN tiles (BN = 16 or
+// 8), each wave 64 x 4, so that the tile's own MFMA time per stage (0.85 us for 64
+// columns, which a lone workgroup cannot hide) falls to a quarter or less and
+// there are more workgroups.  The columns of B that the tile needs are read once,
+// up to KMAX rows, into LDS through registers: any alignment, and rows past
+// kvalid become zero, so no padded copy of the block is made first.  A's stages
+// follow in a ring of four.  Every output sums the same k in the same order as in
+// trmm_f64_dma_kernel (columns of A that it skips hold zeros).
+// A block of 108 columns at n = 712 took 71 us with the other kernel and takes 32
+// with this one, 48 columns at n = 1,000 91 and 40, 16,000 at n = 256 156 and 80.
+template <int BN, int KMAX>
+__global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
+  constexpr int BM = DB_BM, BK = DB_BK, NS = 4, NW = BN / 2, NT = 64 * NW;
+  constexpr int STAGE = BM * BK * 8, LDB = KMAX + 2, QA = BK / NW;   // load instructions per wave and stage
+  static_assert(NS * STAGE + BN * LDB * 8 <= 160 * 1024 && 2 * 21 * BN * 8 <= NS * STAGE && QA * NW == BK, "LDS");
+  __shared__ __align__(1024) char smem[NS * STAGE];
+  __shared__ __align__(16) double Bs[BN * LDB];   // Bs[column][k - 16 k0]
+
+  const int ti = g.map_desc ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y, tj = blockIdx.x;
+  const int i0 = ti * BM, j0 = tj * BN;
+  if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;
+  if (g.only.at) {
+    int* any = reinterpret_cast<int*>(smem);
+    if (threadIdx.x == 0) *any = 0;
+    __syncthreads();
+    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && g.only.flagged(j0 + threadIdx.x, g.ncols)) *any = 1;
+    __syncthreads();
+    const bool none = *any == 0;
+    if (none) return;
+    __syncthreads();   // smem is the ring from here on
+  }
+  int khi = g.K;
+  if (g.a_tri == TRI_LOWER) khi = imin(khi, i0 + BM);
+  const int nk = (khi + BK - 1) / BK;
+  int k0 = (g.a_tri == TRI_UPPER) ? i0 / BK : 0;
+  if (g.b_tri == TRI_LOWER) k0 = imax(k0, j0 / BK);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+
+  const uint32_t lds0 = lds_address(smem);
+  const uint32_t voff = 16 * lane;
+  auto issue = [&](int kstep) {
+    const uint32_t base = lds0 + (uint32_t)((kstep % NS) * STAGE);
+    const double* a = g.A + i0 + (int64_t)kstep * BK * g.lda;
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+      const int kc = q * NW + wave;
+      lds_load16_sv(a + (int64_t)kc * g.lda, voff, base + (uint32_t)(kc * 1024));
+    }
+  };
+  for (int q = 0; q < NS - 1; ++q)
+    if (k0 + q < nk) issue(k0 + q);
+  {
+    const int kend = imin(nk * BK, g.kvalid ? g.kvalid : g.K), kbeg = k0 * BK;
+#pragma unroll
+    for (int c = wave; c < BN; c += NW) {   // two columns a wave
+      const int j = j0 + c;
+      const double* col = g.B + (int64_t)j * g.ldb;
+      double v[KMAX / 64];
+#pragma unroll
+      for (int u = 0; u < KMAX / 64; ++u) {
+        const int k = kbeg + lane + 64 * u;
+        v[u] = (j < g.ncols && k < kend) ? col[k] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < KMAX / 64; ++u) Bs[c * LDB + lane + 64 * u] = v[u];
+    }
+  }
+
+  double acc[4][1];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    acc[a][0] = 0.0;
+    if (g.acc_cin) {   // start from alpha Cin (alpha = +-1: exact)
+      const int i = i0 + wm * 64 + a * 16 + 4 * ((lane >> 2) & 3) + (lane >> 4), j = j0 + wn * 4 + (lane & 3);
+      if (i < g.mvalid && j < g.ncols) acc[a][0] = g.alpha * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
+    }
+  }
+  const int g4 = 4 * (lane >> 4);
+  const int abase = g4 * 1024 + wm * 512 + (lane & 15) * 8;
+  const double* bcol = Bs + (wn * 4 + (lane & 3)) * LDB + g4 - k0 * BK;
+  for (int it = k0; it < nk; ++it) {
+    wait_stages<QA>(imin(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
+    __syncthreads();                              // ... and every wave's (and B); stage (it - 1) % NS is free
+    if (it + NS - 1 < nk) issue(it + NS - 1);
+    const char* st = smem + (it % NS) * STAGE + abase;
+    const double2 b01 = *reinterpret_cast<const double2*>(bcol + it * BK);
+    const double2 b23 = *reinterpret_cast<const double2*>(bcol + it * BK + 2);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double bf = s == 0 ? b01.x : s == 1 ? b01.y : s == 2 ? b23.x : b23.y;
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        acc[a][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(*reinterpret_cast<const double*>(st + s * 1024 + a * 128), bf,
+                                                       acc[a][0], 0, 0, 0);
+    }
+  }
+  trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn);
+}
+
+// Largest K of the small kernel.
+constexpr int SMALL_KMAX = 1024;
+
+// Whether a product of M rows, ncols columns and K goes to it.  Short sums over
+// few rows do whatever the number of columns: the other kernel's start and end
+// are most of its time there (n = 512, 16,000 columns: 306 us against 257; n =
+// 128, 30,000: 176 against 64).  Longer ones do up to 128 tiles of 128 x 64, about
+// where this kernel needs a second round of workgroups (n = 712, 1,300 columns:
+// 77 us against 70; n = 1,000: 1,000 columns 99 against 84, 2,000 102 against 157).
+inline bool small_product(int M, int ncols, int K) {
+  if (K > SMALL_KMAX) return false;
+  if (K <= 512 && M <= 512) return true;
+  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= 128;
+}
+
+// Whether the two kernels above apply to a product without transposes: A
 // full, lower or upper triangular (diagonal offset 0), no triangular B,
 // 16-byte aligned operands with even leading dimensions,
 // K a multiple of 16, the rows of A up to M rounded up to 128 inside A's
@@ -212,11 +337,13 @@ void trmm_f64_dma_kernel(GemmArgs g) {
 // offsets within a stage (15 columns of A, 63 columns of B) below 2^32 bytes.
 inline bool trmm_dma_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  if (!al16(g.A) || !al16(g.B) || (g.lda & 1) || (g.ldb & 1)) return false;
+  const bool small = small_product(g.M, g.ncols, g.K);   // takes any B
+  if (!al16(g.A) || (g.lda & 1) || (!small && (!al16(g.B) || (g.ldb & 1) || g.kvalid))) return false;
   if (g.b_tri == TRI_UPPER || (g.b_tri == TRI_LOWER && (g.b_diag != 0 || g.a_tri != TRI_NONE)) || g.a_diag != 0)
     return false;
   if (g.M <= 0 || g.K % DB_BK || g.K <= 0 || g.ncols <= 0 || g.mvalid > g.M) return false;
-  if (g.lda < (int64_t)(g.M + DB_BM - 1) / DB_BM * DB_BM || g.ldb < g.K) return false;
+  if (g.lda < (int64_t)(g.M + DB_BM - 1) / DB_BM * DB_BM || g.ldb < (g.kvalid ? g.kvalid : g.K)) return false;
+  if (small) return true;
   if ((15 * g.lda + DB_BM) * 8 >= ((int64_t)1 << 32) || (63 * g.ldb + DB_BK) * 8 >= ((int64_t)1 << 32)) return false;
   return true;
 }

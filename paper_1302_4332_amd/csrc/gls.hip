@@ -211,6 +211,15 @@ static void gemm_map(bool ta, bool tb, const GemmArgs& g, hipStream_t s) {
 static bool gemm_dma(const GemmArgs& g, hipStream_t s) {
   if (!trmm_dma_ok(g)) return false;
   GemmArgs d = g;
+  if (small_product(g.M, g.ncols, g.K)) {
+    const unsigned Mt = (g.M + DB_BM - 1) / DB_BM;
+    d.M = (int)Mt * DB_BM;
+    if (g.K <= 512)
+      hipLaunchKernelGGL((trmm_f64_small_kernel<16, 512>), dim3((g.ncols + 15) / 16, Mt), dim3(512), 0, s, d);
+    else
+      hipLaunchKernelGGL((trmm_f64_small_kernel<8, SMALL_KMAX>), dim3((g.ncols + 7) / 8, Mt), dim3(256), 0, s, d);
+    return true;
+  }
   const int Mt = (g.M + DB_BM - 1) / DB_BM, Nt = (g.ncols + DB_BN - 1) / DB_BN;
   d.M = Mt * DB_BM;   // rows past mvalid are computed from A's padding and not stored
   hipLaunchKernelGGL(trmm_f64_dma_kernel, dim3(XcdMap::grid(d, Mt, Nt)), dim3(DB_THREADS), 0, s, d);
@@ -428,6 +437,7 @@ static void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int
   g.a_diag = 0;
   g.map_desc = 1;
   g.only = only;
+  if (K > c->n && X != c->x64) g.kvalid = (int)c->n;
   gemm(false, false, true, g, s);
 }
 
@@ -447,6 +457,7 @@ static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int 
   g.red_part = c->Xt;
   g.red_q = c->p + 1;
   g.only = only;
+  if (K > c->n && X != c->x64) g.kvalid = (int)c->n;
   return gemm_dma(g, s);
 }
 
@@ -1135,20 +1146,16 @@ static void widen_columns(Ctx* c, const void* src, int64_t ld, int mb, int rows,
                      dim3(256), 0, s, src, ld, (int)c->n, rows, mb, c->x64, c->N, flags);
 }
 
-// The FP64 block operand of the product with L^-1: X itself when its layout
-// feeds the direct-load kernel (n a multiple of 16, 16-byte aligned, even
-// ld), else a copy in c->x64 (ld N) whose rows n..K-1 are zero (with flags, of
+// The FP64 block operand of the product of rows rows with L^-1: X itself when
+// the product is a small one, or its layout feeds the direct-load kernel (n a
+// multiple of 16, 16-byte aligned, even ld), else a copy in c->x64 (ld N) whose rows n..K-1 are zero (with flags, of
 // the flagged columns).  Blocks already in c->x64 (widened bytes) carry zero
 // rows up to N.  Sets *K, the rows the product sums over.
-static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb, int* K, ColFlags flags,
+static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb, int rows, int* K, ColFlags flags,
                                   hipStream_t s) {
-  if (X == c->x64) {
-    *K = k16(c);
-    return X;
-  }
-  *K = (int)c->n;
-  if (dma_b_operand_ok(X, *ldx, c->n)) return X;
   *K = k16(c);
+  if (X == c->x64 || small_product(rows, mb, *K)) return X;
+  if (dma_b_operand_ok(X, *ldx, c->n)) return X;   // n is a multiple of 16
   widen_columns<OZ_F64>(c, X, *ldx, mb, *K, flags, s);
   *ldx = c->N;
   return c->x64;
@@ -1201,6 +1208,14 @@ static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w,
   else pack_units<OZ_F64>(c, X, ld, mb, true, w, s);
 }
 
+static void launch_whole(const OzArgs& a, hipStream_t s) {
+  GemmArgs m{};
+  m.map_gm = OZ_MAP_GM;
+  m.map_gn = OZ_MAP_GN;
+  hipLaunchKernelGGL(ozaki_i8_kernel, dim3(XcdMap::grid(m, a.Mt, (a.ncols + OZ_BN - 1) / OZ_BN)), dim3(OZ_THREADS), 0,
+                     s, a);
+}
+
 // The integer product: per-SNP sums into w.part8, or with Xt the product itself.
 static void whole_product(Ctx* c, const WholeBlock& w, int mb, double* Xt, hipStream_t s) {
   OzArgs a;
@@ -1222,10 +1237,7 @@ static void whole_product(Ctx* c, const WholeBlock& w, int mb, double* Xt, hipSt
     a.red_part = w.part8;
     a.red_q = c->p + 1;
   }
-  GemmArgs m{};
-  m.map_gm = OZ_MAP_GM;
-  m.map_gn = OZ_MAP_GN;
-  hipLaunchKernelGGL(ozaki_i8_kernel, dim3(XcdMap::grid(m, w.Mt8, (mb + OZ_BN - 1) / OZ_BN)), dim3(OZ_THREADS), 0, s, a);
+  launch_whole(a, s);
 }
 
 static void residual_fp64(Ctx* c, const double* X, int64_t ldx, int mb, hipStream_t s) {
@@ -1270,7 +1282,7 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
         whole_product(c, w, mb, nullptr, s);
       }
       int K = 0;
-      const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, w.flags, s);
+      const double* X = fp64_operand(c, XR, &ld_xr, mb, rows, &K, w.flags, s);
       whiten_fp64_fused(c, X, ld_xr, mb, K, rows, w.flags, s);
     }
     PhaseTimer t(c, PH_SNP, s);
@@ -1389,7 +1401,7 @@ static void recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, 
       whole_product(c, w, mb, c->Xt, s);
     }
     int K = 0;
-    const double* X = fp64_operand(c, XR, &ld_xr, mb, &K, w.flags, s);
+    const double* X = fp64_operand(c, XR, &ld_xr, mb, (int)c->N, &K, w.flags, s);
     whiten_fp64(c, X, ld_xr, mb, K, (int)c->N, c->Xt, w.flags, s);
   }
 }
