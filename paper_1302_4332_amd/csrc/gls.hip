@@ -404,25 +404,32 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
 }
 
 template <int P>
-static void tri_apply_p(Ctx* c, const double* V, double* part, double* W, hipStream_t s) {
+static void tri_apply_p(Ctx* c, const double* XL, int64_t ld_xl, const double* y, double* part, hipStream_t s) {
   const int N = (int)c->N;
   hipLaunchKernelGGL(tri_apply_partial_kernel<P>, dim3(N / 64, (N + TA_KC - 1) / TA_KC), dim3(256), 0, s, c->Linv, N,
-                     V, part);
-  hipLaunchKernelGGL(tri_apply_sum_kernel, dim3(grid_for((int64_t)N * P)), dim3(256), 0, s, part, N, P, W);
+                     (int)c->n, XL, ld_xl, y, part);
 }
 
-// W (N x p) = L^-1 V for the covariate block V (N x p, ld N); part holds
-// ceil(N / TA_KC) partial N x p blocks.
-static void tri_apply(Ctx* c, const double* V, double* part, double* W, hipStream_t s) {
-  switch (c->p) {
+// W (N x p) = L^-1 [X_L | y], its Gram matrix and the factor of S_TL; part
+// holds ceil(N / TA_KC) partial N x p blocks.
+static void whiten_covariates(Ctx* c, const double* XL, int64_t ld_xl, const double* y, double* part, hipStream_t s) {
+  const int N = (int)c->N, p = c->p;
+  switch (p) {
 #define GLS_P_CASE(P) \
-  case P: tri_apply_p<P>(c, V, part, W, s); break;
+  case P: tri_apply_p<P>(c, XL, ld_xl, y, part, s); break;
     GLS_P_CASE(1) GLS_P_CASE(2) GLS_P_CASE(3) GLS_P_CASE(4) GLS_P_CASE(5) GLS_P_CASE(6) GLS_P_CASE(7)
     GLS_P_CASE(8) GLS_P_CASE(9) GLS_P_CASE(10) GLS_P_CASE(11) GLS_P_CASE(12) GLS_P_CASE(13) GLS_P_CASE(14)
     GLS_P_CASE(15) GLS_P_CASE(16) GLS_P_CASE(17) GLS_P_CASE(18) GLS_P_CASE(19) GLS_P_CASE(20)
 #undef GLS_P_CASE
     default: break;
   }
+  if (N <= COV_MAX) {
+    hipLaunchKernelGGL(covariates_kernel, dim3(1), dim3(1024), 0, s, part, N, p, c->W, c->gram, c->small, c->info + 1);
+    return;
+  }
+  hipLaunchKernelGGL(tri_apply_sum_kernel, dim3(grid_for((int64_t)N * p)), dim3(256), 0, s, part, N, p, c->W);
+  hipLaunchKernelGGL(gram_kernel, dim3(p * (p + 1) / 2), dim3(256), 0, s, c->W, N, p, c->gram);
+  hipLaunchKernelGGL(small_factor_kernel, dim3(1), dim3(64), 0, s, c->gram, p, c->small, c->info + 1);
 }
 
 // X~ (rows x mb, ld N) = L^-1 X   for an n x mb block X (ld ldx) summed over
@@ -594,11 +601,8 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     return st;
   };
   // info[0]: failing pivot of M, info[1]: failing pivot of S_TL
-  hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<double*>(c->info), (int64_t)4, 0.0);
-  hipLaunchKernelGGL(form_m_kernel, dim3(grid_for(N * N)), dim3(256), 0, s, c->L, (int)N, (int)n, Phi, ld_phi, h2);
-  // L^-1 = 0 but for the identity on rows past the factored leaves
-  hipLaunchKernelGGL(identity_tail_kernel, dim3(grid_for(N * N)), dim3(256), 0, s, c->Linv, (int)N,
-                     pl.leaves * NB_LEAF);
+  hipLaunchKernelGGL(setup_init_kernel, dim3((unsigned)N), dim3(256), 0, s, c->L, c->Linv, (int)N,
+                     (int)n, pl.leaves * NB_LEAF, Phi, ld_phi, h2, c->info);
   {
     SetupSide side;
     if (side_st && (e = side.init(side_st, reinterpret_cast<double*>(ws + pl.off_side))) != hipSuccess)
@@ -643,13 +647,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     hipLaunchKernelGGL(keep_phi_kernel, dim3(grid_for(N * N)), dim3(256), 0, s, c->Phi, (int)N, (int)n, Phi, ld_phi);
     reset_adjoint(c, s);
   }
-  // [X~_L | y~] = L^-1 [X_L | y]
-  double* Wp = c->Xt;
-  hipLaunchKernelGGL(pack_covariates_kernel, dim3(grid_for(N * p)), dim3(256), 0, s, Wp, (int)N, (int)n, (int)p, XL,
-                     ld_xl, y);
-  tri_apply(c, Wp, Wp + N * p, c->W, s);
-  hipLaunchKernelGGL(gram_kernel, dim3(p * (p + 1) / 2), dim3(256), 0, s, c->W, (int)N, (int)p, c->gram);
-  hipLaunchKernelGGL(small_factor_kernel, dim3(1), dim3(64), 0, s, c->gram, (int)p, c->small, c->info + 1);
+  whiten_covariates(c, XL, ld_xl, y, c->Xt, s);   // [X~_L | y~] = L^-1 [X_L | y]
   if ((e = hipGetLastError()) != hipSuccess) return fail(hip_fail(e, "gls_setup: launch"));
   if ((e = hipMemcpyAsync(hinfo, c->info, sizeof hinfo, hipMemcpyDeviceToHost, s)) != hipSuccess)
     return fail(hip_fail(e, "gls_setup: info copy"));
@@ -1068,8 +1066,8 @@ static double lp_target(int precision) { return precision == GLS_FP16_IR ? 16384
 void prepare_low_precision(Ctx* c, hipStream_t s) {
   const int64_t N = c->N;
   double* part = c->red + 8;
-  hipLaunchKernelGGL(maxabs_kernel, dim3(1024), dim3(256), 0, s, c->Linv, N * N, part);
-  hipLaunchKernelGGL(maxabs_kernel, dim3(1), dim3(256), 0, s, part, (int64_t)1024, part + 1024);
+  hipLaunchKernelGGL(maxabs_lower_kernel, dim3(1024), dim3(256), 0, s, c->Linv, (int)N, part);
+  hipLaunchKernelGGL(maxabs_lower_kernel, dim3(1), dim3(256), 0, s, part, 1024, part + 1024);
   const double tgt = lp_target(c->opts.precision);
   const int g = grid_for(N * N);
   switch (c->opts.precision) {

@@ -240,19 +240,21 @@ __global__ void convert_factor_kernel(const double* __restrict__ Li, int N, T* _
   const int64_t total = (int64_t)N * N;
   for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(idx / N), k = (int)(idx % N);
-    out[idx] = (T)ldexp(Li[(int64_t)i + (int64_t)k * N], e);
+    out[idx] = (k <= i) ? (T)ldexp(Li[(int64_t)i + (int64_t)k * N], e) : (T)0.0f;   // above the diagonal: not set
   }
 }
 
-// Largest magnitude of an array: out[blockIdx.x] = max over a grid-stride
-// share (run once over the data with many workgroups, then once with one
-// workgroup over the partial maxima).
-__global__ __launch_bounds__(256) void maxabs_kernel(const double* __restrict__ p, int64_t count,
-                                                     double* __restrict__ out) {
+// Largest magnitude of the lower triangle of A (N x N): out[blockIdx.x] = max
+// over a share of its columns.  With one workgroup it is the largest of the N
+// values of A's first column instead (the partial maxima).
+__global__ __launch_bounds__(256) void maxabs_lower_kernel(const double* __restrict__ A, int N,
+                                                           double* __restrict__ out) {
   __shared__ double red[256];
   double m = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
-    m = fmax(m, fabs(p[i]));
+  const int cols = gridDim.x == 1 ? 1 : N;
+  for (int j = blockIdx.x; j < cols; j += gridDim.x)
+#pragma unroll 4
+    for (int i = j + threadIdx.x; i < N; i += 256) m = fmax(m, fabs(A[(int64_t)i + (int64_t)j * N]));
   red[threadIdx.x] = m;
   __syncthreads();
   for (int off = 128; off > 0; off >>= 1) {

@@ -12,30 +12,39 @@ constexpr int NB_LEAF = 128;
 
 // L <- M = h2 * Phi + (1 - h2) * I in the lower triangle of the leading n x n
 // block (read from Phi's lower triangle), identity on the padding rows
-// n..N-1, zeros above the diagonal.  N x N column-major, ld = N.
-__global__ void form_m_kernel(double* __restrict__ L, int N, int n,
-                              const double* __restrict__ Phi, int64_t ld_phi, double h2) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)N * N;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    int i = (int)(idx % N);
-    int j = (int)(idx / N);
-    double v = 0.0;
-    if (i >= j) {
-      if (i < n) v = h2 * Phi[(int64_t)i + (int64_t)j * ld_phi] + (i == j ? (1.0 - h2) : 0.0);
-      else if (i == j) v = 1.0;
+// n..N-1, and zeros above the diagonal within its diagonal blocks of NB_LEAF;
+// Li <- zeros in its diagonal blocks, and the identity in rows r0..N-1 (past the
+// factored blocks); info <- 0.  N x N column-major, ld = N.  Nothing reads L or
+// L^-1 above the diagonal blocks, and the factorization writes every block of
+// L^-1 below them, so the rest is left as it is (N = 10,240: two kernels that
+// wrote both matrices in full took 350 us, this one 150 us).
+// One column per workgroup in turn, so that a thread's index needs no division.
+__global__ __launch_bounds__(256) void setup_init_kernel(double* __restrict__ L, double* __restrict__ Li, int N, int n,
+                                                         int r0, const double* __restrict__ Phi, int64_t ld_phi,
+                                                         double h2, int* __restrict__ info) {
+  if (blockIdx.x == 0 && threadIdx.x < 2) info[threadIdx.x] = 0;
+  for (int j = blockIdx.x; j < N; j += gridDim.x) {
+    double2* Lc = reinterpret_cast<double2*>(L + (int64_t)j * N);
+    double* Ic = Li + (int64_t)j * N;
+    const double* Pc = Phi + (int64_t)j * ld_phi;
+    const int d0 = j / NB_LEAF * NB_LEAF;   // first row of the column's diagonal block
+#pragma unroll 4
+    for (int r = d0 / 2 + threadIdx.x; r < N / 2; r += 256) {
+      double v[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = 2 * r + u;
+        v[u] = 0.0;
+        if (k >= j) {
+          if (k < n) v[u] = h2 * Pc[k] + (k == j ? (1.0 - h2) : 0.0);
+          else if (k == j) v[u] = 1.0;
+        }
+      }
+      Lc[r] = double2{v[0], v[1]};
     }
-    L[idx] = v;
-  }
-}
-
-// N x N zeros with ones on the diagonal from row r0 on.
-__global__ void identity_tail_kernel(double* __restrict__ p, int N, int r0) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)N * N;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(idx % N), j = (int)(idx / N);
-    p[idx] = (i == j && i >= r0) ? 1.0 : 0.0;
+    if (threadIdx.x < NB_LEAF) Ic[d0 + threadIdx.x] = 0.0;
+    __syncthreads();   // the padding's ones come after its zeros
+    for (int i = r0 + threadIdx.x; i < N; i += 256) Ic[i] = (i == j) ? 1.0 : 0.0;
   }
 }
 
@@ -80,22 +89,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(double* __restrict__ dst
   }
 }
 
-// Wpack (N x p, ld N) <- [X_L | y] with zero rows n..N-1.
-__global__ void pack_covariates_kernel(double* __restrict__ Wp, int N, int n, int p,
-                                       const double* __restrict__ XL, int64_t ld_xl,
-                                       const double* __restrict__ y) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)N * p;
-  for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    int i = (int)(idx % N);
-    int j = (int)(idx / N);
-    double v = 0.0;
-    if (i < n) v = (j < p - 1) ? XL[(int64_t)i + (int64_t)j * ld_xl] : y[i];
-    Wp[idx] = v;
-  }
-}
-
-// W = L^-1 V for the thin covariate block V = [X_L | y] (N x P, ld N) and the
+// W = L^-1 V for the thin covariate block V = [X_L | y] (n x P) and the
 // lower-triangular inverse factor (N x N, ld N): a matrix-vector-shaped
 // product bound by reading L^-1's lower triangle once, so it runs split over
 // k on the vector units.  Workgroup (r, s) takes rows 64 r .. 64 r + 63 and
@@ -107,8 +101,9 @@ __global__ void pack_covariates_kernel(double* __restrict__ Wp, int N, int n, in
 constexpr int TA_KC = 256;
 
 template <int P>
-__global__ __launch_bounds__(256) void tri_apply_partial_kernel(const double* __restrict__ Li, int N,
-                                                                const double* __restrict__ V,
+__global__ __launch_bounds__(256) void tri_apply_partial_kernel(const double* __restrict__ Li, int N, int n,
+                                                                const double* __restrict__ XL, int64_t ld_xl,
+                                                                const double* __restrict__ y,
                                                                 double* __restrict__ part) {
   __shared__ double v[TA_KC * P];       // v[kk * P + j] = V[k0 + kk][j]; then the group sums
   const int i0 = blockIdx.x * 64, s = blockIdx.y, k0 = s * TA_KC;
@@ -118,7 +113,8 @@ __global__ __launch_bounds__(256) void tri_apply_partial_kernel(const double* __
   {
     double x[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) x[j] = (k0 + t < N) ? V[(int64_t)(k0 + t) + (int64_t)j * N] : 0.0;
+    for (int j = 0; j < P; ++j)
+      x[j] = (k0 + t >= n) ? 0.0 : (j < P - 1) ? XL[(int64_t)(k0 + t) + (int64_t)j * ld_xl] : y[k0 + t];
 #pragma unroll
     for (int j = 0; j < P; ++j) v[t * P + j] = x[j];
   }
@@ -158,15 +154,19 @@ __global__ __launch_bounds__(256) void tri_apply_partial_kernel(const double* __
   }
 }
 
+// Row-wise sums of the chunks that reach a row tile.
+__device__ __forceinline__ double tri_apply_row(const double* __restrict__ part, int64_t total, int64_t idx, int i) {
+  const int last = (i / 64 * 64 + 63) / TA_KC;   // chunks s <= last reach row tile i / 64
+  double x = 0.0;
+  for (int s = 0; s <= last; ++s) x += part[(int64_t)s * total + idx];
+  return x;
+}
+
 __global__ void tri_apply_sum_kernel(const double* __restrict__ part, int N, int P, double* __restrict__ W) {
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = (int64_t)N * P;
   for (; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(idx % N);
-    const int last = (i / 64 * 64 + 63) / TA_KC;   // chunks s <= last reach row tile i / 64
-    double x = 0.0;
-    for (int s = 0; s <= last; ++s) x += part[(int64_t)s * total + idx];
-    W[idx] = x;
+    W[idx] = tri_apply_row(part, total, idx, (int)(idx % N));
   }
 }
 
@@ -516,9 +516,7 @@ constexpr double RANK_REL = 9.094947017729282e-13;  // 2^-40
 // Single-thread factorization of S_TL = G[0:q, 0:q] and the hoisted
 // right-hand side.  Sets *info_rank = j + 1 for the first pivot at or below
 // the floor.
-__global__ void small_factor_kernel(const double* __restrict__ G, int p, double* __restrict__ small,
-                                    int* __restrict__ info_rank) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ inline void small_factor(const double* G, int p, double* __restrict__ small, int* __restrict__ info_rank) {
   const int q = p - 1;
   double* Lt = small + SmallLayout::Lt(p);
   double* zT = small + SmallLayout::zT(p);
@@ -545,6 +543,43 @@ __global__ void small_factor_kernel(const double* __restrict__ G, int p, double*
   const double c = G[q + q * p];
   small[SmallLayout::c(p)] = c;
   small[SmallLayout::qres(p)] = c - zz;
+}
+
+__global__ void small_factor_kernel(const double* __restrict__ G, int p, double* __restrict__ small,
+                                    int* __restrict__ info_rank) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) small_factor(G, p, small, info_rank);
+}
+
+// tri_apply_sum_kernel, gram_kernel and small_factor_kernel in one launch by one
+// workgroup, for studies of up to COV_MAX padded rows, whose three launches take
+// longer than their work: W from its partial sums, its Gram matrix (a wave per
+// pair in turn), the factor.
+constexpr int COV_MAX = 2048;
+
+__global__ __launch_bounds__(1024) void covariates_kernel(const double* __restrict__ part, int N, int p,
+                                                          double* __restrict__ W, double* __restrict__ G,
+                                                          double* __restrict__ small, int* __restrict__ info_rank) {
+  __shared__ double g[20 * 20];
+  const int64_t total = (int64_t)N * p;
+  for (int64_t idx = threadIdx.x; idx < total; idx += 1024) W[idx] = tri_apply_row(part, total, idx, (int)(idx % N));
+  __syncthreads();   // the workgroup's own stores to W are visible to it
+  const int lane = threadIdx.x & 63, pairs = p * (p + 1) / 2;
+  for (int pair = threadIdx.x >> 6; pair < pairs; pair += 16) {
+    int j = 0;
+    while ((j + 1) * (j + 2) / 2 <= pair) ++j;
+    const int k = pair - j * (j + 1) / 2;
+    double s = 0.0;
+    for (int r = lane; r < N; r += 64) s += W[r + (int64_t)j * N] * W[r + (int64_t)k * N];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) {
+      g[j + k * p] = s;
+      g[k + j * p] = s;
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < p * p; e += 1024) G[e] = g[e];
+  if (threadIdx.x == 0) small_factor(g, p, small, info_rank);
 }
 
 }  // namespace gls
