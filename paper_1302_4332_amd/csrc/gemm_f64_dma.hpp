@@ -1,8 +1,8 @@
 // FP64 product C = alpha op(A) B + beta Cin for the per-block solve
 // X~ = L^-1 X and the refinement residual X - L X~ (also the setup's panel and
 // trailing products and the adjoint's L-bar update): A column-major and lower
-// or upper triangular (or full), B column-major (full, or lower triangular
-// under a full A), C column-major, optionally only the tiles that reach C's
+// or upper triangular (or full), B column-major (full or lower
+// triangular), C column-major, optionally only the tiles that reach C's
 // lower part.  The same
 // v_mfma_f64_4x4x4_4b_f64 accumulation as gemm_f64_kernel with the k order
 // permuted within each 16-deep stage; operands reach LDS by direct
@@ -330,7 +330,7 @@ inline bool small_product(int M, int ncols, int K) {
 }
 
 // Whether the two kernels above apply to a product without transposes: A
-// full, lower or upper triangular (diagonal offset 0), no triangular B,
+// full, lower or upper triangular, B full or lower triangular (diagonal offsets 0),
 // 16-byte aligned operands with even leading dimensions,
 // K a multiple of 16, the rows of A up to M rounded up to 128 inside A's
 // leading dimension (they are read; rows past M are not stored), and lane
@@ -339,8 +339,7 @@ inline bool trmm_dma_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   const bool small = small_product(g.M, g.ncols, g.K);   // takes any B
   if (!al16(g.A) || (g.lda & 1) || (!small && (!al16(g.B) || (g.ldb & 1) || g.kvalid))) return false;
-  if (g.b_tri == TRI_UPPER || (g.b_tri == TRI_LOWER && (g.b_diag != 0 || g.a_tri != TRI_NONE)) || g.a_diag != 0)
-    return false;
+  if (g.b_tri == TRI_UPPER || (g.b_tri == TRI_LOWER && g.b_diag != 0) || g.a_diag != 0) return false;
   if (g.M <= 0 || g.K % DB_BK || g.K <= 0 || g.ncols <= 0 || g.mvalid > g.M) return false;
   if (g.lda < (int64_t)(g.M + DB_BM - 1) / DB_BM * DB_BM || g.ldb < (g.kvalid ? g.kvalid : g.K)) return false;
   if (small) return true;

@@ -14,6 +14,7 @@
 #include "gemm_f64_dma.hpp"
 #include "gls.h"
 #include "adjoint_kernels.hpp"
+#include "crt_i8.hpp"
 #include "gls_internal.hpp"
 #include "lp_gemm.hpp"
 #include "ozaki_i8.hpp"
@@ -60,6 +61,17 @@ static_assert(NPAD % NB_LEAF == 0 && NPAD % LP_BM == 0 && NPAD % OZ_BM == 0 && N
 // FP64 handles look for SNPs of whole numbers from this padded sample count on (see OZ_MIN_N's use in the plan): the
 // integer product of such SNPs needs L^-1 sliced at setup and a packed copy of each block.
 constexpr int64_t OZ_MIN_N = 512;
+
+// Nodes of the factorization of at least this many rows and columns form their products on the integer matrix cores
+// (crt_i8.hpp).  The fifteen products grow with the node's cube, the conversions with its square: at 5,000 a product
+// takes 1.0 + 0.3 ms where the FP64 one takes 2.4 (a study of 10,000 samples 23.0 -> 19.7 ms), at 2,500 0.28 + 0.1
+// against 0.38 (19.7 -> 19.3 ms), and at 2,048 the gradient at n = 4,096 goes from 9.35 to 9.7 ms.
+constexpr int64_t CRT_MIN_W = 2304;
+
+// Scratch of a node's products: two operands, the residues, norms.
+static size_t crt_space_bytes(int64_t w) {
+  return 3 * CRT_P * (size_t)(w * w) + (size_t)(w / 256 + 1) * w * 12 + 8 * (size_t)w + 8 * 256;
+}
 
 // Largest T1 buffer of the recursive factorization: (b - mid) * (mid - a) leaves.
 static int64_t recursion_temp_leaves(int a, int b) {
@@ -124,6 +136,14 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
     }
     pl->side_products = at > 0;
     pl->off_side = take(sizeof(double) * std::max<int64_t>(at, 1));
+  }
+  {
+    const int64_t w = (Kt + 1) / 2 * NB_LEAF;   // the widest node
+    pl->crt_w = w >= CRT_MIN_W ? w : 0;
+    if (pl->crt_w) {
+      pl->off_crt = take(crt_space_bytes(w));
+      pl->off_sc = take(sizeof(double) * (N + 1));
+    }
   }
   pl->off_buf0 = take(sizeof(double) * n * bc);
   pl->off_buf1 = take(sizeof(double) * n * bc);
@@ -313,6 +333,75 @@ static void tri_strips(const double* Li, int64_t ld, double* S, int w, int strip
   else hipLaunchKernelGGL((tri_strip_kernel<1024, ROWS>), grid, block, 0, s, Li, ld, S, w, alpha);
 }
 
+// A node's products on the integer matrix cores.
+struct CrtSpace {
+  int8_t* planes[2];
+  uint32_t* out;
+  double* ss;
+  int* e;
+  int* ex[2];
+  CrtSpace(char* at, int64_t w) {
+    auto take = [&](size_t bytes) {
+      char* p = at;
+      at += align_up(bytes, 256);
+      return p;
+    };
+    for (auto& p : planes) p = reinterpret_cast<int8_t*>(take(CRT_P * (size_t)(w * w)));
+    out = reinterpret_cast<uint32_t*>(take(CRT_P * (size_t)(w * w)));
+    ss = reinterpret_cast<double*>(take((size_t)(w / 256 + 1) * w * 8));
+    e = reinterpret_cast<int*>(take((size_t)(w / 256 + 1) * w * 4));
+    for (auto& p : ex) p = reinterpret_cast<int*>(take(4 * (size_t)w));
+  }
+  CrtOperand operand(int which, int vectors, int K) const {
+    CrtOperand o;
+    o.planes = planes[which];
+    o.ex = ex[which];
+    o.G = (vectors + 15) / 16;
+    o.KB = (K + 63) / 64;
+    o.stride = (int64_t)o.G * o.KB * 1024;
+    return o;
+  }
+  CrtOperand rows(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s) const {
+    const CrtOperand o = operand(which, n, K);
+    hipLaunchKernelGGL(crt_row_norm_kernel, dim3((n + 63) / 64, (K + 255) / 256), dim3(256), 0, s, X, ld, n, K,
+                       (int)lower, ss, e);
+    hipLaunchKernelGGL(crt_row_exp_kernel, dim3((n + 255) / 256), dim3(256), 0, s, ss, e, n, K, (int)lower, o.ex);
+    hipLaunchKernelGGL(crt_rows_kernel, dim3(o.KB, (n + 63) / 64), dim3(256), 0, s, X, ld, n, K, (int)lower, o);
+    return o;
+  }
+  CrtOperand cols(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s) const {
+    const CrtOperand o = operand(which, n, K);
+    hipLaunchKernelGGL(crt_col_exp_kernel, dim3((n + 3) / 4), dim3(256), 0, s, X, ld, K, n, (int)lower, o.ex);
+    hipLaunchKernelGGL(crt_cols_kernel, dim3(o.G, (o.KB + 3) / 4), dim3(256), 0, s, X, ld, K, n, (int)lower, o);
+    return o;
+  }
+  CrtArgs args(const CrtOperand& a, const CrtOperand& b, int M, int N, int K, double alpha, double* C, int64_t ldc) const {
+    CrtArgs g;
+    std::memset(&g, 0, sizeof g);
+    g.a = a;
+    g.b = b;
+    g.M = M;
+    g.N = N;
+    g.K = K;
+    g.out = out;
+    g.out_stride = (int64_t)a.G * b.G * 64;
+    g.alpha = alpha;
+    g.Cin = C;
+    g.ldcin = ldc;
+    g.C = C;
+    g.ldc = ldc;
+    return g;
+  }
+  static void product(const CrtArgs& g, hipStream_t s) {
+    GemmArgs m{};
+    m.map_gm = crt_map_gm(g);
+    m.map_gn = crt_map_gn(g);
+    const int Mt = (g.M + CRT_BM - 1) / CRT_BM, Nt = (g.N + CRT_BN - 1) / CRT_BN;
+    hipLaunchKernelGGL(crt_gemm_kernel, dim3(XcdMap::grid(m, Mt, Nt), CRT_P), dim3(CRT_THREADS), 0, s, g);
+    hipLaunchKernelGGL(crt_finish_kernel, dim3((g.a.G + 15) / 16, g.b.G), dim3(256), 0, s, g);
+  }
+};
+
 static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipStream_t s) {
   const int64_t N = c->N;
   double* L = c->L;
@@ -346,6 +435,36 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
     hipLaunchKernelGGL(gemm_f64_pair_kernel, dim3(std::max(w1, w2) / PAIR_BN, w2 / PAIR_BM, 2), dim3(256), 0, s, u, t);
     chol_inv_rec(c, mid, b, depth + 1, side, s);
     tri_strips<false>(Li22, N, Li21, w2, w1, -1.0, s);   // (L^-1)21 = -L22^-1 T
+    return;
+  }
+  if (c->plan.crt_w && std::min(w1, w2) >= CRT_MIN_W) {
+    const CrtSpace crt(reinterpret_cast<char*>(c->crt), c->plan.crt_w);
+    {  // L21 = A21 L11^-T
+      const CrtOperand A = crt.rows(0, A21, N, w2, w1, false, s), B = crt.rows(1, Li11, N, w1, w1, true, s);
+      CrtArgs g = crt.args(A, B, w2, w1, w1, 1.0, A21, N);
+      g.b_upper = 1;
+      CrtSpace::product(g, s);
+    }
+    const CrtOperand L21 = crt.rows(0, A21, N, w2, w1, false, s);
+    {  // A22 -= L21 L21^T
+      CrtArgs g = crt.args(L21, L21, w2, w2, w1, -1.0, A22, N);
+      g.beta = 1.0;
+      g.c_lower = 1;
+      CrtSpace::product(g, s);
+    }
+    {  // T = L21 L11^-1, kept in the block of L^-1 that its last product overwrites
+      const CrtOperand B = crt.cols(1, Li11, N, w1, w1, true, s);
+      CrtArgs g = crt.args(L21, B, w2, w1, w1, 1.0, Li21, N);
+      g.b_lower = 1;
+      CrtSpace::product(g, s);
+    }
+    chol_inv_rec(c, mid, b, depth + 1, side, s);
+    {  // (L^-1)21 = -L22^-1 T
+      const CrtOperand A = crt.rows(0, Li22, N, w2, w2, true, s), B = crt.cols(1, Li21, N, w1, w2, false, s);
+      CrtArgs g = crt.args(A, B, w2, w1, w2, -1.0, Li21, N);
+      g.a_lower = 1;
+      CrtSpace::product(g, s);
+    }
     return;
   }
   double* T = c->Xt;  // w2 x w1, ld w2
@@ -585,6 +704,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
   c->L = reinterpret_cast<double*>(ws + pl.off_L);
   c->Linv = reinterpret_cast<double*>(ws + pl.off_Linv);
   c->W = reinterpret_cast<double*>(ws + pl.off_W);
+  c->crt = pl.crt_w ? ws + pl.off_crt : nullptr;
   c->Xt = reinterpret_cast<double*>(ws + pl.off_Xt);
   c->buf[0] = reinterpret_cast<double*>(ws + pl.off_buf0);
   c->buf[1] = reinterpret_cast<double*>(ws + pl.off_buf1);
@@ -601,8 +721,15 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     return st;
   };
   // info[0]: failing pivot of M, info[1]: failing pivot of S_TL
-  hipLaunchKernelGGL(setup_init_kernel, dim3((unsigned)N), dim3(256), 0, s, c->L, c->Linv, (int)N,
-                     (int)n, pl.leaves * NB_LEAF, Phi, ld_phi, h2, c->info);
+  double* sc = nullptr;   // with products by residues: the diagonal scaling of M
+  if (pl.crt_w) {
+    sc = reinterpret_cast<double*>(ws + pl.off_sc);
+    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(64), 0, s, sc + N, (int64_t)1, 0.0);
+    hipLaunchKernelGGL(diagonal_scale_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, Phi, ld_phi, (int)n,
+                       (int)N, h2, sc);
+  }
+  hipLaunchKernelGGL(setup_init_kernel, dim3((unsigned)N), dim3(256), 0, s, c->L, c->Linv, (int)N, (int)n,
+                     pl.leaves * NB_LEAF, Phi, ld_phi, h2, (const double*)sc, c->info);
   {
     SetupSide side;
     if (side_st && (e = side.init(side_st, reinterpret_cast<double*>(ws + pl.off_side))) != hipSuccess)
@@ -611,6 +738,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     // every side product is joined into s by its node's last product
     if (side.err != hipSuccess) return fail(hip_fail(side.err, "gls_setup: side stream fork/join"));
   }
+  if (sc) hipLaunchKernelGGL(unscale_factor_kernel, dim3(2048), dim3(256), 0, s, c->L, c->Linv, (int)N, (const double*)sc);
   c->ub[0] = reinterpret_cast<uint8_t*>(ws + pl.off_ub0);
   c->ub[1] = reinterpret_cast<uint8_t*>(ws + pl.off_ub1);
   if (pl.whole) {
@@ -1346,15 +1474,20 @@ gls_status block_forward_u2(Ctx* c, int mb, const uint8_t* G2, int64_t ldg, doub
   return block_forward(c, mb, c->x64, c->N, b, ld_b, s2, v, st, s);
 }
 
-void reset_adjoint(Ctx* c, hipStream_t s) {
+static void reset_adjoint_sums(Ctx* c, hipStream_t s) {
   const int64_t N = c->N;
-  // T2 holds (L^-1)^T until the Cholesky adjoint of the pass's finish step reuses it: the per-block
-  // X_R bar = L^-T X~_R bar then reads an upper-triangular A without a transpose (the direct-load product)
-  hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)((N + 31) / 32), (unsigned)((N + 31) / 32)), dim3(256), 0, s,
-                     c->T2, N, c->Linv, N, (int)N, (int)N);
   hipLaunchKernelGGL(fill_kernel, dim3(grid_for(N * N)), dim3(256), 0, s, c->Lbar, N * N, 0.0);
   hipLaunchKernelGGL(fill_kernel, dim3(grid_for(N * c->p)), dim3(256), 0, s, c->Wb, N * c->p, 0.0);
   hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(256), 0, s, c->acc, (int64_t)adj_nc(c->p), 0.0);
+}
+
+void reset_adjoint(Ctx* c, hipStream_t s) {
+  const int64_t N = c->N;
+  // T2 holds (L^-1)^T, so that the per-block X_R bar = L^-T X~_R bar reads an upper-triangular A without a transpose
+  // (the direct-load product); the finish step ends with it there again
+  hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)((N + 31) / 32), (unsigned)((N + 31) / 32)), dim3(256), 0, s,
+                     c->T2, N, c->Linv, N, (int)N, (int)N);
+  reset_adjoint_sums(c, s);
 }
 
 template <int P>
@@ -1486,40 +1619,40 @@ gls_status finish_backward(Ctx* c, double* y_grad, double* h2_grad, hipStream_t 
   }
   const int gN = grid_for(N * N);
   hipLaunchKernelGGL(lower_part_kernel, dim3(gN), dim3(256), 0, s, c->Lbar, (int)N, 0);
-  {  // T1 = lower part of L^T Lbar   (op(A) = L^T upper, op(B) = Lbar lower)
-    GemmArgs g = gemm_args(c->L, N, c->Lbar, N, c->T1, N, (int)N, (int)N, (int)N, 1.0);
+  // Three triangular products without transposed operands, so that they run on the direct-load kernel: T2 holds L^T,
+  // then (L^-1)^T, which the next pass's blocks read, and the second product takes Lbar's place.
+  auto transpose_to_t2 = [&](const double* X) {
+    hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)((N + 31) / 32), (unsigned)((N + 31) / 32)), dim3(256), 0, s,
+                       c->T2, N, X, N, (int)N, (int)N);
+  };
+  transpose_to_t2(c->L);
+  {  // T1 = lower part of L^T Lbar   (A = L^T upper, B = Lbar lower; k from the row: low row tiles first)
+    GemmArgs g = gemm_args(c->T2, N, c->Lbar, N, c->T1, N, (int)N, (int)N, (int)N, 1.0);
     g.a_tri = TRI_UPPER;
-    g.a_diag = 0;
     g.b_tri = TRI_LOWER;
-    g.b_diag = 0;
     g.c_lower = 1;
-    g.c_diag = 0;
-    gemm(true, false, true, g, s);   // k from the row: low row tiles first
+    gemm(false, false, true, g, s);
   }
   hipLaunchKernelGGL(lower_part_kernel, dim3(gN), dim3(256), 0, s, c->T1, (int)N, 1);
-  {  // T2 = T1 L^-1   (lower x lower = lower)
-    GemmArgs g = gemm_args(c->T1, N, c->Linv, N, c->T2, N, (int)N, (int)N, (int)N, 1.0);
+  {  // Lbar = T1 L^-1   (lower x lower = lower; k in [column, row]: high row tiles first)
+    GemmArgs g = gemm_args(c->T1, N, c->Linv, N, c->Lbar, N, (int)N, (int)N, (int)N, 1.0);
     g.a_tri = TRI_LOWER;
-    g.a_diag = 0;
     g.b_tri = TRI_LOWER;
-    g.b_diag = 0;
     g.c_lower = 1;
-    g.c_diag = 0;
     g.map_desc = 1;
-    gemm(false, false, true, g, s);   // k in [column, row]: high row tiles first
+    gemm(false, false, true, g, s);
   }
-  {  // T1 = L^-T T2   (the adjoint of M, up to symmetrisation)
-    GemmArgs g = gemm_args(c->Linv, N, c->T2, N, c->T1, N, (int)N, (int)N, (int)N, 1.0);
+  transpose_to_t2(c->Linv);
+  {  // T1 = L^-T Lbar   (the adjoint of M, up to symmetrisation)
+    GemmArgs g = gemm_args(c->T2, N, c->Lbar, N, c->T1, N, (int)N, (int)N, (int)N, 1.0);
     g.a_tri = TRI_UPPER;
-    g.a_diag = 0;
     g.b_tri = TRI_LOWER;
-    g.b_diag = 0;
-    gemm(true, false, true, g, s);   // k from the row: low row tiles first
+    gemm(false, false, true, g, s);
   }
   double* part = c->acc + adj_nc(p);
   hipLaunchKernelGGL(h2_contract_kernel, dim3(1024), dim3(256), 0, s, c->T1, c->Phi, (int)N, (int)c->n, part);
   if (h2_grad) hipLaunchKernelGGL(sum_ordered_kernel, dim3(1), dim3(64), 0, s, part, 1024, h2_grad);
-  reset_adjoint(c, s);
+  reset_adjoint_sums(c, s);
   return GLS_OK;
 }
 

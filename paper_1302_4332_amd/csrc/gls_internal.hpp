@@ -38,6 +38,9 @@ struct Plan {
   size_t off_side = 0;
   int64_t side_at[16] = {0};
   bool side_products = false;   // some node's product runs there
+  // setup: scratch of the products on the integer matrix cores (widest node; 0: none)
+  int64_t crt_w = 0;
+  size_t off_crt = 0, off_sc = 0;
   int leaves = 0;   // NB_LEAF-row diagonal blocks factored: rows n..N-1 past them are the identity
   size_t total = 0;
 };
@@ -57,6 +60,7 @@ struct gls_ctx {
   double* small = nullptr;  // factor of S_TL and hoisted right-hand side
   double* gram = nullptr;   // [X~_L | y~]^T [X~_L | y~]  (p x p)
   double* L = nullptr;      // N x N lower Cholesky factor of M (identity padding)
+  char* crt = nullptr;      // scratch of the setup's products on the integer matrix cores
   double* Linv = nullptr;   // N x N lower, L^-1
   double* W = nullptr;      // N x p, [X~_L | y~]
   double* Xt = nullptr;     // N x block_cols, X~_R of the current block (also setup scratch)

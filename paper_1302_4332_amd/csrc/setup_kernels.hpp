@@ -19,15 +19,18 @@ constexpr int NB_LEAF = 128;
 // L^-1 below them, so the rest is left as it is (N = 10,240: two kernels that
 // wrote both matrices in full took 350 us, this one 150 us).
 // One column per workgroup in turn, so that a thread's index needs no division.
+// With sc, M[i, j] is scaled by sc[i] sc[j] (powers of two).
 __global__ __launch_bounds__(256) void setup_init_kernel(double* __restrict__ L, double* __restrict__ Li, int N, int n,
                                                          int r0, const double* __restrict__ Phi, int64_t ld_phi,
-                                                         double h2, int* __restrict__ info) {
+                                                         double h2, const double* __restrict__ sc,
+                                                         int* __restrict__ info) {
   if (blockIdx.x == 0 && threadIdx.x < 2) info[threadIdx.x] = 0;
   for (int j = blockIdx.x; j < N; j += gridDim.x) {
     double2* Lc = reinterpret_cast<double2*>(L + (int64_t)j * N);
     double* Ic = Li + (int64_t)j * N;
     const double* Pc = Phi + (int64_t)j * ld_phi;
     const int d0 = j / NB_LEAF * NB_LEAF;   // first row of the column's diagonal block
+    const double sj = sc ? sc[j] : 1.0;
 #pragma unroll 4
     for (int r = d0 / 2 + threadIdx.x; r < N / 2; r += 256) {
       double v[2];
@@ -38,6 +41,7 @@ __global__ __launch_bounds__(256) void setup_init_kernel(double* __restrict__ L,
         if (k >= j) {
           if (k < n) v[u] = h2 * Pc[k] + (k == j ? (1.0 - h2) : 0.0);
           else if (k == j) v[u] = 1.0;
+          if (sc) v[u] *= sc[k] * sj;
         }
       }
       Lc[r] = double2{v[0], v[1]};
@@ -45,6 +49,39 @@ __global__ __launch_bounds__(256) void setup_init_kernel(double* __restrict__ L,
     if (threadIdx.x < NB_LEAF) Ic[d0 + threadIdx.x] = 0.0;
     __syncthreads();   // the padding's ones come after its zeros
     for (int i = r0 + threadIdx.x; i < N; i += 256) Ic[i] = (i == j) ? 1.0 : 0.0;
+  }
+}
+
+// Powers of two that bring M's diagonal into [1/2, 2]: sc[i] = 2^-e with
+// M[i, i] 4^-e there, and sc[N] = 1 if one of them is not 1 (else 0; set to 0
+// before the launch).  A product formed by residues rounds its operands at a
+// fraction of their row's norm, which is harmless against an error bound like
+// that of the Cholesky factorization, sqrt(M_ii M_jj) 2^-53 per entry, only where
+// the rows of M are of one scale.
+__global__ void diagonal_scale_kernel(const double* __restrict__ Phi, int64_t ld_phi, int n, int N, double h2,
+                                      double* __restrict__ sc) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  const double d = i < n ? h2 * Phi[(int64_t)i * (ld_phi + 1)] + (1.0 - h2) : 1.0;
+  int e = 0;
+  if (d > 0.0 && d < __builtin_inf() && !(d >= 0.5 && d <= 2.0)) {
+    frexp(d, &e);   // d 2^-e in [1/2, 1)
+    e = e >= 0 ? e / 2 : -((1 - e) / 2);
+  }
+  sc[i] = ldexp(1.0, -e);
+  if (e != 0) sc[N] = 1.0;
+}
+
+// The factor and its inverse of M from those of the scaled matrix: L[i, j] /= sc[i], Li[i, j] *= sc[j] (lower parts).
+__global__ __launch_bounds__(256) void unscale_factor_kernel(double* __restrict__ L, double* __restrict__ Li, int N,
+                                                             const double* __restrict__ sc) {
+  if (sc[N] == 0.0) return;
+  for (int j = blockIdx.x; j < N; j += gridDim.x) {
+    const double sj = sc[j];
+    for (int i = j + threadIdx.x; i < N; i += 256) {
+      L[(int64_t)i + (int64_t)j * N] /= sc[i];
+      Li[(int64_t)i + (int64_t)j * N] *= sj;
+    }
   }
 }
 
