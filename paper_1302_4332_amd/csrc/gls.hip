@@ -160,7 +160,7 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
   // the refinement residual and the adjoint; without those its region is free and holds them.
   pl->whole = pl->lp_bytes == 0 && (o->precision == GLS_INT8_EMU || N >= OZ_MIN_N);
   if (pl->whole) {
-    const size_t at = align_up(oz_factor_bytes(N), 256), ex = sizeof(int) * N;
+    const size_t at = align_up(oz_factor_bytes(N), 256), ex = sizeof(int) * (N + 1);
     if (o->flags & GLS_KEEP_FOR_GRAD) pl->off_sl = take(at + ex);
     else pl->off_sl = pl->off_L;
     pl->off_ex = pl->off_sl + at;
@@ -745,6 +745,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     c->sl = reinterpret_cast<int8_t*>(ws + pl.off_sl);
     c->ex = reinterpret_cast<int*>(ws + pl.off_ex);
     const unsigned T = (unsigned)(N / OZ_TM);
+    hipLaunchKernelGGL(diagonal_range_kernel, dim3(1), dim3(1024), 0, s, Phi, ld_phi, (int)n, h2, c->ex + N);
     hipLaunchKernelGGL(row_max_kernel, dim3(T, (unsigned)((N + 255) / 256)), dim3(256), 0, s, c->Linv, (int)N, c->Xt);
     hipLaunchKernelGGL(slice_factor_kernel, dim3(T, T), dim3(256), 0, s, c->Linv, (int)N, (const double*)c->Xt, c->ex,
                        c->sl);
@@ -1326,7 +1327,7 @@ static void pack_units(Ctx* c, const void* src, int64_t ld, int mb, bool check, 
   const int xmax = (int)std::min<int64_t>(127, (((int64_t)1 << 31) - 1) / (128 * c->n));
   if (check) w->flags = ColFlags{w->flags_at, chunks};
   hipLaunchKernelGGL(pack_units_kernel<SRC>, dim3(w->Jb, chunks), dim3(256), 0, s, src, ld, (int)c->n, w->nkb, mb,
-                     w->Jb, chunk, xmax, w->units, check ? w->flags_at : nullptr);
+                     w->Jb, chunk, xmax, w->units, check ? w->flags_at : nullptr, (const int*)(c->ex + c->N));
 }
 
 static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w, hipStream_t s) {
@@ -1436,8 +1437,9 @@ void widen_u2(Ctx* c, const uint8_t* G2, int64_t ldg, int mb, hipStream_t s) {
 
 // Bytes (or 2-bit codes) on the integer matrix cores without a detour over
 // FP64.  In an FP64 handle, bytes above the int8 range are flagged and take the
-// FP64 product, as the same values given in FP64 do; a GLS_INT8_EMU handle's
-// bytes are the caller's promise, and 2-bit codes always qualify (n <= 2^20).
+// FP64 product, as the same values given in FP64 do (as does every SNP of a study
+// that does not qualify, see diagonal_range_kernel); a GLS_INT8_EMU handle's
+// values are the caller's promise.
 template <int SRC>
 static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t ldg, double* b, int64_t ld_b,
                                       double* s2, double* v, int* st, hipStream_t s) {
@@ -1446,7 +1448,7 @@ static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t 
   {
     PhaseTimer t(c, PH_WHITEN, s);
     w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
-    const bool check = SRC == OZ_U8 && c->opts.precision != GLS_INT8_EMU;
+    const bool check = c->opts.precision != GLS_INT8_EMU;
     pack_units<SRC>(c, G, ldg, mb, check, &w, s);
     whole_product(c, w, mb, nullptr, s);
     if (check) {

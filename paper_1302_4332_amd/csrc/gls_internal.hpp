@@ -79,7 +79,7 @@ struct gls_ctx {
   uint8_t* ub[2] = {nullptr, nullptr};  // streaming staging, n x block_cols bytes
   double* x64 = nullptr;    // N x block_cols FP64: bytes widened, or a block copied with zero rows past n
   int8_t* sl = nullptr;     // int8 slices of L^-1 (plan.whole; in L's region unless the handle keeps L)
-  int* ex = nullptr;        // N row exponents of L^-1
+  int* ex = nullptr;        // N row exponents of L^-1; [N]: the study qualifies (diagonal_range_kernel)
   // adjoint state (GLS_KEEP_FOR_GRAD)
   bool grad = false;
   double* Phi = nullptr;    // N x N, lower triangle of Phi (zero padding)

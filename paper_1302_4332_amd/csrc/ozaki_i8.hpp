@@ -106,6 +106,39 @@ __global__ __launch_bounds__(256) void slice_factor_kernel(const double* __restr
     *reinterpret_cast<uint4*>(o + s * OZ_UNIT) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
+// *ok = 1 if M's diagonal spans a factor of at most 256, else 0.  The digits are
+// fixed-point at the scale of their row of L^-1, whose columns go with
+// M_jj^-1/2: over wildly different scales a SNP that is zero at the dominant
+// samples would lose the others' low bits, and FP64 handles then form every
+// product in FP64.
+__global__ __launch_bounds__(1024) void diagonal_range_kernel(const double* __restrict__ Phi, int64_t ld_phi, int n,
+                                                              double h2, int* __restrict__ ok) {
+  __shared__ double lo[16], hi[16];
+  double a = __builtin_inf(), b = 0.0;
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    const double d = h2 * Phi[(int64_t)i * (ld_phi + 1)] + (1.0 - h2);
+    a = fmin(a, d);
+    b = fmax(b, d);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    a = fmin(a, __shfl_xor(a, off, 64));
+    b = fmax(b, __shfl_xor(b, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    lo[threadIdx.x >> 6] = a;
+    hi[threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      a = fmin(a, lo[w]);
+      b = fmax(b, hi[w]);
+    }
+    *ok = (b <= 256.0 * a) ? 1 : 0;
+  }
+}
+
 // Packed dosages: four 2-bit codes per byte, sample k of a column in bits
 // [2 (k % 4), 2 (k % 4) + 2) of the column's byte k / 4; code value = dosage
 // (0..3).  Bits of the last byte past row n - 1 are ignored.
@@ -125,22 +158,23 @@ enum { OZ_F64 = 0, OZ_F64_ALIGNED = 1, OZ_U8 = 2, OZ_U2 = 3 };
 // A block's SNP values as units [k block][SNP group of 16] (Jb groups).  flags
 // (nullptr: none are needed) receives, for every k chunk c and SNP j,
 // flags[c mb + j] = 1 if a value of the chunk is not a whole number of magnitude
-// at most xmax.  A wave whose SNPs are all flagged stops: their results come
+// at most xmax, or always if *ok is 0.  A wave whose SNPs are all flagged stops: their results come
 // from the FP64 product.  Workgroup (group, chunk of chunk_kb k blocks), four
 // waves over the chunk's k blocks; a lane holds its 16 bytes' values, so FP64
 // columns are read as whole 128-byte lines.
 template <int SRC>
 __global__ __launch_bounds__(256) void pack_units_kernel(const void* __restrict__ src, int64_t ld, int n, int nkb,
                                                          int mb, int Jb, int chunk_kb, int xmax,
-                                                         uint8_t* __restrict__ out, int* __restrict__ flags) {
+                                                         uint8_t* __restrict__ out, int* __restrict__ flags,
+                                                         const int* __restrict__ ok_study) {
   __shared__ int seen[4];
   const int jb = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = jb * 16 + (lane & 15), kq = lane >> 4;
   const bool col = j < mb;
   const unsigned cols = (mb - jb * 16 >= 16) ? 0xffffu : (1u << (mb - jb * 16)) - 1u;
   const int kb1 = min(nkb, (int)(blockIdx.y + 1) * chunk_kb);
-  unsigned bad = 0;   // flagged columns (wave-uniform)
-  for (int kb = blockIdx.y * chunk_kb + wave; kb < kb1; kb += 4) {
+  unsigned bad = (flags && !*ok_study) ? cols : 0u;   // flagged columns (wave-uniform)
+  if (bad != cols) for (int kb = blockIdx.y * chunk_kb + wave; kb < kb1; kb += 4) {
     const int k0 = kb * 64 + kq * 16;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
     if constexpr (SRC == OZ_F64 || SRC == OZ_F64_ALIGNED) {

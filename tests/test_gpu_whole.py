@@ -124,3 +124,21 @@ def test_gradient_of_a_mixed_study(n, bc):
         grads.append([g.cpu().numpy() for g in torch.autograd.grad(t2_loss(*out), (yt, Xt, h2))])
     for a, b in zip(*grads):
         assert np.abs(a - b).max() <= 1e-9 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("fmt", ["f64", "u8", "u2"])
+def test_scales_apart(fmt):
+    """Samples of scales 2^+-30: whole numbers stay on the FP64 product, whose terms keep their own precision (the SNPs
+    are zero at the samples of large weight).  The oracle solves the same study with every sample brought to scale 1."""
+    n, mb = 600, 40
+    Phi, XL, y, XR = _study(n, 3, mb)
+    rng = np.random.default_rng(1)
+    s = 2.0 ** rng.integers(-30, 31, n)
+    M = Phi * 0.4 + 0.6 * np.eye(n)
+    XR = np.where(s[None, :] < 1.0, 0.0, XR)
+    ref = O.gls_sequence(M, 1.0, XL / s[:, None], y / s, XR / s)
+    X = {"f64": XR, "u8": XR.astype(np.uint8), "u2": synth.pack_dosages_2bit(XR.astype(np.uint8))}[fmt]
+    ctx = GLSContext(_t(s[:, None] * M * s), 1.0, _t(XL), _t(y), block_cols=mb)
+    call = {"f64": ctx.block, "u8": ctx.block_u8, "u2": ctx.block_u2}[fmt]
+    compare(as_numpy(call(_t(X))), ref, 1e-10)
+    ctx.close()
