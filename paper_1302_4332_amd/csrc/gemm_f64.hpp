@@ -98,8 +98,11 @@ __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 
 // XCD-aware workgroup -> tile mapping.  Workgroups are dispatched to the 8
-// XCDs round-robin (workgroup id % 8), so row tiles are dealt to the XCDs in
-// a snake order (balanced k-work) and, on each XCD, groups of GM local row
+// XCDs round-robin (workgroup id % 8), so row tiles are dealt to the XCDs, eight
+// a round, in an order that balances triangular k-work: there and back in turn
+// (a snake), and for an odd number of rounds the first three by permutations
+// whose sums over the rounds are 10 or 11 for every XCD (a snake's are 7 to 14:
+// at 24 row tiles one XCD got a fifth more than another).  On each XCD, groups of GM local row
 // tiles x GN column tiles run together so the operand strips they share stay
 // in that XCD's L2.  Row groups are issued heavy-first.
 struct XcdMap {
@@ -137,7 +140,13 @@ struct XcdMap {
     int kl = rgi * GM + (w % GM);     // local row index on this XCD
     int j = cgi * GN + (w / GM);
     if (kl >= R || j >= Nt) return false;
-    int pos = (kl & 1) ? (7 - x) : x;
+    int pos;
+    if ((R & 1) && kl < 3) {
+      const uint32_t perm = kl == 0 ? 0x76543210u : kl == 1 ? 0x10576243u : 0x34102657u;   // nibble x: XCD x's row
+      pos = (int)((perm >> (4 * x)) & 7u);
+    } else {
+      pos = ((kl ^ R) & 1) ? (7 - x) : x;
+    }
     int ro = kl * 8 + pos;
     if (ro >= Mt) return false;
     *ti = ga.map_desc ? (Mt - 1 - ro) : ro;
