@@ -1216,6 +1216,28 @@ void prepare_low_precision(Ctx* c, hipStream_t s) {
   hipLaunchKernelGGL(fill_kernel, dim3(grid_for(N * c->plan.bcp)), dim3(256), 0, s, c->R, N * c->plan.bcp, 0.0);
 }
 
+// Products of up to 512 tiles of 256 x 128 (one round of two workgroups per compute unit, as long as the factor's
+// last rows) or of up to 1,024 rows take 64 x 64 ones.  Refined blocks, large tiles against small: n = 300, 400 SNPs
+// in FP32 195 against 66 us; n = 6,000, 2,000 SNPs 3.08 against 2.55 ms, 4,096 (768 tiles) 5.04 against 5.25; n =
+// 1,000, 20,000 SNPs 2.22 against 1.26 ms; n = 3,000, 8,000 SNPs in FP16 (756 tiles) 3.36 against 3.56.
+static bool lp_small(int64_t N, int mb) {
+  return N <= 1024 || (N / LpBig::BM) * ((mb + LpBig::BN - 1) / LpBig::BN) <= 512;
+}
+
+template <typename T, typename C>
+static void launch_lp(LpArgs a, hipStream_t s) {
+  // XCD groups of one row tile x 32 column tiles, heavy row tiles first (measured per 8,192-column launch at
+  // n = 10,000: FP32 140 TFLOP/s against 101 with 2 x 8 groups and 75 with 4 x 8, FP16 781 against 678; at
+  // n = 4,096 FP32 133 against 74; 1 x 8 and 1 x 16 within 8% of 1 x 32)
+  a.map_gm = 1;
+  a.map_gn = 32;
+  GemmArgs m{};
+  m.map_gm = a.map_gm;
+  m.map_gn = a.map_gn;
+  hipLaunchKernelGGL((lp_gemm_kernel<T, C>), dim3(XcdMap::grid(m, a.M / C::BM, (a.ncols + C::BN - 1) / C::BN)),
+                     dim3(C::THREADS), 0, s, a);
+}
+
 template <typename T>
 static void lp_solve_t(Ctx* c, const double* src, int64_t lds, int mb, double beta, hipStream_t s) {
   const int64_t N = c->N;
@@ -1238,17 +1260,9 @@ static void lp_solve_t(Ctx* c, const double* src, int64_t lds, int mb, double be
   a.ncols = mb;
   a.K = (int)N;
   a.beta = beta;
-  // XCD groups of one row tile x 32 column tiles, heavy row tiles first (measured per 8,192-column launch at
-  // n = 10,000: FP32 140 TFLOP/s against 101 with 2 x 8 groups and 75 with 4 x 8, FP16 781 against 678; at
-  // n = 4,096 FP32 133 against 74; 1 x 8 and 1 x 16 within 8% of 1 x 32)
-  a.map_gm = 1;
-  a.map_gn = 32;
   a.map_desc = 1;
-  const int Mt = (int)(N / LP_BM), Nt = (mb + LP_BN - 1) / LP_BN;
-  GemmArgs m{};
-  m.map_gm = a.map_gm;
-  m.map_gn = a.map_gn;
-  hipLaunchKernelGGL(lp_gemm_kernel<T>, dim3(XcdMap::grid(m, Mt, Nt)), dim3(LP_THREADS), 0, s, a);
+  if (lp_small(N, mb)) launch_lp<T, LpSmall>(a, s);
+  else launch_lp<T, LpBig>(a, s);
 }
 
 // Xt (N x mb) = L^-1 src in the handle's low precision with FP32 accumulation;

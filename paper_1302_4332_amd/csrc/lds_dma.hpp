@@ -50,13 +50,16 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Wait until at most n whole stages of L loads each are in flight (n <= 3).
-template <int L>
+// Wait until at most n whole stages of L loads each are in flight (n <= M; M L <= 63).
+template <int L, int M = 3>
 __device__ __forceinline__ void wait_stages(int n) {
-  if (n <= 0) wait_vmcnt<0>();
-  else if (n == 1) wait_vmcnt<L>();
-  else if (n == 2) wait_vmcnt<2 * L>();
-  else wait_vmcnt<3 * L>();
+  static_assert(M * L <= 63, "vmcnt");
+  if constexpr (M > 0) {
+    if (n < M) wait_stages<L, M - 1>(n);
+    else wait_vmcnt<M * L>();
+  } else {
+    wait_vmcnt<0>();
+  }
 }
 
 }  // namespace gls

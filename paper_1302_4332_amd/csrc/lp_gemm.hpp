@@ -80,21 +80,37 @@ template <> struct LpMfma<__bf16> {
 // Requires 16-byte aligned A and B, lda and ldb multiples of 8 elements, K a
 // multiple of 32 and lane offsets within a tile below 2^32 bytes (the callers
 // pad every operand to N, a multiple of 256).
-constexpr int LP_BM = 256, LP_BN = 128, LP_RB = 64, LP_THREADS = 512, LP_STAGES = 3;
+//
+// Blocks of few samples or SNPs have few such tiles, and one takes 1.9 us of FP32
+// matrix time a stage on its compute unit (a block of 400 SNPs at n = 300 took 77
+// us a solve).  They take 64 x 64 tiles instead: four waves of 32 x 32, a ring of
+// six 8 KB stages, three workgroups to a compute unit.  Every element sums the
+// same k in the same order, so the choice does not show in the results.
+template <int BM_, int BN_, int NWI_, int NWJ_, int NS_, int WG_>
+struct LpTile {
+  static constexpr int BM = BM_, BN = BN_;         // rows of A, columns of B
+  static constexpr int NWI = NWI_, NWJ = NWJ_;     // waves along them
+  static constexpr int NS = NS_, WG = WG_;         // stages, workgroups per compute unit
+  static constexpr int THREADS = 64 * NWI * NWJ;
+};
+using LpBig = LpTile<256, 128, 4, 2, 3, 2>;
+using LpSmall = LpTile<64, 64, 2, 2, 6, 3>;
+constexpr int LP_BM = LpBig::BM, LP_BN = LpBig::BN, LP_RB = 64;
 
 __device__ __forceinline__ int lp_swz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
 
-template <typename T>
-__global__ __launch_bounds__(LP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 8)))
+template <typename T, typename C>
+__global__ __launch_bounds__(C::THREADS) __attribute__((amdgpu_waves_per_eu(C::WG * C::THREADS / 256, 8)))
 void lp_gemm_kernel(LpArgs g) {
-  constexpr int BM = LP_BM, BN = LP_BN, RB = LP_RB, NW = LP_THREADS / 64, NS = LP_STAGES;
+  constexpr int BM = C::BM, BN = C::BN, RB = LP_RB, NW = C::THREADS / 64, NS = C::NS;
+  constexpr int WTM = BM / C::NWI, WTN = BN / C::NWJ, FA = WTM / 16, FB = WTN / 16;   // a wave's block, in 16 x 16
   constexpr int CPR = RB / 16;               // 16-byte chunks per LDS row
   constexpr int RPI = 1024 / RB;             // rows per 1 KB load instruction
   constexpr int BKE = RB / (int)sizeof(T);   // k per stage
   constexpr int STAGE = (BM + BN) * RB;      // bytes
   constexpr int NLD = (BM + BN) / RPI / NW;  // load instructions per wave and stage
-  static_assert(NLD * RPI * NW == BM + BN && BM % RPI == 0 && BM == 4 * 64 && BN == 2 * 64 && NW == 8, "tile split");
-  static_assert(RB == 64 && NS * STAGE <= 80 * 1024, "two workgroups per compute unit");
+  static_assert(NLD * RPI * NW == BM + BN && BM % RPI == 0, "tile split");
+  static_assert(RB == 64 && C::WG * NS * STAGE <= 160 * 1024, "workgroups per compute unit");
   __shared__ __align__(1024) char smem[NS * STAGE];
 
   int ti, tj;
@@ -111,7 +127,7 @@ void lp_gemm_kernel(LpArgs g) {
   const int nk = (khi + BKE - 1) / BKE;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wi = wave & 3, wj = wave >> 2;
+  const int wi = wave % C::NWI, wj = wave / C::NWI;
 
   // loader: instruction q of this wave fills stage rows RPI (q NW + wave) ..
   // + RPI - 1, all of A's tile (rows i0..) or all of B's (columns j0..; columns
@@ -142,51 +158,56 @@ void lp_gemm_kernel(LpArgs g) {
   };
 
   // fragment offsets within a stage: lane group lane >> 4 reads chunk lane >> 4 of its row
-  int offa[4], offb[4];
+  int offa[FA], offb[FB];
+  const int ck = lane >> 4;
 #pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    const int ra = wi * 64 + f * 16 + (lane & 15), rb = BM + wj * 64 + f * 16 + (lane & 15);
-    const int c = lane >> 4;
-    offa[f] = ra * RB + 16 * (c ^ lp_swz(ra));
-    offb[f] = rb * RB + 16 * (c ^ lp_swz(rb));
+  for (int f = 0; f < FA; ++f) {
+    const int ra = wi * WTM + f * 16 + (lane & 15);
+    offa[f] = ra * RB + 16 * (ck ^ lp_swz(ra));
+  }
+#pragma unroll
+  for (int f = 0; f < FB; ++f) {
+    const int rb = BM + wj * WTN + f * 16 + (lane & 15);
+    offb[f] = rb * RB + 16 * (ck ^ lp_swz(rb));
   }
 
-  f4_t acc[4][4];   // [column block][row block], transposed 16 x 16 products
+  f4_t acc[FB][FA];   // [column block][row block], transposed 16 x 16 products
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < FB; ++b)
 #pragma unroll
-    for (int a = 0; a < 4; ++a) acc[b][a] = f4_t{0.f, 0.f, 0.f, 0.f};
+    for (int a = 0; a < FA; ++a) acc[b][a] = f4_t{0.f, 0.f, 0.f, 0.f};
 
   for (int q = 0; q < NS - 1; ++q)
     if (q < nk) issue(q);
   for (int it = 0; it < nk; ++it) {
-    wait_stages<NLD>(min(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
-    __syncthreads();                              // ... and every wave's; stage (it - 1) % NS is free
+    wait_stages<NLD, NS - 2>(min(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
+    __syncthreads();                                      // ... and every wave's; stage (it - 1) % NS is free
     if (it + NS - 1 < nk) issue(it + NS - 1);
     const char* st = smem + (it % NS) * STAGE;
-    uint4 fa[4], fb[4];
+    uint4 fa[FA], fb[FB];
+    // (the two blocks' reads in turn)
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      fa[f] = *reinterpret_cast<const uint4*>(st + offa[f]);
-      fb[f] = *reinterpret_cast<const uint4*>(st + offb[f]);
+    for (int f = 0; f < (FA > FB ? FA : FB); ++f) {
+      if (f < FA) fa[f] = *reinterpret_cast<const uint4*>(st + offa[f]);
+      if (f < FB) fb[f] = *reinterpret_cast<const uint4*>(st + offb[f]);
     }
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < FB; ++b)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) acc[b][a] = LpMfma<T>::mma(fb[b], fa[a], acc[b][a]);
+      for (int a = 0; a < FA; ++a) acc[b][a] = LpMfma<T>::mma(fb[b], fa[a], acc[b][a]);
   }
 
-  // acc[b][a][t] = C[i0 + wi 64 + 16 a + lane % 16][j0 + wj 64 + 16 b + 4 (lane / 16) + t]
+  // acc[b][a][t] = C[i0 + wi WTM + 16 a + lane % 16][j0 + wj WTN + 16 b + 4 (lane / 16) + t]
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
+  for (int b = 0; b < FB; ++b) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int j = j0 + wj * 64 + b * 16 + 4 * (lane >> 4) + t;
+      const int j = j0 + wj * WTN + b * 16 + 4 * (lane >> 4) + t;
       if (j >= g.ncols) continue;
       const double cs = g.cscale[j];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int i = i0 + wi * 64 + a * 16 + (lane & 15);
+      for (int a = 0; a < FA; ++a) {
+        const int i = i0 + wi * WTM + a * 16 + (lane & 15);
         if (i >= g.mvalid) continue;
         double v = cs * (double)acc[b][a][t];
         if (g.beta != 0.0) v += g.beta * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
