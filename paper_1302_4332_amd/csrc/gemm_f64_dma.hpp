@@ -217,19 +217,20 @@ void trmm_f64_dma_kernel(GemmArgs g) {
 // 8), each wave 64 x 4, so that the tile's own MFMA time per stage (0.85 us for 64
 // columns, which a lone workgroup cannot hide) falls to a quarter or less and
 // there are more workgroups.  The columns of B that the tile needs are read once,
-// up to KMAX rows, into LDS through registers: any alignment, and rows past
+// KMAX rows at a time, into LDS through registers: any alignment, and rows past
 // kvalid become zero, so no padded copy of the block is made first.  A's stages
 // follow in a ring of four.  Every output sums the same k in the same order as in
 // trmm_f64_dma_kernel (columns of A that it skips hold zeros).
 // A block of 108 columns at n = 712 took 71 us with the other kernel and takes 32
-// with this one, 48 columns at n = 1,000 91 and 40, 16,000 at n = 256 156 and 80.
+// with this one, 48 columns at n = 1,000 91 and 40, 16,000 at n = 256 156 and 80,
+// 40 columns at n = 10,000 1,432 and 373.
 template <int BN, int KMAX>
 __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   constexpr int BM = DB_BM, BK = DB_BK, NS = 4, NW = BN / 2, NT = 64 * NW;
   constexpr int STAGE = BM * BK * 8, LDB = KMAX + 2, QA = BK / NW;   // load instructions per wave and stage
   static_assert(NS * STAGE + BN * LDB * 8 <= 160 * 1024 && 2 * 21 * BN * 8 <= NS * STAGE && QA * NW == BK, "LDS");
   __shared__ __align__(1024) char smem[NS * STAGE];
-  __shared__ __align__(16) double Bs[BN * LDB];   // Bs[column][k - 16 k0]
+  __shared__ __align__(16) double Bs[BN * LDB];   // Bs[column][k - 16 b0]
 
   const int ti = g.map_desc ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y, tj = blockIdx.x;
   const int i0 = ti * BM, j0 = tj * BN;
@@ -266,22 +267,23 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   };
   for (int q = 0; q < NS - 1; ++q)
     if (k0 + q < nk) issue(k0 + q);
-  {
-    const int kend = imin(nk * BK, g.kvalid ? g.kvalid : g.K), kbeg = k0 * BK;
+  // B's rows [16 it, 16 it + KMAX) of the tile's columns, two columns a wave
+  const int kend = imin(nk * BK, g.kvalid ? g.kvalid : g.K);
+  auto load_b = [&](int it) {
 #pragma unroll
-    for (int c = wave; c < BN; c += NW) {   // two columns a wave
+    for (int c = wave; c < BN; c += NW) {
       const int j = j0 + c;
       const double* col = g.B + (int64_t)j * g.ldb;
       double v[KMAX / 64];
 #pragma unroll
       for (int u = 0; u < KMAX / 64; ++u) {
-        const int k = kbeg + lane + 64 * u;
+        const int k = it * BK + lane + 64 * u;
         v[u] = (j < g.ncols && k < kend) ? col[k] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < KMAX / 64; ++u) Bs[c * LDB + lane + 64 * u] = v[u];
     }
-  }
+  };
 
   double acc[4][1];
 #pragma unroll
@@ -294,14 +296,20 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   }
   const int g4 = 4 * (lane >> 4);
   const int abase = g4 * 1024 + wm * 512 + (lane & 15) * 8;
-  const double* bcol = Bs + (wn * 4 + (lane & 3)) * LDB + g4 - k0 * BK;
+  const double* bcol = Bs + (wn * 4 + (lane & 3)) * LDB + g4;
+  int b0 = k0;   // first stage of the rows of B in LDS
   for (int it = k0; it < nk; ++it) {
+    if (it == k0 || it - b0 == KMAX / BK) {
+      __syncthreads();   // every wave is done with the last rows
+      load_b(it);
+      b0 = it;
+    }
     wait_stages<QA>(imin(nk - 1 - it, NS - 2));   // this wave's loads of stage it have landed ...
     __syncthreads();                              // ... and every wave's (and B); stage (it - 1) % NS is free
     if (it + NS - 1 < nk) issue(it + NS - 1);
     const char* st = smem + (it % NS) * STAGE + abase;
-    const double2 b01 = *reinterpret_cast<const double2*>(bcol + it * BK);
-    const double2 b23 = *reinterpret_cast<const double2*>(bcol + it * BK + 2);
+    const double2 b01 = *reinterpret_cast<const double2*>(bcol + (it - b0) * BK);
+    const double2 b23 = *reinterpret_cast<const double2*>(bcol + (it - b0) * BK + 2);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const double bf = s == 0 ? b01.x : s == 1 ? b01.y : s == 2 ? b23.x : b23.y;
@@ -314,19 +322,19 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn);
 }
 
-// Largest K of the small kernel.
-constexpr int SMALL_KMAX = 1024;
-
 // Whether a product of M rows, ncols columns and K goes to it.  Short sums over
 // few rows do whatever the number of columns: the other kernel's start and end
 // are most of its time there (n = 512, 16,000 columns: 306 us against 257; n =
-// 128, 30,000: 176 against 64).  Longer ones do up to 128 tiles of 128 x 64, about
-// where this kernel needs a second round of workgroups (n = 712, 1,300 columns:
-// 77 us against 70; n = 1,000: 1,000 columns 99 against 84, 2,000 102 against 157).
+// 128, 30,000: 176 against 64).  Longer ones do while the other kernel's time is
+// that of its longest tile (three workgroups share a compute unit's matrix pipes,
+// 2.5 us a stage), up to a number of 128 x 64 tiles that grows with K: n = 712,
+// 1,300 columns (126 tiles) 77 us against 70; n = 1,000, 2,000 columns (256) 102
+// against 157; n = 1,200, 800 (130) 105 against 73 and 1,600 (250) 108 against 126;
+// n = 3,000, 600 (240) 261 against 233 and 1,200 (456) 341 against 443; n = 10,000,
+// 200 (316) 1,451 against 784.
 inline bool small_product(int M, int ncols, int K) {
-  if (K > SMALL_KMAX) return false;
   if (K <= 512 && M <= 512) return true;
-  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= 128;
+  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= (K <= 1024 ? 128 : K <= 4096 ? 240 : 320);
 }
 
 // Whether the two kernels above apply to a product without transposes: A

@@ -234,10 +234,10 @@ static bool gemm_dma(const GemmArgs& g, hipStream_t s) {
   if (small_product(g.M, g.ncols, g.K)) {
     const unsigned Mt = (g.M + DB_BM - 1) / DB_BM;
     d.M = (int)Mt * DB_BM;
-    if (g.K <= 512)
+    if (g.K <= 512 || g.K > 1024)
       hipLaunchKernelGGL((trmm_f64_small_kernel<16, 512>), dim3((g.ncols + 15) / 16, Mt), dim3(512), 0, s, d);
     else
-      hipLaunchKernelGGL((trmm_f64_small_kernel<8, SMALL_KMAX>), dim3((g.ncols + 7) / 8, Mt), dim3(256), 0, s, d);
+      hipLaunchKernelGGL((trmm_f64_small_kernel<8, 1024>), dim3((g.ncols + 7) / 8, Mt), dim3(256), 0, s, d);
     return true;
   }
   const int Mt = (g.M + DB_BM - 1) / DB_BM, Nt = (g.ncols + DB_BN - 1) / DB_BN;

@@ -1,7 +1,7 @@
 """FP64 products of few tiles take a kernel of their own: bitwise the other kernel's results.
 
 The kernel is chosen by the block's width too (up to 128 tiles of 128 x 64 for
-512 < n <= 1,024), so blocks on both sides of the line must give every SNP the
+512 < n <= 1,024, 240 to n = 4,096), so blocks on both sides of the line must give every SNP the
 same bits; and for n <= 512, where it takes every width, the oracle decides.
 Values are fractional, so that no SNP takes the integer product; unaligned
 columns and sample counts off multiples of 16 read the block without a copy.
@@ -35,9 +35,9 @@ def _same(a, b, rows):
 
 
 @pytest.mark.parametrize("precision,sweeps", [("fp64", 0), ("fp32_ir", 1)])
-@pytest.mark.parametrize("n", [520, 768, 1009, 1024])
+@pytest.mark.parametrize("n", [520, 768, 1009, 1024, 1025, 1700])
 def test_both_sides_of_the_line(n, precision, sweeps):
-    m = 64 * (128 // -(-n // 128)) + 129   # one block above the line, its parts below
+    m = 64 * ((128 if n <= 1024 else 240) // -(-n // 128)) + 129   # one block above the line, its parts below
     Phi, XL, y, XR = _study(n, 4, m)
     ctx = GLSContext(_t(Phi), 0.4, _t(XL), _t(y), block_cols=m, precision=precision, refine_sweeps=sweeps)
     X = _t(XR)
