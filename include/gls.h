@@ -72,7 +72,7 @@ typedef enum {
 typedef enum {
   GLS_FP64 = 0,     /* plain FP64 MFMA; a SNP whose values are all whole numbers of
                        magnitude at most 127 (dosages) takes the product of
-                       GLS_INT8_EMU if n > 256 and M's diagonal spans a factor
+                       GLS_INT8_EMU if n > 512 and M's diagonal spans a factor
                        of at most 256                                            */
   GLS_FP32_IR = 1,  /* FP32 MFMA bulk + FP64 residual refinement sweeps          */
   GLS_FP16_IR = 2,  /* FP16 MFMA (power-of-two column scaling) + FP64 refinement */

@@ -58,9 +58,11 @@ int64_t padded_n(int64_t n) { return (n + NPAD - 1) / NPAD * NPAD; }
 static_assert(NPAD % NB_LEAF == 0 && NPAD % LP_BM == 0 && NPAD % OZ_BM == 0 && NPAD % DB_BM == 0 && NPAD % 64 == 0,
               "the row padding must be a multiple of every row tile");
 
-// FP64 handles look for SNPs of whole numbers from this padded sample count on (see OZ_MIN_N's use in the plan): the
-// integer product of such SNPs needs L^-1 sliced at setup and a packed copy of each block.
-constexpr int64_t OZ_MIN_N = 512;
+// FP64 handles look for SNPs of whole numbers from this padded sample count on: the integer product of such SNPs needs
+// L^-1 sliced at setup (three launches) and a packed copy of each block, and below it FP64 blocks take two launches.
+// With 512 instead, n = 300, 20 SNPs 18 -> 23 us, n = 500, 300 SNPs 24 -> 23, n = 512, 2,000 SNPs 33 -> 27 and 6,000
+// 90 -> 50, and a study of 512 samples and 2,048 SNPs 302 -> 323 us.
+constexpr int64_t OZ_MIN_N = 768;
 
 // Nodes of the factorization of at least this many rows and columns form their products on the integer matrix cores
 // (crt_i8.hpp).  The fifteen products grow with the node's cube, the conversions with its square: at 5,000 a product
@@ -1350,6 +1352,10 @@ static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w,
 }
 
 static void launch_whole(const OzArgs& a, hipStream_t s) {
+  if (a.Mt * ((a.ncols + OZS_BN - 1) / OZS_BN) <= OZS_TILES) {
+    hipLaunchKernelGGL(ozaki_i8_small_kernel, dim3((a.ncols + OZS_BN - 1) / OZS_BN, a.Mt), dim3(OZS_THREADS), 0, s, a);
+    return;
+  }
   GemmArgs m{};
   m.map_gm = OZ_MAP_GM;
   m.map_gn = OZ_MAP_GN;

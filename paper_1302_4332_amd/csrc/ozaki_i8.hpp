@@ -440,4 +440,123 @@ void ozaki_i8_kernel(OzArgs g) {
   }
 }
 
+// The same product, bitwise, for few SNPs: 32 rows x 64 SNPs per workgroup, eight
+// waves of a 16-row strip each (wave & 1) that share the sum over k four ways
+// (every fourth k block), so that a row tile's chain of stages is a quarter as
+// long and there are no stage barriers: a wave reads its fragments straight from
+// memory, the next block's ahead of this one's MFMAs.  The int32 sums are exact, so
+// adding the four in LDS in any order gives the same integers; the FP64 steps are
+// those of ozaki_i8_kernel.  Up to 512 tiles (two
+// rounds of workgroups): n = 2,500, 64 SNPs 51 -> 29 us a block, n = 6,000, 20 SNPs
+// 96 -> 51, n = 12,000, 60 SNPs 216 -> 154; beyond, the larger tiles' fewer reads
+// win (n = 6,000, 200 SNPs, 752 tiles: 107 us against 120).
+constexpr int OZS_BN = 64, OZS_THREADS = 512, OZS_SPLIT = 4, OZS_TILES = 512;
+
+__global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
+  constexpr int S = OZ_SLICES, FC = OZS_BN / 16, QC = 10;
+  static_assert(2 * OZS_SPLIT * 64 == OZS_THREADS && FC == OZS_SPLIT, "a wave forms one 16 x 16 block at the end");
+  __shared__ int sums[2 * S * FC * 256];           // [strip][digit][SNP group][element][lane]
+  __shared__ double red[2 * QC * OZS_BN];
+  __shared__ int any;
+  const int ti = gridDim.y - 1 - blockIdx.y, tj = blockIdx.x;
+  const int j0 = tj * OZS_BN, jb0 = tj * FC;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ws = wave & 1, wk = wave >> 1;
+  if (threadIdx.x == 0) any = g.flags.at == nullptr;
+  __syncthreads();
+  if (g.flags.at && threadIdx.x < OZS_BN && j0 + (int)threadIdx.x < g.ncols &&
+      !g.flags.flagged(j0 + threadIdx.x, g.ncols))
+    any = 1;
+  for (int e = threadIdx.x; e < 2 * S * FC * 256; e += OZS_THREADS) sums[e] = 0;
+  __syncthreads();
+  if (!any) return;
+
+  const int nk = ti * OZ_BM / OZ_TM + 1;
+  const int8_t* A = g.A + (int64_t)(nk - 1) * nk / 2 * OZ_ATILE + ((ti % (OZ_TM / OZ_BM)) * OZ_STRIPS + ws) * (S * OZ_UNIT) +
+                    16 * lane;
+  const uint8_t* B = g.B + 16 * lane;
+  i4_t a[2][S], b[2][FC];
+  auto load = [&](int kb, int buf) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) a[buf][s] = *reinterpret_cast<const i4_t*>(A + (int64_t)kb * OZ_ATILE + s * OZ_UNIT);
+#pragma unroll
+    for (int c = 0; c < FC; ++c)
+      b[buf][c] = *reinterpret_cast<const i4_t*>(B + ((int64_t)kb * g.Jb + min(jb0 + c, g.Jb - 1)) * OZ_UNIT);
+  };
+  i4_t acc[S][FC];
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int c = 0; c < FC; ++c) acc[s][c] = i4_t{0, 0, 0, 0};
+  auto mma = [&](int buf) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int c = 0; c < FC; ++c)
+        acc[s][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[buf][s], b[buf][c], acc[s][c], 0, 0, 0);
+  };
+  if (wk < nk) load(wk, 0);
+  for (int kb = wk; kb < nk; kb += 2 * OZS_SPLIT) {
+    if (kb + OZS_SPLIT < nk) load(kb + OZS_SPLIT, 1);
+    mma(0);
+    if (kb + 2 * OZS_SPLIT < nk) load(kb + 2 * OZS_SPLIT, 0);
+    if (kb + OZS_SPLIT < nk) mma(1);
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int c = 0; c < FC; ++c)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) atomicAdd(&sums[((ws * S + s) * FC + c) * 256 + t * 64 + lane], acc[s][c][t]);
+  __syncthreads();
+
+  // wave (strip ws, SNP group wk)
+  const int i = ti * OZ_BM + ws * 16 + 4 * (lane >> 4);
+  const int4 e = *reinterpret_cast<const int4*>(g.ex + i);
+  double v[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int* at = sums + (ws * S * FC + wk) * 256 + t * 64 + lane;
+    double x = (double)at[0];
+#pragma unroll
+    for (int s = 1; s < S; ++s) x = fma(x, 1.0 / 256.0, (double)at[s * FC * 256]);
+    v[t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 55 + 8 * (S - 1));
+  }
+  if (g.red_q == 0) {
+    const int j = j0 + wk * 16 + (lane & 15);
+    if (j >= g.ncols || (g.flags.at && g.flags.flagged(j, g.ncols))) return;
+    double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)j * g.ldc);
+    o[0] = double2{v[0], v[1]};
+    o[1] = double2{v[2], v[3]};
+    return;
+  }
+  for (int q0 = 0; q0 < g.red_q; q0 += QC) {
+    const int qn = min(QC, g.red_q - q0);
+    __syncthreads();
+    for (int qq = 0; qq < qn; ++qq) {
+      const int q = q0 + qq;
+      const bool norm = q == g.red_q - 1;
+      double w[4] = {0.0, 0.0, 0.0, 0.0};
+      if (!norm) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) w[t] = g.W[(int64_t)(i + t) + (int64_t)q * g.ldw];
+      }
+      double x = 0.0;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x += v[t] * (norm ? v[t] : w[t]);
+      x += __shfl_xor(x, 16, 64);
+      x += __shfl_xor(x, 32, 64);
+      if (lane < 16) red[(ws * QC + qq) * OZS_BN + wk * 16 + lane] = x;
+    }
+    __syncthreads();
+    for (int f = threadIdx.x; f < qn * OZS_BN; f += OZS_THREADS) {
+      const int qq = f / OZS_BN, jl = f % OZS_BN;
+      if (j0 + jl < g.ncols)
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
+            red[qq * OZS_BN + jl] + red[(QC + qq) * OZS_BN + jl];
+    }
+  }
+}
+
 }  // namespace gls

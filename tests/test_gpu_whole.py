@@ -1,10 +1,10 @@
 """SNPs of whole numbers on the integer matrix cores, beside SNPs that are not.
 
-A GLS_FP64 handle with n > 256 samples gives every SNP whose values are whole
+A GLS_FP64 handle with n > 512 samples gives every SNP whose values are whole
 numbers of magnitude at most 127 to the int8-slice product and every other one
 to the FP64 product.  Checked at the edges of both products' tiles (32 rows and
 192 SNPs; 128 rows and 64 SNPs), of the 16-SNP groups and of the 256-row
-padding, for aligned and unaligned columns:
+padding, for aligned and unaligned columns, and on both sides of the line between the integer product's two kernels:
 
 - every output against the CPU oracle at the plain-FP64 bar (1e-10);
 - each SNP's outputs bitwise the same alone and in the mixed block;
@@ -54,7 +54,7 @@ def _mix(XR):
 
 
 @pytest.mark.parametrize("n,p,mb", [
-    (257, 4, 1), (320, 1, 15), (448, 3, 17), (511, 20, 191), (512, 4, 192), (513, 2, 193), (641, 8, 400), (1000, 4, 64),
+    (257, 4, 1), (320, 1, 15), (448, 3, 17), (511, 20, 191), (512, 4, 192), (513, 2, 193), (641, 8, 400), (1000, 4, 64), (1025, 4, 1089),
 ])
 def test_mixed_block(n, p, mb):
     Phi, XL, y, XR = _study(n, p, mb)
@@ -124,6 +124,23 @@ def test_gradient_of_a_mixed_study(n, bc):
         grads.append([g.cpu().numpy() for g in torch.autograd.grad(t2_loss(*out), (yt, Xt, h2))])
     for a, b in zip(*grads):
         assert np.abs(a - b).max() <= 1e-9 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("n,p", [(520, 20), (1000, 4), (1281, 1)])
+def test_few_snps_and_many(n, p):
+    """Blocks of up to 512 tiles of 32 x 64 share the sum over k; larger ones do not: the same bits."""
+    m = 64 * (512 // -(-n // 32)) + 100
+    Phi, XL, y, XR = _study(n, p, m)
+    for precision in ("fp64", "int8_emu"):
+        ctx = GLSContext(_t(Phi), 0.4, _t(XL) if p > 1 else None, _t(y), block_cols=m, precision=precision)
+        call = ctx.block if precision == "fp64" else ctx.block_u8
+        X = _t(XR if precision == "fp64" else XR.astype(np.uint8))
+        big = as_numpy(call(X))
+        for j0, j1 in ((0, 1), (60, 125), (m - 300, m)):
+            part = as_numpy(call(X[j0:j1]))
+            for k in ("b", "sigma2", "v", "status"):
+                assert np.array_equal(big[k][j0:j1].view(np.uint8), part[k].view(np.uint8)), k
+        ctx.close()
 
 
 @pytest.mark.parametrize("fmt", ["f64", "u8", "u2"])
