@@ -88,15 +88,26 @@ __device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const doubl
 // compiler is held to six waves per SIMD (76 VGPRs, no spills).  With 99 VGPRs
 // (two workgroups per compute unit) the same instruction stream ran 6-8%
 // slower at n = 10,000 and n = 20,000.
+//
+// With 128 x 32 tiles (eight waves of 64 x 8, 20 KB a stage) a product of few
+// tiles has twice as many and its longest one ends sooner: a single workgroup
+// on a compute unit takes 1.45 us a stage of 64 columns, whose MFMAs take 0.92.
 constexpr int DB_BM = 128, DB_BN = 64, DB_BK = 16, DB_THREADS = 512, DB_STAGES = 2;
+// Products of up to this many 128 x 64 tiles, what the chip holds at once, take tiles of 128 x 32.  n = 3,325, 998
+// columns (416 tiles) 331 -> 237 us a block, n = 5,000, 600 (400) 535 -> 436, n = 10,000, 300 (395) 1,432 -> 887, n = 2,000,
+// 3,000 (752) 287 -> 262; beyond, A's columns are read twice as often for it: n = 5,000, 1,500 (960) 711 -> 776, 4,096
+// (2,560) 1,715 -> 1,900.
+constexpr int DB_NARROW_TILES = 768;
 
+template <int BN>
 __global__ __launch_bounds__(DB_THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void trmm_f64_dma_kernel(GemmArgs g) {
-  constexpr int BM = DB_BM, BN = DB_BN, BK = DB_BK, NS = DB_STAGES, NW = DB_THREADS / 64;
+  constexpr int BM = DB_BM, BK = DB_BK, NS = DB_STAGES, NW = DB_THREADS / 64;
   constexpr int WGM = BM / 64, WTN = BN / (NW / WGM), FC = WTN / 4;
   constexpr int ASZ = BM * BK * 8, BSZ = BN * BK * 8, STAGE = ASZ + BSZ;
   constexpr int AINS = ASZ / 1024;   // load instructions of A per stage, one k-column each
-  static_assert(BM == 128 && BK == 16 && FC == 4 && AINS == 2 * NW && BSZ == NW * 1024, "tile split");
+  constexpr int BINS = BSZ / 1024;   // load instructions of B per stage, eight columns each
+  static_assert(BM == 128 && BK == 16 && 16 * FC == BN && AINS == 2 * NW && BINS <= NW, "tile split");
   static_assert(2 * 21 * BN * 8 <= NS * STAGE, "the ring holds the fused sums (p + 1 <= 21)");
   __shared__ __align__(1024) char smem[NS * STAGE];
 
@@ -128,7 +139,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
   const int wm = wave % WGM, wn = wave / WGM;
 
   // loader: this wave issues instructions wave and wave + 8 (A's k-columns) and
-  // wave + 16 (B's columns 8 wave .. 8 wave + 7) of every stage
+  // wave + 16 (B's columns 8 wave .. 8 wave + 7, if the tile has them) of every stage
   uint32_t voff[3];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
@@ -152,7 +163,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
     const double* b = Bbase + kt;
     lds_load16_sv(a, voff[0], base + (uint32_t)(wave * 1024));
     lds_load16_sv(a, voff[1], base + (uint32_t)((NW + wave) * 1024));
-    lds_load16_sv(b, voff[2], base + (uint32_t)(ASZ + wave * 1024));
+    if (BINS == NW || wave < BINS) lds_load16_sv(b, voff[2], base + (uint32_t)(ASZ + wave * 1024));
   };
 
   double acc[4][FC];
@@ -325,16 +336,17 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
 // Whether a product of M rows, ncols columns and K goes to it.  Short sums over
 // few rows do whatever the number of columns: the other kernel's start and end
 // are most of its time there (n = 512, 16,000 columns: 306 us against 257; n =
-// 128, 30,000: 176 against 64).  Longer ones do while the other kernel's time is
-// that of its longest tile (three workgroups share a compute unit's matrix pipes,
-// 2.5 us a stage), up to a number of 128 x 64 tiles that grows with K: n = 712,
-// 1,300 columns (126 tiles) 77 us against 70; n = 1,000, 2,000 columns (256) 102
-// against 157; n = 1,200, 800 (130) 105 against 73 and 1,600 (250) 108 against 126;
-// n = 3,000, 600 (240) 261 against 233 and 1,200 (456) 341 against 443; n = 10,000,
-// 200 (316) 1,451 against 784.
+// 128, 30,000: 176 against 64).  Longer ones do while there are few tiles of
+// 128 x 64, so that the other kernel's time is that of its longest one.  Times of
+// a block, the tiles of 128 x 32 first: n = 1,100, 1,500 columns (216 tiles) 103
+// us against 100; n = 2,000, 500 (128) 97 against 92 and 800 (208) 101 against 145;
+// n = 3,000, 300 (120) 155 against 123 and 450 (192) 154 against 187; n = 5,000, 190
+// (120) 302 against 195 and 380 (240) 302 against 358; n = 10,000, 200 (316) 883 against
+// 733.  A study of 10,000 samples, whose setup has such products, takes 18.85 ms
+// with 128 for K = 1,280 too and 18.6 with 240.
 inline bool small_product(int M, int ncols, int K) {
   if (K <= 512 && M <= 512) return true;
-  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= (K <= 1024 ? 128 : K <= 4096 ? 240 : 320);
+  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= (K <= 1024 ? 128 : K <= 1280 ? 240 : K <= 8192 ? 128 : 320);
 }
 
 // Whether the two kernels above apply to a product without transposes: A

@@ -244,7 +244,12 @@ static bool gemm_dma(const GemmArgs& g, hipStream_t s) {
   }
   const int Mt = (g.M + DB_BM - 1) / DB_BM, Nt = (g.ncols + DB_BN - 1) / DB_BN;
   d.M = Mt * DB_BM;   // rows past mvalid are computed from A's padding and not stored
-  hipLaunchKernelGGL(trmm_f64_dma_kernel, dim3(XcdMap::grid(d, Mt, Nt)), dim3(DB_THREADS), 0, s, d);
+  if ((int64_t)Mt * Nt <= DB_NARROW_TILES) {
+    const int Nh = (g.ncols + DB_BN / 2 - 1) / (DB_BN / 2);
+    hipLaunchKernelGGL(trmm_f64_dma_kernel<DB_BN / 2>, dim3(XcdMap::grid(d, Mt, Nh)), dim3(DB_THREADS), 0, s, d);
+  } else {
+    hipLaunchKernelGGL(trmm_f64_dma_kernel<DB_BN>, dim3(XcdMap::grid(d, Mt, Nt)), dim3(DB_THREADS), 0, s, d);
+  }
   return true;
 }
 

@@ -1,7 +1,7 @@
 """FP64 products of few tiles take a kernel of their own: bitwise the other kernel's results.
 
 The kernel is chosen by the block's width too (up to 128 tiles of 128 x 64 for
-512 < n <= 1,024, 240 to n = 4,096), so blocks on both sides of the line must give every SNP the
+512 < n <= 1,024, 240 to n = 1,280, 128 beyond), and of the others those of up to 768 take narrower ones, so blocks on both sides of the line must give every SNP the
 same bits; and for n <= 512, where it takes every width, the oracle decides.
 Values are fractional, so that no SNP takes the integer product; unaligned
 columns and sample counts off multiples of 16 read the block without a copy.
@@ -44,6 +44,19 @@ def test_both_sides_of_the_line(n, precision, sweeps):
     big = as_numpy(ctx.block(X))
     for j0, j1 in ((0, 1), (5, 22), (64, 700), (m - 9, m)):
         j1 = min(j1, m)
+        _same(big, as_numpy(ctx.block(X[j0:j1])), slice(j0, j1))
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,p", [(1025, 20), (1700, 4), (2309, 2), (2560, 1)])
+def test_narrow_and_wide_tiles(n, p):
+    """Above 768 tiles of 128 x 64, the wide tiles; the parts take the narrow ones or the kernel of few tiles."""
+    m = 64 * (768 // -(-n // 128)) + 129
+    Phi, XL, y, XR = _study(n, p, m)
+    ctx = GLSContext(_t(Phi), 0.4, _t(XL) if p > 1 else None, _t(y), block_cols=m)
+    X = _t(XR)
+    big = as_numpy(ctx.block(X))
+    for j0, j1 in ((3, 4), (64, 1100), (31, m - 1), (m - 700, m)):
         _same(big, as_numpy(ctx.block(X[j0:j1])), slice(j0, j1))
     ctx.close()
 
