@@ -229,7 +229,8 @@ __device__ __forceinline__ double lane_value(double x, int k) {
 // LDS as 8 x 8 blocks of 16 x 16 and is factored panel by panel (16 columns); the
 // inverse is formed row block by row block behind it.
 //   Panel p: up to three waves, each with the 16 rows of the diagonal block in
-//     lanes 0..15 (factored by every wave alike, so none waits for another) and
+//     lanes 0..15 (factored by every wave alike, so none waits for another; the
+//     first wave stores them once all have loaded them) and
 //     48 of the rows below in the others, a row's 16 values in registers.  Step j
 //     scales column j by 1 / sqrt(pivot) and subtracts its products with
 //     L[k][j], read from lane k.  Rows 128..143 of each panel are the identity's:
@@ -292,15 +293,18 @@ __device__ __forceinline__ void leaf_st_acc(double* p, l4_t v, int lane) {
 // Panel waves that panel p needs for its rows below the diagonal block.
 __device__ __forceinline__ int leaf_panel_waves(int p) { return (LROWS - LT * (p + 1) + LPR - 1) / LPR; }
 
-// Panel p by wave `wave` of its panel waves.  Returns the first non-positive
-// pivot (1-based within the leaf) or 0.
-__device__ __forceinline__ int leaf_panel(double* S, int p, int wave, int lane) {
+// Panel p by wave `wave` of its panel waves: its rows below the diagonal block
+// are stored.  The block's own rows, in lanes 0..15 of every panel wave, stay in
+// x, their pivots in own: another wave may only now be loading them from LDS, so
+// they are stored by leaf_store_diag, past the next barrier.  Returns the first
+// non-positive pivot (1-based within the leaf) or 0.
+__device__ __forceinline__ int leaf_panel(double* S, int p, int wave, int lane, double (&x)[LT], double& own) {
   const int row = LT * p + (lane < LT ? lane : lane + LPR * wave);   // past the last row: a spare one, not stored
   double* P = S + (LT * p) * LD + min(row, LROWS);
-  double x[LT];
 #pragma unroll
   for (int k = 0; k < LT; ++k) x[k] = P[k * LD];
-  double d = lane_value(x[0], 0), own = 0.0;   // the pivot; lane j's own
+  double d = lane_value(x[0], 0);   // the pivot; lane j keeps its own
+  own = 0.0;
 #pragma unroll
   for (int j = 0; j < LT; ++j) {
     own = (lane == j) ? d : own;
@@ -328,12 +332,20 @@ __device__ __forceinline__ int leaf_panel(double* S, int p, int wave, int lane) 
   }
   const unsigned bads = (unsigned)__ballot(!(own > 0.0)) & 0xffffu;
   const int bad = bads ? LT * p + __ffs(bads) : 0;
-  if (lane < LT ? wave == 0 : row < LROWS) {   // the diagonal block's upper triangle is not read again
+  if (lane >= LT && row < LROWS) {
 #pragma unroll
     for (int k = 0; k < LT; ++k) P[k * LD] = x[k];
   }
-  if (wave == 0 && lane < LT) P[lane * LD] = sqrt(own);
   return bad;
+}
+
+// Panel p's diagonal block, by one of its panel waves (its upper triangle is not read again).
+__device__ __forceinline__ void leaf_store_diag(double* S, int p, int lane, const double (&x)[LT], double own) {
+  if (lane >= LT) return;
+  double* P = S + (LT * p) * LD + LT * p + lane;
+#pragma unroll
+  for (int k = 0; k < LT; ++k) P[k * LD] = x[k];
+  P[lane * LD] = sqrt(own);
 }
 
 // What waves other than the panel's do once panel p is final (wave w of n):
@@ -407,9 +419,13 @@ __global__ __launch_bounds__(512) void leaf_potrf_trtri_kernel(double* __restric
   }
   __syncthreads();
   int bad = 0;   // meaningful in wave 0
-  if (wave < leaf_panel_waves(0)) bad = leaf_panel(S, 0, wave, lane);
+  double x[LT], own = 0.0;   // a panel wave's values of its last panel
+#pragma unroll
+  for (int k = 0; k < LT; ++k) x[k] = 0.0;
+  if (wave < leaf_panel_waves(0)) bad = leaf_panel(S, 0, wave, lane, x, own);
   __syncthreads();
   for (int p = 0; p < LNB - 1; ++p) {
+    if (wave == 0) leaf_store_diag(S, p, lane, x, own);   // read from the next barrier on
     const int bi = p + 1 + wave;
     if (bi < LNB) {   // A[i][p + 1] -= L[i][p] L[p + 1][p]^T
       double* C = leaf_blk(S, bi, p + 1);
@@ -420,13 +436,15 @@ __global__ __launch_bounds__(512) void leaf_potrf_trtri_kernel(double* __restric
     __syncthreads();
     const int np = leaf_panel_waves(p + 1);
     if (wave < np) {
-      const int b = leaf_panel(S, p + 1, wave, lane);
+      const int b = leaf_panel(S, p + 1, wave, lane, x, own);
       if (bad == 0) bad = b;
     } else {
       leaf_behind(S, A, Ainv, ld, p, wave - np, LNB - np, lane);
     }
     __syncthreads();
   }
+  if (wave == 0) leaf_store_diag(S, LNB - 1, lane, x, own);
+  __syncthreads();
   leaf_behind(S, A, Ainv, ld, LNB - 1, wave, LNB, lane);
   if (wave == 0 && lane == 0 && bad != 0 && *info == 0) *info = row0 + bad;
 }
