@@ -70,17 +70,19 @@ typedef enum {
 
 /* Arithmetic of the per-block triangular solve (everything else is FP64). */
 typedef enum {
-  GLS_FP64 = 0,     /* plain FP64 MFMA; a SNP whose values are all whole numbers of
-                       magnitude at most 127 (dosages) takes the product of
-                       GLS_INT8_EMU if n > 512 and M's diagonal spans a factor
-                       of at most 256                                            */
+  GLS_FP64 = 0,     /* plain FP64 MFMA; if n > 512 and M's diagonal spans a factor
+                       of at most 256, a SNP whose values are all whole numbers of
+                       magnitude at most 127 (dosages) takes exact int8 products
+                       with L^-1 in eight base-256 digits a row (2^-64 of the
+                       row's largest entry; entries down to 2^-10 of it exact)   */
   GLS_FP32_IR = 1,  /* FP32 MFMA bulk + FP64 residual refinement sweeps          */
   GLS_FP16_IR = 2,  /* FP16 MFMA (power-of-two column scaling) + FP64 refinement */
   GLS_BF16_IR = 3,  /* BF16 MFMA (power-of-two column scaling) + FP64 refinement */
   GLS_INT8_EMU = 4  /* dosage input only (the _u8 and _u2 entry points): the product
                        with L^-1 as seven exact int8 slice products on the integer
-                       matrix cores, combined in FP64 (FP64-level accuracy); FP64
-                       input on such a handle is treated as by GLS_FP64          */
+                       matrix cores, combined in FP64 (FP64-level accuracy: L^-1
+                       at 2^-56 of its row's largest entry); FP64 input on such a
+                       handle runs the plain FP64 product                        */
 } gls_precision;
 
 /* gls_opts.flags: keep Phi and the factor terms needed by the adjoint. */

@@ -160,9 +160,10 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
   pl->off_ub1 = take((size_t)n * bc);
   // Sliced L^-1 and its row exponents (under half of an N x N FP64 matrix).  L itself is read after setup only by
   // the refinement residual and the adjoint; without those its region is free and holds them.
-  pl->whole = pl->lp_bytes == 0 && (o->precision == GLS_INT8_EMU || N >= OZ_MIN_N);
-  if (pl->whole) {
-    const size_t at = align_up(oz_factor_bytes(N), 256), ex = sizeof(int) * (N + 1);
+  if (o->precision == GLS_INT8_EMU) pl->digits = OZ_DIGITS_EMU;
+  else if (pl->lp_bytes == 0 && N >= OZ_MIN_N) pl->digits = OZ_DIGITS_FP64;
+  if (pl->digits) {
+    const size_t at = align_up(oz_factor_bytes(N, pl->digits), 256), ex = sizeof(int) * (N + 1);
     if (o->flags & GLS_KEEP_FOR_GRAD) pl->off_sl = take(at + ex);
     else pl->off_sl = pl->off_L;
     pl->off_ex = pl->off_sl + at;
@@ -748,14 +749,14 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
   if (sc) hipLaunchKernelGGL(unscale_factor_kernel, dim3(2048), dim3(256), 0, s, c->L, c->Linv, (int)N, (const double*)sc);
   c->ub[0] = reinterpret_cast<uint8_t*>(ws + pl.off_ub0);
   c->ub[1] = reinterpret_cast<uint8_t*>(ws + pl.off_ub1);
-  if (pl.whole) {
+  if (pl.digits) {
     c->sl = reinterpret_cast<int8_t*>(ws + pl.off_sl);
     c->ex = reinterpret_cast<int*>(ws + pl.off_ex);
     const unsigned T = (unsigned)(N / OZ_TM);
     hipLaunchKernelGGL(diagonal_range_kernel, dim3(1), dim3(1024), 0, s, Phi, ld_phi, (int)n, h2, c->ex + N);
     hipLaunchKernelGGL(row_max_kernel, dim3(T, (unsigned)((N + 255) / 256)), dim3(256), 0, s, c->Linv, (int)N, c->Xt);
-    hipLaunchKernelGGL(slice_factor_kernel, dim3(T, T), dim3(256), 0, s, c->Linv, (int)N, (const double*)c->Xt, c->ex,
-                       c->sl);
+    hipLaunchKernelGGL(pl.digits == OZ_DIGITS_FP64 ? slice_factor_kernel<OZ_DIGITS_FP64> : slice_factor_kernel<OZ_DIGITS_EMU>,
+                       dim3(T, T), dim3(256), 0, s, c->Linv, (int)N, (const double*)c->Xt, c->ex, c->sl);
   }
   c->x64 = reinterpret_cast<double*>(ws + pl.off_x64);
   if (pl.lp_bytes) {
@@ -1356,16 +1357,17 @@ static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w,
   else pack_units<OZ_F64>(c, X, ld, mb, true, w, s);
 }
 
+template <int S>
 static void launch_whole(const OzArgs& a, hipStream_t s) {
   if (a.Mt * ((a.ncols + OZS_BN - 1) / OZS_BN) <= OZS_TILES) {
-    hipLaunchKernelGGL(ozaki_i8_small_kernel, dim3((a.ncols + OZS_BN - 1) / OZS_BN, a.Mt), dim3(OZS_THREADS), 0, s, a);
+    hipLaunchKernelGGL(ozaki_i8_small_kernel<S>, dim3((a.ncols + OZS_BN - 1) / OZS_BN, a.Mt), dim3(OZS_THREADS), 0, s, a);
     return;
   }
   GemmArgs m{};
   m.map_gm = OZ_MAP_GM;
   m.map_gn = OZ_MAP_GN;
-  hipLaunchKernelGGL(ozaki_i8_kernel, dim3(XcdMap::grid(m, a.Mt, (a.ncols + OZ_BN - 1) / OZ_BN)), dim3(OZ_THREADS), 0,
-                     s, a);
+  hipLaunchKernelGGL(ozaki_i8_kernel<S>, dim3(XcdMap::grid(m, a.Mt, (a.ncols + oz_bn(S) - 1) / oz_bn(S))),
+                     dim3(OZ_THREADS), 0, s, a);
 }
 
 // The integer product: per-SNP sums into w.part8, or with Xt the product itself.
@@ -1389,7 +1391,8 @@ static void whole_product(Ctx* c, const WholeBlock& w, int mb, double* Xt, hipSt
     a.red_part = w.part8;
     a.red_q = c->p + 1;
   }
-  launch_whole(a, s);
+  if (c->plan.digits == OZ_DIGITS_FP64) launch_whole<OZ_DIGITS_FP64>(a, s);
+  else launch_whole<OZ_DIGITS_EMU>(a, s);
 }
 
 static void residual_fp64(Ctx* c, const double* X, int64_t ldx, int mb, hipStream_t s) {
@@ -1428,7 +1431,7 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
     WholeBlock w;
     {
       PhaseTimer t(c, PH_WHITEN, s);
-      if (c->plan.whole) {
+      if (whole_f64(c)) {
         w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
         pack_f64(c, XR, ld_xr, mb, &w, s);
         whole_product(c, w, mb, nullptr, s);
@@ -1489,14 +1492,14 @@ static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t 
 
 gls_status block_forward_u8(Ctx* c, int mb, const uint8_t* G, int64_t ldg, double* b, int64_t ld_b, double* s2,
                             double* v, int* st, hipStream_t s) {
-  if (c->plan.whole) return block_forward_whole<OZ_U8>(c, mb, G, ldg, b, ld_b, s2, v, st, s);
+  if (c->plan.digits) return block_forward_whole<OZ_U8>(c, mb, G, ldg, b, ld_b, s2, v, st, s);
   widen_u8(c, G, ldg, mb, s);
   return block_forward(c, mb, c->x64, c->N, b, ld_b, s2, v, st, s);
 }
 
 gls_status block_forward_u2(Ctx* c, int mb, const uint8_t* G2, int64_t ldg, double* b, int64_t ld_b, double* s2,
                             double* v, int* st, hipStream_t s) {
-  if (c->plan.whole) return block_forward_whole<OZ_U2>(c, mb, G2, ldg, b, ld_b, s2, v, st, s);
+  if (c->plan.digits) return block_forward_whole<OZ_U2>(c, mb, G2, ldg, b, ld_b, s2, v, st, s);
   widen_u2(c, G2, ldg, mb, s);
   return block_forward(c, mb, c->x64, c->N, b, ld_b, s2, v, st, s);
 }
@@ -1553,7 +1556,7 @@ static void recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, 
     }
   } else {
     WholeBlock w;
-    if (c->plan.whole) {   // the int8 operand in Xtb, which is written after X~
+    if (whole_f64(c)) {   // the int8 operand in Xtb, which is written after X~
       w = whole_block(c, c->Xtb, false, mb, (int)c->N);
       pack_f64(c, XR, ld_xr, mb, &w, s);
       whole_product(c, w, mb, c->Xt, s);

@@ -27,8 +27,8 @@ struct Plan {
   size_t off_Llp = 0, off_Blp = 0, off_R = 0, off_cs = 0, off_red = 0;
   // byte input
   size_t off_ub0 = 0, off_ub1 = 0, off_x64 = 0;
-  // SNPs of whole numbers: L^-1 sliced for the integer matrix cores
-  bool whole = false;
+  // SNPs of whole numbers: L^-1 sliced for the integer matrix cores into this many digits (0: no such route)
+  int digits = 0;
   size_t off_sl = 0, off_ex = 0;
   // adjoint (GLS_KEEP_FOR_GRAD)
   size_t off_Phi = 0, off_Lbar = 0, off_T1 = 0, off_T2 = 0, off_Xtb = 0, off_Xb = 0;
@@ -78,7 +78,7 @@ struct gls_ctx {
   // byte input
   uint8_t* ub[2] = {nullptr, nullptr};  // streaming staging, n x block_cols bytes
   double* x64 = nullptr;    // N x block_cols FP64: bytes widened, or a block copied with zero rows past n
-  int8_t* sl = nullptr;     // int8 slices of L^-1 (plan.whole; in L's region unless the handle keeps L)
+  int8_t* sl = nullptr;     // int8 slices of L^-1 (plan.digits; in L's region unless the handle keeps L)
   int* ex = nullptr;        // N row exponents of L^-1; [N]: the study qualifies (diagonal_range_kernel)
   // adjoint state (GLS_KEEP_FOR_GRAD)
   bool grad = false;
@@ -115,6 +115,10 @@ struct gls_ctx {
 namespace gls {
 
 using Ctx = gls_ctx;
+
+// FP64 columns that are whole numbers take the integer product (a GLS_INT8_EMU handle's FP64 input does not: its
+// factor is held in fewer digits, for the bytes that its caller chose it for).
+inline bool whole_f64(const Ctx* c) { return c->plan.digits != 0 && c->opts.precision == GLS_FP64; }
 
 enum { PH_WHITEN = 0, PH_RESIDUAL = 1, PH_SNP = 2, PH_BACKWARD = 3 };
 

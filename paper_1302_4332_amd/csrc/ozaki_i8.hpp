@@ -2,19 +2,24 @@
 // that are whole numbers (genotype dosages), held as FP64, bytes or packed
 // 2-bit codes.
 //
-// Each row i of L^-1 is rounded to a 56-bit fixed-point number and split into
-// seven signed base-256 digits (the slicing of Ozaki, Ogita, Oishi and Rump's
+// Each row i of L^-1 is rounded to an 8 S-bit fixed-point number and split into
+// S signed base-256 digits (the slicing of Ozaki, Ogita, Oishi and Rump's
 // error-free matrix product transformation, with balanced digits):
-//     L^-1[i, k] = 2^(e_i - 55) * sum_{s<7} a_s[i, k] * 256^s  +  r_ik,
-//     -128 <= a_s <= 127,  |r_ik| <= 2^(e_i - 56),  max_k |L^-1[i, k]| <= 0.99 * 2^e_i.
+//     L^-1[i, k] = 2^(e_i - 8 S + 1) * sum_{s<S} a_s[i, k] * 256^s  +  r_ik,
+//     -128 <= a_s <= 127,  |r_ik| <= 2^(e_i - 8 S),  max_k |L^-1[i, k]| <= 0.99 * 2^e_i.
 // Whole numbers x with |x| <= 127 are exact in int8, so
-//     (L^-1 X)[i, j] = sum_s 2^(e_i - 55) 256^s (a_s X)[i, j]   (+ r)
-// where each a_s X is an exact int32 sum (n * 128 * max|x| < 2^31).  The
-// rounding r is below 2^-55 of the row's largest entry, under FP64 rounding of
-// the result, and there is one FP64 rounding per digit instead of one per
-// sample.  Balanced digits carry eight bits each, so seven of them hold what
-// eight truncated 7-bit slices did (the same 2^-56 bound) with an eighth less
-// work.
+//     (L^-1 X)[i, j] = sum_s 2^(e_i - 8 S + 1) 256^s (a_s X)[i, j]   (+ r)
+// where each a_s X is an exact int32 sum (n * 128 * max|x| < 2^31), and there is
+// one FP64 rounding per digit instead of one per sample.  The rounding r is
+// relative to the row's largest entry (2^(e_i - 1) at most below it), not to the
+// entry itself:
+//   S = 8 (FP64 handles): entries down to 2^-10 of 2^e_i are exact, any other is
+//     off by 2^-64 of it at most.  Against sums in 64-bit significands the whitened
+//     values are off by 0.12 to 0.7 times as much as those of FP64 sums (kinships
+//     of 500 to 2,000 markers, n = 800 to 5,000, h2 = 0.1 to 0.999; seven digits: 0.4
+//     to 6 times).
+//   S = 7 (GLS_INT8_EMU): 2^-56 of 2^e_i, the bound of eight truncated 7-bit slices
+//     with an eighth less work.
 //
 // Operands are kept in the order the matrix instruction reads them.  A unit is
 // 1 KB: 16 rows (of L^-1) or 16 SNPs times 64 k, byte b of lane l being element
@@ -32,17 +37,19 @@
 
 namespace gls {
 
-constexpr int OZ_SLICES = 7;
+constexpr int OZ_DIGITS_FP64 = 8, OZ_DIGITS_EMU = 7;
 constexpr int OZ_UNIT = 1024;                        // bytes of a unit
 constexpr int OZ_BM = 32, OZ_BK = 64;                // rows of a product tile and k per stage
 constexpr int OZ_STRIPS = OZ_BM / 16;
 constexpr int OZ_TM = 64;                            // rows of a tile of the sliced factor
-constexpr int OZ_ATILE = OZ_TM / 16 * OZ_SLICES * OZ_UNIT;   // one (row tile, k block) of the sliced factor
+
+// Bytes of one (row tile, k block) of the factor sliced into S digits.
+constexpr int oz_atile(int S) { return OZ_TM / 16 * S * OZ_UNIT; }
 
 // Bytes of the sliced factor: row tile t holds the k blocks 0..t that reach the lower triangle.
-inline size_t oz_factor_bytes(int64_t N) {
+inline size_t oz_factor_bytes(int64_t N, int S) {
   const int64_t T = N / OZ_TM;
-  return (size_t)(T * (T + 1) / 2) * OZ_ATILE;
+  return (size_t)(T * (T + 1) / 2) * oz_atile(S);
 }
 
 typedef int i4_t __attribute__((ext_vector_type(4)));
@@ -69,6 +76,7 @@ __global__ __launch_bounds__(256) void row_max_kernel(const double* __restrict__
 // top digit stays within [-128, 127] after the lower digits' carries.  Thread
 // (row r, k group kq) reads 16 consecutive k of its row (coalesced over rows)
 // and writes its lane's 16 bytes of each digit's unit.
+template <int S>
 __global__ __launch_bounds__(256) void slice_factor_kernel(const double* __restrict__ Li, int N,
                                                            const double* __restrict__ part, int* __restrict__ ex,
                                                            int8_t* __restrict__ out) {
@@ -84,25 +92,25 @@ __global__ __launch_bounds__(256) void slice_factor_kernel(const double* __restr
   int e = 0;
   if (m > 0.0 && frexp(m, &e) > 0.99) ++e;
   if (kb == 0 && kq == 0) ex[i] = e;
-  uint32_t w[OZ_SLICES][4];
+  uint32_t w[S][4];
 #pragma unroll
-  for (int s = 0; s < OZ_SLICES; ++s)
+  for (int s = 0; s < S; ++s)
 #pragma unroll
     for (int q = 0; q < 4; ++q) w[s][q] = 0u;
 #pragma unroll
   for (int b = 0; b < 16; ++b) {
-    long long q = __double2ll_rn(ldexp(x[b], 55 - e));
+    long long q = __double2ll_rn(ldexp(x[b], 8 * S - 1 - e));   // below 0.99 * 2^(8 S - 1)
 #pragma unroll
-    for (int s = 0; s < OZ_SLICES; ++s) {
+    for (int s = 0; s < S; ++s) {
       const int d = (int)(int8_t)(q & 255);
       q = (q - d) >> 8;
       w[s][b >> 2] |= (uint32_t)(d & 255) << (8 * (b & 3));
     }
   }
-  int8_t* o = out + ((int64_t)ti * (ti + 1) / 2 + kb) * OZ_ATILE + (r >> 4) * (OZ_SLICES * OZ_UNIT) +
+  int8_t* o = out + ((int64_t)ti * (ti + 1) / 2 + kb) * oz_atile(S) + (r >> 4) * (S * OZ_UNIT) +
               16 * (kq * 16 + (r & 15));
 #pragma unroll
-  for (int s = 0; s < OZ_SLICES; ++s)
+  for (int s = 0; s < S; ++s)
     *reinterpret_cast<uint4*>(o + s * OZ_UNIT) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
 }
 
@@ -272,7 +280,7 @@ __global__ __launch_bounds__(256) void widen_columns_kernel(const void* __restri
 }
 
 struct OzArgs {
-  const int8_t* A;        // sliced factor: row tile t's k blocks 0..t of OZ_ATILE bytes
+  const int8_t* A;        // sliced factor: row tile t's k blocks 0..t of oz_atile(S) bytes
   const int* ex;          // row exponents
   const uint8_t* B;       // units [k block][Jb]
   int Jb;                 // SNP groups of 16
@@ -285,10 +293,11 @@ struct OzArgs {
   double* C; int64_t ldc; // red_q == 0: the product itself, N x ncols FP64
 };
 
-// A workgroup of four waves owns 32 rows x 192 SNPs: wave w takes the 16-row
-// strip w & 1 and the 96-SNP half w >> 1 with all seven digits, 7 x 6
-// accumulators of 16 x 16 (168 registers; two waves per SIMD).  Per 64-deep
-// stage it reads seven + six 1 KB fragments for 42 MFMAs; sixteen waves of
+// A workgroup of four waves owns 32 rows x 192 SNPs with seven digits, 32 x 160 with
+// eight (26 KB a stage either way): wave w takes the 16-row
+// strip w & 1 and the half w >> 1 of the SNPs with all the digits, 7 x 6 or 8 x 5
+// accumulators of 16 x 16 (168 or 160 registers; two waves per SIMD).  Per 64-deep
+// stage it reads thirteen 1 KB fragments for 42 or 40 MFMAs; sixteen waves of
 // 4 x 4 accumulators on a 32 x 256 tile read eight for 16 and kept the LDS port
 // busy for longer than the MFMA pipes.  Stages move straight from global memory
 // into a ring of three LDS buffers, two ahead of the MFMAs.
@@ -304,17 +313,19 @@ struct OzArgs {
 // A wave's accumulator element t of lane l is row 4 (l / 16) + t, SNP l % 16 of
 // its 16 x 16 block, so a sum over the rows is four values of the lane and two
 // lane exchanges.
-constexpr int OZ_BN = 192, OZ_THREADS = 256, OZ_STAGES = 3;
+constexpr int OZ_THREADS = 256, OZ_STAGES = 3;
+constexpr int oz_bn(int S) { return S == 7 ? 192 : 160; }
 constexpr int OZ_MAP_GM = 4, OZ_MAP_GN = 8;
 
+template <int S>
 __global__ __launch_bounds__(OZ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ozaki_i8_kernel(OzArgs g) {
-  constexpr int S = OZ_SLICES, NW = OZ_THREADS / 64, NS = OZ_STAGES;
-  constexpr int BU = OZ_BN / 16, FC = BU / 2;              // SNP groups per tile and per wave
+  constexpr int NW = OZ_THREADS / 64, NS = OZ_STAGES, BN = oz_bn(S);
+  constexpr int BU = BN / 16, FC = BU / 2;              // SNP groups per tile and per wave
   constexpr int AU = OZ_STRIPS * S, STAGE = (AU + BU) * OZ_UNIT;
   constexpr int NLD = (AU + BU + NW - 1) / NW, FULL = AU + BU - (NLD - 1) * NW;   // loads a stage; waves < FULL do NLD, the others one less
   constexpr int QC = 10;                                   // sums per pass of the epilogue's LDS exchange
-  static_assert(NS * STAGE <= 80 * 1024 && OZ_STRIPS * QC * OZ_BN * 8 <= NS * STAGE, "LDS");
+  static_assert(NS * STAGE <= 80 * 1024 && OZ_STRIPS * QC * BN * 8 <= NS * STAGE, "LDS");
   __shared__ __align__(1024) int8_t smem[NS * STAGE];
   __shared__ int any;
 
@@ -324,15 +335,15 @@ void ozaki_i8_kernel(OzArgs g) {
     m.map_gm = OZ_MAP_GM;
     m.map_gn = OZ_MAP_GN;
     m.map_desc = 1;
-    if (!XcdMap::tile(m, blockIdx.x, g.Mt, (g.ncols + OZ_BN - 1) / OZ_BN, &ti, &tj)) return;
+    if (!XcdMap::tile(m, blockIdx.x, g.Mt, (g.ncols + BN - 1) / BN, &ti, &tj)) return;
   }
   const int nk = ti * OZ_BM / OZ_TM + 1;   // lower triangular factor
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ws = wave & 1, wc = wave >> 1;
-  const int j0 = tj * OZ_BN, jb0 = tj * BU;
+  const int j0 = tj * BN, jb0 = tj * BU;
 
-  const int8_t* Abase = g.A + (int64_t)(nk - 1) * nk / 2 * OZ_ATILE + ti % (OZ_TM / OZ_BM) * (AU * OZ_UNIT);
+  const int8_t* Abase = g.A + (int64_t)(nk - 1) * nk / 2 * oz_atile(S) + ti % (OZ_TM / OZ_BM) * (AU * OZ_UNIT);
   const uint32_t lds0 = lds_address(smem);
   const uint32_t voff = 16 * lane;
   auto issue = [&](int kb) {
@@ -341,7 +352,7 @@ void ozaki_i8_kernel(OzArgs g) {
     for (int q = 0; q < NLD; ++q) {
       const int u = q * NW + wave;
       if (u >= AU + BU) break;       // wave-uniform: A's units, then B's (groups past the end: the last one's, dropped)
-      const void* p = (u < AU) ? (const void*)(Abase + (int64_t)kb * OZ_ATILE + u * OZ_UNIT)
+      const void* p = (u < AU) ? (const void*)(Abase + (int64_t)kb * oz_atile(S) + u * OZ_UNIT)
                                : (const void*)(g.B + ((int64_t)kb * g.Jb + min(jb0 + u - AU, g.Jb - 1)) * OZ_UNIT);
       lds_load16_sv(p, voff, base + (uint32_t)(u * OZ_UNIT));
     }
@@ -351,7 +362,7 @@ void ozaki_i8_kernel(OzArgs g) {
   if (g.flags.at) {   // a tile whose every SNP is flagged has nothing to do
     if (threadIdx.x == 0) any = 0;
     __syncthreads();
-    if (threadIdx.x < OZ_BN && j0 + (int)threadIdx.x < g.ncols && !g.flags.flagged(j0 + threadIdx.x, g.ncols)) any = 1;
+    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && !g.flags.flagged(j0 + threadIdx.x, g.ncols)) any = 1;
     __syncthreads();
     if (!any) {
       wait_vmcnt<0>();   // no load into this workgroup's LDS may outlive it
@@ -394,7 +405,7 @@ void ozaki_i8_kernel(OzArgs g) {
       double x = (double)acc[0][c][t];
 #pragma unroll
       for (int s = 1; s < S; ++s) x = fma(x, 1.0 / 256.0, (double)acc[s][c][t]);
-      v[c][t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 55 + 8 * (S - 1));
+      v[c][t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 7);
     }
   if (g.red_q == 0) {
 #pragma unroll
@@ -426,16 +437,16 @@ void ozaki_i8_kernel(OzArgs g) {
         for (int t = 0; t < 4; ++t) x += v[c][t] * (norm ? v[c][t] : w[t]);
         x += __shfl_xor(x, 16, 64);
         x += __shfl_xor(x, 32, 64);
-        if (lane < 16) red[(ws * QC + qq) * OZ_BN + (wc * FC + c) * 16 + lane] = x;
+        if (lane < 16) red[(ws * QC + qq) * BN + (wc * FC + c) * 16 + lane] = x;
       }
     }
     __syncthreads();
-    for (int f = threadIdx.x; f < qn * OZ_BN; f += OZ_THREADS) {   // the strips in order
-      const int qq = f / OZ_BN, jl = f % OZ_BN;
-      const double* r = red + qq * OZ_BN + jl;
+    for (int f = threadIdx.x; f < qn * BN; f += OZ_THREADS) {   // the strips in order
+      const int qq = f / BN, jl = f % BN;
+      const double* r = red + qq * BN + jl;
       if (j0 + jl < g.ncols)
         g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
-            r[0] + r[QC * OZ_BN];
+            r[0] + r[QC * BN];
     }
   }
 }
@@ -452,8 +463,9 @@ void ozaki_i8_kernel(OzArgs g) {
 // win (n = 6,000, 200 SNPs, 752 tiles: 107 us against 120).
 constexpr int OZS_BN = 64, OZS_THREADS = 512, OZS_SPLIT = 4, OZS_TILES = 512;
 
+template <int S>
 __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
-  constexpr int S = OZ_SLICES, FC = OZS_BN / 16, QC = 10;
+  constexpr int FC = OZS_BN / 16, QC = 10;
   static_assert(2 * OZS_SPLIT * 64 == OZS_THREADS && FC == OZS_SPLIT, "a wave forms one 16 x 16 block at the end");
   __shared__ int sums[2 * S * FC * 256];           // [strip][digit][SNP group][element][lane]
   __shared__ double red[2 * QC * OZS_BN];
@@ -473,13 +485,13 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   if (!any) return;
 
   const int nk = ti * OZ_BM / OZ_TM + 1;
-  const int8_t* A = g.A + (int64_t)(nk - 1) * nk / 2 * OZ_ATILE + ((ti % (OZ_TM / OZ_BM)) * OZ_STRIPS + ws) * (S * OZ_UNIT) +
+  const int8_t* A = g.A + (int64_t)(nk - 1) * nk / 2 * oz_atile(S) + ((ti % (OZ_TM / OZ_BM)) * OZ_STRIPS + ws) * (S * OZ_UNIT) +
                     16 * lane;
   const uint8_t* B = g.B + 16 * lane;
   i4_t a[2][S], b[2][FC];
   auto load = [&](int kb, int buf) {
 #pragma unroll
-    for (int s = 0; s < S; ++s) a[buf][s] = *reinterpret_cast<const i4_t*>(A + (int64_t)kb * OZ_ATILE + s * OZ_UNIT);
+    for (int s = 0; s < S; ++s) a[buf][s] = *reinterpret_cast<const i4_t*>(A + (int64_t)kb * oz_atile(S) + s * OZ_UNIT);
 #pragma unroll
     for (int c = 0; c < FC; ++c)
       b[buf][c] = *reinterpret_cast<const i4_t*>(B + ((int64_t)kb * g.Jb + min(jb0 + c, g.Jb - 1)) * OZ_UNIT);
@@ -521,7 +533,7 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
     double x = (double)at[0];
 #pragma unroll
     for (int s = 1; s < S; ++s) x = fma(x, 1.0 / 256.0, (double)at[s * FC * 256]);
-    v[t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 55 + 8 * (S - 1));
+    v[t] = ldexp(x, (t == 0 ? e.x : t == 1 ? e.y : t == 2 ? e.z : e.w) - 7);
   }
   if (g.red_q == 0) {
     const int j = j0 + wk * 16 + (lane & 15);

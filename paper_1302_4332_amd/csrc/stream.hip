@@ -109,7 +109,7 @@ std::vector<int64_t> block_schedule(int64_t bc, int64_t total) {
 constexpr int STREAM_PARTS = 4, STREAM_PART_COLS = 512;
 
 int parts_of(const Ctx* c, const double*, int64_t cols) {
-  return c->plan.whole ? (int)std::min<int64_t>(STREAM_PARTS, std::max<int64_t>(1, cols / STREAM_PART_COLS)) : 1;
+  return whole_f64(c) ? (int)std::min<int64_t>(STREAM_PARTS, std::max<int64_t>(1, cols / STREAM_PART_COLS)) : 1;
 }
 int parts_of(const Ctx*, const void*, int64_t) { return 1; }
 

@@ -10,9 +10,9 @@ padding, for aligned and unaligned columns, and on both sides of the line betwee
 - each SNP's outputs bitwise the same alone and in the mixed block;
 - the same values as bytes, bitwise (values above 127 included).
 
-The integer product's own error bound: L^-1 is rounded at 2^-56 of its row's
-largest entry and each digit's sum is exact, so x~ is off by at most
-2^-55 n max|x| rowmax, below the FP64 product's n 2^-53 bound.
+The integer product's own error bound: L^-1 is rounded at 2^-64 of the power of
+two above its row's largest entry and each digit's sum is exact, so x~ is off by at
+most 2^-63 n max|x| rowmax, below the FP64 product's n 2^-53 bound for the same terms.
 """
 import numpy as np
 import pytest
@@ -159,3 +159,55 @@ def test_scales_apart(fmt):
     call = {"f64": ctx.block, "u8": ctx.block_u8, "u2": ctx.block_u2}[fmt]
     compare(as_numpy(call(_t(X))), ref, 1e-10)
     ctx.close()
+
+
+@pytest.mark.parametrize("fmt", ["f64", "u8", "u2"])
+@pytest.mark.parametrize("mb", [3, 1100])
+def test_factor_keeps_its_low_bits(mb, fmt):
+    """Entries of L^-1 far below their row's largest keep all 53 bits in an FP64 handle, on both kernels of the integer
+    product (3 and 1,100 SNPs are 32 and 576 tiles of 32 x 64).
+
+    M = [[I, c I], [c I, (1 + c^2) I]] has L^-1 = [[I, 0], [-c I, I]] exactly, c = 2^-18 + 2^-58 below a diagonal of
+    ones.  With SNPs that are zero in the second half of the samples and a phenotype that is zero in the first, b is
+    -c sum(x y) / sum(x^2 (1 + c^2)) over positive terms: 2 n roundings at most in either sum, and a few more.  At
+    2^-56 of the row's largest entry c would lose its last bit, and b be off by 2^-40."""
+    n = 1024
+    h, c = n // 2, 2.0 ** -18 + 2.0 ** -58
+    M = np.eye(n)
+    M[h:, :h] = c * np.eye(h)
+    M[:h, h:] = c * np.eye(h)
+    M[h:, h:] += c * c * np.eye(h)
+    y = np.zeros(n)
+    y[h:] = 1.0 + np.arange(h) / h
+    X = np.zeros((mb, n))
+    X[:, :h] = synth.genotypes(h, 0, mb, 5) % 3
+    X[:, 0] = 1.0 + np.arange(mb) % 2
+    held = {"f64": X, "u8": X.astype(np.uint8), "u2": synth.pack_dosages_2bit(X.astype(np.uint8))}[fmt]
+    ctx = GLSContext(_t(M), 1.0, None, _t(y), block_cols=mb)
+    call = {"f64": ctx.block, "u8": ctx.block_u8, "u2": ctx.block_u2}[fmt]
+    got = as_numpy(call(_t(held)))
+    ctx.close()
+    ref = -c * (X[:, :h] @ y[h:]) / ((X[:, :h] ** 2).sum(1) * (1.0 + c * c))
+    err = np.abs(got["b"][:, 0] / ref - 1.0).max()
+    print(f"mb={mb} {fmt}: {err:.1e}")
+    assert err <= (2 * n + 8) * 2.0 ** -53   # 2.3e-13; 2^-40 is 9.1e-13
+
+
+def test_fp64_input_of_an_emulation_handle():
+    """FP64 columns of a GLS_INT8_EMU handle run the FP64 product: bitwise the outputs of whole numbers that an FP64
+    handle of so few samples (n <= 512) forms there too, and within the FP64 bar for more."""
+    for n, exact in ((500, True), (700, False)):
+        Phi, XL, y, XR = _study(n, 4, 70)
+        outs = []
+        for precision in ("int8_emu", "fp64"):
+            ctx = GLSContext(_t(Phi), 0.4, _t(XL), _t(y), block_cols=70, precision=precision)
+            outs.append(as_numpy(ctx.block(_t(XR))))
+            outs.append(as_numpy(ctx.block(_t(XR * 0.5))))
+            ctx.close()
+        a, a2, b, b2 = outs
+        assert np.array_equal(a2["b"].view(np.uint8), b2["b"].view(np.uint8))   # halves of dosages: both on the FP64 product
+        # powers of two change no rounding: dosages and their halves give the same FP64 product
+        assert np.array_equal(a["b"][:, -1], a2["b"][:, -1] * 0.5)
+        if exact:
+            assert np.array_equal(a["b"].view(np.uint8), b["b"].view(np.uint8))
+        compare(a, O.gls_sequence(Phi, 0.4, XL, y, XR), 1e-10)
