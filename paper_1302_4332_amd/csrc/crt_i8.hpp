@@ -3,17 +3,32 @@
 // Uchino and Imamura's Ozaki scheme II).
 //
 // Row i of op(A) and column j of op(B) are scaled by powers of two so that their
-// 2-norms lie in [2^57, 2^58) and rounded to integers a_ik, b_kj.  Then
-//     |sum_k a_ik b_kj| <= ||a_i|| ||b_j|| < 2^116.01 < P / 2,
-// P the product of fifteen coprime moduli m_p <= 256, so the integer sum is known
-// from its residues: fifteen int8 products of the residues (|r| <= 128, summed
-// exactly in int32 for K <= 2^16), one per modulus, give t_p = sum q_p mod m_p with
+// 2-norms lie in [2^61, 2^62) and rounded to integers a_ik, b_kj.  Then
+//     |sum_k a_ik b_kj| <= ||a_i|| ||b_j|| < 2^124.01 < P / 2,
+// P the product of sixteen coprime moduli m_p <= 256, so the integer sum is known
+// from its residues: sixteen int8 products of the residues (|r| <= 128, summed
+// exactly in int32 for K <= CRT_MAX_K), one per modulus, give t_p = sum q_p mod m_p with
 // q_p = (P / m_p)^-1 mod m_p, and
 //     sum / P = sum_p t_p / m_p  mod 1,
-// evaluated to 2^-70 of P in two exact FP64 sums.  The only rounding errors are
-// those of the inputs, below 2^-58 of their row's (column's) norm each, and of the
-// result: against sum_k |a_ik b_kj| the error is that of a single FP64 rounding
-// where FP64 accumulation has one per k.
+// evaluated to 2^-70 of P in two exact FP64 sums.
+//
+// The rounding errors are those of the inputs, at most 2^-62 of their row's
+// (column's) norm an element, and one of the result.  The bound is normwise:
+//     |error| <= 2^-53 |result| + (2^-61 sqrt(K) + 2^-66) ||a_i|| ||b_j||
+// (with independent roundings about 2^-62 ||a_i|| ||b_j||), where FP64 accumulation
+// has a rounding of every partial sum: 2^-53 sum_k |sum_{l<=k} a_il b_lj|, for vectors
+// without structure about 2^-55 ||a_i|| ||b_j||.  Where the large entries of row and
+// column do not meet, sum_k |a_ik b_kj| can be far below the norms' product, and an
+// element far below its vector's norm keeps fewer than its 53 bits; the
+// factorization's own error is bounded by such norms.  Bringing M's diagonal to
+// one scale (diagonal_scale_kernel) makes that bound one of each entry of A22 -
+// L21 L21^T; it does not bound the spread within a row of L^-1 of an
+// ill-conditioned M.
+//
+// Modelled on the CPU for the four products of a node (kinships of 300 and 2,000
+// markers, n = 1,600, h2 = 0.1 to 0.999) the error is 0.42 to 0.59 times 2^-53 of the
+// result, rms, and that of an FP64 library product 0.44 to 34 times; at 2^-58 of the
+// norms, which fifteen moduli allow, it was 0.48 to 12.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -25,9 +40,10 @@
 
 namespace gls {
 
-constexpr int CRT_P = 15;
-constexpr int CRT_M[CRT_P] = {256, 251, 247, 243, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193};
-constexpr int CRT_NORM = 58;        // norms below 2^58
+constexpr int CRT_P = 16;
+constexpr int CRT_M[CRT_P] = {256, 251, 247, 243, 241, 239, 235, 233, 229, 227, 223, 217, 211, 199, 197, 193};
+constexpr int CRT_NORM = 62;        // norms below 2^62
+constexpr int CRT_MAX_K = 1 << 16;  // longest sum: below 2^30, and its recombination below 2^24
 constexpr int CRT_NAN = 1 << 30;    // exponent of a vector with a NaN or an infinity
 
 constexpr int crt_gcd(int a, int b) { return b ? crt_gcd(b, a % b) : a; }
@@ -43,15 +59,12 @@ struct CrtTables {
   int q[CRT_P];          // (P / m)^-1 mod m
   double hi[CRT_P];      // 1 / m = (hi + lo 2^-40) 2^-40 up to 2^-81, hi and lo integers
   double lo[CRT_P];
-  int pow15[CRT_P][4];   // 2^(15 j) mod m, symmetric
-  double P;
+  int pow16[CRT_P][4];   // 2^(16 j) mod m, symmetric
 };
 constexpr CrtTables crt_tables() {
   CrtTables t{};
-  t.P = 1.0;
   for (int p = 0; p < CRT_P; ++p) {
     const int m = CRT_M[p];
-    t.P *= m;   // rounded: a relative 2^-50 at most
     int r = 1;
     for (int o = 0; o < CRT_P; ++o)
       if (o != p) r = r * (CRT_M[o] % m) % m;
@@ -64,20 +77,22 @@ constexpr CrtTables crt_tables() {
     t.lo[p] = (double)((long long)(inv - (hi << 40)));
     int w = 1;
     for (int j = 0; j < 4; ++j) {
-      t.pow15[p][j] = w > m / 2 ? w - m : w;
-      w = (int)((long long)w * 32768 % m);
+      t.pow16[p][j] = w > m / 2 ? w - m : w;
+      w = (int)((long long)w * 65536 % m);
     }
   }
   return t;
 }
 constexpr CrtTables CRT_T = crt_tables();
-// P to full precision: the first eight factors' product is below 2^64, the rest's below 2^54, both exact; one rounding
-constexpr double crt_P() {
-  unsigned long long a = 1, b = 1;
-  for (int p = 0; p < 7; ++p) a *= (unsigned long long)CRT_M[p];       // < 2^56
-  for (int p = 7; p < CRT_P; ++p) b *= (unsigned long long)CRT_M[p];   // < 2^62
-  return (double)((unsigned __int128)a * b);
+// P = 2^125.2: exact in 128 bits, then one rounding.
+constexpr unsigned __int128 crt_product() {
+  unsigned __int128 a = 1;
+  for (int p = 0; p < CRT_P; ++p) a *= (unsigned)CRT_M[p];
+  return a;
 }
+static_assert(crt_product() >> 125 == 1 && (crt_product() - ((unsigned __int128)1 << 125)) >> 122 != 0,
+              "P / 2 above 2^124.16, the largest sum's bound");
+constexpr double crt_P() { return (double)crt_product(); }
 
 // One operand: vectors (rows of op(A) or columns of op(B)) in groups of 16, k in
 // blocks of 64; plane p holds unit (k block, group) at (kb G + g) KB, in the
@@ -217,10 +232,11 @@ __device__ __forceinline__ uint32_t crt_byte(float off, int t, uint32_t w) {
 }
 
 // A lane's 16 elements as residues of every modulus, into its 16 bytes of each
-// plane's unit.  The integer is cut into four 15-bit pieces (the last of 13), so
-// that its residue is a sum below 2^23 that FP32 holds exactly; the quotient's
-// rounding leaves |r| <= 0.504 m, at most 127 for the odd moduli.  The byte for
-// m = 256 is the integer's lowest.
+// plane's unit.  The integer (below 2^62) is cut into four signed 16-bit pieces, so
+// that its residue is a sum below 2^24 (2^15 + 125 (2^15 + 2^15 + 2^14) + 128 at most)
+// that FP32 holds exactly; the quotient, below 53,300, is off by 2^-23 of itself at most
+// before it is rounded, which leaves |r| <= 0.507 m, and at most 0.505 m = 126 for m =
+// 251.  The byte for m = 256 is the integer's lowest.
 __device__ __forceinline__ void crt_store_unit(const double (&x)[16], int e, int8_t* o, int64_t stride) {
   float c[16][4];
   uint32_t low[4] = {0u, 0u, 0u, 0u};
@@ -230,8 +246,8 @@ __device__ __forceinline__ void crt_store_unit(const double (&x)[16], int e, int
     low[b >> 2] |= (uint32_t)((int)v & 255) << (8 * (b & 3));
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      const int d = (int)((v & 32767) ^ 16384) - 16384;
-      v = (v - d) >> 15;
+      const int d = (int)(int16_t)(v & 65535);
+      v = (v - d) >> 16;
       c[b][j] = (float)(j == 0 ? d + 128 : d);
     }
     c[b][3] = (float)(int)v;
@@ -240,7 +256,7 @@ __device__ __forceinline__ void crt_store_unit(const double (&x)[16], int e, int
 #pragma unroll
   for (int p = 1; p < CRT_P; ++p) {
     const float m = (float)CRT_M[p], inv = 1.0f / (float)CRT_M[p];
-    const float k1 = (float)CRT_T.pow15[p][1], k2 = (float)CRT_T.pow15[p][2], k3 = (float)CRT_T.pow15[p][3];
+    const float k1 = (float)CRT_T.pow16[p][1], k2 = (float)CRT_T.pow16[p][2], k3 = (float)CRT_T.pow16[p][3];
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int b = 0; b < 16; ++b) {
@@ -304,8 +320,8 @@ struct CrtArgs {
 
 // One modulus's product (blockIdx.y): 192 x 192 tiles, four waves of 96 x 96 (6 x 6
 // accumulators), stages of 64 k from global memory into a ring of three LDS
-// buffers, two workgroups to a compute unit.  At w = 5,000 the fifteen triangular
-// products take 0.95-1.01 ms (1,900 TOPS).
+// buffers, two workgroups to a compute unit.  At w = 5,000 sixteen triangular
+// products take 1.01-1.08 ms (1,900 TOPS).
 // XCD groups: one row tile x 16 column tiles, and 4 x 8 where the sums start at the
 // columns' diagonal (w = 5,000: 0.95-1.01 ms against 1.03-1.57 with 4 x 8, and
 // 1.02 against 1.19).

@@ -65,10 +65,21 @@ static_assert(NPAD % NB_LEAF == 0 && NPAD % LP_BM == 0 && NPAD % OZ_BM == 0 && N
 constexpr int64_t OZ_MIN_N = 768;
 
 // Nodes of the factorization of at least this many rows and columns form their products on the integer matrix cores
-// (crt_i8.hpp).  The fifteen products grow with the node's cube, the conversions with its square: at 5,000 a product
-// takes 1.0 + 0.3 ms where the FP64 one takes 2.4 (a study of 10,000 samples 23.0 -> 19.7 ms), at 2,500 0.28 + 0.1
-// against 0.38 (19.7 -> 19.3 ms), and at 2,048 the gradient at n = 4,096 goes from 9.35 to 9.7 ms.
+// (crt_i8.hpp).  The products grow with the node's cube, the conversions with its square: with fifteen moduli, at
+// 5,000 a product takes 1.0 + 0.3 ms where the FP64 one takes 2.4 (a study of 10,000 samples 23.0 -> 19.7 ms), at 2,500
+// 0.28 + 0.1 against 0.38 (19.7 -> 19.3 ms), and at 2,048 the gradient at n = 4,096 goes from 9.35 to 9.7 ms.  Nodes with
+// sums longer than CRT_MAX_K, whose residues' sums could leave their exact range, stay on the FP64 products.
 constexpr int64_t CRT_MIN_W = 2304;
+static bool crt_node(int64_t w1, int64_t w2) { return std::min(w1, w2) >= CRT_MIN_W && std::max(w1, w2) <= CRT_MAX_K; }
+
+// Widest side of a node of leaves [a, b) or below it whose products are formed there (0: none).
+static int64_t crt_widest(int a, int b) {
+  if (b - a <= 1) return 0;
+  const int mid = (a + b) / 2;
+  const int64_t w1 = (int64_t)(mid - a) * NB_LEAF, w2 = (int64_t)(b - mid) * NB_LEAF;   // w2 >= w1
+  if (w2 < CRT_MIN_W) return 0;
+  return crt_node(w1, w2) ? w2 : std::max(crt_widest(a, mid), crt_widest(mid, b));
+}
 
 // Scratch of a node's products: two operands, the residues, norms.
 static size_t crt_space_bytes(int64_t w) {
@@ -140,10 +151,9 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
     pl->off_side = take(sizeof(double) * std::max<int64_t>(at, 1));
   }
   {
-    const int64_t w = (Kt + 1) / 2 * NB_LEAF;   // the widest node
-    pl->crt_w = w >= CRT_MIN_W ? w : 0;
+    pl->crt_w = crt_widest(0, Kt);
     if (pl->crt_w) {
-      pl->off_crt = take(crt_space_bytes(w));
+      pl->off_crt = take(crt_space_bytes(pl->crt_w));
       pl->off_sc = take(sizeof(double) * (N + 1));
     }
   }
@@ -445,7 +455,7 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
     tri_strips<false>(Li22, N, Li21, w2, w1, -1.0, s);   // (L^-1)21 = -L22^-1 T
     return;
   }
-  if (c->plan.crt_w && std::min(w1, w2) >= CRT_MIN_W) {
+  if (crt_node(w1, w2)) {
     const CrtSpace crt(reinterpret_cast<char*>(c->crt), c->plan.crt_w);
     {  // L21 = A21 L11^-T
       const CrtOperand A = crt.rows(0, A21, N, w2, w1, false, s), B = crt.rows(1, Li11, N, w1, w1, true, s);
