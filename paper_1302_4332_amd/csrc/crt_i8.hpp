@@ -96,28 +96,31 @@ constexpr double crt_P() { return (double)crt_product(); }
 
 // One operand: vectors (rows of op(A) or columns of op(B)) in groups of 16, k in
 // blocks of 64; plane p holds unit (k block, group) at (kb G + g) KB, in the
-// matrix instruction's operand order (see ozaki_i8.hpp).
+// matrix instruction's operand order (see ozaki_i8.hpp).  count groups of them,
+// from planes on, are the operand: all G, or the columns that a product takes at a
+// time (crt_columns), whose first is column d0 of the whole op(B).
 struct CrtOperand {
   int8_t* planes;
   int64_t stride;   // bytes per plane
   int* ex;          // ||vector|| < 2^ex
-  int G, KB;
+  int G, KB, count, d0;
 };
 
 // Exponents.  Vector v of the matrix X (column-major, ld): row v (ROWS) or column
-// v, elements k0(v) <= k < k1(v) (lower: of a lower-triangular X).
+// v, elements k0(v) <= k < k1(v) (lower: of a lower-triangular matrix whose row or
+// column d0 is X's first).
 //
 // ROWS, first part: for 64 rows and 256 columns the largest magnitude's exponent
 // and the sum of squares scaled by it.
 __global__ __launch_bounds__(256) void crt_row_norm_kernel(const double* __restrict__ X, int64_t ld, int rows, int K,
-                                                           int lower, double* __restrict__ part_ss,
+                                                           int lower, int d0, double* __restrict__ part_ss,
                                                            int* __restrict__ part_e) {
   __shared__ double red[256];
   __shared__ int re[64];
   const int i0 = blockIdx.x * 64, k0 = blockIdx.y * 256;
   const int r = threadIdx.x & 63, g = threadIdx.x >> 6, i = i0 + r;
-  if (lower && k0 > i0 + 63) return;
-  const int kend = i < rows ? (lower ? min(K, i + 1) : K) : 0;
+  if (lower && k0 > d0 + i0 + 63) return;
+  const int kend = i < rows ? (lower ? min(K, d0 + i + 1) : K) : 0;
   double x[64], m = 0.0;
 #pragma unroll
   for (int u = 0; u < 64; ++u) {
@@ -169,11 +172,11 @@ __device__ __forceinline__ int crt_exponent(double ss, int e) {
 // ROWS, second part: ex[i] from the chunks that reach row i.
 __global__ __launch_bounds__(256) void crt_row_exp_kernel(const double* __restrict__ part_ss,
                                                           const int* __restrict__ part_e, int rows, int K, int lower,
-                                                          int* __restrict__ ex) {
+                                                          int d0, int* __restrict__ ex) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= rows) return;
   const int R = (rows + 63) / 64 * 64;
-  const int n = lower ? min((K + 255) / 256, (i / 64 * 64 + 63) / 256 + 1) : (K + 255) / 256;
+  const int n = lower ? min((K + 255) / 256, (d0 + i / 64 * 64 + 63) / 256 + 1) : (K + 255) / 256;
   int e = -100000;
   bool any = false;
   for (int s = 0; s < n; ++s) {
@@ -194,11 +197,11 @@ __global__ __launch_bounds__(256) void crt_row_exp_kernel(const double* __restri
 
 // Columns: one wave per column.
 __global__ __launch_bounds__(256) void crt_col_exp_kernel(const double* __restrict__ X, int64_t ld, int K, int cols,
-                                                          int lower, int* __restrict__ ex) {
+                                                          int lower, int d0, int* __restrict__ ex) {
   const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= cols) return;
   const double* c = X + (int64_t)j * ld;
-  const int kb = lower ? j : 0;
+  const int kb = lower ? d0 + j : 0;
   double m = 0.0;
 #pragma unroll 4
   for (int k = kb + lane; k < K; k += 64) {
@@ -270,12 +273,14 @@ __device__ __forceinline__ void crt_store_unit(const double (&x)[16], int e, int
 
 // Tile of the product kernel: k blocks are taken in or left out for whole tiles.
 constexpr int CRT_BM = 192, CRT_BN = 192, CRT_THREADS = 256;
+static_assert(CRT_BM == CRT_BN, "one trim of the triangles for rows and columns");
 
 // Residues of 64 rows x 64 k (ROWS).  lower: zeros past the diagonal, up to the tile's last k block.
 __global__ __launch_bounds__(256) void crt_rows_kernel(const double* __restrict__ X, int64_t ld, int rows, int K,
                                                        int lower, CrtOperand op) {
   const int kb = blockIdx.x, i0 = blockIdx.y * 64;
-  if (lower && kb * 64 > (i0 + 63) / CRT_BM * CRT_BM + CRT_BM - 1) return;
+  const int d0 = op.d0;   // a multiple of CRT_BN = CRT_BM
+  if (lower && kb * 64 > d0 + (i0 + 63) / CRT_BM * CRT_BM + CRT_BM - 1) return;
   const int r = threadIdx.x & 63, kq = threadIdx.x >> 6, i = i0 + r;
   const int g = i >> 4;
   if (g >= op.G) return;
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(256) void crt_rows_kernel(const double* __restrict_
 #pragma unroll
   for (int b = 0; b < 16; ++b) {
     const int k = kb * 64 + kq * 16 + b;
-    x[b] = (i < rows && k < K && !(lower && k > i)) ? X[(int64_t)i + (int64_t)k * ld] : 0.0;
+    x[b] = (i < rows && k < K && !(lower && k > d0 + i)) ? X[(int64_t)i + (int64_t)k * ld] : 0.0;
   }
   crt_store_unit(x, i < rows ? op.ex[i] : 0, op.planes + ((int64_t)kb * op.G + g) * 1024 + 16 * (kq * 16 + (r & 15)),
                  op.stride);
@@ -294,23 +299,24 @@ __global__ __launch_bounds__(256) void crt_cols_kernel(const double* __restrict_
                                                        int lower, CrtOperand op) {
   const int g = blockIdx.x, lane = threadIdx.x & 63;
   const int kb = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (kb >= op.KB || (lower && kb * 64 + 63 < g * 16 / CRT_BN * CRT_BN)) return;
+  const int d0 = op.d0;
+  if (kb >= op.KB || (lower && kb * 64 + 63 < d0 + g * 16 / CRT_BN * CRT_BN)) return;
   const int j = g * 16 + (lane & 15), k0 = kb * 64 + (lane >> 4) * 16;
   double x[16];
   const double* c = X + (int64_t)j * ld + k0;
 #pragma unroll
-  for (int b = 0; b < 16; ++b) x[b] = (j < cols && k0 + b < K && !(lower && k0 + b < j)) ? c[b] : 0.0;
+  for (int b = 0; b < 16; ++b) x[b] = (j < cols && k0 + b < K && !(lower && k0 + b < d0 + j)) ? c[b] : 0.0;
   crt_store_unit(x, j < cols ? op.ex[j] : 0, op.planes + ((int64_t)kb * op.G + g) * 1024 + 16 * lane, op.stride);
 }
 
 struct CrtArgs {
   CrtOperand a, b;
-  int M, N, K;         // result rows and columns, sum length
+  int M, N, K;         // result rows and columns, sum length; columns [b.d0, b.d0 + N) of the whole result
   int a_lower;         // op(A)[i, k] = 0 for k > i
   int b_lower;         // op(B)[k, j] = 0 for k < j
   int b_upper;         // op(B)[k, j] = 0 for k > j
   int c_lower;         // only 16 x 16 tiles that reach the lower part of C
-  uint32_t* out;       // residues t_p: plane p, 16 x 16 tile (row group rg, column group cg) at (cg GA + rg) 64 dwords
+  uint32_t* out;       // residues t_p: plane p, 16 x 16 tile (row group rg, column group cg) at (cg a.count + rg) 64 dwords
   int64_t out_stride;  // dwords per plane
   // crt_finish_kernel: C = alpha op(A) op(B) + beta Cin
   double alpha, beta;
@@ -321,7 +327,7 @@ struct CrtArgs {
 // One modulus's product (blockIdx.y): 192 x 192 tiles, four waves of 96 x 96 (6 x 6
 // accumulators), stages of 64 k from global memory into a ring of three LDS
 // buffers, two workgroups to a compute unit.  At w = 5,000 sixteen triangular
-// products take 1.01-1.08 ms (1,900 TOPS).
+// products take 1.10 ms (1,800 TOPS).
 // XCD groups: one row tile x 16 column tiles, and 4 x 8 where the sums start at the
 // columns' diagonal (w = 5,000: 0.95-1.01 ms against 1.03-1.57 with 4 x 8, and
 // 1.02 against 1.19).
@@ -331,7 +337,7 @@ __host__ __device__ inline int crt_map_gn(const CrtArgs& g) { return g.b_lower ?
 __global__ __launch_bounds__(CRT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void crt_gemm_kernel(CrtArgs g) {
   constexpr int NS = 3, NW = 4, U = 12, F = 6, STAGE = 2 * U * 1024, NLD = 2 * U / NW;
-  static_assert(NLD * NW == 2 * U, "loads");
+  static_assert(NLD * NW == 2 * U && NLD % 2 == 0, "loads");
   __shared__ __align__(1024) int8_t smem[NS * STAGE];
   const int p = blockIdx.y;
   int ti, tj;
@@ -344,7 +350,7 @@ void crt_gemm_kernel(CrtArgs g) {
     const int bid = (blockIdx.x & ~7) | ((blockIdx.x + p) & 7);
     if (!XcdMap::tile(m, bid, (g.M + CRT_BM - 1) / CRT_BM, (g.N + CRT_BN - 1) / CRT_BN, &ti, &tj)) return;
   }
-  const int i0 = ti * CRT_BM, j0 = tj * CRT_BN;
+  const int i0 = ti * CRT_BM, j0 = g.b.d0 + tj * CRT_BN;
   if (g.c_lower && i0 + CRT_BM - 1 < j0) return;
   int k0 = 0, k1 = g.a.KB;
   if (g.a_lower) k1 = imin(k1, (i0 + CRT_BM + 63) / 64);
@@ -357,15 +363,19 @@ void crt_gemm_kernel(CrtArgs g) {
   const int8_t* A = g.a.planes + p * g.a.stride;
   const int8_t* B = g.b.planes + p * g.b.stride;
   const uint32_t lds0 = lds_address(smem), voff = 16 * lane;
+  int at[NLD];   // this wave's units within a k block: A's, then B's (groups past the end: the last one's, dropped)
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) {
+    const int u = q * NW + wave;
+    at[q] = (q < NLD / 2 ? imin(ga0 + u, g.a.count - 1) : imin(gb0 + u - U, g.b.count - 1)) * 1024;
+  }
+  const int64_t sa = (int64_t)g.a.G * 1024, sb = (int64_t)g.b.G * 1024;
   auto issue = [&](int kb) {
     const uint32_t base = lds0 + (uint32_t)((kb - k0) % NS * STAGE);
+    const int8_t *a = A + kb * sa, *b = B + kb * sb;
 #pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-      const int u = q * NW + wave;   // groups past the end: the last one's, dropped
-      const int8_t* s = (u < U) ? A + ((int64_t)kb * g.a.G + imin(ga0 + u, g.a.G - 1)) * 1024
-                                : B + ((int64_t)kb * g.b.G + imin(gb0 + u - U, g.b.G - 1)) * 1024;
-      lds_load16_sv(s, voff, base + (uint32_t)(u * 1024));
-    }
+    for (int q = 0; q < NLD; ++q)
+      lds_load16_sv((q < NLD / 2 ? a : b) + at[q], voff, base + (uint32_t)((q * NW + wave) * 1024));
   };
   i4_t acc[F][F];
 #pragma unroll
@@ -400,11 +410,11 @@ void crt_gemm_kernel(CrtArgs g) {
 #pragma unroll
   for (int a = 0; a < F; ++a) {
     const int rg = ga0 + wr * F + a;
-    if (rg >= g.a.G) continue;
+    if (rg >= g.a.count) continue;
 #pragma unroll
     for (int c = 0; c < F; ++c) {
       const int cg = gb0 + wc * F + c;
-      if (cg >= g.b.G || (g.c_lower && rg < cg)) continue;
+      if (cg >= g.b.count || (g.c_lower && rg < cg + g.b.d0 / 16)) continue;
       uint32_t w = 0;
       if (p == 0) {
 #pragma unroll
@@ -418,7 +428,7 @@ void crt_gemm_kernel(CrtArgs g) {
         }
         w ^= 0x80808080u;
       }
-      out[((int64_t)cg * g.a.G + rg) * 64 + lane] = w;
+      out[((int64_t)cg * g.a.count + rg) * 64 + lane] = w;
     }
   }
 }
@@ -449,10 +459,10 @@ __global__ __launch_bounds__(256) void crt_finish_kernel(CrtArgs g) {
   const int cg = blockIdx.y;
   const int j = cg * 16 + (lane & 15);
   const int ej = j < g.N ? g.b.ex[j] : 0;
-  for (int rg = blockIdx.x * 4 + wave; rg < g.a.G; rg += gridDim.x * 4) {
-    if (g.c_lower && rg < cg) continue;
+  for (int rg = blockIdx.x * 4 + wave; rg < g.a.count; rg += gridDim.x * 4) {
+    if (g.c_lower && rg < cg + g.b.d0 / 16) continue;
     double v[4];
-    crt_value(g.out + ((int64_t)cg * g.a.G + rg) * 64 + lane, g.out_stride, v);
+    crt_value(g.out + ((int64_t)cg * g.a.count + rg) * 64 + lane, g.out_stride, v);
     const int i = rg * 16 + 4 * (lane >> 4);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {

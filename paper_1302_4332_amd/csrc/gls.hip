@@ -64,6 +64,11 @@ static_assert(NPAD % NB_LEAF == 0 && NPAD % LP_BM == 0 && NPAD % OZ_BM == 0 && N
 // 90 -> 50, and a study of 512 samples and 2,048 SNPs 302 -> 323 us.
 constexpr int64_t OZ_MIN_N = 768;
 
+// A handle for the adjoint keeps L, so that its slices need a region of their own: 4 N^2 bytes beside 55 N^2.  Beyond
+// this padded sample count (4.3 GB beside 59) it does without, and the largest study that the card holds, of some
+// 72,000 samples, is what it would be without the integer product.
+constexpr int64_t OZ_GRAD_MAX_N = 32768;
+
 // Nodes of the factorization of at least this many rows and columns form their products on the integer matrix cores
 // (crt_i8.hpp).  The products grow with the node's cube, the conversions with its square: with fifteen moduli, at
 // 5,000 a product takes 1.0 + 0.3 ms where the FP64 one takes 2.4 (a study of 10,000 samples 23.0 -> 19.7 ms), at 2,500
@@ -81,10 +86,30 @@ static int64_t crt_widest(int a, int b) {
   return crt_node(w1, w2) ? w2 : std::max(crt_widest(a, mid), crt_widest(mid, b));
 }
 
-// Scratch of a node's products: two operands, the residues, norms.
-static size_t crt_space_bytes(int64_t w) {
-  return 3 * CRT_P * (size_t)(w * w) + (size_t)(w / 256 + 1) * w * 12 + 8 * (size_t)w + 8 * 256;
-}
+// Scratch of the products of nodes of at most w rows and columns: one operand whole, of the other and of the result as
+// many columns as there is room for (a multiple of the tiles' width, 192 at least), norms.
+struct CrtLayout {
+  size_t planes[2], out, ss, e, ex[2], end;
+  int64_t cols;
+  CrtLayout(int64_t w, size_t bytes) {
+    size_t at = 0;
+    auto take = [&](size_t b) {
+      const size_t p = at;
+      at = align_up(at + b, 256);
+      return p;
+    };
+    planes[0] = take(CRT_P * (size_t)(w * w));
+    ss = take((size_t)(w / 256 + 1) * w * 8);
+    e = take((size_t)(w / 256 + 1) * w * 4);
+    for (auto& x : ex) x = take(4 * (size_t)w);
+    const int64_t most = (w + CRT_BN - 1) / CRT_BN * CRT_BN;
+    const int64_t fit = bytes > at + 512 ? (int64_t)((bytes - at - 512) / (2 * CRT_P * (size_t)w)) / CRT_BN * CRT_BN : 0;
+    cols = std::min(most, std::max<int64_t>(fit, CRT_BN));
+    planes[1] = take(CRT_P * (size_t)(cols * w));
+    out = take(CRT_P * (size_t)(cols * w));
+    end = at;
+  }
+};
 
 // Largest T1 buffer of the recursive factorization: (b - mid) * (mid - a) leaves.
 static int64_t recursion_temp_leaves(int a, int b) {
@@ -151,11 +176,11 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
     pl->off_side = take(sizeof(double) * std::max<int64_t>(at, 1));
   }
   {
+    // Scratch of the products by residues.  While they run nothing else lives in the workspace from X~ on: the regions
+    // below are written after the factorization, and the panels of X~ and the side products belong to other nodes, whose
+    // work has been joined (with a node above them on the FP64 products that would not hold).
     pl->crt_w = crt_widest(0, Kt);
-    if (pl->crt_w) {
-      pl->off_crt = take(crt_space_bytes(pl->crt_w));
-      pl->off_sc = take(sizeof(double) * (N + 1));
-    }
+    pl->off_crt = crt_node(Kt / 2 * NB_LEAF, (Kt - Kt / 2) * NB_LEAF) ? pl->off_Xt : off;
   }
   pl->off_buf0 = take(sizeof(double) * n * bc);
   pl->off_buf1 = take(sizeof(double) * n * bc);
@@ -171,7 +196,8 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
   // Sliced L^-1 and its row exponents (under half of an N x N FP64 matrix).  L itself is read after setup only by
   // the refinement residual and the adjoint; without those its region is free and holds them.
   if (o->precision == GLS_INT8_EMU) pl->digits = OZ_DIGITS_EMU;
-  else if (pl->lp_bytes == 0 && N >= OZ_MIN_N) pl->digits = OZ_DIGITS_FP64;
+  else if (pl->lp_bytes == 0 && N >= OZ_MIN_N && (N <= OZ_GRAD_MAX_N || !(o->flags & GLS_KEEP_FOR_GRAD)))
+    pl->digits = OZ_DIGITS_FP64;
   if (pl->digits) {
     const size_t at = align_up(oz_factor_bytes(N, pl->digits), 256), ex = sizeof(int) * (N + 1);
     if (o->flags & GLS_KEEP_FOR_GRAD) pl->off_sl = take(at + ex);
@@ -200,6 +226,12 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
     pl->off_Wb = take(sizeof(double) * N * p);
     pl->off_W0b = take(sizeof(double) * N * p);
     pl->off_acc = take(sizeof(double) * (nc + 2048));
+  }
+  if (pl->crt_w) {
+    const size_t have = off - pl->off_crt;   // what the other regions span anyway
+    const CrtLayout need(pl->crt_w, have);
+    pl->crt_bytes = std::max(need.end, have);
+    if (need.end > have) take(need.end - have);
   }
   pl->total = off;
   return true;
@@ -353,70 +385,77 @@ static void tri_strips(const double* Li, int64_t ld, double* S, int w, int strip
 
 // A node's products on the integer matrix cores.
 struct CrtSpace {
-  int8_t* planes[2];
-  uint32_t* out;
-  double* ss;
-  int* e;
-  int* ex[2];
-  CrtSpace(char* at, int64_t w) {
-    auto take = [&](size_t bytes) {
-      char* p = at;
-      at += align_up(bytes, 256);
-      return p;
-    };
-    for (auto& p : planes) p = reinterpret_cast<int8_t*>(take(CRT_P * (size_t)(w * w)));
-    out = reinterpret_cast<uint32_t*>(take(CRT_P * (size_t)(w * w)));
-    ss = reinterpret_cast<double*>(take((size_t)(w / 256 + 1) * w * 8));
-    e = reinterpret_cast<int*>(take((size_t)(w / 256 + 1) * w * 4));
-    for (auto& p : ex) p = reinterpret_cast<int*>(take(4 * (size_t)w));
+  char* at;
+  CrtLayout l;
+  CrtSpace(const Ctx* c, int64_t w) : at(c->crt), l(w, c->plan.crt_bytes) {}
+  template <typename T>
+  T* ptr(size_t off) const {
+    return reinterpret_cast<T*>(at + off);
   }
-  CrtOperand operand(int which, int vectors, int K) const {
+  CrtOperand operand(int which, int vectors, int K, int d0) const {
     CrtOperand o;
-    o.planes = planes[which];
-    o.ex = ex[which];
-    o.G = (vectors + 15) / 16;
+    o.planes = ptr<int8_t>(l.planes[which]);
+    o.ex = ptr<int>(l.ex[which]);
+    o.G = o.count = (vectors + 15) / 16;
     o.KB = (K + 63) / 64;
     o.stride = (int64_t)o.G * o.KB * 1024;
+    o.d0 = d0;
     return o;
   }
-  CrtOperand rows(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s) const {
-    const CrtOperand o = operand(which, n, K);
+  // Rows [d0, d0 + n) or columns of a matrix, X at the first of them.
+  CrtOperand rows(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s, int d0 = 0) const {
+    const CrtOperand o = operand(which, n, K, d0);
+    double* ss = ptr<double>(l.ss);
+    int* e = ptr<int>(l.e);
     hipLaunchKernelGGL(crt_row_norm_kernel, dim3((n + 63) / 64, (K + 255) / 256), dim3(256), 0, s, X, ld, n, K,
-                       (int)lower, ss, e);
-    hipLaunchKernelGGL(crt_row_exp_kernel, dim3((n + 255) / 256), dim3(256), 0, s, ss, e, n, K, (int)lower, o.ex);
+                       (int)lower, d0, ss, e);
+    hipLaunchKernelGGL(crt_row_exp_kernel, dim3((n + 255) / 256), dim3(256), 0, s, ss, e, n, K, (int)lower, d0, o.ex);
     hipLaunchKernelGGL(crt_rows_kernel, dim3(o.KB, (n + 63) / 64), dim3(256), 0, s, X, ld, n, K, (int)lower, o);
     return o;
   }
-  CrtOperand cols(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s) const {
-    const CrtOperand o = operand(which, n, K);
-    hipLaunchKernelGGL(crt_col_exp_kernel, dim3((n + 3) / 4), dim3(256), 0, s, X, ld, K, n, (int)lower, o.ex);
+  CrtOperand cols(int which, const double* X, int64_t ld, int n, int K, bool lower, hipStream_t s, int d0 = 0) const {
+    const CrtOperand o = operand(which, n, K, d0);
+    hipLaunchKernelGGL(crt_col_exp_kernel, dim3((n + 3) / 4), dim3(256), 0, s, X, ld, K, n, (int)lower, d0, o.ex);
     hipLaunchKernelGGL(crt_cols_kernel, dim3(o.G, (o.KB + 3) / 4), dim3(256), 0, s, X, ld, K, n, (int)lower, o);
     return o;
   }
-  CrtArgs args(const CrtOperand& a, const CrtOperand& b, int M, int N, int K, double alpha, double* C, int64_t ldc) const {
-    CrtArgs g;
-    std::memset(&g, 0, sizeof g);
-    g.a = a;
-    g.b = b;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.out = out;
-    g.out_stride = (int64_t)a.G * b.G * 64;
-    g.alpha = alpha;
-    g.Cin = C;
-    g.ldcin = ldc;
-    g.C = C;
-    g.ldc = ldc;
-    return g;
+  // Vectors [d0, d0 + n) of an operand that is there whole.
+  static CrtOperand part(CrtOperand o, int d0, int n) {
+    o.planes += (int64_t)(d0 / 16) * 1024;
+    o.ex += d0;
+    o.count = (n + 15) / 16;
+    o.d0 = d0;
+    return o;
   }
-  static void product(const CrtArgs& g, hipStream_t s) {
-    GemmArgs m{};
-    m.map_gm = crt_map_gm(g);
-    m.map_gn = crt_map_gn(g);
-    const int Mt = (g.M + CRT_BM - 1) / CRT_BM, Nt = (g.N + CRT_BN - 1) / CRT_BN;
-    hipLaunchKernelGGL(crt_gemm_kernel, dim3(XcdMap::grid(m, Mt, Nt), CRT_P), dim3(CRT_THREADS), 0, s, g);
-    hipLaunchKernelGGL(crt_finish_kernel, dim3((g.a.G + 15) / 16, g.b.G), dim3(256), 0, s, g);
+  // C (M x N) = alpha op(A) op(B) + beta C, some columns at a time: form(j0, n) gives op(B)'s columns [j0, j0 + n).
+  // C's columns may be those that form reads, not later ones.  set fills in the triangles and beta.
+  template <typename Form, typename Set>
+  void product(const CrtOperand& A, int M, int N, int K, double alpha, double* C, int64_t ldc, Form form, Set set,
+               hipStream_t s) const {
+    for (int j0 = 0; j0 < N; j0 += (int)l.cols) {
+      const int n = (int)std::min<int64_t>(l.cols, N - j0);
+      CrtArgs g;
+      std::memset(&g, 0, sizeof g);
+      g.a = A;
+      g.b = form(j0, n);
+      g.M = M;
+      g.N = n;
+      g.K = K;
+      g.out = ptr<uint32_t>(l.out);
+      g.out_stride = (int64_t)A.count * g.b.count * 64;
+      g.alpha = alpha;
+      g.C = C + (int64_t)j0 * ldc;
+      g.ldc = ldc;
+      g.Cin = g.C;
+      g.ldcin = ldc;
+      set(g);
+      GemmArgs m{};
+      m.map_gm = crt_map_gm(g);
+      m.map_gn = crt_map_gn(g);
+      const int Mt = (M + CRT_BM - 1) / CRT_BM, Nt = (n + CRT_BN - 1) / CRT_BN;
+      hipLaunchKernelGGL(crt_gemm_kernel, dim3(XcdMap::grid(m, Mt, Nt), CRT_P), dim3(CRT_THREADS), 0, s, g);
+      hipLaunchKernelGGL(crt_finish_kernel, dim3((A.count + 15) / 16, g.b.count), dim3(256), 0, s, g);
+    }
   }
 };
 
@@ -456,33 +495,32 @@ static void chol_inv_rec(Ctx* c, int a, int b, int depth, SetupSide* side, hipSt
     return;
   }
   if (crt_node(w1, w2)) {
-    const CrtSpace crt(reinterpret_cast<char*>(c->crt), c->plan.crt_w);
-    {  // L21 = A21 L11^-T
-      const CrtOperand A = crt.rows(0, A21, N, w2, w1, false, s), B = crt.rows(1, Li11, N, w1, w1, true, s);
-      CrtArgs g = crt.args(A, B, w2, w1, w1, 1.0, A21, N);
-      g.b_upper = 1;
-      CrtSpace::product(g, s);
-    }
+    const CrtSpace crt(c, std::max(w1, w2));
+    // L21 = A21 L11^-T
+    crt.product(
+        crt.rows(0, A21, N, w2, w1, false, s), w2, w1, w1, 1.0, A21, N,
+        [&](int j0, int n) { return crt.rows(1, Li11 + j0, N, n, w1, true, s, j0); },
+        [](CrtArgs& g) { g.b_upper = 1; }, s);
     const CrtOperand L21 = crt.rows(0, A21, N, w2, w1, false, s);
-    {  // A22 -= L21 L21^T
-      CrtArgs g = crt.args(L21, L21, w2, w2, w1, -1.0, A22, N);
-      g.beta = 1.0;
-      g.c_lower = 1;
-      CrtSpace::product(g, s);
-    }
-    {  // T = L21 L11^-1, kept in the block of L^-1 that its last product overwrites
-      const CrtOperand B = crt.cols(1, Li11, N, w1, w1, true, s);
-      CrtArgs g = crt.args(L21, B, w2, w1, w1, 1.0, Li21, N);
-      g.b_lower = 1;
-      CrtSpace::product(g, s);
-    }
+    // A22 -= L21 L21^T
+    crt.product(
+        L21, w2, w2, w1, -1.0, A22, N, [&](int j0, int n) { return CrtSpace::part(L21, j0, n); },
+        [](CrtArgs& g) {
+          g.beta = 1.0;
+          g.c_lower = 1;
+        },
+        s);
+    // T = L21 L11^-1, kept in the block of L^-1 that its last product overwrites
+    crt.product(
+        L21, w2, w1, w1, 1.0, Li21, N,
+        [&](int j0, int n) { return crt.cols(1, Li11 + (int64_t)j0 * N, N, n, w1, true, s, j0); },
+        [](CrtArgs& g) { g.b_lower = 1; }, s);
     chol_inv_rec(c, mid, b, depth + 1, side, s);
-    {  // (L^-1)21 = -L22^-1 T
-      const CrtOperand A = crt.rows(0, Li22, N, w2, w2, true, s), B = crt.cols(1, Li21, N, w1, w2, false, s);
-      CrtArgs g = crt.args(A, B, w2, w1, w2, -1.0, Li21, N);
-      g.a_lower = 1;
-      CrtSpace::product(g, s);
-    }
+    // (L^-1)21 = -L22^-1 T
+    crt.product(
+        crt.rows(0, Li22, N, w2, w2, true, s), w2, w1, w2, -1.0, Li21, N,
+        [&](int j0, int n) { return crt.cols(1, Li21 + (int64_t)j0 * N, N, n, w2, false, s, j0); },
+        [](CrtArgs& g) { g.a_lower = 1; }, s);
     return;
   }
   double* T = c->Xt;  // w2 x w1, ld w2
@@ -739,12 +777,14 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     return st;
   };
   // info[0]: failing pivot of M, info[1]: failing pivot of S_TL
-  double* sc = nullptr;   // with products by residues: the diagonal scaling of M
-  if (pl.crt_w) {
-    sc = reinterpret_cast<double*>(ws + pl.off_sc);
-    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(64), 0, s, sc + N, (int64_t)1, 0.0);
+  // With products by residues: the diagonal scaling of M, and whether there is any, in regions that the covariates'
+  // products fill later.
+  double* const sc = pl.crt_w ? c->W : nullptr;
+  double* const scaled = c->small;
+  if (sc) {
+    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(64), 0, s, scaled, (int64_t)1, 0.0);
     hipLaunchKernelGGL(diagonal_scale_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, Phi, ld_phi, (int)n,
-                       (int)N, h2, sc);
+                       (int)N, h2, sc, scaled);
   }
   hipLaunchKernelGGL(setup_init_kernel, dim3((unsigned)N), dim3(256), 0, s, c->L, c->Linv, (int)N, (int)n,
                      pl.leaves * NB_LEAF, Phi, ld_phi, h2, (const double*)sc, c->info);
@@ -756,7 +796,8 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
     // every side product is joined into s by its node's last product
     if (side.err != hipSuccess) return fail(hip_fail(side.err, "gls_setup: side stream fork/join"));
   }
-  if (sc) hipLaunchKernelGGL(unscale_factor_kernel, dim3(2048), dim3(256), 0, s, c->L, c->Linv, (int)N, (const double*)sc);
+  if (sc) hipLaunchKernelGGL(unscale_factor_kernel, dim3(2048), dim3(256), 0, s, c->L, c->Linv, (int)N, (const double*)sc,
+                             (const double*)scaled);
   c->ub[0] = reinterpret_cast<uint8_t*>(ws + pl.off_ub0);
   c->ub[1] = reinterpret_cast<uint8_t*>(ws + pl.off_ub1);
   if (pl.digits) {

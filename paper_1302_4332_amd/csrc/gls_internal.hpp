@@ -38,9 +38,9 @@ struct Plan {
   size_t off_side = 0;
   int64_t side_at[16] = {0};
   bool side_products = false;   // some node's product runs there
-  // setup: scratch of the products on the integer matrix cores (widest node; 0: none)
+  // setup: scratch of the products on the integer matrix cores (widest node; 0: none), over regions filled later
   int64_t crt_w = 0;
-  size_t off_crt = 0, off_sc = 0;
+  size_t off_crt = 0, crt_bytes = 0;
   int leaves = 0;   // NB_LEAF-row diagonal blocks factored: rows n..N-1 past them are the identity
   size_t total = 0;
 };

@@ -53,13 +53,13 @@ __global__ __launch_bounds__(256) void setup_init_kernel(double* __restrict__ L,
 }
 
 // Powers of two that bring M's diagonal into [1/2, 2]: sc[i] = 2^-e with
-// M[i, i] 4^-e there, and sc[N] = 1 if one of them is not 1 (else 0; set to 0
-// before the launch).  A product formed by residues rounds its operands at a
+// M[i, i] 4^-e there, and *any = 1 if one of them is not 1 (set to 0 before the
+// launch).  A product formed by residues rounds its operands at a
 // fraction of their row's norm, which is harmless against an error bound like
 // that of the Cholesky factorization, sqrt(M_ii M_jj) 2^-53 per entry, only where
 // the rows of M are of one scale.
 __global__ void diagonal_scale_kernel(const double* __restrict__ Phi, int64_t ld_phi, int n, int N, double h2,
-                                      double* __restrict__ sc) {
+                                      double* __restrict__ sc, double* __restrict__ any) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
   const double d = i < n ? h2 * Phi[(int64_t)i * (ld_phi + 1)] + (1.0 - h2) : 1.0;
@@ -69,13 +69,14 @@ __global__ void diagonal_scale_kernel(const double* __restrict__ Phi, int64_t ld
     e = e >= 0 ? e / 2 : -((1 - e) / 2);
   }
   sc[i] = ldexp(1.0, -e);
-  if (e != 0) sc[N] = 1.0;
+  if (e != 0) *any = 1.0;
 }
 
 // The factor and its inverse of M from those of the scaled matrix: L[i, j] /= sc[i], Li[i, j] *= sc[j] (lower parts).
 __global__ __launch_bounds__(256) void unscale_factor_kernel(double* __restrict__ L, double* __restrict__ Li, int N,
-                                                             const double* __restrict__ sc) {
-  if (sc[N] == 0.0) return;
+                                                             const double* __restrict__ sc,
+                                                             const double* __restrict__ any) {
+  if (*any == 0.0) return;
   for (int j = blockIdx.x; j < N; j += gridDim.x) {
     const double sj = sc[j];
     for (int i = j + threadIdx.x; i < N; i += 256) {

@@ -156,3 +156,24 @@ def test_near_singular(n):
     mine, theirs = rms(b.cpu().numpy().astype(np.longdouble)), rms(f64)
     print(f"n={n}: {mine:.1e} against {theirs:.1e}")
     assert mine <= 2.0 * theirs
+
+
+@pytest.mark.parametrize("n,scaled", [(4700, False), (9100, True)])
+def test_room_for_fewer_columns(n, scaled):
+    """Handles of small blocks form the products some 192 k columns at a time, those of large ones at once: the same
+    integers, so the same factor and the same results, bit for bit.  (9,100 samples have wide nodes at two depths.)"""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    G = torch.randn(n, 600, generator=g, device=DEV, dtype=torch.float64)
+    M = (G @ G.T) / 600 + 0.5 * torch.eye(n, dtype=torch.float64, device=DEV)
+    if scaled:
+        s = 2.0 ** torch.randint(-9, 10, (n,), generator=g, device=DEV).double()
+        M = s[:, None] * M * s
+    y = torch.randn(n, generator=g, device=DEV, dtype=torch.float64)
+    XR = torch.randn(8, n, generator=g, device=DEV, dtype=torch.float64)
+    outs = []
+    for bc in (8, 8192):
+        ctx = GLSContext(M.contiguous(), 1.0, None, y, block_cols=bc)
+        outs.append([t.cpu().numpy().copy() for t in ctx.block(XR)])
+        ctx.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8))

@@ -46,3 +46,14 @@ def test_status_strings():
     L = gls.lib()
     for code in gls.STATUS:
         assert L.gls_status_string(code)
+
+
+@pytest.mark.parametrize("n,precision,keep,most", [
+    (10000, "fp64", False, 2.90e9), (20000, "fp64", False, 10.31e9), (100000, "fp64", False, 232.5e9),
+    (100000, "fp32_ir", False, 275.0e9), (72000, "fp64", True, 291.1e9),
+])
+def test_workspace_of_large_studies(n, precision, keep, most):
+    """The factor, its inverse, the panels of the factorization and blocks of 2,048 SNPs, and nothing beside them: the
+    integer products' operands lie in regions that are filled later, so that the largest studies still fit the card."""
+    o = gls.make_opts(2048, precision=precision, keep_for_grad=keep)
+    assert gls.workspace_bytes(n, 4, o) <= most
