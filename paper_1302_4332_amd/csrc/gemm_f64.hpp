@@ -44,20 +44,36 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 enum { TRI_NONE = 0, TRI_LOWER = 1, TRI_UPPER = 2 };
 enum { MAP_GRID = 0, MAP_XCD = 1 };
 
-// Per-column flags of a block: column j is flagged if any of its count chunks
-// is (at[c ncols + j] != 0).  at == nullptr: no flags.  Eight loads in flight:
-// one after another they held up every tile of a block with 13 chunks by 3 us.
+// Per-column flags of a block in groups of 16 columns: column j is flagged if bit
+// j % 16 of a chunk's word at[c groups + j / 16] is set.  at == nullptr: no flags.
+// Eight loads in flight: one after another they held up every tile of a block with
+// 13 chunks by 3 us.
 struct ColFlags {
   const int* at;
-  int count;
-  __device__ __forceinline__ bool flagged(int j, int ncols) const {
+  int count, groups;   // chunks, words of one
+  __device__ __forceinline__ int word(int g) const {
     int f = 0;
     for (int c = 0; c < count; c += 8)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) f |= at[(int64_t)min(c + q, count - 1) * ncols + j];
-    return f != 0;
+      for (int q = 0; q < 8; ++q) f |= at[(int64_t)min(c + q, count - 1) * groups + g];
+    return f;
   }
+  __device__ __forceinline__ bool flagged(int j) const { return (word(j >> 4) >> (j & 15)) & 1; }
 };
+
+// Columns of a block in ascending order: at[0] of them, at[1 + i] the i-th.  at == nullptr: all, column i the i-th.
+struct ColList {
+  const int* at;
+  __device__ __forceinline__ int count(int ncols) const { return at ? at[0] : ncols; }
+  __device__ __forceinline__ int operator[](int i) const { return at ? at[1 + i] : i; }
+};
+
+// Lengths of a list for which a kernel does anything: above < count <= upto.
+struct ColRange {
+  int above, upto;
+  __device__ __forceinline__ bool holds(int count) const { return count > above && count <= upto; }
+};
+constexpr ColRange ANY_COUNT = {-1, 0x7fffffff};
 
 struct GemmArgs {
   const double* A; int64_t lda;     // op(A) = A (TRANS_A false) or A^T
@@ -89,7 +105,15 @@ struct GemmArgs {
   // the running value in order, so a sum split over launches at stage
   // boundaries gives bitwise the result of one launch
   int acc_cin;
-  // trmm_f64_dma_kernel only: with flags, tiles without a flagged column do
+  // trmm_f64_dma_kernel and trmm_f64_small_kernel only: C's columns (and with
+  // b_listed B's) are the listed ones, if there are as many as range says; without
+  // b_listed B holds them one after another.  The grid covers tile_cols of them (0:
+  // ncols).
+  ColList cols;
+  int b_listed;
+  ColRange range;
+  int tile_cols;
+  // trmm_f64_small_kernel only: with flags, tiles without a flagged column do
   // nothing and only flagged columns of C are stored
   ColFlags only;
   // trmm_f64_small_kernel only: rows >= kvalid of op(B) are not in memory and

@@ -20,9 +20,10 @@ namespace gls {
 // Results of a tile of 128 rows (two strips wm of 64) x BN columns: lane holds
 // C[4 ((lane >> 2) & 3) + (lane >> 4)][lane & 3] of each of its wave's 4 x FC
 // slices of 16 x 4.  red: LDS for 2 red_q BN doubles.
+// The tile's columns are j0.. of the count listed in cols.
 template <int BN, int FC, int NT>
 __device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const double (&acc)[4][FC], double* red, int ti,
-                                                  int i0, int j0, int wm, int wn) {
+                                                  int i0, int j0, int wm, int wn, ColList cols, int count) {
   constexpr int WTN = 4 * FC;
   const int lane = threadIdx.x & 63;
   if (g.red_q > 0) {
@@ -51,8 +52,9 @@ __device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const doubl
     __syncthreads();
     for (int e = threadIdx.x; e < g.red_q * BN; e += NT) {
       const int q = e / BN, jl = e % BN;
-      if (j0 + jl < g.ncols)
-        g.red_part[(int64_t)(ti * g.red_q + q) * g.ncols + j0 + jl] = red[q * BN + jl] + red[(g.red_q + q) * BN + jl];
+      if (j0 + jl < count)
+        g.red_part[(int64_t)(ti * g.red_q + q) * g.ncols + cols[j0 + jl]] =
+            red[q * BN + jl] + red[(g.red_q + q) * BN + jl];
     }
     return;
   }
@@ -62,8 +64,9 @@ __device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const doubl
     if (i >= g.mvalid) continue;
 #pragma unroll
     for (int c = 0; c < FC; ++c) {
-      const int j = j0 + wn * WTN + c * 4 + (lane & 3);
-      if (j >= g.ncols || (g.only.at && !g.only.flagged(j, g.ncols))) continue;
+      int j = j0 + wn * WTN + c * 4 + (lane & 3);
+      if (j >= count || (g.only.at && !g.only.flagged(j))) continue;
+      j = cols[j];
       double val = g.alpha * acc[a][c];
       if (g.beta != 0.0 && !g.acc_cin) val += g.beta * g.Cin[(int64_t)i + (int64_t)j * g.ldcin];
       g.C[(int64_t)i + (int64_t)j * g.ldc] = val;
@@ -112,20 +115,12 @@ void trmm_f64_dma_kernel(GemmArgs g) {
   __shared__ __align__(1024) char smem[NS * STAGE];
 
   int ti, tj;
-  const int Mt = g.M / BM, Nt = (g.ncols + BN - 1) / BN;
+  const int Mt = g.M / BM, Nt = ((g.tile_cols ? g.tile_cols : g.ncols) + BN - 1) / BN;
   if (!XcdMap::tile(g, blockIdx.x, Mt, Nt, &ti, &tj)) return;
   const int i0 = ti * BM, j0 = tj * BN;
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;   // a tile wholly above the lower part
-  if (g.only.at) {
-    int* any = reinterpret_cast<int*>(smem);
-    if (threadIdx.x == 0) *any = 0;
-    __syncthreads();
-    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && g.only.flagged(j0 + threadIdx.x, g.ncols)) *any = 1;
-    __syncthreads();
-    const bool none = *any == 0;
-    if (none) return;
-    __syncthreads();   // smem is the ring from here on
-  }
+  const int count = g.cols.count(g.ncols);
+  if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
   // k range of the tile: a lower-triangular A ends at the tile's last row, an upper-triangular one starts at its
   // first, a lower-triangular B starts at the tile's first column (each holds explicit zeros across its diagonal
   // block)
@@ -150,11 +145,11 @@ void trmm_f64_dma_kernel(GemmArgs g) {
   {
     const int jl = 8 * wave + (lane >> 3);
     const int c = (lane & 7) ^ (jl & 7);
-    const int j = imin(j0 + jl, g.ncols - 1) - j0;   // columns past the end: any valid one, dropped
-    voff[2] = (uint32_t)((2 * c + (int64_t)j * g.ldb) * 8);
+    const int j = imin(j0 + jl, count - 1);   // columns past the end: any valid one, dropped
+    voff[2] = (uint32_t)((2 * c + (int64_t)(g.b_listed ? g.cols[j] - g.cols[j0] : j - j0) * g.ldb) * 8);
   }
   const double* Abase = g.A + i0;
-  const double* Bbase = g.B + (int64_t)j0 * g.ldb;
+  const double* Bbase = g.B + (int64_t)(g.b_listed ? g.cols[j0] : j0) * g.ldb;
   const uint32_t lds0 = lds_address(smem);
   auto issue = [&](int kstep) {
     const uint32_t base = lds0 + (uint32_t)((kstep % NS) * STAGE);
@@ -221,7 +216,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
     }
   }
 
-  trmm_f64_epilogue<BN, FC, DB_THREADS>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn);
+  trmm_f64_epilogue<BN, FC, DB_THREADS>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, g.cols, count);
 }
 
 // The same product, bitwise, for short sums and grids of few tiles: 128 x BN tiles (BN = 16 or
@@ -246,11 +241,13 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   const int ti = g.map_desc ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y, tj = blockIdx.x;
   const int i0 = ti * BM, j0 = tj * BN;
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;
+  const int count = g.cols.count(g.ncols);
+  if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
   if (g.only.at) {
     int* any = reinterpret_cast<int*>(smem);
     if (threadIdx.x == 0) *any = 0;
     __syncthreads();
-    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && g.only.flagged(j0 + threadIdx.x, g.ncols)) *any = 1;
+    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && g.only.flagged(j0 + threadIdx.x)) *any = 1;
     __syncthreads();
     const bool none = *any == 0;
     if (none) return;
@@ -284,12 +281,12 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
 #pragma unroll
     for (int c = wave; c < BN; c += NW) {
       const int j = j0 + c;
-      const double* col = g.B + (int64_t)j * g.ldb;
+      const double* col = g.B + (int64_t)(g.b_listed && j < count ? g.cols[j] : j) * g.ldb;
       double v[KMAX / 64];
 #pragma unroll
       for (int u = 0; u < KMAX / 64; ++u) {
         const int k = it * BK + lane + 64 * u;
-        v[u] = (j < g.ncols && k < kend) ? col[k] : 0.0;
+        v[u] = (j < count && k < kend) ? col[k] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < KMAX / 64; ++u) Bs[c * LDB + lane + 64 * u] = v[u];
@@ -330,7 +327,7 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
                                                        acc[a][0], 0, 0, 0);
     }
   }
-  trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn);
+  trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, g.cols, count);
 }
 
 // Whether a product of M rows, ncols columns and K goes to it.  Short sums over
@@ -344,17 +341,21 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
 // (120) 302 against 195 and 380 (240) 302 against 358; n = 10,000, 200 (316) 883 against
 // 733.  A study of 10,000 samples, whose setup has such products, takes 18.85 ms
 // with 128 for K = 1,280 too and 18.6 with 240.
+inline int small_tiles(int K) { return K <= 1024 ? 128 : K <= 1280 ? 240 : K <= 8192 ? 128 : 320; }
 inline bool small_product(int M, int ncols, int K) {
   if (K <= 512 && M <= 512) return true;
-  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= (K <= 1024 ? 128 : K <= 1280 ? 240 : K <= 8192 ? 128 : 320);
+  return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= small_tiles(K);
 }
+
+// Columns that a tile's lane offsets into B span: 64 adjacent ones, or with a list any of the block.
+inline int64_t dma_b_span(int ncols, bool listed) { return listed ? ncols - 1 : 63; }
 
 // Whether the two kernels above apply to a product without transposes: A
 // full, lower or upper triangular, B full or lower triangular (diagonal offsets 0),
 // 16-byte aligned operands with even leading dimensions,
 // K a multiple of 16, the rows of A up to M rounded up to 128 inside A's
 // leading dimension (they are read; rows past M are not stored), and lane
-// offsets within a stage (15 columns of A, 63 columns of B) below 2^32 bytes.
+// offsets within a stage (15 columns of A, a tile's columns of B) below 2^32 bytes.
 inline bool trmm_dma_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   const bool small = small_product(g.M, g.ncols, g.K);   // takes any B
@@ -363,15 +364,16 @@ inline bool trmm_dma_ok(const GemmArgs& g) {
   if (g.M <= 0 || g.K % DB_BK || g.K <= 0 || g.ncols <= 0 || g.mvalid > g.M) return false;
   if (g.lda < (int64_t)(g.M + DB_BM - 1) / DB_BM * DB_BM || g.ldb < (g.kvalid ? g.kvalid : g.K)) return false;
   if (small) return true;
-  if ((15 * g.lda + DB_BM) * 8 >= ((int64_t)1 << 32) || (63 * g.ldb + DB_BK) * 8 >= ((int64_t)1 << 32)) return false;
+  if ((15 * g.lda + DB_BM) * 8 >= ((int64_t)1 << 32) || (dma_b_span(g.ncols, g.b_listed) * g.ldb + DB_BK) * 8 >= ((int64_t)1 << 32))
+    return false;
   return true;
 }
 
 // Whether a column-major B operand with K rows can feed trmm_f64_dma_kernel
 // as it is (otherwise it is first copied into a buffer of that shape).
-inline bool dma_b_operand_ok(const double* B, int64_t ldb, int64_t K) {
+inline bool dma_b_operand_ok(const double* B, int64_t ldb, int64_t K, int ncols, bool listed) {
   return ((uintptr_t)B & 15) == 0 && (ldb & 1) == 0 && K % DB_BK == 0 && ldb >= K &&
-         (63 * ldb + DB_BK) * 8 < ((int64_t)1 << 32);
+         (dma_b_span(ncols, listed) * ldb + DB_BK) * 8 < ((int64_t)1 << 32);
 }
 
 }  // namespace gls

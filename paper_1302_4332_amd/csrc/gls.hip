@@ -272,27 +272,57 @@ static void gemm_map(bool ta, bool tb, const GemmArgs& g, hipStream_t s) {
   else launch_gemm_cfg<true, true, MAP, VEC>(g, s);
 }
 
-// The direct-load kernel for a product it takes (false: not launched).
+// From this length of the sums on, a product whose columns are listed runs on the kernel that suits their number, which
+// only the device knows: the others are launched as well and do nothing (5 us each).  A product of few columns takes as
+// long as its longest tile: n = 10,000, 1,000 SNPs of which one in 64 is fractional 1.77 -> 1.30 ms, n = 5,008, 4,096
+// SNPs 0.96 -> 0.61.
+constexpr int LISTED_K = 4096;
+
+// The direct-load kernels for a product they take (false: not launched).
 static bool gemm_dma(const GemmArgs& g, hipStream_t s) {
   if (!trmm_dma_ok(g)) return false;
   GemmArgs d = g;
-  if (small_product(g.M, g.ncols, g.K)) {
-    const unsigned Mt = (g.M + DB_BM - 1) / DB_BM;
-    d.M = (int)Mt * DB_BM;
-    if (g.K <= 512 || g.K > 1024)
-      hipLaunchKernelGGL((trmm_f64_small_kernel<16, 512>), dim3((g.ncols + 15) / 16, Mt), dim3(512), 0, s, d);
-    else
-      hipLaunchKernelGGL((trmm_f64_small_kernel<8, 1024>), dim3((g.ncols + 7) / 8, Mt), dim3(256), 0, s, d);
-    return true;
-  }
   const int Mt = (g.M + DB_BM - 1) / DB_BM, Nt = (g.ncols + DB_BN - 1) / DB_BN;
   d.M = Mt * DB_BM;   // rows past mvalid are computed from A's padding and not stored
-  if ((int64_t)Mt * Nt <= DB_NARROW_TILES) {
-    const int Nh = (g.ncols + DB_BN / 2 - 1) / (DB_BN / 2);
-    hipLaunchKernelGGL(trmm_f64_dma_kernel<DB_BN / 2>, dim3(XcdMap::grid(d, Mt, Nh)), dim3(DB_THREADS), 0, s, d);
-  } else {
-    hipLaunchKernelGGL(trmm_f64_dma_kernel<DB_BN>, dim3(XcdMap::grid(d, Mt, Nt)), dim3(DB_THREADS), 0, s, d);
+  // each kernel for lists of more columns than `above` and at most `upto`; the grid covers that many
+  auto with = [&](int above, int upto) {
+    GemmArgs q = d;
+    q.range = ColRange{above, upto};
+    q.tile_cols = std::min(upto, g.ncols);
+    return q;
+  };
+  auto few = [&](int upto) {
+    const GemmArgs q = with(-1, upto);
+    if (g.K <= 512 || g.K > 1024)
+      hipLaunchKernelGGL((trmm_f64_small_kernel<16, 512>), dim3((q.tile_cols + 15) / 16, Mt), dim3(512), 0, s, q);
+    else
+      hipLaunchKernelGGL((trmm_f64_small_kernel<8, 1024>), dim3((q.tile_cols + 7) / 8, Mt), dim3(256), 0, s, q);
+  };
+  auto narrow = [&](int above, int upto) {
+    constexpr int BN = DB_BN / 2;
+    const GemmArgs q = with(above, upto);
+    hipLaunchKernelGGL(trmm_f64_dma_kernel<BN>, dim3(XcdMap::grid(q, Mt, (q.tile_cols + BN - 1) / BN)), dim3(DB_THREADS), 0,
+                       s, q);
+  };
+  if (small_product(g.M, g.ncols, g.K)) {
+    few(ANY_COUNT.upto);
+    return true;
   }
+  if ((int64_t)Mt * Nt <= DB_NARROW_TILES) {
+    narrow(-1, ANY_COUNT.upto);
+    return true;
+  }
+  int above = -1;
+  if (g.cols.at && g.K >= LISTED_K) {
+    const int f = small_tiles(g.K) / Mt * DB_BN, n = DB_NARROW_TILES / Mt * DB_BN;
+    if (f > 0) few(above = f);
+    if (n > f) {
+      narrow(above, n);
+      above = n;
+    }
+  }
+  const GemmArgs q = with(above, ANY_COUNT.upto);
+  hipLaunchKernelGGL(trmm_f64_dma_kernel<DB_BN>, dim3(XcdMap::grid(q, Mt, Nt)), dim3(DB_THREADS), 0, s, q);
   return true;
 }
 
@@ -607,20 +637,42 @@ static void whiten_covariates(Ctx* c, const double* XL, int64_t ld_xl, const dou
   hipLaunchKernelGGL(small_factor_kernel, dim3(1), dim3(64), 0, s, c->gram, p, c->small, c->info + 1);
 }
 
-// X~ (rows x mb, ld N) = L^-1 X   for an n x mb block X (ld ldx) summed over
-// its first K rows: K = n, or n rounded up to 16 when X's rows n..K-1 are
-// zero.  rows = N, or n rounded up to the product's 128-row tiles when only
-// the sample rows (and the zero rows up to that tile edge) are read later.
-// With flags, only flagged columns are formed.
-static void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, double* Xt, ColFlags only,
+// The columns of a block that the FP64 product forms: all, or the flagged ones, by their list or (without one, on the
+// kernel of few tiles only) by their flags.  A copy of the block in c->x64 holds the listed columns one after another.
+struct Fp64Columns {
+  ColFlags flags{nullptr, 0, 0};
+  ColList list{nullptr};
+};
+
+// The FP64 product's block operand: X (ld), of which the first K rows are summed over.
+struct Fp64Operand {
+  const double* X;
+  int64_t ld;
+  int K;
+  int kvalid;    // rows of X in memory, if fewer than K (0: all)
+  bool copied;   // X holds the listed columns, one after another (if there is a list)
+};
+
+static void set_operand(GemmArgs* g, const Fp64Operand& x, const Fp64Columns& only) {
+  g->kvalid = x.kvalid;
+  g->cols = only.list;
+  g->b_listed = only.list.at != nullptr && !x.copied;
+  if (!only.list.at) g->only = only.flags;
+}
+
+// X~ (rows x mb, ld N) = L^-1 X for an n x mb block X summed over its first K
+// rows: n rounded up to 16.  rows = N, or n rounded up to the product's 128-row
+// tiles when only the sample rows (and the zero rows up to that tile edge) are
+// read later.
+// As whiten_fp64_fused, false if the direct-load kernel does not take the shape.
+static bool whiten_fp64(Ctx* c, const Fp64Operand& x, int mb, int rows, double* Xt, const Fp64Columns& only,
                         hipStream_t s) {
-  GemmArgs g = gemm_args(c->Linv, c->N, X, ldx, Xt, c->N, rows, mb, K, 1.0);
+  GemmArgs g = gemm_args(c->Linv, c->N, x.X, x.ld, Xt, c->N, rows, mb, x.K, 1.0);
   g.a_tri = TRI_LOWER;
   g.a_diag = 0;
   g.map_desc = 1;
-  g.only = only;
-  if (K > c->n && X != c->x64) g.kvalid = (int)c->n;
-  gemm(false, false, true, g, s);
+  set_operand(&g, x, only);
+  return gemm_dma(g, s);
 }
 
 // The same product with the per-SNP sums fused into its epilogue: instead of
@@ -628,9 +680,9 @@ static void whiten_fp64(Ctx* c, const double* X, int64_t ldx, int mb, int K, int
 // [X~_L | y~] and of x~^2 over the tile's rows ((t (p + 1) + q) mb + j).
 // Returns false, launching nothing, when the direct-load kernel does not
 // take the shape.
-static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int K, int rows, ColFlags only,
+static bool whiten_fp64_fused(Ctx* c, const Fp64Operand& x, int mb, int rows, const Fp64Columns& only,
                               hipStream_t s) {
-  GemmArgs g = gemm_args(c->Linv, c->N, X, ldx, c->Xt, c->N, rows, mb, K, 1.0);
+  GemmArgs g = gemm_args(c->Linv, c->N, x.X, x.ld, c->Xt, c->N, rows, mb, x.K, 1.0);
   g.a_tri = TRI_LOWER;
   g.a_diag = 0;
   g.map_desc = 1;
@@ -638,8 +690,7 @@ static bool whiten_fp64_fused(Ctx* c, const double* X, int64_t ldx, int mb, int 
   g.ld_red_W = c->N;
   g.red_part = c->Xt;
   g.red_q = c->p + 1;
-  g.only = only;
-  if (K > c->n && X != c->x64) g.kvalid = (int)c->n;
+  set_operand(&g, x, only);
   return gemm_dma(g, s);
 }
 
@@ -1339,38 +1390,40 @@ static void lp_solve(Ctx* c, const double* src, int64_t lds, int mb, double beta
 // every whitened block are zero off the identity padding, so sums may run to it.
 static int k16(const Ctx* c) { return (int)((c->n + DB_BK - 1) / DB_BK * DB_BK); }
 
-// Columns of a block into the zero-padded FP64 buffer x64 (rows n..rows-1 zero): all of them, or only the flagged.
+// Columns of a block into a zero-padded FP64 buffer (ld N, rows n..rows-1 zero): all of them, or those that the FP64
+// product forms (listed ones one after another, flagged ones in place).
 template <int SRC>
-static void widen_columns(Ctx* c, const void* src, int64_t ld, int mb, int rows, ColFlags flags, hipStream_t s) {
+static void widen_columns(Ctx* c, const void* src, int64_t ld, int mb, int rows, const Fp64Columns& only, double* out,
+                          hipStream_t s) {
   hipLaunchKernelGGL(widen_columns_kernel<SRC>, dim3(std::min(mb, 1024), (unsigned)((rows + WIDEN_ROWS - 1) / WIDEN_ROWS)),
-                     dim3(256), 0, s, src, ld, (int)c->n, rows, mb, c->x64, c->N, flags);
+                     dim3(256), 0, s, src, ld, (int)c->n, rows, mb, out, c->N,
+                     only.list.at ? ColFlags{nullptr, 0, 0} : only.flags, only.list);
 }
 
-// The FP64 block operand of the product of rows rows with L^-1: X itself when
-// the product is a small one, or its layout feeds the direct-load kernel (n a
-// multiple of 16, 16-byte aligned, even ld), else a copy in c->x64 (ld N) whose rows n..K-1 are zero (with flags, of
-// the flagged columns).  Blocks already in c->x64 (widened bytes) carry zero
-// rows up to N.  Sets *K, the rows the product sums over.
-static const double* fp64_operand(Ctx* c, const double* X, int64_t* ldx, int mb, int rows, int* K, ColFlags flags,
-                                  hipStream_t s) {
-  *K = k16(c);
-  if (X == c->x64 || small_product(rows, mb, *K)) return X;
-  if (dma_b_operand_ok(X, *ldx, c->n)) return X;   // n is a multiple of 16
-  widen_columns<OZ_F64>(c, X, *ldx, mb, *K, flags, s);
-  *ldx = c->N;
-  return c->x64;
+// The block X (ld) as the operand of the product of rows rows with L^-1: itself when the product is a small one, or its
+// layout feeds the direct-load kernel (n a multiple of 16, 16-byte aligned, even ld; a block already in c->x64, widened
+// bytes, has it, with zero rows up to N), else a copy in `room` (N x mb) of the columns that the product forms.
+static Fp64Operand fp64_operand(Ctx* c, const double* X, int64_t ld, int mb, int rows, const Fp64Columns& only,
+                                double* room, hipStream_t s) {
+  const int K = k16(c), held = X == c->x64 ? K : (int)c->n;
+  if (small_product(rows, mb, K)) return Fp64Operand{X, ld, K, held < K ? held : 0, false};
+  if (dma_b_operand_ok(X, ld, held, mb, only.list.at != nullptr)) return Fp64Operand{X, ld, K, 0, false};
+  widen_columns<OZ_F64>(c, X, ld, mb, K, only, room, s);
+  return Fp64Operand{room, c->N, K, 0, true};
 }
 
 // Products with L^-1 of SNPs that are whole numbers, on the integer matrix
 // cores.  The block's int8 operand lies in units[], after the per-SNP sums of
 // the two products (their 128- and 32-row tiles) in c->Xt:
-// (p + 1) (8 / 128 + 8 / 32) + 1 + 1 / 64 < 7.6 of the 8 bytes per row and SNP.
+// (p + 1) (8 / 128 + 8 / 32) + 1 + 1 / 1,024 < 7.6 of the 8 bytes per row and SNP, of
+// 768 rows or more where there are flags, and behind them two words and a bit a SNP.
 struct WholeBlock {
   uint8_t* units = nullptr;
   int* flags_at = nullptr;
   double* part8 = nullptr;
   int nkb = 0, Jb = 0, Mt8 = 0;
-  ColFlags flags{nullptr, 0};
+  ColList whole{nullptr};   // the integer product's columns, where it takes them by a list
+  Fp64Columns f64;          // the FP64 product's
 };
 
 static WholeBlock whole_block(Ctx* c, double* region, bool sums, int mb, int rows) {
@@ -1398,7 +1451,7 @@ static void pack_units(Ctx* c, const void* src, int64_t ld, int mb, bool check, 
   while (chunk > 4 && w->Jb * ((w->nkb + chunk - 1) / chunk) < 1024) chunk /= 2;
   const int chunks = (w->nkb + chunk - 1) / chunk;
   const int xmax = (int)std::min<int64_t>(127, (((int64_t)1 << 31) - 1) / (128 * c->n));
-  if (check) w->flags = ColFlags{w->flags_at, chunks};
+  if (check) w->f64.flags = ColFlags{w->flags_at, chunks, w->Jb};
   hipLaunchKernelGGL(pack_units_kernel<SRC>, dim3(w->Jb, chunks), dim3(256), 0, s, src, ld, (int)c->n, w->nkb, mb,
                      w->Jb, chunk, xmax, w->units, check ? w->flags_at : nullptr, (const int*)(c->ex + c->N));
 }
@@ -1408,11 +1461,38 @@ static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w,
   else pack_units<OZ_F64>(c, X, ld, mb, true, w, s);
 }
 
+static bool whole_small(int Mt, int mb) { return (int64_t)Mt * ((mb + OZS_BN - 1) / OZS_BN) <= OZS_TILES; }
+
+// The two products' columns as lists, unless either product is a single round of workgroups on its kernel of few tiles
+// (256 of 128 x 16 for the FP64 one), where each may as well look at every tile: n = 1,000, 48 SNPs, half of them imputed,
+// 50 us (40 if all are, 83 before there were two products), n = 1,500, 300 SNPs 81 (66, 125).  The lists' launch takes 5.
+static void split_columns(WholeBlock* w, int mb, int rows, hipStream_t s) {
+  const int64_t tiles = (int64_t)((rows + DB_BM - 1) / DB_BM) * ((mb + DB_BN - 1) / DB_BN);
+  if (whole_small(w->Mt8, mb) && tiles <= 64) return;
+  int* words = w->flags_at + (size_t)w->f64.flags.count * w->Jb;
+  int *whole = words + w->Jb, *f64 = whole + mb + 1;
+  hipLaunchKernelGGL(columns_kernel, dim3(1), dim3(CL_THREADS), 0, s, w->f64.flags, mb, words, whole, f64);
+  w->f64.flags = ColFlags{words, 1, w->Jb};
+  w->f64.list = ColList{f64};
+  w->whole = ColList{whole};
+}
+
 template <int S>
-static void launch_whole(const OzArgs& a, hipStream_t s) {
-  if (a.Mt * ((a.ncols + OZS_BN - 1) / OZS_BN) <= OZS_TILES) {
-    hipLaunchKernelGGL(ozaki_i8_small_kernel<S>, dim3((a.ncols + OZS_BN - 1) / OZS_BN, a.Mt), dim3(OZS_THREADS), 0, s, a);
+static void launch_whole(OzArgs a, hipStream_t s) {
+  auto few = [&](int upto) {
+    a.range = ColRange{-1, upto};
+    hipLaunchKernelGGL(ozaki_i8_small_kernel<S>, dim3((std::min(upto, a.ncols) + OZS_BN - 1) / OZS_BN, a.Mt),
+                       dim3(OZS_THREADS), 0, s, a);
+  };
+  a.range = ANY_COUNT;
+  if (whole_small(a.Mt, a.ncols)) {
+    few(ANY_COUNT.upto);
     return;
+  }
+  if (a.cols.at && a.N >= LISTED_K && OZS_TILES / a.Mt > 0) {   // as gemm_dma does
+    const int f = OZS_TILES / a.Mt * OZS_BN;
+    few(f);
+    a.range = ColRange{f, ANY_COUNT.upto};
   }
   GemmArgs m{};
   m.map_gm = OZ_MAP_GM;
@@ -1432,7 +1512,8 @@ static void whole_product(Ctx* c, const WholeBlock& w, int mb, double* Xt, hipSt
   a.N = (int)c->N;
   a.Mt = w.Mt8;
   a.ncols = mb;
-  a.flags = w.flags;
+  a.cols = w.whole;
+  if (!w.whole.at) a.flags = w.f64.flags;
   if (Xt) {
     a.C = Xt;
     a.ldc = c->N;
@@ -1455,6 +1536,12 @@ static void residual_fp64(Ctx* c, const double* X, int64_t ldx, int mb, hipStrea
   g.a_diag = 0;
   g.map_desc = 1;
   gemm(false, false, true, g, s);
+}
+
+// The operands of a block's FP64 product are laid out for its kernels (fp64_operand): a refusal is a mistake here.
+static gls_status shape_fail() {
+  set_err("internal: the FP64 product refused a block's operands");
+  return GLS_ERR_STATE;
 }
 
 gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double* b, int64_t ld_b, double* s2,
@@ -1485,14 +1572,14 @@ gls_status block_forward(Ctx* c, int mb, const double* XR, int64_t ld_xr, double
       if (whole_f64(c)) {
         w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
         pack_f64(c, XR, ld_xr, mb, &w, s);
+        split_columns(&w, mb, rows, s);
         whole_product(c, w, mb, nullptr, s);
       }
-      int K = 0;
-      const double* X = fp64_operand(c, XR, &ld_xr, mb, rows, &K, w.flags, s);
-      whiten_fp64_fused(c, X, ld_xr, mb, K, rows, w.flags, s);
+      const Fp64Operand x = fp64_operand(c, XR, ld_xr, mb, rows, w.f64, c->x64, s);
+      if (!whiten_fp64_fused(c, x, mb, rows, w.f64, s)) return shape_fail();
     }
     PhaseTimer t(c, PH_SNP, s);
-    snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.flags, mb, b, ld_b, s2, v, st, s);
+    snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.f64.flags, mb, b, ld_b, s2, v, st, s);
     return GLS_OK;
   }
   {
@@ -1508,10 +1595,10 @@ namespace gls {
 
 // Dosage bytes (or packed 2-bit dosages) of a block widened into the zero-padded FP64 buffer x64 (ld N).
 void widen_u8(Ctx* c, const uint8_t* G, int64_t ldg, int mb, hipStream_t s) {
-  widen_columns<OZ_U8>(c, G, ldg, mb, (int)c->N, ColFlags{nullptr, 0}, s);
+  widen_columns<OZ_U8>(c, G, ldg, mb, (int)c->N, Fp64Columns{}, c->x64, s);
 }
 void widen_u2(Ctx* c, const uint8_t* G2, int64_t ldg, int mb, hipStream_t s) {
-  widen_columns<OZ_U2>(c, G2, ldg, mb, (int)c->N, ColFlags{nullptr, 0}, s);
+  widen_columns<OZ_U2>(c, G2, ldg, mb, (int)c->N, Fp64Columns{}, c->x64, s);
 }
 
 // Bytes (or 2-bit codes) on the integer matrix cores without a detour over
@@ -1529,15 +1616,16 @@ static gls_status block_forward_whole(Ctx* c, int mb, const uint8_t* G, int64_t 
     w = whole_block(c, c->Xt, true, mb, (int)((c->n + OZ_TM - 1) / OZ_TM * OZ_TM));
     const bool check = c->opts.precision != GLS_INT8_EMU;
     pack_units<SRC>(c, G, ldg, mb, check, &w, s);
+    const int K = k16(c);
+    if (check) split_columns(&w, mb, rows, s);
     whole_product(c, w, mb, nullptr, s);
     if (check) {
-      const int K = k16(c);
-      widen_columns<SRC>(c, G, ldg, mb, K, w.flags, s);
-      whiten_fp64_fused(c, c->x64, c->N, mb, K, rows, w.flags, s);
+      widen_columns<SRC>(c, G, ldg, mb, K, w.f64, c->x64, s);
+      if (!whiten_fp64_fused(c, Fp64Operand{c->x64, c->N, K, 0, true}, mb, rows, w.f64, s)) return shape_fail();
     }
   }
   PhaseTimer t(c, PH_SNP, s);
-  snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.flags, mb, b, ld_b, s2, v, st, s);
+  snp_partials_solve(c, rows / DB_BM, w.part8, w.Mt8, w.f64.flags, mb, b, ld_b, s2, v, st, s);
   return GLS_OK;
 }
 
@@ -1598,7 +1686,7 @@ static void wbar_shared_p(Ctx* c, hipStream_t s) {
   }
 
 // X~ of a block again (the adjoint recomputes instead of storing X~_R).
-static void recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, hipStream_t s) {
+static gls_status recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, hipStream_t s) {
   if (c->plan.lp_bytes) {
     lp_solve(c, XR, ld_xr, mb, 0.0, s);
     for (int sweep = 0; sweep < c->opts.refine_sweeps; ++sweep) {
@@ -1610,19 +1698,22 @@ static void recompute_whitened(Ctx* c, int mb, const double* XR, int64_t ld_xr, 
     if (whole_f64(c)) {   // the int8 operand in Xtb, which is written after X~
       w = whole_block(c, c->Xtb, false, mb, (int)c->N);
       pack_f64(c, XR, ld_xr, mb, &w, s);
+      split_columns(&w, mb, (int)c->N, s);
       whole_product(c, w, mb, c->Xt, s);
     }
-    int K = 0;
-    const double* X = fp64_operand(c, XR, &ld_xr, mb, (int)c->N, &K, w.flags, s);
-    whiten_fp64(c, X, ld_xr, mb, K, (int)c->N, c->Xt, w.flags, s);
+    // a copy of a block that lies in x64 itself goes to Xb, which is written after X~
+    const Fp64Operand x = fp64_operand(c, XR, ld_xr, mb, (int)c->N, w.f64, XR == c->x64 ? c->Xb : c->x64, s);
+    if (!whiten_fp64(c, x, mb, (int)c->N, c->Xt, w.f64, s)) return shape_fail();
   }
+  return GLS_OK;
 }
 
 gls_status block_backward(Ctx* c, int mb, const double* XR, int64_t ld_xr, const double* bbar, const double* s2bar,
                           const double* vbar, double* XR_grad, hipStream_t s) {
   const int64_t N = c->N;
   PhaseTimer t(c, PH_BACKWARD, s);
-  recompute_whitened(c, mb, XR, ld_xr, s);
+  const gls_status st = recompute_whitened(c, mb, XR, ld_xr, s);
+  if (st != GLS_OK) return st;
 #define GLS_ADJ(P) adjoint_snp_p<P>(c, mb, bbar, s2bar, vbar, s)
   GLS_P_SWITCH(c->p, GLS_ADJ)
 #undef GLS_ADJ

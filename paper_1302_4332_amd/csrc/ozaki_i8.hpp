@@ -164,12 +164,14 @@ __device__ __forceinline__ uint32_t unpack_quad(const uint8_t* __restrict__ G2, 
 enum { OZ_F64 = 0, OZ_F64_ALIGNED = 1, OZ_U8 = 2, OZ_U2 = 3 };
 
 // A block's SNP values as units [k block][SNP group of 16] (Jb groups).  flags
-// (nullptr: none are needed) receives, for every k chunk c and SNP j,
-// flags[c mb + j] = 1 if a value of the chunk is not a whole number of magnitude
-// at most xmax, or always if *ok is 0.  A wave whose SNPs are all flagged stops: their results come
+// (nullptr: none are needed) receives, for every k chunk c and SNP group, the SNPs
+// with a value in the chunk that is not a whole number of magnitude
+// at most xmax (ColFlags; all SNPs if *ok is 0).  A wave whose SNPs are all flagged stops: their results come
 // from the FP64 product.  Workgroup (group, chunk of chunk_kb k blocks), four
 // waves over the chunk's k blocks; a lane holds its 16 bytes' values, so FP64
-// columns are read as whole 128-byte lines.
+// columns are read as whole 128-byte lines.  The waves first look at four values of
+// each SNP, the same ones: a group of imputed SNPs mostly ends there, having read
+// 8 KB instead of a k block a wave.
 template <int SRC>
 __global__ __launch_bounds__(256) void pack_units_kernel(const void* __restrict__ src, int64_t ld, int n, int nkb,
                                                          int mb, int Jb, int chunk_kb, int xmax,
@@ -182,6 +184,13 @@ __global__ __launch_bounds__(256) void pack_units_kernel(const void* __restrict_
   const unsigned cols = (mb - jb * 16 >= 16) ? 0xffffu : (1u << (mb - jb * 16)) - 1u;
   const int kb1 = min(nkb, (int)(blockIdx.y + 1) * chunk_kb);
   unsigned bad = (flags && !*ok_study) ? cols : 0u;   // flagged columns (wave-uniform)
+  if constexpr (SRC == OZ_F64 || SRC == OZ_F64_ALIGNED) {
+    const int k = blockIdx.y * chunk_kb * 64 + kq * 16;
+    const double x = (col && k < n) ? static_cast<const double*>(src)[(int64_t)j * ld + k] : 0.0;
+    const int v = (int)x;   // saturates; NaN gives 0
+    const unsigned long long m = __ballot(!((double)v == x && v <= xmax && v >= -xmax));
+    bad |= (unsigned)((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xffffu);
+  }
   if (bad != cols) for (int kb = blockIdx.y * chunk_kb + wave; kb < kb1; kb += 4) {
     const int k0 = kb * 64 + kq * 16;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
@@ -247,23 +256,74 @@ __global__ __launch_bounds__(256) void pack_units_kernel(const void* __restrict_
   if (flags) {
     if (lane == 0) seen[wave] = (int)bad;
     __syncthreads();
-    if (threadIdx.x < 16 && j < mb)
-      flags[(int64_t)blockIdx.y * mb + j] = ((seen[0] | seen[1] | seen[2] | seen[3]) >> threadIdx.x) & 1;
+    if (threadIdx.x == 0) flags[(int64_t)blockIdx.y * Jb + jb] = seen[0] | seen[1] | seen[2] | seen[3];
+  }
+}
+
+// The two products' columns of a block, from its flags: words, the flags of a single
+// chunk, and the lists of the columns that the integer (whole) and the FP64 product
+// (f64) form.  Products that formed every tile of the block with one of their
+// columns did each other's work where the two kinds are mixed: 8,192 SNPs at n =
+// 10,000 with one whole in 64 took 15.7 ms, where the FP64 product of all of them
+// takes 13.3, and now take 13.8; with every other one whole 8.1.  One workgroup, a
+// group of 16 columns a thread at a time, 5 us.  Blocks of few SNPs do without (see
+// split_columns).
+constexpr int CL_THREADS = 1024;
+
+__global__ __launch_bounds__(CL_THREADS) void columns_kernel(ColFlags flags, int mb, int* __restrict__ words,
+                                                             int* __restrict__ whole, int* __restrict__ f64) {
+  __shared__ int sums[CL_THREADS / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int before = 0;   // flagged columns of the groups below g0
+  for (int g0 = 0; g0 < flags.groups; g0 += CL_THREADS) {
+    const int g = g0 + t;
+    const int w = g < flags.groups ? flags.word(g) : 0;   // no bits past the last column
+    const int own = __popc(w);
+    int sum = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(sum, off, 64);
+      if (lane >= off) sum += o;
+    }
+    if (lane == 63) sums[wave] = sum;
+    __syncthreads();
+    int r = before + sum - own;   // flagged columns before this group's next one
+    for (int o = 0; o < CL_THREADS / 64; ++o) {
+      if (o < wave) r += sums[o];
+      before += sums[o];
+    }
+    if (g < flags.groups) {
+      words[g] = w;
+      const int c1 = min(16, mb - 16 * g);
+      for (int c = 0; c < c1; ++c) {
+        const int j = 16 * g + c;
+        if ((w >> c) & 1) f64[1 + r++] = j;
+        else whole[1 + j - r] = j;
+      }
+    }
+    __syncthreads();   // sums is written again
+  }
+  if (t == 0) {
+    f64[0] = before;
+    whole[0] = mb - before;
   }
 }
 
 // Columns of a block widened (or copied) into the zero-padded FP64 buffer out
 // (ld ldo, rows n..rows-1 zero): every column, or with flags only the flagged
-// ones.  Workgroup (x, y): rows [WIDEN_ROWS y, ...) of columns x, x + gridDim.x, ...
+// ones, or with a list the listed ones, one after another.  Workgroup (x, y): rows
+// [WIDEN_ROWS y, ...) of columns x, x + gridDim.x, ...
 constexpr int WIDEN_ROWS = 2048;
 
 template <int SRC>
 __global__ __launch_bounds__(256) void widen_columns_kernel(const void* __restrict__ src, int64_t ld, int n, int rows,
                                                             int mb, double* __restrict__ out, int64_t ldo,
-                                                            ColFlags flags) {
-  for (int j = blockIdx.x; j < mb; j += gridDim.x) {
-    if (flags.at && !flags.flagged(j, mb)) continue;
-    double* o = out + (int64_t)j * ldo;
+                                                            ColFlags flags, ColList cols) {
+  const int count = cols.count(mb);
+  for (int i = blockIdx.x; i < count; i += gridDim.x) {
+    const int j = cols[i];
+    if (flags.at && !flags.flagged(j)) continue;
+    double* o = out + (int64_t)i * ldo;
     const int k1 = min(rows, (int)(blockIdx.y + 1) * WIDEN_ROWS);
 #pragma unroll 4
     for (int k = blockIdx.y * WIDEN_ROWS + threadIdx.x; k < k1; k += 256) {
@@ -285,7 +345,9 @@ struct OzArgs {
   const uint8_t* B;       // units [k block][Jb]
   int Jb;                 // SNP groups of 16
   int N, Mt, ncols;       // Mt row tiles of OZ_BM
-  ColFlags flags;         // flagged columns are left out (at == nullptr: none)
+  ColList cols;           // the columns to form, if there are as many as range says
+  ColRange range;
+  ColFlags flags;         // without a list: flagged columns are left out (at == nullptr: none)
   // per-SNP sums (red_q > 0): red_part[(t red_q + q) ncols + j] as in GemmArgs, over row tile t of OZ_BM rows
   const double* W; int64_t ldw;
   double* red_part;
@@ -327,7 +389,6 @@ void ozaki_i8_kernel(OzArgs g) {
   constexpr int QC = 10;                                   // sums per pass of the epilogue's LDS exchange
   static_assert(NS * STAGE <= 80 * 1024 && OZ_STRIPS * QC * BN * 8 <= NS * STAGE, "LDS");
   __shared__ __align__(1024) int8_t smem[NS * STAGE];
-  __shared__ int any;
 
   int ti, tj;
   {
@@ -341,34 +402,37 @@ void ozaki_i8_kernel(OzArgs g) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ws = wave & 1, wc = wave >> 1;
-  const int j0 = tj * BN, jb0 = tj * BU;
+  const int j0 = tj * BN;
+  const int count = g.cols.count(g.ncols);
+  if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
 
   const int8_t* Abase = g.A + (int64_t)(nk - 1) * nk / 2 * oz_atile(S) + ti % (OZ_TM / OZ_BM) * (AU * OZ_UNIT);
   const uint32_t lds0 = lds_address(smem);
-  const uint32_t voff = 16 * lane;
+  // Lane offsets of this wave's loads: within A's unit, or of the lane's SNP and k within B's k block (SNPs past the
+  // end: the last one, dropped).
+  uint32_t voff[NLD];
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) {
+    const int u = q * NW + wave;
+    voff[q] = 16 * lane;
+    if (u >= AU) {
+      const int j = g.cols[imin(j0 + (u - AU) * 16 + (lane & 15), count - 1)];
+      voff[q] = (uint32_t)((j >> 4) * OZ_UNIT + 16 * ((lane >> 4) * 16 + (j & 15)));
+    }
+  }
   auto issue = [&](int kb) {
     const uint32_t base = lds0 + (uint32_t)((kb % NS) * STAGE);
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
       const int u = q * NW + wave;
-      if (u >= AU + BU) break;       // wave-uniform: A's units, then B's (groups past the end: the last one's, dropped)
+      if (u >= AU + BU) break;       // wave-uniform: A's units, then B's
       const void* p = (u < AU) ? (const void*)(Abase + (int64_t)kb * oz_atile(S) + u * OZ_UNIT)
-                               : (const void*)(g.B + ((int64_t)kb * g.Jb + min(jb0 + u - AU, g.Jb - 1)) * OZ_UNIT);
-      lds_load16_sv(p, voff, base + (uint32_t)(u * OZ_UNIT));
+                               : (const void*)(g.B + (int64_t)kb * g.Jb * OZ_UNIT);
+      lds_load16_sv(p, voff[q], base + (uint32_t)(u * OZ_UNIT));
     }
   };
   for (int q = 0; q < NS - 1; ++q)
     if (q < nk) issue(q);
-  if (g.flags.at) {   // a tile whose every SNP is flagged has nothing to do
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
-    if (threadIdx.x < BN && j0 + (int)threadIdx.x < g.ncols && !g.flags.flagged(j0 + threadIdx.x, g.ncols)) any = 1;
-    __syncthreads();
-    if (!any) {
-      wait_vmcnt<0>();   // no load into this workgroup's LDS may outlive it
-      return;
-    }
-  }
 
   i4_t acc[S][FC];
 #pragma unroll
@@ -411,8 +475,8 @@ void ozaki_i8_kernel(OzArgs g) {
 #pragma unroll
     for (int c = 0; c < FC; ++c) {
       const int j = j0 + (wc * FC + c) * 16 + (lane & 15);
-      if (j >= g.ncols || (g.flags.at && g.flags.flagged(j, g.ncols))) continue;
-      double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)j * g.ldc);
+      if (j >= count) continue;
+      double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)g.cols[j] * g.ldc);
       o[0] = double2{v[c][0], v[c][1]};
       o[1] = double2{v[c][2], v[c][3]};
     }
@@ -444,8 +508,8 @@ void ozaki_i8_kernel(OzArgs g) {
     for (int f = threadIdx.x; f < qn * BN; f += OZ_THREADS) {   // the strips in order
       const int qq = f / BN, jl = f % BN;
       const double* r = red + qq * BN + jl;
-      if (j0 + jl < g.ncols)
-        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
+      if (j0 + jl < count)
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + g.cols[j0 + jl]] =
             r[0] + r[QC * BN];
     }
   }
@@ -471,14 +535,16 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   __shared__ double red[2 * QC * OZS_BN];
   __shared__ int any;
   const int ti = gridDim.y - 1 - blockIdx.y, tj = blockIdx.x;
-  const int j0 = tj * OZS_BN, jb0 = tj * FC;
+  const int j0 = tj * OZS_BN;
+  const int count = g.cols.count(g.ncols);
+  if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ws = wave & 1, wk = wave >> 1;
   if (threadIdx.x == 0) any = g.flags.at == nullptr;
   __syncthreads();
   if (g.flags.at && threadIdx.x < OZS_BN && j0 + (int)threadIdx.x < g.ncols &&
-      !g.flags.flagged(j0 + threadIdx.x, g.ncols))
+      !g.flags.flagged(j0 + threadIdx.x))
     any = 1;
   for (int e = threadIdx.x; e < 2 * S * FC * 256; e += OZS_THREADS) sums[e] = 0;
   __syncthreads();
@@ -487,14 +553,19 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   const int nk = ti * OZ_BM / OZ_TM + 1;
   const int8_t* A = g.A + (int64_t)(nk - 1) * nk / 2 * oz_atile(S) + ((ti % (OZ_TM / OZ_BM)) * OZ_STRIPS + ws) * (S * OZ_UNIT) +
                     16 * lane;
-  const uint8_t* B = g.B + 16 * lane;
+  uint32_t ob[FC];   // the lane's SNPs and k within a k block of B (SNPs past the end: the last one, dropped)
+#pragma unroll
+  for (int c = 0; c < FC; ++c) {
+    const int j = g.cols[imin(j0 + 16 * c + (lane & 15), count - 1)];
+    ob[c] = (uint32_t)((j >> 4) * OZ_UNIT + 16 * ((lane >> 4) * 16 + (j & 15)));
+  }
   i4_t a[2][S], b[2][FC];
   auto load = [&](int kb, int buf) {
 #pragma unroll
     for (int s = 0; s < S; ++s) a[buf][s] = *reinterpret_cast<const i4_t*>(A + (int64_t)kb * oz_atile(S) + s * OZ_UNIT);
 #pragma unroll
     for (int c = 0; c < FC; ++c)
-      b[buf][c] = *reinterpret_cast<const i4_t*>(B + ((int64_t)kb * g.Jb + min(jb0 + c, g.Jb - 1)) * OZ_UNIT);
+      b[buf][c] = *reinterpret_cast<const i4_t*>(g.B + (int64_t)kb * g.Jb * OZ_UNIT + ob[c]);
   };
   i4_t acc[S][FC];
 #pragma unroll
@@ -537,8 +608,8 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   }
   if (g.red_q == 0) {
     const int j = j0 + wk * 16 + (lane & 15);
-    if (j >= g.ncols || (g.flags.at && g.flags.flagged(j, g.ncols))) return;
-    double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)j * g.ldc);
+    if (j >= count || (g.flags.at && g.flags.flagged(j))) return;
+    double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)g.cols[j] * g.ldc);
     o[0] = double2{v[0], v[1]};
     o[1] = double2{v[2], v[3]};
     return;
@@ -564,8 +635,8 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
     __syncthreads();
     for (int f = threadIdx.x; f < qn * OZS_BN; f += OZS_THREADS) {
       const int qq = f / OZS_BN, jl = f % OZS_BN;
-      if (j0 + jl < g.ncols)
-        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + j0 + jl] =
+      if (j0 + jl < count)
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + g.cols[j0 + jl]] =
             red[qq * OZS_BN + jl] + red[(QC + qq) * OZS_BN + jl];
     }
   }

@@ -166,7 +166,7 @@ void snp_partials_solve_kernel(const double* __restrict__ part, int Mt, const do
 #pragma unroll
   for (int q = 0; q <= P; ++q) sv[q] = 0.0;
   if (j < mb) {
-    const bool f64 = !part8 || (sel.at && sel.flagged(j, mb));
+    const bool f64 = !part8 || (sel.at && sel.flagged(j));
     const double* pt = (f64 ? part : part8) + j;
     const int T = f64 ? Mt : Mt8;
 #pragma unroll 2
