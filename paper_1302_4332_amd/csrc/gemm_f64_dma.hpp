@@ -334,14 +334,19 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
 // few rows do whatever the number of columns: the other kernel's start and end
 // are most of its time there (n = 512, 16,000 columns: 306 us against 257; n =
 // 128, 30,000: 176 against 64).  Longer ones do while there are few tiles of
-// 128 x 64, so that the other kernel's time is that of its longest one.  Times of
-// a block, the tiles of 128 x 32 first: n = 1,100, 1,500 columns (216 tiles) 103
-// us against 100; n = 2,000, 500 (128) 97 against 92 and 800 (208) 101 against 145;
-// n = 3,000, 300 (120) 155 against 123 and 450 (192) 154 against 187; n = 5,000, 190
-// (120) 302 against 195 and 380 (240) 302 against 358; n = 10,000, 200 (316) 883 against
-// 733.  A study of 10,000 samples, whose setup has such products, takes 18.85 ms
-// with 128 for K = 1,280 too and 18.6 with 240.
-inline int small_tiles(int K) { return K <= 1024 ? 128 : K <= 1280 ? 240 : K <= 8192 ? 128 : 320; }
+// 128 x 64, so that the other kernel's time is that of its longest one, which sets
+// the line by the length of the sum.  Blocks of fractional SNPs, the time with this
+// kernel over that with tiles of 128 x 32 (n: tiles ratio ...):
+//   640: 95 0.80, 125 0.98, 140 1.13;  800: 63 1.00, 91 1.35;  1,024: 64 0.85, 96 1.21
+//   (sums of 513 to 1,024 take 8 columns a tile);  1,152: 126 1.02, 144 1.18, 180 0.86,
+//   234 1.07;  1,280: 120 0.96, 160 1.28, 200 0.90, 240 1.06;  2,048: 128 0.92, 160 1.22;
+//   3,072: 144 0.93, 168 1.10;  4,096: 160 0.98, 192 1.12;  6,144: 192 0.89, 240 1.03;
+//   8,192: 256 0.90, 320 1.15;  10,240: 240 0.78, 320 1.04.
+// (Between 160 and 208 tiles at 1,152 to 1,280 it would be ahead again, for the other
+// kernel's second round; 1% of a study of 10,000 samples, whose setup has such products.)
+inline int small_tiles(int K) {
+  return K <= 640 ? 128 : K <= 1024 ? 64 : K <= 4096 ? 128 : K <= 6144 ? 192 : K <= 8192 ? 256 : 320;
+}
 inline bool small_product(int M, int ncols, int K) {
   if (K <= 512 && M <= 512) return true;
   return (int64_t)((M + DB_BM - 1) / DB_BM) * ((ncols + DB_BN - 1) / DB_BN) <= small_tiles(K);

@@ -1,8 +1,8 @@
 """FP64 products of few tiles take a kernel of their own: bitwise the other kernel's results.
 
-The kernel is chosen by the block's width too (up to 128 tiles of 128 x 64 for
-512 < n <= 1,024, 240 to n = 1,280, 128 beyond), and of the others those of up to 768 take narrower ones, so blocks on both sides of the line must give every SNP the
-same bits; and for n <= 512, where it takes every width, the oracle decides.
+The kernel is chosen by the block's width too (for n > 512 up to 64 to 320 tiles of
+128 x 64, by the length of the sum), and of the others those of up to 768 tiles take
+narrower ones, so blocks on both sides of the lines must give every SNP the same bits; and for n <= 512, where it takes every width, the oracle decides.
 Values are fractional, so that no SNP takes the integer product; unaligned
 columns and sample counts off multiples of 16 read the block without a copy.
 """
