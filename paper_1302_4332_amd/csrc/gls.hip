@@ -1326,12 +1326,15 @@ void prepare_low_precision(Ctx* c, hipStream_t s) {
   hipLaunchKernelGGL(fill_kernel, dim3(grid_for(N * c->plan.bcp)), dim3(256), 0, s, c->R, N * c->plan.bcp, 0.0);
 }
 
-// Products of up to 512 tiles of 256 x 128 (one round of two workgroups per compute unit, as long as the factor's
-// last rows) or of up to 1,024 rows take 64 x 64 ones.  Refined blocks, large tiles against small: n = 300, 400 SNPs
-// in FP32 195 against 66 us; n = 6,000, 2,000 SNPs 3.08 against 2.55 ms, 4,096 (768 tiles) 5.04 against 5.25; n =
-// 1,000, 20,000 SNPs 2.22 against 1.26 ms; n = 3,000, 8,000 SNPs in FP16 (756 tiles) 3.36 against 3.56.
-static bool lp_small(int64_t N, int mb) {
-  return N <= 1024 || (N / LpBig::BM) * ((mb + LpBig::BN - 1) / LpBig::BN) <= 512;
+// Products of few tiles of 256 x 128, as long as the factor's last rows, or of up to 1,024 rows take 64 x 64 ones: in
+// FP32 up to 512 tiles (one round of two workgroups per compute unit), in 16 bits, whose matrix time is an eighth of
+// that and whose small tiles read each operand more often for it, up to 256.  Refined blocks, large tiles against
+// small: n = 300, 400 SNPs in FP32 195 against 66 us; n = 6,000, 2,000 SNPs 3.08 against 2.55 ms, 4,096 (768 tiles) 5.04
+// against 5.25; n = 1,000, 20,000 SNPs 2.22 against 1.26 ms; in FP16 n = 2,503, 1,500 SNPs (120 tiles) 0.80 against
+// 0.65 ms, n = 4,900, 1,500 (240) 1.97 against 1.89, n = 7,000, 1,500 (336) 3.27 against 3.33, n = 6,000, 2,500 (480)
+// 3.79 against 4.09.
+static bool lp_small(int64_t N, int mb, size_t elem) {
+  return N <= 1024 || (N / LpBig::BM) * ((mb + LpBig::BN - 1) / LpBig::BN) <= (elem == 2 ? 256 : 512);
 }
 
 template <typename T, typename C>
@@ -1371,7 +1374,7 @@ static void lp_solve_t(Ctx* c, const double* src, int64_t lds, int mb, double be
   a.K = (int)N;
   a.beta = beta;
   a.map_desc = 1;
-  if (lp_small(N, mb)) launch_lp<T, LpSmall>(a, s);
+  if (lp_small(N, mb, sizeof(T))) launch_lp<T, LpSmall>(a, s);
   else launch_lp<T, LpBig>(a, s);
 }
 
