@@ -345,6 +345,7 @@ void crt_gemm_kernel(CrtArgs g) {
     GemmArgs m{};
     m.map_gm = crt_map_gm(g);
     m.map_gn = crt_map_gn(g);
+    m.map_slots = 512;
     m.map_desc = g.a_lower | g.c_lower;
     // rows are dealt to the XCDs anew for each modulus: with some tens of row tiles some XCDs get a row more
     const int bid = (blockIdx.x & ~7) | ((blockIdx.x + p) & 7);

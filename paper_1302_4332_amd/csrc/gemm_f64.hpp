@@ -92,6 +92,7 @@ struct GemmArgs {
   // map_gm x map_gn tiles per co-resident group on one XCD (0 = defaults)
   int map_desc;
   int map_gm, map_gn;
+  int map_slots;  // workgroups that the chip holds at once (0: 768, three to a compute unit)
   int map_slab;   // 1: column groups outer (a slab of GN column tiles meets every row tile in turn)
   // trmm_f64_dma_kernel only: with red_q > 0, C is not stored; instead each
   // row tile ti writes, for every column j, the red_q sums over its rows
@@ -129,7 +130,13 @@ __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 // a round, in an order that balances triangular k-work: there and back in turn
 // (a snake), and for an odd number of rounds the first three by permutations
 // whose sums over the rounds are 10 or 11 for every XCD (a snake's are 7 to 14:
-// at 24 row tiles one XCD got a fifth more than another).  On each XCD, groups of GM local row
+// at 24 row tiles one XCD got a fifth more than another).  That is for grids of one
+// and a half times the tiles that the chip holds at once and more, where an XCD's
+// total is its time: n = 3,008, 4,096 and 8,192 fractional columns (2 and 4 times)
+// 637 -> 608 and 1,258 -> 1,208 us, refined FP32 at n = 6,000 (1.5 times) 5.06 -> 5.00 ms,
+// FP16 at 5,100 4.39 -> 4.24.  With little more than a round an XCD is as long as what
+// follows its longest tiles, and the snake is ahead: 2,500 columns (1.25 times) 444
+// against 462.  On each XCD, groups of GM local row
 // tiles x GN column tiles run together so the operand strips they share stay
 // in that XCD's L2.  Row groups are issued heavy-first.
 struct XcdMap {
@@ -168,7 +175,7 @@ struct XcdMap {
     int j = cgi * GN + (w / GM);
     if (kl >= R || j >= Nt) return false;
     int pos;
-    if ((R & 1) && kl < 3) {
+    if ((R & 1) && kl < 3 && 2 * (int64_t)Mt * Nt >= 3 * (ga.map_slots ? ga.map_slots : 768)) {
       const uint32_t perm = kl == 0 ? 0x76543210u : kl == 1 ? 0x10576243u : 0x34102657u;   // nibble x: XCD x's row
       pos = (int)((perm >> (4 * x)) & 7u);
     } else {

@@ -119,6 +119,7 @@ void lp_gemm_kernel(LpArgs g) {
     m.map_gm = g.map_gm;
     m.map_gn = g.map_gn;
     m.map_desc = g.map_desc;
+    m.map_slots = 256 * C::WG;
     const int Mt = g.M / BM, Nt = (g.ncols + BN - 1) / BN;
     if (!XcdMap::tile(m, blockIdx.x, Mt, Nt, &ti, &tj)) return;
   }

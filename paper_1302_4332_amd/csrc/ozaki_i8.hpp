@@ -395,6 +395,7 @@ void ozaki_i8_kernel(OzArgs g) {
     GemmArgs m{};
     m.map_gm = OZ_MAP_GM;
     m.map_gn = OZ_MAP_GN;
+    m.map_slots = 512;
     m.map_desc = 1;
     if (!XcdMap::tile(m, blockIdx.x, g.Mt, (g.ncols + BN - 1) / BN, &ti, &tj)) return;
   }
