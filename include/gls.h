@@ -183,8 +183,8 @@ typedef struct {
  * (block_cols / 8, growing by a quarter per block, multiples of 64), so the
  * first copy, which nothing overlaps, is short; results are bitwise the same
  * for any blocking.  A handle that solves SNPs of whole numbers on the
- * integer matrix cores copies each block in up to four parts of 512 columns
- * or more and solves them as they arrive.
+ * integer matrix cores copies a block that looks like such SNPs in up to four
+ * parts of 64 MB or more and solves them as they arrive.
  * copy_stream NULL (recommended): the study runs on the handle's own compute
  * and copy streams, after the work already queued on compute_stream.  HIP
  * multiplexes streams onto a few hardware queues, and on a shared queue the

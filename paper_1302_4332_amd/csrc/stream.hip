@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cerrno>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstdio>
 #include <mutex>
@@ -98,20 +99,43 @@ std::vector<int64_t> block_schedule(int64_t bc, int64_t total) {
   return bstart;
 }
 
+// Whether a block in host memory looks like SNPs of whole numbers: a few values all over it are.  The answer decides
+// only how the block is scheduled.  (A pointer that the host cannot read, which the copies would take, does not.)
+bool looks_whole(const double* X, int64_t rows, int64_t ld, int64_t cols) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, X) != hipSuccess) (void)hipGetLastError();   // not known to HIP: pageable memory
+  else if (at.type == hipMemoryTypeDevice) return false;
+  constexpr int64_t LOOKS = 128;
+  for (int64_t i = 0; i < LOOKS; ++i) {
+    const double x = X[(i * cols / LOOKS) * ld + i * 7919 % rows];
+    if (!(x == std::rint(x) && std::fabs(x) <= 127.0)) return false;
+  }
+  return true;
+}
+
 // Parts a block is copied and solved in.  FP64 columns cost 8 n bytes on the
 // link, and where SNPs of whole numbers take the integer product their solve is
 // a fifth of that (n = 10,000: 1.4 us a SNP on the link, 0.3 us in the solve):
 // the stream is bound by its copies, and a block solved only once it is whole
 // leaves its solve behind the last copy (2.6 ms for 8,192 SNPs).  Such blocks
-// are copied in up to four parts of at least 512 columns, each solved as it
-// arrives.  Other formats and handles are bound by the solve, which is faster
-// on whole blocks.
-constexpr int STREAM_PARTS = 4, STREAM_PART_COLS = 512;
+// are copied in up to four parts of at least 64 MB, each solved as it
+// arrives; smaller parts cost more in copies to start than the last solve is long
+// (n = 700, 32,768 SNPs in blocks of 46 MB 3.65 ms whole, 3.9 in four parts).  Other
+// formats, handles and values are bound by the solve, which is faster on whole
+// blocks: n = 10,000, 24,576 fractional SNPs in blocks of 8,192 43.5 ms, 46.8 in parts.
+constexpr int STREAM_PARTS = 4;
+constexpr int64_t STREAM_PART_BYTES = (int64_t)64 << 20;
 
-int parts_of(const Ctx* c, const double*, int64_t cols) {
-  return whole_f64(c) ? (int)std::min<int64_t>(STREAM_PARTS, std::max<int64_t>(1, cols / STREAM_PART_COLS)) : 1;
+int most_parts(const Ctx* c, const double*, int64_t cols) {
+  const int64_t fit = c->n * cols * (int64_t)sizeof(double) / STREAM_PART_BYTES;
+  return whole_f64(c) ? (int)std::min<int64_t>(STREAM_PARTS, std::max<int64_t>(1, fit)) : 1;
 }
-int parts_of(const Ctx*, const void*, int64_t) { return 1; }
+int most_parts(const Ctx*, const void*, int64_t) { return 1; }
+int parts_of(const Ctx* c, const double* X, int64_t ld, int64_t cols) {
+  const int most = most_parts(c, X, cols);
+  return most > 1 && looks_whole(X, c->n, ld, cols) ? most : 1;
+}
+int parts_of(const Ctx*, const void*, int64_t, int64_t) { return 1; }
 
 // First column of part q of a block of cols columns (q == parts: its end).
 int64_t part_start(int64_t cols, int parts, int q) {
@@ -176,7 +200,7 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
   EventPool pool;
   hipError_t e;
   // per block: compute start/stop; wall start/stop; the arrival of the two buffers' parts after the first
-  const int more = parts_of(c, XR_host, bc) - 1;
+  const int more = most_parts(c, XR_host, bc) - 1;
   if ((e = pool.make(2 * nblk + 2 + 2 * more)) != hipSuccess) return hip_fail(e, "gls_stream: event create");
   hipEvent_t wall0 = pool.ev[2 * nblk], wall1 = pool.ev[2 * nblk + 1];
   auto arrived = [&](int buf, int q) { return q == 0 ? c->ev_copy[buf] : pool.ev[2 * nblk + 2 + buf * more + q - 1]; };
@@ -184,10 +208,10 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
   auto cols_of = [&](int64_t blk) { return bstart[blk + 1] - bstart[blk]; };
   auto src_of = [&](int64_t blk) { return XR_host + (col0 + bstart[blk]) * ld_xr; };
 
-  auto parts = [&](int64_t blk) { return sx == sc ? 1 : parts_of(c, XR_host, cols_of(blk)); };
+  int parts[2] = {1, 1};   // of the block in each buffer
   auto copy_block = [&](int64_t blk, int buf) -> hipError_t {
     const int64_t cols = cols_of(blk);
-    const int np = parts(blk);
+    const int np = parts[buf] = sx == sc ? 1 : parts_of(c, src_of(blk), ld_xr, cols);
     for (int q = 0; q < np; ++q) {
       const int64_t j0 = part_start(cols, np, q), j1 = part_start(cols, np, q + 1);
       hipError_t r = h2d_block(stage(c, buf, XR_host) + j0 * rows, rows, src_of(blk) + j0 * ld_xr, ld_xr, j1 - j0, sx);
@@ -213,7 +237,7 @@ static gls_status stream_run(gls_handle h, int64_t m, int64_t col0, const T* XR_
     }
     // serial: this block's copy only now, behind the previous results
     if (sx == sc && blk >= 1 && (e = copy_block(blk, cur)) != hipSuccess) return hip_fail(e, "gls_stream: H2D");
-    const int np = parts(blk);
+    const int np = parts[cur];
     for (int q = 0; q < np; ++q) {
       const int64_t j0 = part_start(cols, np, q), j1 = part_start(cols, np, q + 1);
       if ((e = hipStreamWaitEvent(sc, arrived(cur, q), 0)) != hipSuccess) return hip_fail(e, "gls_stream: wait");

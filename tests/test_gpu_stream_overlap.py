@@ -1,15 +1,14 @@
 """Copies overlap the solves in every streamed pass (Sec. 3.1, double buffering).
 
-A streamed study given no copy stream runs on the handle's own compute and copy
-streams, which gls_setup checks do not share a hardware queue.  Were copies and
-solves on streams that share a queue, each block's copy would run after the
-solve before it and a pass's device wall would approach its copies plus its
-solves, about twice the solves at n = 10,000, where a block's copy takes about
-as long as its product (a second live handle with an unchecked pair did exactly
-that).
-Here every pass of two live handles, used in turn, must stay within 1.4 times
-its summed solve time (plus 5 ms for the opening copy), and all passes give
-bitwise the same outputs.
+A streamed study given no copy stream runs on a pair of streams that are checked
+not to share a hardware queue.  Were copies and solves on streams that share a
+queue, each block's copy would run after the solve before it (a second live
+handle with an unchecked pair did exactly that).
+Here every pass of two live handles, used in turn, must stay within 1.4 times its
+compute_ms (plus 5 ms for the opening copy), and all passes give bitwise the same
+outputs.  The SNPs are whole numbers, whose blocks are solved in parts as they
+arrive, so that compute_ms holds the waits for the later parts: what a stream
+takes without overlap is measured in test_gpu_stream_parts.py.
 """
 import numpy as np
 import pytest
