@@ -913,13 +913,7 @@ static gls_status setup_into(Ctx* c, const Plan& pl, int64_t n, int32_t p, const
 // `comp` must finish while c still runs.  (Kernels of different streams on one
 // queue do overlap, so sharing c's queue does not fail the check; a slow host
 // can only make its answer a false "shared".)  The copy stream is re-created
-// until the check passes, at most four times.
-//
-// Creating and checking a pair takes about 0.8 ms, as long as the whole of a
-// study of 512 samples, and a stream keeps its hardware queue for life.  So a
-// handle takes its pair at its first streamed study without a copy stream, and
-// gives it back when it is destroyed; idle pairs (and the setup's side streams)
-// of each device wait in a pool of at most POOL_MAX for the next handle.
+// until the check passes, at most four times (StreamPool::take_pair).
 __global__ void idle_kernel(int rounds) {
   for (int r = 0; r < rounds; ++r) __builtin_amdgcn_s_sleep(127);
 }
@@ -938,107 +932,18 @@ static bool wait_is_isolated(hipStream_t comp, hipStream_t copy, hipStream_t c, 
   return ok;
 }
 
-constexpr size_t POOL_MAX = 4;   // idle pairs, and idle side streams, kept per device
-
-struct IdleStreams {
-  struct Pair {
-    int device;
-    hipStream_t st[2];
-  };
-  struct Side {
-    int device;
-    hipStream_t st;
-  };
-  std::mutex mu;
-  std::vector<Pair> pairs;
-  std::vector<Side> sides;
-};
 // never destroyed: a handle may be closed while the process ends
-static IdleStreams& idle_streams() {
-  static IdleStreams* pool = new IdleStreams;
+static StreamPool& idle_streams() {
+  alignas(StreamPool) static char at[sizeof(StreamPool)];
+  static StreamPool* pool = new (at) StreamPool;
   return *pool;
 }
 
-static hipError_t take_side_stream(int device, hipStream_t* st) {
-  {
-    IdleStreams& pool = idle_streams();
-    std::lock_guard<std::mutex> lock(pool.mu);
-    for (size_t i = 0; i < pool.sides.size(); ++i) {
-      if (pool.sides[i].device != device) continue;
-      *st = pool.sides[i].st;
-      pool.sides.erase(pool.sides.begin() + i);
-      return hipSuccess;
-    }
-  }
-  return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
-}
-
-// The stream has nothing left to run.
-static void give_side_stream(int device, hipStream_t st) {
-  {
-    IdleStreams& pool = idle_streams();
-    std::lock_guard<std::mutex> lock(pool.mu);
-    size_t have = 0;
-    for (const auto& s : pool.sides) have += s.device == device;
-    if (have < POOL_MAX) {
-      pool.sides.push_back({device, st});
-      return;
-    }
-  }
-  (void)hipStreamDestroy(st);
-}
-
-static hipError_t make_stream_pair(hipStream_t st[2], hipStream_t caller, hipEvent_t ev) {
-  hipError_t e = hipStreamCreateWithFlags(&st[0], hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&st[1], hipStreamNonBlocking);
-  if (e != hipSuccess) return e;
-  std::vector<hipStream_t> rejected;
-  for (int tries = 0; tries < 4 && !wait_is_isolated(st[0], st[1], caller, ev); ++tries) {
-    hipStream_t fresh = nullptr;
-    if (hipStreamCreateWithFlags(&fresh, hipStreamNonBlocking) != hipSuccess) {
-      (void)hipGetLastError();
-      break;
-    }
-    rejected.push_back(st[1]);   // kept until the search ends, so its queue is not handed out again
-    st[1] = fresh;
-  }
-  for (hipStream_t r : rejected) (void)hipStreamDestroy(r);
-  return hipSuccess;
-}
-
 hipError_t take_stream_pair(Ctx* c, hipStream_t caller) {
-  if (c->own_st[0]) return hipSuccess;
-  {
-    IdleStreams& pool = idle_streams();
-    std::lock_guard<std::mutex> lock(pool.mu);
-    for (size_t i = 0; i < pool.pairs.size(); ++i) {
-      if (pool.pairs[i].device != c->device) continue;
-      c->own_st[0] = pool.pairs[i].st[0];
-      c->own_st[1] = pool.pairs[i].st[1];
-      pool.pairs.erase(pool.pairs.begin() + i);
-      return hipSuccess;
-    }
-  }
-  return make_stream_pair(c->own_st, caller, c->ev_join);
-}
-
-static void give_stream_pair(Ctx* c) {
-  hipStream_t* st = c->own_st;
-  bool idle = st[0] && st[1];
-  for (int i = 0; i < 2; ++i)
-    if (st[i] && hipStreamSynchronize(st[i]) != hipSuccess) idle = false;
-  if (idle) {
-    IdleStreams& pool = idle_streams();
-    std::lock_guard<std::mutex> lock(pool.mu);
-    size_t have = 0;
-    for (const auto& q : pool.pairs) have += q.device == c->device;
-    if (have < POOL_MAX) {
-      pool.pairs.push_back({c->device, {st[0], st[1]}});
-      st[0] = st[1] = nullptr;
-    }
-  }
-  for (int i = 0; i < 2; ++i)
-    if (st[i]) (void)hipStreamDestroy(st[i]);
+  if (c->own.there()) return hipSuccess;
+  return idle_streams().take_pair(
+      c->device, [&](hipStream_t comp, hipStream_t copy) { return wait_is_isolated(comp, copy, caller, c->ev_join); },
+      &c->own);
 }
 
 }  // namespace gls
@@ -1102,13 +1007,13 @@ gls_status gls_setup(gls_handle* out, int64_t n, int32_t p, const double* Phi, i
     return hip_fail(e, "gls_setup: device");
   }
   hipStream_t side = nullptr;   // the factorization's side products, where it has any
-  if (pl.side_products && (e = take_side_stream(c->device, &side)) != hipSuccess) {
+  if (pl.side_products && (e = idle_streams().take_side(c->device, &side)) != hipSuccess) {
     gls_destroy(c);
     return hip_fail(e, "gls_setup: side stream create");
   }
   st = setup_into(c, pl, n, p, Phi, ld_phi, h2, XL, ld_xl, y, static_cast<char*>(workspace), opts, side,
                   static_cast<hipStream_t>(stream), info);
-  if (side) give_side_stream(c->device, side);   // joined into `stream`, which setup_into synchronized
+  if (side) idle_streams().give_side(c->device, side);   // joined into `stream`, which setup_into synchronized
   if (st != GLS_OK) {
     gls_destroy(c);
     return st;
@@ -1215,7 +1120,7 @@ void gls_destroy(gls_handle h) {
     (void)hipEventDestroy(r.b);
   }
   for (hipEvent_t e : c->prof_free) (void)hipEventDestroy(e);
-  give_stream_pair(c);
+  idle_streams().give_pair(c->device, &c->own);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
   for (int i = 0; i < 2; ++i) {
     if (c->ev_copy[i]) (void)hipEventDestroy(c->ev_copy[i]);

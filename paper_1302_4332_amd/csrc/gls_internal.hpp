@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "gls.h"
+#include "stream_pool.hpp"
 
 namespace gls {
 
@@ -98,7 +99,7 @@ struct gls_ctx {
   hipEvent_t ev_comp[2] = {nullptr, nullptr};
   // the handle's own compute and copy streams for streamed studies (from its
   // first one on), and the event that orders them after the caller's stream
-  hipStream_t own_st[2] = {nullptr, nullptr};
+  gls::StreamPair own;
   hipEvent_t ev_join = nullptr;
   // phase timing (gls_profile_*)
   struct ProfRec {

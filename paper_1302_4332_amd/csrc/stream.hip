@@ -162,8 +162,8 @@ hipError_t run_streams(Ctx* c, void* compute_stream, void* copy_stream, RunStrea
   if (e == hipSuccess) e = take_stream_pair(c, caller);
   if (current != c->device) (void)hipSetDevice(current);
   if (e != hipSuccess) return e;
-  r->sc = c->own_st[0];
-  r->sx = c->own_st[1];
+  r->sc = c->own.st[0];
+  r->sx = c->own.st[1];
   e = hipEventRecord(c->ev_join, caller);
   if (e == hipSuccess) e = hipStreamWaitEvent(r->sc, c->ev_join, 0);
   if (e == hipSuccess) e = hipStreamWaitEvent(r->sx, c->ev_join, 0);
