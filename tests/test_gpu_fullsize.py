@@ -63,13 +63,15 @@ def _sample(j0, j1, k, seed):
 
 
 def _run(name, tail, forms, k=48, n=None):
-    """forms: (precision, refinement sweeps, input) with input "f64", "u8" or "u2"."""
+    """forms: (precision, refinement sweeps, input) with input "f64", "u8", "u2" or "half": the dosages halved, which are no
+    whole numbers and take the FP64 product."""
     w, st, bc, blocks = _study_blocks(name, tail, n)
     print(f"{name}: n={st.Phi.shape[0]} p={w.p} blocks {blocks}", flush=True)
     ost = O.Study(st.Phi, w.h2, st.XL, st.y)
     Phi, XL, y = _t(st.Phi), _t(st.XL), _t(st.y)
     errs = {}
     for prec, sweeps, inp in forms:
+        scale = 0.5 if inp == "half" else 1.0
         ctx = GLSContext(Phi, w.h2, XL, y, block_cols=bc, precision=prec, refine_sweeps=sweeps)
         for bi, (j0, j1) in enumerate(blocks):
             if inp == "u8":
@@ -77,14 +79,14 @@ def _run(name, tail, forms, k=48, n=None):
             elif inp == "u2":
                 b, s2, v, status = ctx.block_u2(_t(st.snps_u2(j0, j1)))
             else:
-                b, s2, v, status = ctx.block(_t(st.snps(j0, j1)))
+                b, s2, v, status = ctx.block(_t(st.snps(j0, j1) * scale))
             torch.cuda.synchronize()
             idx = _sample(j0, j1, k, 100 + bi)
             if st.causal is not None and j0 <= st.causal < j1:
                 idx = np.unique(np.r_[idx, st.causal])
             g = {"b": b.cpu().numpy()[idx - j0], "sigma2": s2.cpu().numpy()[idx - j0],
                  "v": v.cpu().numpy()[idx - j0], "status": status.cpu().numpy()[idx - j0]}
-            cols = np.concatenate([st.snps(int(j), int(j) + 1) for j in idx])
+            cols = np.concatenate([st.snps(int(j), int(j) + 1) for j in idx]) * scale
             r = ost.block(cols.T)
             errs[(f"{prec}x{sweeps}/{inp}", bi)] = _check(g, r, TOL[prec])
         ctx.close()
@@ -93,6 +95,12 @@ def _run(name, tail, forms, k=48, n=None):
 
 def test_fullsize_n10k_fp64_and_int8_slices():
     _run("c1_n10k_m100k", 100000 % 8192, (("fp64", 0, "f64"), ("int8_emu", 0, "u8"), ("int8_emu", 0, "u2")))
+
+
+@pytest.mark.parametrize("n", [10000, 10007])
+def test_fullsize_fp64_product(n):
+    """SNPs of whole numbers take the integer product in the FP64 runs here: the FP64 product in the same launches."""
+    _run("c1_n10k_m100k", 100000 % 8192, (("fp64", 0, "half"),), k=24, n=n)
 
 
 def test_fullsize_n10k_m1M_mixed():

@@ -92,6 +92,23 @@ def test_bytes_beside_their_values(n, m):
     ctx.close()
 
 
+@pytest.mark.parametrize("m", [1727, 1728, 1729])
+def test_emulation_widths(m):
+    """The seven-digit product's tiles of 192 SNPs at their edge (nine tiles), against narrow blocks."""
+    n = 600
+    Phi, XL, y, XR = _study(n, 4, m)
+    G = XR.astype(np.uint8)
+    ctx = GLSContext(_t(Phi), 0.4, _t(XL), _t(y), block_cols=m, precision="int8_emu")
+    Gd = _t(G)
+    whole = as_numpy(ctx.block_u8(Gd))
+    _same(as_numpy(ctx.block_u2(_t(synth.pack_dosages_2bit(G)))), whole, "2-bit codes")
+    for j0 in range(0, m, 191):
+        j1 = min(m, j0 + 191)
+        _same({k: whole[k][j0:j1] for k in KEYS}, as_numpy(ctx.block_u8(Gd[j0:j1])), f"SNPs {j0}..{j1 - 1}")
+    compare({k: whole[k][-40:] for k in KEYS}, O.gls_sequence(Phi, 0.4, XL, y, XR[-40:]), 1e-10)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n", [600, 608])
 def test_gradient(n):
     """The adjoint recomputes blocks of both kinds: the SNPs' gradients bitwise those of narrow blocks, whose kernels are

@@ -2,9 +2,11 @@
 
 A GLS_FP64 handle with n > 512 samples gives every SNP whose values are whole
 numbers of magnitude at most 127 to the int8-slice product and every other one
-to the FP64 product.  Checked at the edges of both products' tiles (32 rows and
-192 SNPs; 128 rows and 64 SNPs), of the 16-SNP groups and of the 256-row
-padding, for aligned and unaligned columns, and on both sides of the line between the integer product's two kernels:
+to the FP64 product (handles of fewer samples form all of them there).  Checked at
+the edges of the rows of both products' tiles (32; 128), of the 16-SNP groups and of
+the 256-row padding, for aligned and unaligned columns, and on both sides of the
+line between the integer product's two kernels (blocks of many SNPs:
+test_gpu_mixed_blocks.py):
 
 - every output against the CPU oracle at the plain-FP64 bar (1e-10);
 - each SNP's outputs bitwise the same alone and in the mixed block;
