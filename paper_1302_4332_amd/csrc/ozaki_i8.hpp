@@ -355,6 +355,21 @@ struct OzArgs {
   double* C; int64_t ldc; // red_q == 0: the product itself, N x ncols FP64
 };
 
+// Sums over a wave's four rows of 16 lanes, two values or pairs of them at a time:
+// the value's two halves change places between registers, without the LDS port.
+// add_rows16: in even rows a's sums of rows (r, r + 1), in odd ones b's of (r - 1, r);
+// add_rows32: in lanes 0..31 a's sums of lanes (l, l + 32), in the others b's.
+__device__ __forceinline__ double add_rows16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double add_rows32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
 // A workgroup of four waves owns 32 rows x 192 SNPs with seven digits, 32 x 160 with
 // eight (26 KB a stage either way): wave w takes the 16-row
 // strip w & 1 and the half w >> 1 of the SNPs with all the digits, 7 x 6 or 8 x 5
@@ -374,7 +389,9 @@ struct OzArgs {
 //
 // A wave's accumulator element t of lane l is row 4 (l / 16) + t, SNP l % 16 of
 // its 16 x 16 block, so a sum over the rows is four values of the lane and two
-// lane exchanges.
+// exchanges between lanes.  Through the LDS port those were most of the epilogue: n =
+// 3,968, 3,094 SNPs as bytes, p = 20 376 -> 335 us, p = 4 197 -> 188; n = 2,503, 1,001
+// SNPs, p = 8 70.6 -> 65.0.
 constexpr int OZ_THREADS = 256, OZ_STAGES = 3;
 constexpr int oz_bn(int S) { return S == 7 ? 192 : 160; }
 constexpr int OZ_MAP_GM = 4, OZ_MAP_GN = 8;
@@ -495,14 +512,20 @@ void ozaki_i8_kernel(OzArgs g) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) w[t] = g.W[(int64_t)(i + t) + (int64_t)q * g.ldw];
       }
+      // four SNP groups at a time, whose sums end in the four rows of lanes (past the last group: spare ones)
 #pragma unroll
-      for (int c = 0; c < FC; ++c) {
-        double x = 0.0;
+      for (int c0 = 0; c0 < FC; c0 += 4) {
+        double x[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x += v[c][t] * (norm ? v[c][t] : w[t]);
-        x += __shfl_xor(x, 16, 64);
-        x += __shfl_xor(x, 32, 64);
-        if (lane < 16) red[(ws * QC + qq) * BN + (wc * FC + c) * 16 + lane] = x;
+        for (int u = 0; u < 4; ++u) {
+          const int c = c0 + u < FC ? c0 + u : FC - 1;
+          x[u] = 0.0;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) x[u] += v[c][t] * (norm ? v[c][t] : w[t]);
+        }
+        const double s = add_rows32(add_rows16(x[0], x[1]), add_rows16(x[2], x[3]));
+        const int c = c0 + (lane >> 4);
+        if (c < FC) red[(ws * QC + qq) * BN + (wc * FC + c) * 16 + (lane & 15)] = s;
       }
     }
     __syncthreads();
