@@ -66,6 +66,8 @@ struct ColList {
   const int* at;
   __device__ __forceinline__ int count(int ncols) const { return at ? at[0] : ncols; }
   __device__ __forceinline__ int operator[](int i) const { return at ? at[1 + i] : i; }
+  // The same columns without the list if it has all of them: one load less to wait for.
+  __device__ __forceinline__ ColList or_all(int count, int ncols) const { return ColList{count == ncols ? nullptr : at}; }
 };
 
 // Lengths of a list for which a kernel does anything: above < count <= upto.

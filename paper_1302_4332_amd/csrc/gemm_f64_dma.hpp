@@ -121,6 +121,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;   // a tile wholly above the lower part
   const int count = g.cols.count(g.ncols);
   if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
+  const ColList cols = g.cols.or_all(count, g.ncols);
   // k range of the tile: a lower-triangular A ends at the tile's last row, an upper-triangular one starts at its
   // first, a lower-triangular B starts at the tile's first column (each holds explicit zeros across its diagonal
   // block)
@@ -146,10 +147,10 @@ void trmm_f64_dma_kernel(GemmArgs g) {
     const int jl = 8 * wave + (lane >> 3);
     const int c = (lane & 7) ^ (jl & 7);
     const int j = imin(j0 + jl, count - 1);   // columns past the end: any valid one, dropped
-    voff[2] = (uint32_t)((2 * c + (int64_t)(g.b_listed ? g.cols[j] - g.cols[j0] : j - j0) * g.ldb) * 8);
+    voff[2] = (uint32_t)((2 * c + (int64_t)(g.b_listed ? cols[j] - cols[j0] : j - j0) * g.ldb) * 8);
   }
   const double* Abase = g.A + i0;
-  const double* Bbase = g.B + (int64_t)(g.b_listed ? g.cols[j0] : j0) * g.ldb;
+  const double* Bbase = g.B + (int64_t)(g.b_listed ? cols[j0] : j0) * g.ldb;
   const uint32_t lds0 = lds_address(smem);
   auto issue = [&](int kstep) {
     const uint32_t base = lds0 + (uint32_t)((kstep % NS) * STAGE);
@@ -216,7 +217,7 @@ void trmm_f64_dma_kernel(GemmArgs g) {
     }
   }
 
-  trmm_f64_epilogue<BN, FC, DB_THREADS>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, g.cols, count);
+  trmm_f64_epilogue<BN, FC, DB_THREADS>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, cols, count);
 }
 
 // The same product, bitwise, for short sums and grids of few tiles: 128 x BN tiles (BN = 16 or
@@ -243,6 +244,7 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
   if (g.c_lower && (i0 + BM - 1) < (j0 + g.c_diag)) return;
   const int count = g.cols.count(g.ncols);
   if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
+  const ColList cols = g.cols.or_all(count, g.ncols);
   if (g.only.at) {
     int* any = reinterpret_cast<int*>(smem);
     if (threadIdx.x == 0) *any = 0;
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
 #pragma unroll
     for (int c = wave; c < BN; c += NW) {
       const int j = j0 + c;
-      const double* col = g.B + (int64_t)(g.b_listed && j < count ? g.cols[j] : j) * g.ldb;
+      const double* col = g.B + (int64_t)(g.b_listed && j < count ? cols[j] : j) * g.ldb;
       double v[KMAX / 64];
 #pragma unroll
       for (int u = 0; u < KMAX / 64; ++u) {
@@ -327,7 +329,7 @@ __global__ __launch_bounds__(32 * BN) void trmm_f64_small_kernel(GemmArgs g) {
                                                        acc[a][0], 0, 0, 0);
     }
   }
-  trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, g.cols, count);
+  trmm_f64_epilogue<BN, 1, NT>(g, acc, reinterpret_cast<double*>(smem), ti, i0, j0, wm, wn, cols, count);
 }
 
 // Whether a product of M rows, ncols columns and K goes to it.  Short sums over

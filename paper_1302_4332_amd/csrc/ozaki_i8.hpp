@@ -423,6 +423,7 @@ void ozaki_i8_kernel(OzArgs g) {
   const int j0 = tj * BN;
   const int count = g.cols.count(g.ncols);
   if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
+  const ColList cols = g.cols.or_all(count, g.ncols);
 
   const int8_t* Abase = g.A + (int64_t)(nk - 1) * nk / 2 * oz_atile(S) + ti % (OZ_TM / OZ_BM) * (AU * OZ_UNIT);
   const uint32_t lds0 = lds_address(smem);
@@ -434,7 +435,7 @@ void ozaki_i8_kernel(OzArgs g) {
     const int u = q * NW + wave;
     voff[q] = 16 * lane;
     if (u >= AU) {
-      const int j = g.cols[imin(j0 + (u - AU) * 16 + (lane & 15), count - 1)];
+      const int j = cols[imin(j0 + (u - AU) * 16 + (lane & 15), count - 1)];
       voff[q] = (uint32_t)((j >> 4) * OZ_UNIT + 16 * ((lane >> 4) * 16 + (j & 15)));
     }
   }
@@ -494,7 +495,7 @@ void ozaki_i8_kernel(OzArgs g) {
     for (int c = 0; c < FC; ++c) {
       const int j = j0 + (wc * FC + c) * 16 + (lane & 15);
       if (j >= count) continue;
-      double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)g.cols[j] * g.ldc);
+      double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)cols[j] * g.ldc);
       o[0] = double2{v[c][0], v[c][1]};
       o[1] = double2{v[c][2], v[c][3]};
     }
@@ -533,7 +534,7 @@ void ozaki_i8_kernel(OzArgs g) {
       const int qq = f / BN, jl = f % BN;
       const double* r = red + qq * BN + jl;
       if (j0 + jl < count)
-        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + g.cols[j0 + jl]] =
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + cols[j0 + jl]] =
             r[0] + r[QC * BN];
     }
   }
@@ -562,6 +563,7 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   const int j0 = tj * OZS_BN;
   const int count = g.cols.count(g.ncols);
   if (j0 >= count || (g.cols.at && !g.range.holds(count))) return;
+  const ColList cols = g.cols.or_all(count, g.ncols);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ws = wave & 1, wk = wave >> 1;
@@ -580,7 +582,7 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   uint32_t ob[FC];   // the lane's SNPs and k within a k block of B (SNPs past the end: the last one, dropped)
 #pragma unroll
   for (int c = 0; c < FC; ++c) {
-    const int j = g.cols[imin(j0 + 16 * c + (lane & 15), count - 1)];
+    const int j = cols[imin(j0 + 16 * c + (lane & 15), count - 1)];
     ob[c] = (uint32_t)((j >> 4) * OZ_UNIT + 16 * ((lane >> 4) * 16 + (j & 15)));
   }
   i4_t a[2][S], b[2][FC];
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
   if (g.red_q == 0) {
     const int j = j0 + wk * 16 + (lane & 15);
     if (j >= count || (g.flags.at && g.flags.flagged(j))) return;
-    double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)g.cols[j] * g.ldc);
+    double2* o = reinterpret_cast<double2*>(g.C + (int64_t)i + (int64_t)cols[j] * g.ldc);
     o[0] = double2{v[0], v[1]};
     o[1] = double2{v[2], v[3]};
     return;
@@ -660,7 +662,7 @@ __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
     for (int f = threadIdx.x; f < qn * OZS_BN; f += OZS_THREADS) {
       const int qq = f / OZS_BN, jl = f % OZS_BN;
       if (j0 + jl < count)
-        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + g.cols[j0 + jl]] =
+        g.red_part[(int64_t)(ti * g.red_q + q0 + qq) * g.ncols + cols[j0 + jl]] =
             red[qq * OZS_BN + jl] + red[(QC + qq) * OZS_BN + jl];
     }
   }
