@@ -96,11 +96,12 @@ __device__ __forceinline__ void trmm_f64_epilogue(const GemmArgs& g, const doubl
 // tiles has twice as many and its longest one ends sooner: a single workgroup
 // on a compute unit takes 1.45 us a stage of 64 columns, whose MFMAs take 0.92.
 constexpr int DB_BM = 128, DB_BN = 64, DB_BK = 16, DB_THREADS = 512, DB_STAGES = 2;
-// Products of up to this many 128 x 64 tiles, what the chip holds at once, take tiles of 128 x 32.  n = 3,325, 998
+// Products of up to this many 128 x 64 tiles take tiles of 128 x 32: what the chip holds at once.  n = 3,325, 998
 // columns (416 tiles) 331 -> 237 us a block, n = 5,000, 600 (400) 535 -> 436, n = 10,000, 300 (395) 1,432 -> 887, n = 2,000,
 // 3,000 (752) 287 -> 262; beyond, A's columns are read twice as often for it: n = 5,000, 1,500 (960) 711 -> 776, 4,096
-// (2,560) 1,715 -> 1,900.
-constexpr int DB_NARROW_TILES = 768;
+// (2,560) 1,715 -> 1,900.  Sums of up to 896 have few stages to win back and go up and down with the rounds (n = 640,
+// 200, 320, 480 and 640 tiles: 0.93, 1.11, 1.08 and 1.15 of the wide tiles' time): up to 256 tiles.
+inline int narrow_tiles(int K) { return K <= 896 ? 256 : 768; }
 
 template <int BN>
 __global__ __launch_bounds__(DB_THREADS) __attribute__((amdgpu_waves_per_eu(6, 8)))

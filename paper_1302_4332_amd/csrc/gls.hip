@@ -308,13 +308,13 @@ static bool gemm_dma(const GemmArgs& g, hipStream_t s) {
     few(ANY_COUNT.upto);
     return true;
   }
-  if ((int64_t)Mt * Nt <= DB_NARROW_TILES) {
+  if ((int64_t)Mt * Nt <= narrow_tiles(g.K)) {
     narrow(-1, ANY_COUNT.upto);
     return true;
   }
   int above = -1;
   if (g.cols.at && g.K >= LISTED_K) {
-    const int f = small_tiles(g.K) / Mt * DB_BN, n = DB_NARROW_TILES / Mt * DB_BN;
+    const int f = small_tiles(g.K) / Mt * DB_BN, n = narrow_tiles(g.K) / Mt * DB_BN;
     if (f > 0) few(above = f);
     if (n > f) {
       narrow(above, n);
