@@ -132,8 +132,10 @@ __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 // a round, in an order that balances triangular k-work: there and back in turn
 // (a snake), and for an odd number of rounds the first three by permutations
 // whose sums over the rounds are 10 or 11 for every XCD (a snake's are 7 to 14:
-// at 24 row tiles one XCD got a fifth more than another).  That is for grids of one
-// and a half times the tiles that the chip holds at once and more, where an XCD's
+// at 24 row tiles one XCD got a fifth more than another).  That is for a last round
+// of at least five row tiles (with fewer the snake is the more even one: at 17 the
+// largest XCD has 1.05 of the mean, with the permutations 1.20; FP16 at n = 2,176, 7,029
+// SNPs 1.76 ms against 1.90) and for grids of one and a half times the tiles that the chip holds at once and more, where an XCD's
 // total is its time: n = 3,008, 4,096 and 8,192 fractional columns (2 and 4 times)
 // 637 -> 608 and 1,258 -> 1,208 us, refined FP32 at n = 6,000 (1.5 times) 5.06 -> 5.00 ms,
 // FP16 at 5,100 4.39 -> 4.24.  With little more than a round an XCD is as long as what
@@ -177,7 +179,7 @@ struct XcdMap {
     int j = cgi * GN + (w / GM);
     if (kl >= R || j >= Nt) return false;
     int pos;
-    if ((R & 1) && kl < 3 && 2 * (int64_t)Mt * Nt >= 3 * (ga.map_slots ? ga.map_slots : 768)) {
+    if ((R & 1) && kl < 3 && ((Mt - 1) & 7) >= 4 && 2 * (int64_t)Mt * Nt >= 3 * (ga.map_slots ? ga.map_slots : 768)) {
       const uint32_t perm = kl == 0 ? 0x76543210u : kl == 1 ? 0x10576243u : 0x34102657u;   // nibble x: XCD x's row
       pos = (int)((perm >> (4 * x)) & 7u);
     } else {
