@@ -1369,7 +1369,7 @@ static void pack_f64(Ctx* c, const double* X, int64_t ld, int mb, WholeBlock* w,
   else pack_units<OZ_F64>(c, X, ld, mb, true, w, s);
 }
 
-static bool whole_small(int Mt, int mb) { return (int64_t)Mt * ((mb + OZS_BN - 1) / OZS_BN) <= OZS_TILES; }
+static bool whole_small(int Mt, int mb) { return (int64_t)Mt * ((mb + OZS_BN - 1) / OZS_BN) <= small_whole_tiles(Mt); }
 
 // The two products' columns as lists, unless either product is a single round of workgroups on its kernel of few tiles
 // (256 of 128 x 16 for the FP64 one), where each may as well look at every tile: n = 1,000, 48 SNPs, half of them imputed,
@@ -1397,8 +1397,8 @@ static void launch_whole(OzArgs a, hipStream_t s) {
     few(ANY_COUNT.upto);
     return;
   }
-  if (a.cols.at && a.N >= LISTED_K && OZS_TILES / a.Mt > 0) {   // as gemm_dma does
-    const int f = OZS_TILES / a.Mt * OZS_BN;
+  if (a.cols.at && a.N >= LISTED_K && small_whole_tiles(a.Mt) >= a.Mt) {   // as gemm_dma does
+    const int f = small_whole_tiles(a.Mt) / a.Mt * OZS_BN;
     few(f);
     a.range = ColRange{f, ANY_COUNT.upto};
   }

@@ -546,11 +546,14 @@ void ozaki_i8_kernel(OzArgs g) {
 // long and there are no stage barriers: a wave reads its fragments straight from
 // memory, the next block's ahead of this one's MFMAs.  The int32 sums are exact, so
 // adding the four in LDS in any order gives the same integers; the FP64 steps are
-// those of ozaki_i8_kernel.  Up to 512 tiles (two
-// rounds of workgroups): n = 2,500, 64 SNPs 51 -> 29 us a block, n = 6,000, 20 SNPs
-// 96 -> 51, n = 12,000, 60 SNPs 216 -> 154; beyond, the larger tiles' fewer reads
-// win (n = 6,000, 200 SNPs, 752 tiles: 107 us against 120).
-constexpr int OZS_BN = 64, OZS_THREADS = 512, OZS_SPLIT = 4, OZS_TILES = 512;
+// those of ozaki_i8_kernel.  Up to 512 tiles (two rounds of workgroups), or 256 and
+// 384 where there are few stages to share; beyond, the larger tiles' fewer reads
+// win.  Times of a block of whole numbers, this kernel's over the other's (n: tiles
+// ratio ...): 600: 190 0.88, 247 1.01, 380 1.11, 494 1.18;  1,024: 256 0.83, 320 1.07,
+// 448 1.12;  1,500: 282 0.91, 376 1.04, 470 1.06;  2,048: 384 0.94, 512 1.03, 640 1.18;
+// 4,096: 256 0.68, 512 0.93, 640 1.16;  8,192: 512 0.78, 768 1.13.
+constexpr int OZS_BN = 64, OZS_THREADS = 512, OZS_SPLIT = 4;
+inline int small_whole_tiles(int Mt) { return Mt <= 32 ? 256 : Mt <= 64 ? 384 : 512; }
 
 template <int S>
 __global__ __launch_bounds__(OZS_THREADS) void ozaki_i8_small_kernel(OzArgs g) {
