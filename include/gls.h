@@ -70,8 +70,9 @@ typedef enum {
 
 /* Arithmetic of the per-block triangular solve (everything else is FP64). */
 typedef enum {
-  GLS_FP64 = 0,     /* plain FP64 MFMA; if n > 512 and M's diagonal spans a factor
-                       of at most 256, a SNP whose values are all whole numbers of
+  GLS_FP64 = 0,     /* plain FP64 MFMA; if n > 512 (up to 32,768 with
+                       GLS_KEEP_FOR_GRAD) and M's diagonal spans a factor of at
+                       most 256, a SNP whose values are all whole numbers of
                        magnitude at most 127 (dosages) takes exact int8 products
                        with L^-1 in eight base-256 digits a row (2^-64 of the
                        row's largest entry; entries down to 2^-10 of it exact)   */

@@ -193,8 +193,8 @@ bool plan_workspace(int64_t n, int32_t p, const gls_opts* o, Plan* pl) {
                  : (o->precision == GLS_FP16_IR || o->precision == GLS_BF16_IR) ? 2 : 0;
   pl->off_ub0 = take((size_t)n * bc);
   pl->off_ub1 = take((size_t)n * bc);
-  // Sliced L^-1 and its row exponents (under half of an N x N FP64 matrix).  L itself is read after setup only by
-  // the refinement residual and the adjoint; without those its region is free and holds them.
+  // Sliced L^-1 and its row exponents (a little over half of an N x N FP64 matrix).  L itself is read after setup only
+  // by the refinement residual and the adjoint; without those its region is free and holds them.
   if (o->precision == GLS_INT8_EMU) pl->digits = OZ_DIGITS_EMU;
   else if (pl->lp_bytes == 0 && N >= OZ_MIN_N && (N <= OZ_GRAD_MAX_N || !(o->flags & GLS_KEEP_FOR_GRAD)))
     pl->digits = OZ_DIGITS_FP64;

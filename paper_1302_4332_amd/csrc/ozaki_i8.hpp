@@ -381,13 +381,13 @@ __device__ __forceinline__ double add_rows32(double a, double b) {
 // busy for longer than the MFMA pipes.  Stages move straight from global memory
 // into a ring of three LDS buffers, two ahead of the MFMAs.
 //
-// What bounds it: the MFMA pipes are busy 58% of the launch and the clock falls
-// to 2.1 GHz under its power (n = 10,000, 8,192 SNPs: 2.3 ms, 2,500 TOPS; with
-// all-zero SNPs 2.0 ms).  The rest is waits after the stage barrier, which is why
-// two workgroups with barriers of their own share a compute unit: one workgroup
-// of eight waves (64 rows) had its pipes busy 48% and took 2.6 ms.  XCD groups of
-// 4 x 8 tiles; 2 x 16 and 4 x 16 are equal within noise, 8 x 4 and 8 x 8 6%
-// slower.
+// What bounds it (n = 10,000, 8,192 SNPs: eight digits 2.5 ms, 2,600 TOPS; seven 2.2 ms):
+// with seven digits the MFMA pipes were busy 58% of the launch and the clock fell to
+// 2.1 GHz under its power (with all-zero SNPs 2.0 of 2.3 ms).  The rest is waits
+// after the stage barrier, which is why two workgroups with barriers of their own
+// share a compute unit: one workgroup of eight waves (64 rows) had its pipes busy
+// 48% and took 2.6 ms.  XCD groups of 4 x 8 tiles; 2 x 16 and 4 x 16 are equal
+// within noise, 8 x 4 and 8 x 8 6% slower.
 //
 // A wave's accumulator element t of lane l is row 4 (l / 16) + t, SNP l % 16 of
 // its 16 x 16 block, so a sum over the rows is four values of the lane and two
